@@ -805,6 +805,197 @@ __global__ void __launch_bounds__(256) attr_init_reg_kernel(AttrArgs a) {
   }
 }
 
+// Three or four measured ends: the 2^O outcome values of one (init string j,
+// basis string beta, column b) give, by O sum/difference butterflies, the
+// values of all 2^z labels measured in that basis (z digits Z, each I or Z;
+// an X or Y digit keeps its difference).  The basis is the grid's y, so which
+// of the 2^O butterfly results are labels is the same for the whole workgroup.
+// Bound by reading V once.  The measured bits of the outcome index may sit
+// anywhere: STAGE takes 64 columns a wave, loads their 64 * 2^O values in
+// address order (16 bytes a lane; the 6 lowest output bits and the measured
+// bits hold every index bit below the seventh, so a run is at least 512
+// bytes), and regroups them per column through LDS.  Loading each column's
+// values where they are makes a wave touch 64 lines per load when the
+// measured bits are the lowest ones, and the lines leave the 32 KB L1 before
+// their other values are asked for.  Fewer than 64 columns take that plain
+// form (the table is small then).
+// A wave's LDS writes are read by its other lanes (a wave's LDS operations
+// run in order; this keeps the compiler from moving them across).
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+constexpr int kAttrPad = 66;  // doubles between two outcomes' rows of 64 columns in LDS
+
+template <int O, bool STAGE>
+__global__ void __launch_bounds__(256) attr_meas_wht_kernel(AttrArgs a) {
+  constexpr int NM = 1 << O;
+  typedef double d2_t __attribute__((ext_vector_type(2)));
+  __shared__ double sh[STAGE ? 4 : 1][STAGE ? NM * kAttrPad : 1];
+  const int64_t nb = (int64_t)1 << a.n;
+  int64_t nbasis = 1;
+#pragma unroll
+  for (int u = 0; u < O; ++u) nbasis *= 3;
+  const int beta = blockIdx.y;
+  // per butterfly result m: its label lm (or none: an X or Y digit's sum)
+  int digit[O];
+  {
+    int rest = beta;
+#pragma unroll
+    for (int u = O - 1; u >= 0; --u) {
+      digit[u] = rest % 3;
+      rest /= 3;
+    }
+  }
+  const int64_t total = ((int64_t)1 << (2 * a.r)) << a.n;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the grid covers whole waves of columns when STAGE (nb >= 64), so a wave
+  // enters and leaves the loop together
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += step) {
+    const int64_t bl = i & (nb - 1), j = i >> a.n;
+    const double* Vj = a.V + ((j * nbasis + beta) << a.w);
+    double v[NM];
+    if constexpr (STAGE) {
+      // wave's first column deposited around the measured bits (its low 6 bits are 0)
+      int64_t x0 = bl - lane;
+#pragma unroll
+      for (int u = O - 1; u >= 0; --u)  // measured positions ascend from the last slot to the first
+        x0 = ((x0 >> a.meas_pos[u]) << (a.meas_pos[u] + 1)) | (x0 & (((int64_t)1 << a.meas_pos[u]) - 1));
+      // bit t of a value's number in address order: the t-th lowest of the
+      // wave's index bits, a column bit or an outcome bit
+      int64_t xl = 0, xq[NM / 2];
+      int sl = 0, sq[NM / 2], s1 = 0;
+#pragma unroll
+      for (int q = 0; q < NM / 2; ++q) {
+        xq[q] = 0;
+        sq[q] = 0;
+      }
+      int pos = 0, um = O - 1, bc = 0;  // next position, next measured slot, next column bit
+#pragma unroll
+      for (int t = 0; t < 6 + O; ++t) {
+        const bool meas = um >= 0 && (bc >= 6 || a.meas_pos[um >= 0 ? um : 0] == pos);
+        if (meas) pos = a.meas_pos[um];
+        const int place = meas ? kAttrPad << (O - 1 - um) : 1 << bc;
+        if (t == 0) {
+          s1 = place;
+        } else if (t < 7) {
+          xl |= (int64_t)((lane >> (t - 1)) & 1) << pos;
+          sl += ((lane >> (t - 1)) & 1) * place;
+        } else {
+#pragma unroll
+          for (int q = 0; q < NM / 2; ++q)
+            if ((q >> (t - 7)) & 1) {
+              xq[q] |= (int64_t)1 << pos;
+              sq[q] += place;
+            }
+        }
+        um -= meas ? 1 : 0;
+        bc += meas ? 0 : 1;
+        ++pos;
+      }
+      double* S = sh[wave];
+      d2_t ld[NM / 2];
+#pragma unroll
+      for (int q = 0; q < NM / 2; ++q) ld[q] = *reinterpret_cast<const d2_t*>(Vj + (x0 | xl | xq[q]));
+#pragma unroll
+      for (int q = 0; q < NM / 2; ++q) {
+        S[sl + sq[q]] = ld[q][0];
+        S[sl + sq[q] + s1] = ld[q][1];
+      }
+      wave_lds_fence();
+#pragma unroll
+      for (int m = 0; m < NM; ++m) v[m] = S[m * kAttrPad + lane];
+      wave_lds_fence();  // the next columns overwrite S
+    } else {
+      int64_t x0 = bl;
+#pragma unroll
+      for (int u = O - 1; u >= 0; --u)
+        x0 = ((x0 >> a.meas_pos[u]) << (a.meas_pos[u] + 1)) | (x0 & (((int64_t)1 << a.meas_pos[u]) - 1));
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        int64_t x = x0;
+#pragma unroll
+        for (int u = 0; u < O; ++u)
+          if ((m >> (O - 1 - u)) & 1) x |= (int64_t)1 << a.meas_pos[u];
+        v[m] = Vj[x];
+      }
+    }
+#pragma unroll
+    for (int h = 1; h < NM; h <<= 1)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        if (m & h) continue;
+        const double x = v[m], y = v[m | h];
+        v[m] = x + y;
+        v[m | h] = x - y;
+      }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      int lm = 0;
+      bool label = true;
+#pragma unroll
+      for (int u = 0; u < O; ++u) {
+        const int bit = (m >> (O - 1 - u)) & 1;
+        label = label & (digit[u] == 0 || bit == 1);
+        lm = 4 * lm + (digit[u] == 0 ? 3 * bit : digit[u]);
+      }
+      if (label) a.U[((j << (2 * O)) + lm) * nb + bl] = v[m];
+    }
+  }
+}
+
+// Four initialised ends: the 4^4 init strings of one (lm, b) are spread over
+// the four 16-lane groups of a wave by the first digit, 64 to a lane, so three
+// digits transform in registers and the first by cross-lane reads; U is read
+// and E written in runs of 16 columns (128 bytes).  Bound by U and E crossing
+// once each; one thread per entry re-read each U value for every label row in
+// its support (4^8 rows of 2^10 columns with both passes: 15.7 ms then, 0.88
+// ms with this kernel and the one above; 3.25 GB cannot be done without).
+__global__ void __launch_bounds__(256) attr_init4_kernel(AttrArgs a) {
+  const int64_t nb = (int64_t)1 << a.n;
+  const int64_t total = nb << (2 * a.o);  // (lm, b)
+  const int lane = threadIdx.x & 63, grp = lane >> 4, l16 = lane & 15;
+  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int64_t i0 = wave * 16; i0 < total; i0 += waves * 16) {
+    const int64_t i = i0 + l16;
+    const bool in = i < total;
+    const double* src = a.U + (int64_t)grp * 64 * total + (in ? i : total - 1);
+    double u[64];
+#pragma unroll
+    for (int j = 0; j < 64; ++j) u[j] = src[j * total];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int sd = 1 << (2 * (2 - t));  // stride of init digit t + 1
+#pragma unroll
+      for (int j = 0; j < 64; ++j) {
+        if ((j / sd) % 4 != 0) continue;
+        const double d0 = u[j], d1 = u[j + sd], d2 = u[j + 2 * sd], d3 = u[j + 3 * sd];
+        u[j] = d0 + d1;                       // I
+        u[j + sd] = 2.0 * d2 - d0 - d1;       // X
+        u[j + 2 * sd] = 2.0 * d3 - d0 - d1;   // Y
+        u[j + 3 * sd] = d0 - d1;              // Z
+      }
+    }
+    const int64_t b = i & (nb - 1), lm = i >> a.n;
+    int64_t mrow = (int64_t)grp * a.init_w[0];
+    for (int q = 0; q < a.o; ++q) mrow += ((lm >> (2 * (a.o - 1 - q))) & 3) * a.meas_w[q];
+    // group 1 (X) takes 2 d2 - d0 - d1 and group 2 (Y) 2 d3 - d0 - d1
+    const int other = (grp == 1 ? 32 : grp == 2 ? 48 : 0) + l16;
+    const bool two = grp == 1 || grp == 2;
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+      const double d0 = __shfl(u[j], l16), d1 = __shfl(u[j], 16 + l16), d = __shfl(u[j], other);
+      const double x = two ? 2.0 * d - d0 : d0;
+      const double y = grp == 0 ? x + d1 : x - d1;
+      const int64_t row = mrow + (j >> 4) * a.init_w[1] + ((j >> 2) & 3) * a.init_w[2] + (j & 3) * a.init_w[3];
+      if (in) a.E[(row << a.n) + b] = y;
+    }
+  }
+}
+
 // Both passes in one kernel for up to two measured and two initialised cut
 // ends (the dynamic-definition subcircuits): a thread owns one output column
 // b and walks the 3^O measurement bases; for each basis it loads the
@@ -1113,8 +1304,6 @@ hipError_t launch_attribute(const AttrLaunch& l, hipStream_t stream) {
     a.init_w[i] = l.init_w[i];
     a.meas_w[i] = l.meas_w[i];
   }
-  const int64_t total = ((int64_t)1 << (2 * (l.r + l.o))) << l.n;
-  const unsigned grid = grid_for(total);
   if (l.r <= 2 && l.o <= 2) {
     const dim3 gf(grid_for((int64_t)1 << l.n));
 #define CQ_ATTR_FUSED(R, O)                                                          \
@@ -1127,12 +1316,24 @@ hipError_t launch_attribute(const AttrLaunch& l, hipStream_t stream) {
     CQ_ATTR_FUSED(2, 0) CQ_ATTR_FUSED(2, 1) CQ_ATTR_FUSED(2, 2)
 #undef CQ_ATTR_FUSED
   }
-  const dim3 gm(grid_for(((int64_t)1 << (2 * l.r)) << l.n)), gi(grid_for(((int64_t)1 << (2 * l.o)) << l.n));
+  // two passes through U (in slabs of columns whose U stays in the 256 MB
+  // last-level cache the 4^8 x 2^10 case took 0.90-0.96 ms against 0.88)
+  const int64_t nb = (int64_t)1 << l.n;
+  const dim3 gt(grid_for(nb << (2 * (l.r + l.o)))), gm(grid_for(nb << (2 * l.r))), gi(grid_for(nb << (2 * l.o)));
+  const bool stage = l.n >= 6 && (reinterpret_cast<uintptr_t>(l.V) & 15) == 0;
   switch (l.o) {
     case 0: hipLaunchKernelGGL(attr_meas_reg_kernel<0>, gm, dim3(256), 0, stream, a); break;
     case 1: hipLaunchKernelGGL(attr_meas_reg_kernel<1>, gm, dim3(256), 0, stream, a); break;
     case 2: hipLaunchKernelGGL(attr_meas_reg_kernel<2>, gm, dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL(attr_meas_kernel, dim3(grid), dim3(256), 0, stream, a); break;
+    case 3:
+      if (stage) hipLaunchKernelGGL((attr_meas_wht_kernel<3, true>), dim3(gm.x, 27), dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL((attr_meas_wht_kernel<3, false>), dim3(gm.x, 27), dim3(256), 0, stream, a);
+      break;
+    case 4:
+      if (stage) hipLaunchKernelGGL((attr_meas_wht_kernel<4, true>), dim3(gm.x, 81), dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL((attr_meas_wht_kernel<4, false>), dim3(gm.x, 81), dim3(256), 0, stream, a);
+      break;
+    default: hipLaunchKernelGGL(attr_meas_kernel, gt, dim3(256), 0, stream, a); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1141,7 +1342,8 @@ hipError_t launch_attribute(const AttrLaunch& l, hipStream_t stream) {
     case 1: hipLaunchKernelGGL(attr_init_reg_kernel<1>, gi, dim3(256), 0, stream, a); break;
     case 2: hipLaunchKernelGGL(attr_init_reg_kernel<2>, gi, dim3(256), 0, stream, a); break;
     case 3: hipLaunchKernelGGL(attr_init_reg_kernel<3>, gi, dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL(attr_init_kernel, dim3(grid), dim3(256), 0, stream, a); break;
+    case 4: hipLaunchKernelGGL(attr_init4_kernel, dim3(grid_for((nb << (2 * l.o)) * 4)), dim3(256), 0, stream, a); break;
+    default: hipLaunchKernelGGL(attr_init_kernel, gt, dim3(256), 0, stream, a); break;
   }
   return hipGetLastError();
 }
