@@ -398,9 +398,12 @@ cq_status cq_chi2(const double* a, const double* b, int64_t n, double* result, v
  * of a basis-state index: CQ_GATE_U applies the 2 x 2 unitary u (row-major,
  * (re, im) of u00, u01, u10, u11) to qubit q0; CQ_GATE_CZ applies CZ to q0
  * and q1.  The matrix is applied as given (unitarity is not checked).
- * Consecutive gates are applied in groups to tiles of 2^11 amplitudes held
- * in registers (8 per thread; registers narrower than a tile go through LDS),
- * in circuit order, so the state crosses HBM once per group.
+ * Gates are applied in passes to tiles of 2^11 or 2^12 amplitudes held in
+ * registers (registers narrower than a tile go through LDS), in an order that
+ * keeps every gate after the earlier gates it shares a qubit with.  The state
+ * crosses HBM once per pass, and only the part of it that the qubits acted on
+ * so far can reach: amplitudes that must still be zero are neither stored nor
+ * read.
  * ------------------------------------------------------------------------- */
 #define CQ_MAX_SV_QUBITS 34  /* 2^34 amplitudes = 256 GiB of workspace */
 
@@ -418,22 +421,19 @@ cq_status cq_simulate_workspace_size(int32_t n, size_t* bytes);
 
 /* |psi|^2 of gates applied to |0...0>.  gates: host, read during the call.
  * probs: device, 2^n FP64, written.  workspace: device, at least
- * cq_simulate_workspace_size bytes; it holds the state before the last
- * group of gates on return when there are two or more groups (the first
- * group generates |0...0> itself, so a single group leaves it unwritten).
- * Asynchronous on `stream`.  Errors (before any
+ * cq_simulate_workspace_size bytes, contents on entry ignored and on return
+ * unspecified (intermediate amplitudes).  Asynchronous on `stream`.  Errors (before any
  * launch): CQ_ERR_SHAPE for n out of range, CQ_ERR_ARG for a gate with an
  * unknown kind, a qubit out of range, equal CZ qubits or a non-finite
  * matrix entry, CQ_ERR_WORKSPACE. */
 cq_status cq_simulate_probabilities(int32_t n, const cq_gate* gates, int32_t n_gates, double* probs,
                                     void* workspace, size_t workspace_bytes, hipStream_t stream);
 
-/* 16 * 2^width bytes per state.  Registers of at least 11 slots with at most
- * two measured ends hold several states at once: with one or two
- * initialised ends the 2^r computational init strings (every variant is a
- * combination of their results), else up to 16 init strings, within 4 GiB;
- * the size covers that many.  cq_variant_probabilities works with any
- * workspace of at least one state, more slowly below this size. */
+/* 16 * 2^width bytes per state, 2^r states: one for each computational init
+ * string of the r initialised ends (every variant is a combination of their
+ * results).  Never more than the variants themselves take when r or o is
+ * at least 1.  cq_variant_probabilities works with any workspace of at least
+ * one state, more slowly below this size. */
 cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t* bytes);
 
 /* Every variant of subcircuit `sub` running `gates` (qubits = its register
@@ -444,7 +444,8 @@ cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t* bytes);
  * measurement), the probabilities of the 2^width register outcomes.
  * variants: device, FP64, layout (4^r, 3^o, 2^width) as cq_attribute reads
  * it, written whole.  workspace: device, at least one state (16 * 2^width
- * bytes); cq_variants_workspace_size bytes let it batch initial states.
+ * bytes); cq_variants_workspace_size bytes let it simulate the computational
+ * init strings as one batch and write every variant from them in one pass.
  * Asynchronous on `stream`; errors as for cq_simulate_probabilities plus
  * the cut-map checks of the subcircuit. */
 cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq_gate* gates, int32_t n_gates,

@@ -4,13 +4,17 @@
 // initialisation |0>, |1>, |+>, |+i> and each measurement basis Z, X, Y).
 //
 // Amplitudes are FP64 complex, qubit 0 the most significant index bit.
-// Gates run in groups: gates whose qubits fit one tile of kTileBits index
-// bits are applied together to tiles of 2^kTileBits amplitudes staged in
-// LDS (one workgroup a tile, the tile's other index bits fixed), in circuit
-// order, so the state makes one HBM round trip per group instead of one per
-// gate.  A tile always holds the kLowBits lowest index bits, which keeps
-// the gathers coalesced, and a group may take a later gate that commutes
-// with every gate it overtakes (no shared qubit).
+// Gates run in passes: gates whose qubits fit one tile of index bits are
+// applied together to tiles of amplitudes held in registers (one workgroup a
+// tile, the tile's other index bits fixed), so the state makes one HBM round
+// trip per pass instead of one per gate.  A pass may take a later gate that
+// commutes with every gate it overtakes (no shared qubit).
+//
+// A state that starts as a basis state is zero wherever a qubit that no gate
+// has acted on differs from its start, so a pass reads and writes only the
+// amplitudes whose untouched bits agree with it: 2^t of 2^n while t qubits
+// are touched.  The passes are therefore planned so that the touched set
+// grows as late as possible (plan_passes).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,42 +29,55 @@ namespace cq {
 
 namespace {
 
-constexpr int kTileBits = 11;
-constexpr int kLowBits = 4;
-constexpr int kTile = 1 << kTileBits;
+constexpr int kMinTileBits = 11;  // narrower registers take the LDS kernel
+constexpr int kMaxTileBits = 12;
+constexpr int kMaxOps = 160;  // gates of a pass
+constexpr int kMaxU = 36;     // one-qubit unitaries among them
 constexpr int kSvThreads = 256;
-constexpr int kPerThread = kTile / kSvThreads;
-constexpr int kMaxGroupGates = 40;
-constexpr int kMaxBases = 9;  // measurement bases one tile pass writes (two measured slots)
+constexpr int kLdsTile = 1 << (kMinTileBits - 1);
 
-struct TileGate {
-  int32_t kind;  // CQ_GATE_U or CQ_GATE_CZ
-  int32_t a, b;  // tile-local bit positions (b for CZ only)
-  int32_t pad;
-  double u[8];   // (re, im) of u00, u01, u10, u11
-};
+// A gate of a pass in one word (whole words, so that uniform reads of the
+// arguments are aligned scalar loads): bits 0-7 CQ_GATE_U or CQ_GATE_CZ, 8-15
+// and 16-23 tile-local bit positions (the second for CZ only), 24-31 the
+// matrix (CQ_GATE_U).
+typedef uint32_t TileOp;
+__host__ __device__ inline int op_kind(TileOp g) { return (int)(g & 0xffu); }
+__host__ __device__ inline int op_a(TileOp g) { return (int)((g >> 8) & 0xffu); }
+__host__ __device__ inline int op_b(TileOp g) { return (int)((g >> 16) & 0xffu); }
+__host__ __device__ inline int op_u(TileOp g) { return (int)(g >> 24); }
 
-// One launch: the tile's index bits (ascending), the complement bits that
-// number the tiles, and the gates.  mode 0 writes amplitudes back, mode 1
-// writes |amplitude|^2 to `probs` in the same index order.
+// One launch: the tile's index bits by local position, the bits that number
+// the tiles, and the gates.  mode 0 writes amplitudes back, mode 1 writes
+// |amplitude|^2 to `probs` in the same index order.  State blockIdx.y of a
+// batch starts as the basis string whose bit init_bit[t] is bit r - 1 - t of
+// blockIdx.y (all other bits 0) and lies bstride elements after state 0.
 struct TileGroup {
-  int32_t k;          // tile bits (<= kTileBits)
-  int32_t ngates;
+  int32_t k;       // tile bits
+  int32_t nops;
   int32_t mode;
-  int32_t nouter;     // index bits outside the tile
-  uint8_t bits[kTileBits];
-  uint8_t outer[CQ_MAX_SV_QUBITS];
-  TileGate g[kMaxGroupGates];
-  int32_t nbasis;                // sv_reg_kernel<true>: bases and their gate ranges
-  int32_t boff[kMaxBases + 1];
-  int64_t pstride;               // elements between the bases' outputs
-  // sv_reg_kernel with blockIdx.y = state s of a batch: in and out start
-  // s * bstride elements on, probs s * pbstride on (both 0 without a batch)
+  int32_t nouter;  // bits that number the tiles
+  int32_t first;   // the state is still its basis string: nothing is read
+  int32_t r;
+  uint64_t before;  // bits touched before and after the pass: amplitudes whose
+  uint64_t after;   // untouched bits differ from the start are zero and not stored
+  uint64_t full;    // all index bits
+  uint64_t tile;    // the tile's index bits
+  uint64_t fixed;   // bits neither in the tile nor numbering tiles (kept at the start's)
   int64_t bstride;
-  int64_t pbstride;
+  uint32_t init_bit[CQ_MAX_LOCAL_CUTS];
+  uint32_t bits[kMaxTileBits];
+  uint32_t outer[CQ_MAX_SV_QUBITS];
+  TileOp ops[kMaxOps];
+  double u[kMaxU][8];  // (re, im) of u00, u01, u10, u11
 };
 
-static_assert(sizeof(TileGroup) + 3 * sizeof(void*) <= 4096, "kernel arguments exceed 4 KiB");
+static_assert(sizeof(TileGroup) + 2 * sizeof(void*) <= 4096, "kernel arguments exceed 4 KiB");
+
+__device__ inline uint64_t start_string(const TileGroup& G, uint32_t y) {
+  uint64_t s = 0;
+  for (int t = 0; t < G.r; ++t) s |= (uint64_t)((y >> (G.r - 1 - t)) & 1u) << G.init_bit[t];
+  return s;
+}
 
 struct Complex {
   double re, im;
@@ -70,72 +87,69 @@ __device__ inline Complex cmul(double ur, double ui, Complex x) {
   return {ur * x.re - ui * x.im, ur * x.im + ui * x.re};
 }
 
-// `in` and `out` may be the same array (each workgroup reads and writes only
-// its own tile); a null `in` stands for |0...0> (nothing is read).
-__global__ void __launch_bounds__(kSvThreads) sv_tile_kernel(const double2* in, double2* out, double* probs,
-                                                             TileGroup G) {
-  __shared__ double2 S[kTile];
-  // the tile's base address: the workgroup index deposited into the outer bits
-  uint64_t base = 0;
-  const uint64_t w = blockIdx.x;
-  for (int i = 0; i < G.nouter; ++i) base |= ((w >> i) & 1ull) << G.outer[i];
+// Registers narrower than a full tile: the whole state in LDS, a barrier per
+// gate (every amplitude is read and written).
+__global__ void __launch_bounds__(kSvThreads) sv_tile_kernel(double2* psi, double* probs, TileGroup G) {
+  __shared__ double2 S[kLdsTile];
+  psi += blockIdx.y * G.bstride;
+  const uint64_t start = start_string(G, blockIdx.y);
   const int n = 1 << G.k;
-  uint64_t addr[kPerThread];
-#pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const int t = threadIdx.x + e * kSvThreads;
-    uint64_t a = base;
-    for (int i = 0; i < G.k; ++i) a |= (uint64_t)((t >> i) & 1) << G.bits[i];
-    addr[e] = a;
-    if (t < n) S[t] = in ? in[a] : make_double2(a == 0 ? 1.0 : 0.0, 0.0);
-  }
+  for (int t = threadIdx.x; t < n; t += kSvThreads)
+    S[t] = G.first ? make_double2((uint64_t)t == start ? 1.0 : 0.0, 0.0) : psi[t];
   __syncthreads();
-  for (int gi = 0; gi < G.ngates; ++gi) {
-    const TileGate& g = G.g[gi];
-    if (g.kind == CQ_GATE_U) {
-      const int half = n >> 1, m = 1 << g.a;
+  for (int gi = 0; gi < G.nops; ++gi) {
+    const TileOp g = G.ops[gi];
+    if (op_kind(g) == CQ_GATE_U) {
+      const double* u = G.u[op_u(g)];
+      const int ga = op_a(g);
+      const int half = n >> 1, m = 1 << ga;
       for (int p = threadIdx.x; p < half; p += kSvThreads) {
-        const int i0 = ((p >> g.a) << (g.a + 1)) | (p & (m - 1)), i1 = i0 | m;
+        const int i0 = ((p >> ga) << (ga + 1)) | (p & (m - 1)), i1 = i0 | m;
         const Complex x0{S[i0].x, S[i0].y}, x1{S[i1].x, S[i1].y};
-        const Complex a0 = cmul(g.u[0], g.u[1], x0), b0 = cmul(g.u[2], g.u[3], x1);
-        const Complex a1 = cmul(g.u[4], g.u[5], x0), b1 = cmul(g.u[6], g.u[7], x1);
+        const Complex a0 = cmul(u[0], u[1], x0), b0 = cmul(u[2], u[3], x1);
+        const Complex a1 = cmul(u[4], u[5], x0), b1 = cmul(u[6], u[7], x1);
         S[i0] = make_double2(a0.re + b0.re, a0.im + b0.im);
         S[i1] = make_double2(a1.re + b1.re, a1.im + b1.im);
       }
     } else {
-      const int both = (1 << g.a) | (1 << g.b);
+      const int both = (1 << op_a(g)) | (1 << op_b(g));
       for (int t = threadIdx.x; t < n; t += kSvThreads)
         if ((t & both) == both) S[t] = make_double2(-S[t].x, -S[t].y);
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const int t = threadIdx.x + e * kSvThreads;
-    if (t < n) {
-      const double2 v = S[t];
-      if (G.mode == 0) out[addr[e]] = v;
-      else probs[addr[e]] = v.x * v.x + v.y * v.y;
-    }
+  for (int t = threadIdx.x; t < n; t += kSvThreads) {
+    const double2 v = S[t];
+    if (G.mode == 0) psi[t] = v;
+    else probs[t] = v.x * v.x + v.y * v.y;
   }
 }
 
-// Full tiles (kTileBits bits) keep the amplitudes in registers: thread t
-// holds local indices t + 256 e, e = 0..7, so local bits 0-5 are lane bits,
-// 6-7 wave bits and 8-10 register bits.  CZ is a sign flip on elements the
-// thread owns; a one-qubit gate on a register bit pairs two of the thread's
-// own elements; on a lane bit the partner comes from another lane by a
-// cross-lane read; on a wave bit it goes through LDS.  The host places the
-// group's busiest qubits on register bits.
+// Full tiles keep the amplitudes in registers: with 2^TB amplitudes and T
+// threads, thread t holds local indices t + T e, so the local bits are six
+// lane bits, then the wave bits, then the register bits.  A one-qubit gate on
+// a register bit pairs two of the thread's own elements; on a lane bit the
+// partner comes from another lane by a cross-lane read; on a wave bit it goes
+// through LDS.  The host places the pass's busiest qubits on register bits.
+// Tiles of 11 bits run as 256 threads of 8 amplitudes, of 12 bits as 256 of 16
+// (13 bits as 512 of 16 leave one workgroup a compute unit: the 30-qubit
+// circuit took 30.3 ms against 24.6).
+template <int TB>
+struct TileShape {
+  static constexpr int LogT = 8;
+  static constexpr int T = 1 << LogT;
+  static constexpr int NE = 1 << (TB - LogT);
+};
+
 __device__ inline double2 u_row(double r0, double i0, double r1, double i1, double2 x, double2 y) {
   // (r0 + i i0) x + (r1 + i i1) y
   return make_double2(r0 * x.x - i0 * x.y + r1 * y.x - i1 * y.y, r0 * x.y + i0 * x.x + r1 * y.y + i1 * y.x);
 }
 
-template <int R>
-__device__ inline void u_reg(double2 (&v)[kPerThread], const double* u) {
+template <int R, int NE>
+__device__ inline void u_reg(double2 (&v)[NE], const double* u) {
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
+  for (int e = 0; e < NE; ++e) {
     if (e & (1 << R)) continue;
     const double2 x0 = v[e], x1 = v[e | (1 << R)];
     v[e] = u_row(u[0], u[1], u[2], u[3], x0, x1);
@@ -172,195 +186,308 @@ __device__ inline double2 u_exchange(const ExchangeCoef& c, double2 mine, double
   return u_row(c.ar, c.ai, c.br, c.bi, mine, y);
 }
 
-template <int M>
-__device__ inline void u_lane(double2 (&v)[kPerThread], const double* u, int lane) {
+template <int M, int NE>
+__device__ inline void u_lane(double2 (&v)[NE], const double* u, int lane) {
   const ExchangeCoef c = exchange_coef(u, (lane & M) ? 1 : 0);
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
+  for (int e = 0; e < NE; ++e) {
     const double2 y = make_double2(__shfl_xor(v[e].x, M), __shfl_xor(v[e].y, M));
     v[e] = u_exchange(c, v[e], y);
   }
 }
 
-// Gates g0 .. g1 - 1 of the group on a thread's elements (see sv_reg_kernel);
-// S is the workgroup's exchange buffer.
-__device__ __forceinline__ void reg_apply(double2 (&v)[kPerThread], const TileGroup& G, int g0, int g1, int tid,
-                                          int lane, double2* S) {
-  for (int gi = g0; gi < g1; ++gi) {
-    const TileGate& g = G.g[gi];
-    if (g.kind == CQ_GATE_CZ) {
-      // A run of CZs is diagonal: element tid + 256 e changes sign by the
-      // parity, over the run's pairs, of the product of the pair's two bits.
-      // Bits 0-7 are tid's and bits 8-10 e's, so per thread: s, the parity of
-      // the pairs inside tid; p bit r, that of the tid bits paired with bit
-      // 8 + r; rr, which pairs of bits 8-10 occur (an odd number of times).
-      uint32_t sgn = 0, p = 0, rr = 0;
+__device__ inline double flip_sign(double x, uint32_t bit31) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) ^ ((uint64_t)bit31 << 32));
+}
+
+// The pass's gates on a thread's elements; S is the workgroup's exchange
+// buffer of 8 elements a thread.
+template <int TB>
+__device__ __forceinline__ void reg_apply(double2 (&v)[TileShape<TB>::NE], const TileGroup& G, int tid, int lane,
+                                          double2* S) {
+  constexpr int T = TileShape<TB>::T, LogT = TileShape<TB>::LogT, NE = TileShape<TB>::NE;
+  // bit e of bit_of(q): bit q of e
+  auto bit_of = [](int q) -> uint32_t { return (uint32_t)(0xff00f0f0ccccaaaaull >> (16 * q)) & 0xffffu; };
+  for (int gi = 0; gi < G.nops; ++gi) {
+    const TileOp g = G.ops[gi];
+    if (op_kind(g) == CQ_GATE_CZ) {
+      // A run of CZs is diagonal: element tid + T e changes sign by the
+      // parity, over the run's pairs, of the product of the pair's two bits;
+      // bit e of `sg` collects it.
+      uint32_t sg = 0;
       int j = gi;
-      for (; j < g1 && G.g[j].kind == CQ_GATE_CZ; ++j) {
-        const int a = G.g[j].a, b = G.g[j].b;
-        if (a < 8 && b < 8) sgn ^= ((uint32_t)tid >> a) & ((uint32_t)tid >> b) & 1u;
-        else if (a < 8) p ^= (((uint32_t)tid >> a) & 1u) << (b - 8);
-        else if (b < 8) p ^= (((uint32_t)tid >> b) & 1u) << (a - 8);
-        else rr ^= 1u << ((a - 8) + (b - 8) - 1);  // bits (8,9), (8,10), (9,10)
+      for (TileOp o = g; op_kind(o) == CQ_GATE_CZ;) {
+        const int a = op_a(o), b = op_b(o);
+        const uint32_t ma = a < LogT ? 0u - (((uint32_t)tid >> a) & 1u) : bit_of(a - LogT);
+        const uint32_t mb = b < LogT ? 0u - (((uint32_t)tid >> b) & 1u) : bit_of(b - LogT);
+        sg ^= ma & mb;
+        if (++j == G.nops) break;
+        o = G.ops[j];
       }
       gi = j - 1;
 #pragma unroll
-      for (int e = 0; e < kPerThread; ++e) {
-        uint32_t f = sgn;
-        if (e & 1) f ^= p & 1u;
-        if (e & 2) f ^= (p >> 1) & 1u;
-        if (e & 4) f ^= (p >> 2) & 1u;
-        if ((e & 3) == 3) f ^= rr & 1u;
-        if ((e & 5) == 5) f ^= (rr >> 1) & 1u;
-        if ((e & 6) == 6) f ^= (rr >> 2) & 1u;
-        if (f) v[e] = make_double2(-v[e].x, -v[e].y);
+      for (int e = 0; e < NE; ++e) {
+        const uint32_t s = (sg << (31 - e)) & 0x80000000u;
+        v[e] = make_double2(flip_sign(v[e].x, s), flip_sign(v[e].y, s));
       }
-    } else if (g.a >= 8) {
-      if (g.a == 8) u_reg<0>(v, g.u);
-      else if (g.a == 9) u_reg<1>(v, g.u);
-      else u_reg<2>(v, g.u);
-    } else if (g.a < 6) {
-      switch (g.a) {
-        case 0: u_lane<1>(v, g.u, lane); break;
-        case 1: u_lane<2>(v, g.u, lane); break;
-        case 2: u_lane<4>(v, g.u, lane); break;
-        case 3: u_lane<8>(v, g.u, lane); break;
-        case 4: u_lane<16>(v, g.u, lane); break;
-        default: u_lane<32>(v, g.u, lane); break;
+      continue;
+    }
+    const double* u = G.u[op_u(g)];
+    const int ga = op_a(g);
+    if (ga >= LogT) {
+      switch (ga - LogT) {
+        case 0: u_reg<0, NE>(v, u); break;
+        case 1: u_reg<1, NE>(v, u); break;
+        case 2: u_reg<2, NE>(v, u); break;
+        default:
+          if constexpr (NE > 8) u_reg<3, NE>(v, u);
+          break;
+      }
+    } else if (ga < 6) {
+      switch (ga) {
+        case 0: u_lane<1, NE>(v, u, lane); break;
+        case 1: u_lane<2, NE>(v, u, lane); break;
+        case 2: u_lane<4, NE>(v, u, lane); break;
+        case 3: u_lane<8, NE>(v, u, lane); break;
+        case 4: u_lane<16, NE>(v, u, lane); break;
+        default: u_lane<32, NE>(v, u, lane); break;
       }
     } else {
-      const ExchangeCoef c = exchange_coef(g.u, (tid >> g.a) & 1);
-      const int m = 1 << g.a;
-      __syncthreads();  // the previous exchange has read S
+      const ExchangeCoef c = exchange_coef(u, (tid >> ga) & 1);
+      const int m = 1 << ga;
 #pragma unroll
-      for (int e = 0; e < kPerThread; ++e) S[tid + e * kSvThreads] = v[e];
-      __syncthreads();
+      for (int h = 0; h < NE; h += 8) {
+        __syncthreads();  // the previous exchange has read S
 #pragma unroll
-      for (int e = 0; e < kPerThread; ++e) v[e] = u_exchange(c, v[e], S[(tid + e * kSvThreads) ^ m]);
+        for (int e = 0; e < 8; ++e) S[tid + e * T] = v[h + e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[h + e] = u_exchange(c, v[h + e], S[(tid + e * T) ^ m]);
+      }
     }
   }
 }
 
-// MULTI: the group holds the rotations of nbasis measurement bases (gates
-// boff[b] .. boff[b+1] - 1 for basis b); the tile is read once and each
-// basis writes |amplitude|^2 of its rotated copy to probs + b * pstride.
-template <bool MULTI>
-__global__ void __launch_bounds__(kSvThreads) sv_reg_kernel(const double2* in, double2* out, double* probs,
-                                                            TileGroup G) {
-  static_assert(kPerThread == 8 && kSvThreads == 256, "bit layout assumes 8 elements a thread, 256 threads");
-  __shared__ double2 S[kTile];
-  if (blockIdx.y) {  // state blockIdx.y of a batch
-    if (in) in += blockIdx.y * G.bstride;
-    out += blockIdx.y * G.bstride;
-    if (probs) probs += blockIdx.y * G.pbstride;
-  }
-  uint64_t base = 0;
+template <int TB>
+__global__ void __launch_bounds__(TileShape<TB>::T, TB == 12 ? 3 : 5) sv_reg_kernel(double2* psi, double* probs, TileGroup G) {
+  constexpr int T = TileShape<TB>::T, LogT = TileShape<TB>::LogT, NE = TileShape<TB>::NE;
+  __shared__ double2 S[T * 8];
+  psi += blockIdx.y * G.bstride;
+  const uint64_t start = start_string(G, blockIdx.y);
+  uint64_t base = start & G.fixed;
   const uint64_t w = blockIdx.x;
   for (int i = 0; i < G.nouter; ++i) base |= ((w >> i) & 1ull) << G.outer[i];
   const int tid = threadIdx.x, lane = tid & 63;
-  // local index tid + 256 e: its bits 0-7 are tid's (one per-thread part of
-  // the address), bits 8-10 are e's (a part every thread shares), so no
-  // per-element address has to stay live from the load to the store
+  // local index tid + T e: its low bits are tid's (one per-thread part of the
+  // address), the others e's (a part every thread shares), so no per-element
+  // address has to stay live from the load to the store
   uint64_t tpart = base;
-  for (int i = 0; i < 8; ++i) tpart |= (uint64_t)((tid >> i) & 1) << G.bits[i];
-  auto addr_of = [&](int e) -> uint64_t {
-    uint64_t a = tpart;
-    for (int i = 8; i < kTileBits; ++i) a |= (uint64_t)((e >> (i - 8)) & 1) << G.bits[i];
+  for (int i = 0; i < LogT; ++i) tpart |= (uint64_t)((tid >> i) & 1) << G.bits[i];
+  auto epart = [&](int e) -> uint64_t {
+    uint64_t a = 0;
+    for (int i = LogT; i < TB; ++i) a |= (uint64_t)((e >> (i - LogT)) & 1) << G.bits[i];
     return a;
   };
-  double2 v[kPerThread];
+  // bits whose value decides whether an amplitude is stored before / after
+  const uint64_t off0 = G.full & ~G.before, off1 = G.full & ~G.after;
+  const bool zero = ((base ^ start) & off0 & ~G.tile) != 0;  // nothing of this tile is stored: all zero
+  double2 v[NE];
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const uint64_t a = addr_of(e);
-    v[e] = in ? in[a] : make_double2(a == 0 ? 1.0 : 0.0, 0.0);  // null in: |0...0>
-  }
-  if constexpr (MULTI) {
-    for (int b = 0; b < G.nbasis; ++b) {
-      double2 r[kPerThread];
-#pragma unroll
-      for (int e = 0; e < kPerThread; ++e) r[e] = v[e];
-      reg_apply(r, G, G.boff[b], G.boff[b + 1], tid, lane, S);
-      double* const pb = probs + (int64_t)b * G.pstride;
-#pragma unroll
-      for (int e = 0; e < kPerThread; ++e) pb[addr_of(e)] = r[e].x * r[e].x + r[e].y * r[e].y;
+  for (int e = 0; e < NE; ++e) {
+    const uint64_t a = tpart | epart(e);
+    v[e] = make_double2(0.0, 0.0);
+    if (((a ^ start) & off0) == 0) {
+      if (G.first) v[e].x = 1.0;
+      else v[e] = psi[a];
     }
-  } else {
-    reg_apply(v, G, 0, G.ngates, tid, lane, S);
+  }
+  if (!zero) reg_apply<TB>(v, G, tid, lane, S);
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) {
-      const uint64_t a = addr_of(e);
-      if (G.mode == 0) out[a] = v[e];
-      else probs[a] = v[e].x * v[e].x + v[e].y * v[e].y;
+  for (int e = 0; e < NE; ++e) {
+    const uint64_t a = tpart | epart(e);
+    if (G.mode == 0) {
+      if (((a ^ start) & off1) == 0) psi[a] = v[e];
+    } else {
+      probs[a] = v[e].x * v[e].x + v[e].y * v[e].y;
     }
   }
 }
 
 // Variants by linearity.  An init string prepares each init slot t in
-// ket(d_t) = c0(d_t)|0> + c1(d_t)|1> (|0>, |1>, |+>, |+i>), so its
-// post-circuit state is sum over c in {0,1}^r of w_j(c) S_c, with
-// w_j(c) = prod_t c_{c_t}(d_t) and S_c the post-circuit state of the
-// computational init string c (slot t in |c_t>, c_t bit r - 1 - t of c).  The
-// 2^r states S_c (r <= 2) sit `G.bstride` elements apart from `in`; for each
-// measurement basis b every S_c tile is read and rotated (gates
-// boff[b] .. boff[b+1] - 1), and each init string j (digit t of j base 4,
-// first slot most significant) writes |sum_c w_j(c) R_b S_c|^2 to
-// probs + (j * nbasis + b) * pstride.
-__device__ __constant__ double kInitKet[4][4] = {
-    {1.0, 0.0, 0.0, 0.0},
-    {0.0, 0.0, 1.0, 0.0},
-    {0.70710678118654752440, 0.0, 0.70710678118654752440, 0.0},
-    {0.70710678118654752440, 0.0, 0.0, 0.70710678118654752440}};
+// ket(d_t) = |0>, |1>, (|0> + |1>) / sqrt 2 or (|0> + i|1>) / sqrt 2, so its
+// post-circuit state is a sum of the post-circuit states S_c of the 2^r
+// computational init strings (slot t in |c_t>, c_t bit r - 1 - t of c), which
+// sit bstride elements apart; and a measured slot's rotation combines the two
+// halves of that slot's bit with weights that are powers of i over sqrt 2.
+// Every variant is therefore |sum of amplitudes times powers of i|^2 over a
+// power of 2.  A thread owns the 2^o outcomes around one setting of the other
+// bits: it holds the 2^R x 2^O amplitudes of the last R <= 2 init and
+// O <= 2 measured slots, forms each basis by additions in registers and writes
+// that basis's 4^R init strings, so every S_c is read once and every variant
+// written once (bound by that write).  Further slots are the grid's y: their
+// digits (and outcome) choose which amplitudes are added on loading.
+struct CombineArgs {
+  int32_t w, r, o;
+  int32_t vec;  // the last measured slot is index bit 0 and probs is 16-byte aligned
+  int64_t bstride;
+  uint32_t meas_bit[CQ_MAX_LOCAL_CUTS];  // index bit of measured slot u
+};
 
-__global__ void __launch_bounds__(kSvThreads) sv_combine_kernel(const double2* in, double* probs, TileGroup G,
-                                                                int r) {
-  __shared__ double2 S[kTile];
-  uint64_t base = 0;
-  const uint64_t w = blockIdx.x;
-  for (int i = 0; i < G.nouter; ++i) base |= ((w >> i) & 1ull) << G.outer[i];
-  const int tid = threadIdx.x, lane = tid & 63;
-  uint64_t tpart = base;
-  for (int i = 0; i < 8; ++i) tpart |= (uint64_t)((tid >> i) & 1) << G.bits[i];
-  auto addr_of = [&](int e) -> uint64_t {
-    uint64_t a = tpart;
-    for (int i = 8; i < kTileBits; ++i) a |= (uint64_t)((e >> (i - 8)) & 1) << G.bits[i];
-    return a;
-  };
-  const int nc = 1 << r, nj = 1 << (2 * r);
-  for (int b = 0; b < G.nbasis; ++b) {
-    double2 rs[4][kPerThread];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (c >= nc) break;
-#pragma unroll
-      for (int e = 0; e < kPerThread; ++e) rs[c][e] = in[c * G.bstride + addr_of(e)];
-      reg_apply(rs[c], G, G.boff[b], G.boff[b + 1], tid, lane, S);
-    }
-    for (int j = 0; j < nj; ++j) {
-      double wr[4], wi[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        double ar = 1.0, ai = 0.0;
-        for (int t = 0; t < r; ++t) {
-          const int d = (j >> (2 * (r - 1 - t))) & 3, bit = (c >> (r - 1 - t)) & 1;
-          const double kr = kInitKet[d][2 * bit], ki = kInitKet[d][2 * bit + 1];
-          const double nr = ar * kr - ai * ki;
-          ai = ar * ki + ai * kr;
-          ar = nr;
+__device__ inline double2 add_phase(double2 x, double2 y, int p) {  // x + i^p y
+  switch (p & 3) {
+    case 0: return make_double2(x.x + y.x, x.y + y.y);
+    case 1: return make_double2(x.x - y.y, x.y + y.x);
+    case 2: return make_double2(x.x - y.x, x.y - y.y);
+    default: return make_double2(x.x + y.y, x.y - y.x);
+  }
+}
+
+// The amplitude of init digit d from the two halves: |0>, |1>, + and +i
+// (without the 1 / sqrt 2).
+__device__ inline double2 init_amp(int d, double2 x0, double2 x1) {
+  return d == 0 ? x0 : d == 1 ? x1 : add_phase(x0, x1, d - 2);
+}
+
+template <int R, int O>
+__global__ void __launch_bounds__(kSvThreads) sv_combine_kernel(const double2* __restrict__ psi,
+                                                                double* __restrict__ probs, CombineArgs A) {
+  constexpr int NC = 1 << R, NM = 1 << O, NJ = 1 << (2 * R), NB = O == 0 ? 1 : (O == 1 ? 3 : 9);
+  // the outer slots of this workgroup: offsets to the amplitudes and to the
+  // outputs; every bit that takes both values doubles the amplitudes to add
+  // (term q of them: offset off[q], times i^ph[q])
+  constexpr int kMaxTerms = 1 << (CQ_MAX_LOCAL_CUTS - 2);
+  __shared__ int64_t off[kMaxTerms];
+  __shared__ int ph[kMaxTerms];
+  const int ro = A.r - R, oo = A.o - O;
+  int64_t dst = 0, jo = 0, bo = 0;
+  int nt = 0;
+  double outer_scale = 1.0;
+  {
+    unsigned y = blockIdx.y;
+    const int q = threadIdx.x;
+    int64_t src = 0, w4 = 1, w3 = 1;
+    int p = 0;
+    for (int s = ro - 1; s >= 0; --s) {
+      const int d = y & 3;
+      y >>= 2;
+      const int64_t step = A.bstride << (A.r - 1 - s);
+      if (d == 1) src += step;
+      if (d >= 2) {
+        if ((q >> nt) & 1) {
+          src += step;
+          p += d - 2;
         }
-        wr[c] = ar;
-        wi[c] = ai;
+        ++nt;
+        outer_scale *= 0.5;
       }
-      double* const pj = probs + ((int64_t)j * G.nbasis + b) * G.pstride;
-#pragma unroll
-      for (int e = 0; e < kPerThread; ++e) {
-        double xr = 0.0, xi = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (c >= nc) break;
-          xr += wr[c] * rs[c][e].x - wi[c] * rs[c][e].y;
-          xi += wr[c] * rs[c][e].y + wi[c] * rs[c][e].x;
+      jo += d * w4;
+      w4 *= 4;
+    }
+    for (int u = oo - 1; u >= 0; --u) {
+      const int m = y & 1;
+      y >>= 1;
+      const int d = (int)(y % 3);
+      y /= 3;
+      const int64_t step = (int64_t)1 << A.meas_bit[u];
+      if (m) dst += step;
+      if (d == 0) {
+        if (m) src += step;
+      } else {
+        // X: x0 + (-1)^m x1; Y: x0 - i x1 (m = 0), x0 + i x1 (m = 1)
+        if ((q >> nt) & 1) {
+          src += step;
+          p += d == 1 ? 2 * m : (m ? 1 : 3);
         }
-        pj[addr_of(e)] = xr * xr + xi * xi;
+        ++nt;
+        outer_scale *= 0.5;
+      }
+      bo += d * w3;
+      w3 *= 3;
+    }
+    if (q < 1 << nt) {
+      off[q] = src;
+      ph[q] = p;
+    }
+  }
+  __syncthreads();
+  const int64_t t = (int64_t)blockIdx.x * kSvThreads + threadIdx.x;
+  if (t >= (int64_t)1 << (A.w - A.o)) return;
+  int64_t x0 = t;  // around the measured bits, which ascend from the last slot to the first
+  for (int u = A.o - 1; u >= 0; --u)
+    x0 = ((x0 >> A.meas_bit[u]) << (A.meas_bit[u] + 1)) | (x0 & (((int64_t)1 << A.meas_bit[u]) - 1));
+  int64_t xm[NM];  // index bits of the inner outcomes
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    xm[m] = 0;
+#pragma unroll
+    for (int u = 0; u < O; ++u)
+      if ((m >> (O - 1 - u)) & 1) xm[m] |= (int64_t)1 << A.meas_bit[oo + u];
+  }
+  double2 s[NC][NM];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int m = 0; m < NM; ++m) s[c][m] = psi[off[0] + c * A.bstride + (x0 | xm[m])];
+  for (int q = 1; q < 1 << nt; ++q)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) s[c][m] = add_phase(s[c][m], psi[off[q] + c * A.bstride + (x0 | xm[m])], ph[q]);
+  int64_t nbasis = 1;
+  for (int u = 0; u < A.o; ++u) nbasis *= 3;
+  double* const out = probs + (dst | x0);
+#pragma unroll 1
+  for (int b = 0; b < NB; ++b) {
+    double2 v[NC][NM];
+    double scale = outer_scale;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) v[c][m] = s[c][m];
+#pragma unroll
+    for (int u = 0; u < O; ++u) {
+      const int d = (O == 2 && u == 0) ? b / 3 : b % 3;
+      if (d == 0) continue;
+      scale *= 0.5;
+      const int h = 1 << (O - 1 - u);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          if (m & h) continue;
+          const double2 y0 = v[c][m], y1 = v[c][m | h];
+          v[c][m] = d == 1 ? add_phase(y0, y1, 0) : add_phase(y0, y1, 3);
+          v[c][m | h] = d == 1 ? add_phase(y0, y1, 2) : add_phase(y0, y1, 1);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      double p[NM];
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        double2 a;
+        double sc = scale;
+        if constexpr (R == 0) {
+          a = v[0][m];
+        } else if constexpr (R == 1) {
+          a = init_amp(j, v[0][m], v[1][m]);
+          if (j >= 2) sc *= 0.5;
+        } else {
+          const int d0 = j >> 2, d1 = j & 3;  // slot 0 is the state's high bit
+          a = init_amp(d1, init_amp(d0, v[0][m], v[NC / 2][m]), init_amp(d0, v[NC / 4][m], v[NC - 1][m]));
+          if (d0 >= 2) sc *= 0.5;
+          if (d1 >= 2) sc *= 0.5;
+        }
+        p[m] = (a.x * a.x + a.y * a.y) * sc;
+      }
+      double* const row = out + ((((jo << (2 * R)) + j) * nbasis + bo * NB + b) << A.w);
+      if (O >= 1 && A.vec) {
+#pragma unroll
+        for (int m = 0; m < NM; m += 2)
+          if constexpr (NM >= 2) *reinterpret_cast<double2*>(row + xm[m]) = make_double2(p[m], p[m + 1]);
+      } else {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) row[xm[m]] = p[m];
       }
     }
   }
@@ -419,75 +546,170 @@ cq_status check_gates(int32_t n, const cq_gate* gates, int32_t n_gates) {
   return CQ_OK;
 }
 
-// Gates -> groups whose index bits fit one tile together with the kLowBits
-// lowest bits (which keep every gather in runs of 2^kLowBits amplitudes).
-// A gate joins the open group when it fits and shares no qubit with an
-// earlier gate left for a later group, so it commutes with every gate it
-// overtakes; the gates of a group keep their circuit order.
-struct Group {
+// One pass of a plan: its gates (indices into the gate list, circuit order),
+// the qubits they act on as index bits, and the bits touched before and
+// after it.
+struct Pass {
   std::vector<int> gates;
-  uint64_t mask = 0;
+  uint64_t mask = 0, before = 0, after = 0;
 };
 
-std::vector<Group> make_groups(int n, const cq_gate* gates, int n_gates, const std::vector<cq_gate>& tail) {
-  const int k = std::min(n, kTileBits);
-  const uint64_t low = (1ull << std::min(n, kLowBits)) - 1;
-  auto bit = [n](int q) { return 1ull << (n - 1 - q); };
-  const int total = n_gates + (int)tail.size();
-  std::vector<uint64_t> masks(total);
-  for (int i = 0; i < total; ++i) {
-    const cq_gate& g = i < n_gates ? gates[i] : tail[i - n_gates];
-    masks[i] = bit(g.q0) | (g.kind == CQ_GATE_CZ ? bit(g.q1) : 0ull);
+struct GateSet {
+  int n = 0;
+  std::vector<cq_gate> g;
+  std::vector<uint64_t> mask;
+};
+
+uint64_t gate_mask(int n, const cq_gate& g) {
+  return (1ull << (n - 1 - g.q0)) | (g.kind == CQ_GATE_CZ ? 1ull << (n - 1 - g.q1) : 0ull);
+}
+
+// The gates that matter to probabilities: a CZ none of whose qubits sees a
+// later one-qubit gate (of the list, or of the rotations on `rotated`, index
+// bits) commutes to the end, where it only changes phases.
+GateSet gate_set(int n, const cq_gate* gates, int n_gates, uint64_t rotated) {
+  GateSet s;
+  s.n = n;
+  uint64_t live = rotated;
+  std::vector<int> keep;
+  for (int i = n_gates - 1; i >= 0; --i) {
+    const uint64_t m = gate_mask(n, gates[i]);
+    if (gates[i].kind == CQ_GATE_U) live |= m;
+    else if ((m & live) == 0) continue;
+    keep.push_back(i);
   }
-  std::vector<int> rest(total);
-  for (int i = 0; i < total; ++i) rest[i] = i;
-  std::vector<Group> out;
+  for (auto it = keep.rbegin(); it != keep.rend(); ++it) {
+    s.g.push_back(gates[*it]);
+    s.mask.push_back(gate_mask(n, gates[*it]));
+  }
+  return s;
+}
+
+// How a plan is laid out: tile bits, the lowest index bits every tile holds
+// (gathers then read runs of 2^low amplitudes), and how many qubits join the
+// allowed set when no gate inside it can run.
+struct PlanShape {
+  int tile = 0, low = 0, grow = 0;
+};
+
+// Passes for one shape.  A pass takes, in circuit order, every gate inside the
+// allowed qubits that fits the tile and shares no qubit with an earlier gate
+// left for a later pass.  With `track` the state starts as a basis string and
+// the allowed qubits start as the lowest `tile` index bits and grow, lowest
+// first, only when none of their gates can run: while t qubits are touched a
+// pass moves 2^t amplitudes.  Returns the modelled time in microseconds, or
+// anything above `limit` once that is passed.  The model, from traces: 3.5 us
+// a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.55 ms for
+// every one-qubit gate on 2^30 amplitudes, no less than the serial time of
+// those gates in one tile (0.8 us each with 11 bits, 1.4 us with 12).
+double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int states, double limit,
+                   std::vector<Pass>& out) {
+  const int n = s.n;
+  const uint64_t full = (1ull << n) - 1;
+  const uint64_t low = (1ull << std::min(n, sh.low)) - 1;
+  uint64_t allowed = track ? (1ull << std::min(n, sh.tile)) - 1 : full, touched = track ? 0 : full;
+  std::vector<int> rest(s.g.size()), left;
+  for (size_t i = 0; i < rest.size(); ++i) rest[i] = (int)i;
+  out.clear();
+  double us = 0.0;
   while (!rest.empty()) {
-    Group cur;
-    uint64_t blocked = 0;
-    std::vector<int> left;
-    for (int i : rest) {
-      const uint64_t m = masks[i];
-      if ((m & blocked) == 0 && (int)cur.gates.size() < kMaxGroupGates &&
-          __builtin_popcountll(cur.mask | m | low) <= k) {
-        cur.gates.push_back(i);
-        cur.mask |= m;
+    Pass p;
+    uint64_t blocked = 0, cur = low;
+    int nu = 0;
+    left.clear();
+    for (size_t q = 0; q < rest.size(); ++q) {
+      const int i = rest[q];
+      const uint64_t m = s.mask[i];
+      const int is_u = s.g[i].kind == CQ_GATE_U;
+      if ((m & (blocked | ~allowed)) == 0 && (int)p.gates.size() < kMaxOps && nu + is_u <= kMaxU &&
+          __builtin_popcountll(cur | m) <= sh.tile) {
+        p.gates.push_back(i);
+        p.mask |= m;
+        cur |= m;
+        nu += is_u;
       } else {
         blocked |= m;
         left.push_back(i);
+        if ((allowed & ~blocked) == 0) {  // nothing after it can run
+          left.insert(left.end(), rest.begin() + q + 1, rest.end());
+          break;
+        }
       }
     }
-    out.push_back(cur);
+    if (p.gates.empty()) {
+      for (int a = 0; a < sh.grow && allowed != full; ++a) allowed |= allowed + 1;  // the lowest bit not allowed yet
+      continue;
+    }
+    p.before = touched;
+    touched |= p.mask;
+    p.after = touched;
     rest.swap(left);
+    const double before = out.empty() && track ? 0.0 : std::ldexp(16.0, __builtin_popcountll(p.before));
+    const double after = std::ldexp(rest.empty() ? 8.0 : 16.0, rest.empty() ? n : __builtin_popcountll(p.after));
+    const double work = nu * std::max(std::ldexp(5.2e-7 * states, __builtin_popcountll(p.after)),
+                                      sh.tile <= 11 ? 0.8 : 1.4);
+    us += 3.5 + states * (before + after) / 4.4e6 + work;
+    out.push_back(std::move(p));
+    if (us > limit) break;
   }
-  return out;
+  return us;
 }
 
-TileGroup tile_group(int n, const Group& grp, const cq_gate* gates, int n_gates, const std::vector<cq_gate>& tail,
-                     int mode) {
+// The cheapest plan by the model over a few shapes.  Wider tiles mean fewer
+// passes; growing the allowed set by several qubits at a time merges passes
+// that one at a time would leave nearly empty; runs of 8 amplitudes (128
+// bytes, one line) leave a tile one bit more than runs of 16.  Below 18
+// qubits launches decide, so only the extreme shapes are tried there.
+PlanShape best_plan(const GateSet& s, bool track, int states, std::vector<Pass>& out) {
+  PlanShape best;
+  double least = 1e300;
+  std::vector<Pass> cand;
+  for (int tile = std::min(s.n, kMaxTileBits); tile >= std::min(s.n, kMinTileBits); --tile)
+    for (int low = 4; low >= 3; --low)
+      for (int grow : {s.n, 6, 4, 3, 2, 1}) {
+        if (grow != s.n && (!track || s.n < 18)) continue;
+        const PlanShape sh{tile, low, grow};
+        const double us = plan_passes(s, sh, track, states, least, cand);
+        if (us < least) {
+          least = us;
+          best = sh;
+          out.swap(cand);
+        }
+      }
+  return best;
+}
+
+TileGroup tile_group(const GateSet& s, const PlanShape& sh, const Pass& pass, int mode) {
   TileGroup G{};
-  const int k = std::min(n, kTileBits);
-  uint64_t mask = grp.mask | ((1ull << std::min(n, kLowBits)) - 1);
-  for (int b = 0; b < n && __builtin_popcountll(mask) < k; ++b) mask |= 1ull << b;
+  const int n = s.n, k = std::min(n, sh.tile), low = std::min(n, sh.low);
+  uint64_t mask = pass.mask | ((1ull << low) - 1);
+  for (const uint64_t pool : {pass.after, ~(uint64_t)0})  // fill with touched bits first
+    for (int b = 0; b < n && __builtin_popcountll(mask) < k; ++b) mask |= (pool >> b & 1) << b;
   G.k = k;
   G.mode = mode;
-  auto gate = [&](int i) -> const cq_gate& { return i < n_gates ? gates[i] : tail[i - n_gates]; };
+  G.before = pass.before;
+  G.after = mode ? (1ull << n) - 1 : pass.after;
+  G.full = (1ull << n) - 1;
+  G.tile = mask;
   // local positions: ascending global bits for partial tiles; for full
-  // tiles the kLowBits lowest bits first (coalesced lanes), then the other
-  // bits by one-qubit gate count, busiest first, on the register positions
-  // 8-10, then lane positions 4-5, then wave positions 6-7
+  // tiles the lowest bits first (coalesced lanes), then the other bits by
+  // one-qubit gate count, busiest first, on the register positions, then the
+  // lane positions left, then the wave positions
   std::vector<int> order;
   for (int b = 0; b < n; ++b)
     if (mask >> b & 1) order.push_back(b);
-  if (k == kTileBits) {
+  if (k >= kMinTileBits) {
     int uses[64] = {};
-    for (int i : grp.gates)
-      if (gate(i).kind == CQ_GATE_U) ++uses[n - 1 - gate(i).q0];
-    std::vector<int> rest(order.begin() + kLowBits, order.end());
+    for (int i : pass.gates)
+      if (s.g[i].kind == CQ_GATE_U) ++uses[n - 1 - s.g[i].q0];
+    std::vector<int> rest(order.begin() + low, order.end());
     std::stable_sort(rest.begin(), rest.end(), [&](int x, int y) { return uses[x] > uses[y]; });
-    const int slot[kTileBits - kLowBits] = {8, 9, 10, 4, 5, 6, 7};
-    std::vector<int> placed(kTileBits, -1);
-    for (int i = 0; i < kLowBits; ++i) placed[i] = order[i];
+    const int logt = TileShape<kMaxTileBits>::LogT;
+    std::vector<int> slot;
+    for (int i = logt; i < k; ++i) slot.push_back(i);
+    for (int i = low; i < logt; ++i) slot.push_back(i);
+    std::vector<int> placed(k, -1);
+    for (int i = 0; i < low; ++i) placed[i] = order[i];
     for (int i = 0; i < (int)rest.size(); ++i) placed[slot[i]] = rest[i];
     order = placed;
   }
@@ -495,69 +717,103 @@ TileGroup tile_group(int n, const Group& grp, const cq_gate* gates, int n_gates,
   int no = 0;
   for (int i = 0; i < k; ++i) {
     local[order[i]] = i;
-    G.bits[i] = (uint8_t)order[i];
+    G.bits[i] = (uint32_t)order[i];
   }
   for (int b = 0; b < n; ++b)
-    if (!(mask >> b & 1)) G.outer[no++] = (uint8_t)b;
+    if (!(mask >> b & 1)) {
+      if (G.after >> b & 1) G.outer[no++] = (uint32_t)b;
+      else G.fixed |= 1ull << b;
+    }
   G.nouter = no;
-  G.ngates = (int)grp.gates.size();
-  for (int j = 0; j < G.ngates; ++j) {
-    const cq_gate& g = gate(grp.gates[j]);
-    TileGate& t = G.g[j];
-    t.kind = g.kind;
-    t.a = local[n - 1 - g.q0];
-    t.b = g.kind == CQ_GATE_CZ ? local[n - 1 - g.q1] : 0;
-    for (int c = 0; c < 8; ++c) t.u[c] = g.kind == CQ_GATE_U ? g.u[c] : 0.0;
+  G.nops = (int)pass.gates.size();
+  int nu = 0;
+  for (int j = 0; j < G.nops; ++j) {
+    const cq_gate& g = s.g[pass.gates[j]];
+    const uint32_t a = (uint32_t)g.kind | (uint32_t)local[n - 1 - g.q0] << 8;
+    if (g.kind == CQ_GATE_CZ) {
+      G.ops[j] = a | (uint32_t)local[n - 1 - g.q1] << 16;
+    } else {
+      G.ops[j] = a | (uint32_t)nu << 24;
+      for (int c = 0; c < 8; ++c) G.u[nu][c] = g.u[c];
+      ++nu;
+    }
   }
   return G;
 }
 
 // One tile pass: the register kernel for full tiles, the LDS kernel for
 // registers narrower than a tile.
-hipError_t launch_tiles(int n, const TileGroup& G, const double2* in, double2* out, double* probs,
-                        hipStream_t stream) {
-  const unsigned tiles = (unsigned)(1ull << (n - G.k));
-  if (G.k == kTileBits)
-    hipLaunchKernelGGL(sv_reg_kernel<false>, dim3(tiles), dim3(kSvThreads), 0, stream, in, out, probs, G);
-  else
-    hipLaunchKernelGGL(sv_tile_kernel, dim3(tiles), dim3(kSvThreads), 0, stream, in, out, probs, G);
+hipError_t launch_tiles(const TileGroup& G, double2* psi, double* probs, unsigned states, hipStream_t stream) {
+  const dim3 grid((unsigned)(1ull << G.nouter), states);
+  switch (G.k) {
+    case 11: hipLaunchKernelGGL(sv_reg_kernel<11>, grid, dim3(TileShape<11>::T), 0, stream, psi, probs, G); break;
+    case 12: hipLaunchKernelGGL(sv_reg_kernel<12>, grid, dim3(TileShape<12>::T), 0, stream, psi, probs, G); break;
+    default: hipLaunchKernelGGL(sv_tile_kernel, grid, dim3(kSvThreads), 0, stream, psi, probs, G); break;
+  }
   return hipGetLastError();
 }
 
-// Applies `gates` then `tail` to psi in place; the last group writes
-// |amplitude|^2 to probs instead when probs is set (psi then keeps the state
-// before that group), and a probability pass runs alone when there are no
-// gates at all.  With zero_start the state starts as |0...0>, which the
-// first pass generates instead of reading psi.
-hipError_t run_gates(int n, const cq_gate* gates, int n_gates, const std::vector<cq_gate>& tail, double2* psi,
-                     double* probs, hipStream_t stream, bool zero_start = false) {
-  std::vector<Group> groups = make_groups(n, gates, n_gates, tail);
-  if (groups.empty() && (probs || zero_start)) groups.push_back(Group());
-  for (size_t i = 0; i < groups.size(); ++i) {
-    const bool last = i + 1 == groups.size();
-    const int mode = last && probs ? 1 : 0;
-    const TileGroup G = tile_group(n, groups[i], gates, n_gates, tail, mode);
-    const hipError_t e = launch_tiles(n, G, i == 0 && zero_start ? nullptr : psi, psi, probs, stream);
+// Applies the gates to `states` states of a batch.  With init_bits each starts
+// as a basis string (see TileGroup) that the first pass generates; without,
+// as what psi holds.  With probs (one state) the last pass writes
+// |amplitude|^2 there; else it leaves every amplitude in psi.
+hipError_t run_gates(const GateSet& s, double2* psi, double* probs, const std::vector<int>* init_bits,
+                     hipStream_t stream) {
+  const uint64_t full = (1ull << s.n) - 1;
+  const bool track = init_bits != nullptr;
+  const unsigned states = track ? 1u << init_bits->size() : 1u;
+  std::vector<Pass> passes;
+  const PlanShape sh = best_plan(s, track, (int)states, passes);
+  if (passes.empty()) {
+    if (!track && !probs) return hipSuccess;
+    passes.push_back(Pass());
+    passes[0].before = passes[0].after = track ? 0 : full;
+  }
+  passes.back().after = full;  // every amplitude or probability is written
+  for (size_t i = 0; i < passes.size(); ++i) {
+    const bool last = i + 1 == passes.size();
+    TileGroup G = tile_group(s, sh, passes[i], last && probs ? 1 : 0);
+    G.bstride = (int64_t)1 << s.n;
+    if (track) {
+      G.first = i == 0;
+      G.r = (int32_t)init_bits->size();
+      for (int t = 0; t < G.r; ++t) G.init_bit[t] = (uint32_t)(*init_bits)[t];
+    }
+    const hipError_t e = launch_tiles(G, psi, probs, states, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-// States cq_variant_probabilities holds at once on the one-pass-bases path
-// (a full tile, at most kMaxBases bases): the 2^r computational init strings
-// with one or two initialised ends (the linear path), else all init strings
-// up to 16; within 4 GiB and no more than `ws` bytes hold; one otherwise.
-int64_t variant_batch(const SubInfo& si, size_t ws) {
-  const int w = si.width;
-  int64_t n_init = 1, n_basis = 1;
-  for (int i = 0; i < si.r(); ++i) n_init *= 4;
-  for (int i = 0; i < si.o(); ++i) n_basis *= 3;
-  if (w < kTileBits || n_basis > kMaxBases) return 1;
-  const size_t state = (size_t)16 << w;
-  int64_t b = si.r() >= 1 && si.r() <= 2 ? ((int64_t)1 << si.r()) : std::min<int64_t>(n_init, 16);
-  b = std::min<int64_t>(b, (int64_t)(((size_t)4 << 30) / state));
-  b = std::min<int64_t>(b, (int64_t)(ws / state));
-  return b < 1 ? 1 : b;
+template <int R, int O>
+void launch_combine(const CombineArgs& A, const double2* psi, double* probs, hipStream_t stream) {
+  const int64_t nx = (int64_t)1 << (A.w - A.o);
+  unsigned ny = 1u << (2 * (A.r - R));
+  for (int u = 0; u < A.o - O; ++u) ny *= 6;
+  hipLaunchKernelGGL((sv_combine_kernel<R, O>), dim3((unsigned)((nx + kSvThreads - 1) / kSvThreads), ny),
+                     dim3(kSvThreads), 0, stream, psi, probs, A);
+}
+
+hipError_t combine(const SubInfo& si, const double2* psi, double* probs, hipStream_t stream) {
+  CombineArgs A{};
+  A.w = si.width;
+  A.r = si.r();
+  A.o = si.o();
+  A.bstride = (int64_t)1 << si.width;
+  for (int u = 0; u < A.o; ++u) A.meas_bit[u] = (uint32_t)(si.width - 1 - si.meas_slots[u]);
+  A.vec = A.o > 0 && A.meas_bit[A.o - 1] == 0 && (reinterpret_cast<uintptr_t>(probs) & 15) == 0;
+  switch (std::min(A.r, 2) * 3 + std::min(A.o, 2)) {
+    case 0: launch_combine<0, 0>(A, psi, probs, stream); break;
+    case 1: launch_combine<0, 1>(A, psi, probs, stream); break;
+    case 2: launch_combine<0, 2>(A, psi, probs, stream); break;
+    case 3: launch_combine<1, 0>(A, psi, probs, stream); break;
+    case 4: launch_combine<1, 1>(A, psi, probs, stream); break;
+    case 5: launch_combine<1, 2>(A, psi, probs, stream); break;
+    case 6: launch_combine<2, 0>(A, psi, probs, stream); break;
+    case 7: launch_combine<2, 1>(A, psi, probs, stream); break;
+    default: launch_combine<2, 2>(A, psi, probs, stream); break;
+  }
+  return hipGetLastError();
 }
 
 cq_gate u_gate(int q, const double (&m)[8]) {
@@ -588,9 +844,9 @@ extern "C" cq_status cq_simulate_probabilities(int32_t n, const cq_gate* gates, 
   cq_status st = check_gates(n, gates, n_gates);
   if (st != CQ_OK) return st;
   if (!workspace || workspace_bytes < ((size_t)16 << n)) return fail(CQ_ERR_WORKSPACE, "workspace too small");
-  double2* psi = static_cast<double2*>(workspace);
-  // the first pass generates |0...0> itself (no zero fill, no read of it)
-  const hipError_t e = run_gates(n, gates, n_gates, {}, psi, probs, stream, true);
+  const std::vector<int> no_bits;
+  const hipError_t e = run_gates(gate_set(n, gates, n_gates, 0), static_cast<double2*>(workspace), probs, &no_bits,
+                                 stream);
   if (e != hipSuccess) return sv_hip_error(e, "state-vector launch");
   return CQ_OK;
 }
@@ -601,7 +857,7 @@ extern "C" cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t
   cq_status st = build_subinfo(sub, si);
   if (st != CQ_OK) return st;
   if (si.width < 1) return fail(CQ_ERR_SHAPE, "subcircuit has no slots");
-  *bytes = ((size_t)16 << si.width) * (size_t)variant_batch(si, (size_t)-1);
+  *bytes = ((size_t)16 << si.width) << si.r();
   return CQ_OK;
 }
 
@@ -620,6 +876,21 @@ extern "C" cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq
   double2* psi = static_cast<double2*>(workspace);
   const int64_t size = (int64_t)1 << w;
   const int r = si.r(), o = si.o();
+  uint64_t rotated = 0;
+  for (int q : si.meas_slots) rotated |= 1ull << (w - 1 - q);
+  const GateSet circuit = gate_set(w, gates, n_gates, rotated);
+  if (workspace_bytes >> r >= ((size_t)16 << w)) {
+    // the 2^r computational init strings as one batch, then every variant
+    // from them in one pass
+    std::vector<int> init_bits;
+    for (int q : si.init_slots) init_bits.push_back(w - 1 - q);
+    hipError_t e = run_gates(circuit, psi, nullptr, &init_bits, stream);
+    if (e == hipSuccess) e = combine(si, psi, variants, stream);
+    if (e != hipSuccess) return sv_hip_error(e, "variant launch");
+    return CQ_OK;
+  }
+  // one state at a time (a workspace of fewer than 2^r states): each init
+  // string's product state, the circuit, then one pass per measurement basis
   int64_t n_init = 1, n_basis = 1;
   for (int i = 0; i < r; ++i) n_init *= 4;
   for (int i = 0; i < o; ++i) n_basis *= 3;
@@ -630,136 +901,34 @@ extern "C" cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq
   // Y (S^dagger then H, i.e. H S^dagger = [[1, -i], [1, i]] / sqrt 2)
   const double rot_x[8] = {h, 0, h, 0, h, 0, -h, 0};
   const double rot_y[8] = {h, 0, 0, -h, h, 0, 0, h};
-  // rotations of measurement basis b (digit 1: X, 2: Y per measured slot)
-  auto basis_rot = [&](int64_t b) {
-    std::vector<cq_gate> rot;
-    int64_t rest = b;
-    std::vector<int> digits(o);
-    for (int u = o - 1; u >= 0; --u) {
-      digits[u] = (int)(rest % 3);
-      rest /= 3;
+  for (int64_t j = 0; j < n_init; ++j) {
+    Kets K{};
+    K.n = w;
+    for (int q = 0; q < w; ++q) {
+      K.k[q][0] = 1.0;
+      K.k[q][1] = K.k[q][2] = K.k[q][3] = 0.0;
     }
-    for (int u = 0; u < o; ++u) {
-      if (digits[u] == 1) rot.push_back(u_gate(si.meas_slots[u], rot_x));
-      if (digits[u] == 2) rot.push_back(u_gate(si.meas_slots[u], rot_y));
+    for (int t = 0; t < r; ++t) {
+      const int digit = (int)((j >> (2 * (r - 1 - t))) & 3);
+      for (int c = 0; c < 4; ++c) K.k[si.init_slots[t]][c] = init_ket[digit][c];
     }
-    return rot;
-  };
-  // the one-pass-bases path (a full tile, at most kMaxBases bases) takes a
-  // batch of initial states at once, as many as the workspace holds
-  const bool one_pass = w >= kTileBits && n_basis <= kMaxBases;
-  const int64_t batch = variant_batch(si, workspace_bytes);
-  const unsigned tiles = one_pass ? (unsigned)(1ull << (w - kTileBits)) : 0u;
-  TileGroup GB{};
-  if (one_pass) {
-    std::vector<cq_gate> all;
-    std::vector<int> off{0};
-    for (int64_t b = 0; b < n_basis; ++b) {
-      const std::vector<cq_gate> rot = basis_rot(b);
-      all.insert(all.end(), rot.begin(), rot.end());
-      off.push_back((int)all.size());
-    }
-    Group grp;
-    for (int i = 0; i < (int)all.size(); ++i) {
-      grp.gates.push_back(i);
-      grp.mask |= 1ull << (w - 1 - all[i].q0);
-    }
-    GB = tile_group(w, grp, nullptr, 0, all, 1);
-    GB.nbasis = (int)n_basis;
-    for (int b = 0; b <= (int)n_basis; ++b) GB.boff[b] = off[b];
-    GB.pstride = size;
-    GB.bstride = size;
-    GB.pbstride = n_basis * size;
-  }
-  const std::vector<Group> circuit = one_pass ? make_groups(w, gates, n_gates, {}) : std::vector<Group>();
-  // by linearity (one or two init slots): simulate the 2^r computational
-  // init strings only and combine them per init string in the bases pass
-  if (one_pass && r >= 1 && r <= 2 && workspace_bytes >= ((size_t)16 << w) * ((size_t)1 << r)) {
-    const int nc = 1 << r;
-    hipError_t e = hipSuccess;
-    for (int c = 0; c < nc && e == hipSuccess; ++c) {
-      Kets K{};
-      K.n = w;
-      for (int q = 0; q < w; ++q) {
-        K.k[q][0] = 1.0;
-        K.k[q][1] = K.k[q][2] = K.k[q][3] = 0.0;
+    K.zero = 0;
+    for (int q = 0; q < w; ++q)
+      if (K.k[q][0] == 1.0 && K.k[q][1] == 0.0 && K.k[q][2] == 0.0 && K.k[q][3] == 0.0) K.zero |= 1ull << (w - 1 - q);
+    hipLaunchKernelGGL(sv_product_kernel, dim3(fill_grid(size)), dim3(kSvThreads), 0, stream, psi, size, K);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = run_gates(circuit, psi, nullptr, nullptr, stream);
+    for (int64_t b = 0; b < n_basis && e == hipSuccess; ++b) {
+      std::vector<cq_gate> rot;  // basis b: digit 1 X, 2 Y per measured slot
+      int64_t rest = b;
+      for (int u = o - 1; u >= 0; --u, rest /= 3) {
+        if (rest % 3 == 1) rot.push_back(u_gate(si.meas_slots[u], rot_x));
+        if (rest % 3 == 2) rot.push_back(u_gate(si.meas_slots[u], rot_y));
       }
-      for (int t = 0; t < r; ++t) {
-        const int bit = (c >> (r - 1 - t)) & 1;
-        for (int q = 0; q < 4; ++q) K.k[si.init_slots[t]][q] = init_ket[bit][q];
-      }
-      K.zero = 0;
-      for (int q = 0; q < w; ++q)
-        if (K.k[q][0] == 1.0 && K.k[q][1] == 0.0 && K.k[q][2] == 0.0 && K.k[q][3] == 0.0) K.zero |= 1ull << (w - 1 - q);
-      hipLaunchKernelGGL(sv_product_kernel, dim3(fill_grid(size)), dim3(kSvThreads), 0, stream, psi + c * size, size,
-                         K);
-      e = hipGetLastError();
-    }
-    for (size_t g = 0; g < circuit.size() && e == hipSuccess; ++g) {
-      TileGroup G = tile_group(w, circuit[g], gates, n_gates, {}, 0);
-      G.bstride = size;
-      hipLaunchKernelGGL(sv_reg_kernel<false>, dim3(tiles, (unsigned)nc), dim3(kSvThreads), 0, stream,
-                         (const double2*)psi, psi, (double*)nullptr, G);
-      e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(sv_combine_kernel, dim3(tiles), dim3(kSvThreads), 0, stream, (const double2*)psi, variants, GB,
-                         r);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) return sv_hip_error(e, "variant launch");
-    return CQ_OK;
-  }
-  for (int64_t j0 = 0; j0 < n_init; j0 += batch) {
-    const int64_t nb = std::min<int64_t>(batch, n_init - j0);
-    hipError_t e = hipSuccess;
-    for (int64_t jj = 0; jj < nb && e == hipSuccess; ++jj) {
-      const int64_t j = j0 + jj;
-      Kets K{};
-      K.n = w;
-      for (int q = 0; q < w; ++q) {
-        K.k[q][0] = 1.0;
-        K.k[q][1] = K.k[q][2] = K.k[q][3] = 0.0;
-      }
-      for (int t = 0; t < r; ++t) {
-        const int digit = (int)((j >> (2 * (r - 1 - t))) & 3);
-        for (int c = 0; c < 4; ++c) K.k[si.init_slots[t]][c] = init_ket[digit][c];
-      }
-      K.zero = 0;
-      for (int q = 0; q < w; ++q)
-        if (K.k[q][0] == 1.0 && K.k[q][1] == 0.0 && K.k[q][2] == 0.0 && K.k[q][3] == 0.0) K.zero |= 1ull << (w - 1 - q);
-      hipLaunchKernelGGL(sv_product_kernel, dim3(fill_grid(size)), dim3(kSvThreads), 0, stream, psi + jj * size, size,
-                         K);
-      e = hipGetLastError();
-    }
-    if (one_pass) {
-      // the circuit on every state of the batch (grid y = state), then one
-      // pass that reads each post-circuit tile once and writes every basis
-      for (size_t g = 0; g < circuit.size() && e == hipSuccess; ++g) {
-        TileGroup G = tile_group(w, circuit[g], gates, n_gates, {}, 0);
-        G.bstride = size;
-        hipLaunchKernelGGL(sv_reg_kernel<false>, dim3(tiles, (unsigned)nb), dim3(kSvThreads), 0, stream,
-                           (const double2*)psi, psi, (double*)nullptr, G);
-        e = hipGetLastError();
-      }
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(sv_reg_kernel<true>, dim3(tiles, (unsigned)nb), dim3(kSvThreads), 0, stream,
-                           (const double2*)psi, psi, variants + j0 * n_basis * size, GB);
-        e = hipGetLastError();
-      }
-    } else {
-      if (e == hipSuccess) e = run_gates(w, gates, n_gates, {}, psi, nullptr, stream);
-      for (int64_t b = 0; b < n_basis && e == hipSuccess; ++b) {
-        const std::vector<cq_gate> rot = basis_rot(b);
-        // the rotations read psi and write probabilities only, so psi stays
-        // the post-circuit state for the next basis; at most
-        // CQ_MAX_LOCAL_CUTS measured slots, so they form one group
-        double* out = variants + (j0 * n_basis + b) * size;
-        std::vector<Group> groups = make_groups(w, nullptr, 0, rot);
-        if (groups.empty()) groups.push_back(Group());
-        const TileGroup G = tile_group(w, groups[0], nullptr, 0, rot, 1);
-        e = launch_tiles(w, G, psi, psi, out, stream);
-      }
+      // at most CQ_MAX_LOCAL_CUTS rotations, so one pass that reads psi and
+      // writes probabilities only: psi stays the post-circuit state
+      e = run_gates(gate_set(w, rot.data(), (int)rot.size(), 0), psi, variants + (j * n_basis + b) * size, nullptr,
+                    stream);
     }
     if (e != hipSuccess) return sv_hip_error(e, "variant launch");
   }
