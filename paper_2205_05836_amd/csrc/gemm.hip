@@ -876,6 +876,20 @@ typedef float f4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline int swz(int row, int chunk) { return chunk ^ ((row & 3) << 2); }
 
+// An address every lane agrees on, in scalar registers.
+__device__ inline const char* uniform_ptr(const void* p) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
+// LDS DMA of 16 bytes a lane from base + voff (bytes) to LDS address dst
+// (uniform) + 16 lane.  Writing M0 asks for one wait state before an LDS DMA.
+__device__ inline void dma_lds16(uint32_t voff, const char* base, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               : : "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory", "m0");
+}
+
 // s_waitcnt vmcnt(N) lgkmcnt(0)
 template <int N>
 __device__ inline void wait_vm() {
@@ -1607,6 +1621,148 @@ gemm_f32t_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
+// FP64 operands, occupancy form (direct launches with 16-byte aligned rows).
+// The tiled kernel's 128 x 128 tile of eight waves leaves room for one
+// workgroup a compute unit, so its first loads, barriers and output stores
+// idle the matrix cores.  This form takes 64 x 128 tiles with four waves of
+// 32 x 64 (64 accumulator registers), stages of 8 labels (12 KB) by LDS DMA in
+// an NS-deep ring, so that WPE workgroups share a compute unit and one's waits
+// overlap the others' products.  Bound by the FP64 matrix rate, which vector
+// instructions share: with masks and 64-bit address arithmetic in every stage
+// the cores were busy 74% of the time, without them 87%.  30-qubit chain: 15.4
+// ms with the tiled kernel (44.6 TFLOP/s), 11.7, then 10.1 (68 TFLOP/s; a large
+// library product reaches 71).  MFMA block j of a 32-column group takes the columns
+// 2 (l % 16) + j, so one 16-byte LDS read feeds two blocks (a quarter wave
+// reads 256 consecutive bytes: no bank conflicts), and a lane's results of
+// the two blocks are neighbours: 16-byte output stores from registers, 256
+// bytes a row.  k runs in ascending steps of four as in the tiled kernel, so
+// the sums are the same bit for bit.
+// ---------------------------------------------------------------------------
+template <bool NT, int NS, int WPE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+gemm_f64t_kernel(GemmArgs g) {
+  constexpr int BM = 64, BN = 128, BK = 8;
+  constexpr int ROWA = BM * 8, ROWB = BN * 8;  // bytes of an operand row
+  constexpr int TILEA = BK * ROWA, STAGE = TILEA + BK * ROWB;
+  constexpr int LPW = 3;  // DMA instructions per wave per stage: 2 rows of A, 2 x 1 row of B
+  // the hand-counted vmcnt waits below assume LPW DMA loads per stage; the
+  // build checks the assembly against this marker
+  asm volatile("; cq-vm-lpw %0" ::"n"(LPW));
+  static_assert(NS >= 2 && NS <= 4, "stage count");
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
+  CQ_LDS char* const lsm = (CQ_LDS char*)smem;
+  const TileCoord tc = tile_coord<BM, BN>(g);
+  const int64_t m0 = tc.m0, n0 = tc.n0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+  const int nstages = (int)((g.K + BK - 1) / BK);
+  // wave w's instruction for A fills rows 2w and 2w + 1 (32 lanes each), its
+  // two for B rows w and w + 4; a lane fills 16 bytes (two columns).  Columns
+  // past the operand take its last ones (M, N are even); rows past K take row
+  // K - 1 and are masked to zero when read (K below one stage only: longer K
+  // are whole stages).  The address is a uniform base that advances by a
+  // stage, in scalar registers, and a per-lane offset that never changes.
+  const bool whole = nstages * BK == g.K;
+  const int64_t last = g.K - 1;
+  const int64_t ra = 2 * wave, rb0 = wave, rb1 = wave + 4;
+  const int64_t k0 = whole || ra <= last ? ra : last, k1 = whole || rb0 <= last ? rb0 : last,
+                k2 = whole || rb1 <= last ? rb1 : last;
+  const char* base[LPW] = {
+      uniform_ptr(static_cast<const double*>(g.A) + tc.z * g.sAz + k0 * g.sAk + m0),
+      uniform_ptr(static_cast<const double*>(g.B) + tc.z * g.sBz + k1 * g.sBk + n0),
+      uniform_ptr(static_cast<const double*>(g.B) + tc.z * g.sBz + k2 * g.sBk + n0)};
+  const int64_t stepA = BK * 8 * g.sAk, stepB = BK * 8 * g.sBk;
+  uint32_t voff[2];
+  {
+    const int64_t capA = g.M - 2 - m0, capB = g.N - 2 - n0;
+    const int64_t ca = 2 * (lane & 31), cb = 2 * lane;
+    const bool next = lane >= 32 && (whole || ra + 1 <= last);
+    voff[0] = (uint32_t)(8 * ((next ? g.sAk : 0) + (ca > capA ? capA : ca)));
+    voff[1] = (uint32_t)(8 * (cb > capB ? capB : cb));
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lsm;
+  const uint32_t dstA = lds0 + wave * 2 * ROWA, dstB = lds0 + TILEA + wave * ROWB;
+  auto issue = [&](int slot) {
+    dma_lds16(voff[0], base[0], dstA + slot * STAGE);
+    dma_lds16(voff[1], base[1], dstB + slot * STAGE);
+    dma_lds16(voff[1], base[2], dstB + slot * STAGE + 4 * ROWB);
+    base[0] += stepA;
+    base[1] += stepB;
+    base[2] += stepB;
+  };
+  d4_t acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+  const int r = lane >> 4, c = lane & 15;
+  CQ_LDS char* const la = lsm + r * ROWA + (wm + 2 * c) * 8;
+  CQ_LDS char* const lb = lsm + TILEA + r * ROWB + (wn + 2 * c) * 8;
+  // one step of four labels from stage slot `slot`; `mask`: rows past K are zero
+  auto step = [&](int slot, int kk, bool mask) {
+    dv2 a = *(const CQ_LDS dv2*)(la + slot * STAGE + kk * ROWA);
+    dv2 b[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b[j] = *(const CQ_LDS dv2*)(lb + slot * STAGE + kk * ROWB + j * 256);
+    if (mask && kk + r >= g.K) a = b[0] = b[1] = dv2{0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j >> 1][j & 1], acc[i][j], 0, 0, 0);
+  };
+
+  if (whole) {
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+      if (s < nstages) issue(s);
+    // the ring is unrolled so that every LDS address is a constant offset:
+    // vector instructions cost matrix-core time here (FP64 products and the
+    // vector ALUs do not overlap)
+    for (int s0 = 0; s0 < nstages; s0 += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        if (s >= nstages) break;
+        // this wave's loads of stage s have landed once at most `ahead` later
+        // stages are outstanding; the barrier then covers every wave's loads
+        const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
+        if (ahead >= 2) wait_vm<2 * LPW>();
+        else if (ahead == 1) wait_vm<LPW>();
+        else wait_vm<0>();
+        __syncthreads();
+        if (s + NS - 1 < nstages) issue((u + NS - 1) % NS);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 4) step(u, kk, false);
+      }
+    }
+  } else {
+    issue(0);
+    wait_vm<0>();
+    __syncthreads();
+    step(0, 0, true);
+    if (g.K > 4) step(0, 4, true);
+  }
+
+  double* const C = static_cast<double*>(g.C) + tc.z * g.sCz;
+  const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        // item v of lane l is row l/16 + 4v of its block (of every second row
+        // of the wave's 32), column l%16 (of every second column of 32)
+        const int64_t m = m0 + wm + 2 * (r + 4 * v) + i, n = n0 + wn + 32 * j + 2 * c;
+        if (full || (m < g.M && n < g.N))
+          store_out<dv2, NT>(reinterpret_cast<dv2*>(C + m * g.ldc + n),
+                             dv2{g.alpha * acc[i][2 * j][v], g.alpha * acc[i][2 * j + 1][v]});
+      }
+}
+
+// ---------------------------------------------------------------------------
 // FP32 operands, 64 x 64 tiles: for GEMMs with few 128 x 128 tiles (a few
 // hundred outputs per side), four times as many workgroups reach the CUs.
 // Each wave owns one 32 x 32 block; stages hold 16 labels (4 KB per operand,
@@ -2107,6 +2263,27 @@ bool f32p_ok(const GemmArgs& a) {
          a.sCz % 4 == 0 && al(a.A) && al(a.B) && al(a.C);
 }
 
+// FP64 operands for the occupancy kernel: 16-byte aligned rows of an even
+// number of columns, in the operands and the output; K below one stage of
+// labels or whole stages (label counts are powers of four, so every K is);
+// and rows of A close enough for a 32-bit offset from one to the next
+bool f64t_ok(const GemmArgs& a) {
+  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+  return a.K >= 1 && (a.K < 8 || a.K % 8 == 0) && a.sAk >= 0 && a.sAk < (int64_t)1 << 28 && a.M >= 2 && a.N >= 2 && a.M % 2 == 0 && a.N % 2 == 0 && a.sAk % 2 == 0 && a.sBk % 2 == 0 &&
+         a.sAz % 2 == 0 && a.sBz % 2 == 0 && a.ldc % 2 == 0 && a.sCz % 2 == 0 && al(a.A) && al(a.B) && al(a.C);
+}
+
+hipError_t launch_f64t(GemmArgs a, bool nt, hipStream_t s) {
+  const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
+  a.tilesM = (a.M + 63) / 64;
+  a.tiles = a.tilesM * a.tilesN * z;
+  if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.tiles), block(256);
+  if (nt) hipLaunchKernelGGL((gemm_f64t_kernel<true, 3, 4>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_f64t_kernel<false, 3, 4>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 template <int SPLIT, bool F16>
 hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
@@ -2201,6 +2378,7 @@ hipError_t launch_variant(cq_precision prec, GemmArgs a, DType tc, bool nt, int 
   const int impl = v >> 1;
   switch (prec) {
     case CQ_FP64:
+      if (f64t_ok(a)) return launch_f64t(a, nt, stream);
       return nt ? launch(gemm_f64_kernel<true>, a, stream, 512) : launch(gemm_f64_kernel<false>, a, stream, 512);
     case CQ_FP32:
       // 0 = tiled kernel, 1 = 64 x 64 tiles (2 repeats 0), 3 = persistent
