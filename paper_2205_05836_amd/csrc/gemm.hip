@@ -1130,6 +1130,9 @@ __global__ void __launch_bounds__(256) gemm_h16a_kernel(GemmArgs gv, const GemmA
 // so the sums are the same bit for bit.  Operand stages are the latency the
 // kernel hides: with more workgroups resident, one workgroup's wait for its
 // next stage overlaps another's products and stores.
+// The ring is unrolled and the operands' bases advance in scalar registers:
+// with 64-bit address arithmetic and masks as vector instructions in every
+// stage the 30-qubit chain took 2.76 ms (split BF16), without 2.55.
 // ---------------------------------------------------------------------------
 template <int SPLIT, bool F16, int OUT, int NS, int WPE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
@@ -1152,43 +1155,44 @@ gemm_h16t_kernel(GemmArgs g) {
   CQ_LDS char* const lsm = (CQ_LDS char*)smem;
   const TileCoord tc = tile_coord<BM, BN>(g);
   const int64_t m0 = tc.m0, n0 = tc.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
   const int nstages = (int)((g.K + BK - 1) / BK);
-  // wave w's instruction for (operand, plane) fills rows 4w .. 4w + 3
-  const uint16_t* gbase[2][NP];
-  int64_t ccap[2];
+  // wave w's instruction for (operand, plane) fills rows 4w .. 4w + 3: a
+  // uniform base that advances by a stage in scalar registers, and a per-lane
+  // offset that never changes.  Rows past K take row K - 1 and are masked to
+  // zero when read (K below one stage only: longer K are whole stages).
+  const bool whole = nstages * BK == g.K;
+  const int lrow = lane >> 4;
+  const int64_t row0 = whole || 4 * wave < g.K ? 4 * wave : g.K - 1;
+  const char* base[2][NP];
+  uint32_t voff[2];
   {
-    const int64_t za = tc.z * g.sAz, zb = tc.z * g.sBz;
-    gbase[0][0] = static_cast<const uint16_t*>(g.A) + za + m0;
-    gbase[1][0] = static_cast<const uint16_t*>(g.B) + zb + n0;
+    const int64_t za = tc.z * g.sAz + row0 * g.sAk + m0, zb = tc.z * g.sBz + row0 * g.sBk + n0;
+    base[0][0] = uniform_ptr(static_cast<const uint16_t*>(g.A) + za);
+    base[1][0] = uniform_ptr(static_cast<const uint16_t*>(g.B) + zb);
     if constexpr (NP == 2) {
-      gbase[0][NP - 1] = static_cast<const uint16_t*>(g.A_lo) + za + m0;
-      gbase[1][NP - 1] = static_cast<const uint16_t*>(g.B_lo) + zb + n0;
+      base[0][NP - 1] = uniform_ptr(static_cast<const uint16_t*>(g.A_lo) + za);
+      base[1][NP - 1] = uniform_ptr(static_cast<const uint16_t*>(g.B_lo) + zb);
     }
-    ccap[0] = ((g.M - 8) & ~(int64_t)7) - m0;
-    ccap[1] = ((g.N - 8) & ~(int64_t)7) - n0;
-  }
-  const int pc = wave * 64 + lane;  // 16-byte chunk of the stage plane this lane fills
-  const int lrow = pc >> 4;
-  int64_t lcol[2];
+    // last 8-column chunk that stays inside the operand (M, N >= 8)
+    const int64_t cap[2] = {((g.M - 8) & ~(int64_t)7) - m0, ((g.N - 8) & ~(int64_t)7) - n0};
+    const int64_t more = whole || row0 + lrow < g.K ? lrow : g.K - 1 - row0;
 #pragma unroll
-  for (int op = 0; op < 2; ++op) {
-    lcol[op] = (int64_t)swz(lrow, pc & 15) * 8;
-    if (lcol[op] > ccap[op]) lcol[op] = ccap[op];
+    for (int op = 0; op < 2; ++op) {
+      const int64_t col = (int64_t)swz(lrow, lane & 15) * 8;
+      voff[op] = (uint32_t)(2 * (more * (op ? g.sBk : g.sAk) + (col > cap[op] ? cap[op] : col)));
+    }
   }
-  auto issue = [&](int s) {
-    int64_t k = (int64_t)s * BK + lrow;
-    if (k >= g.K) k = g.K - 1;  // rows past K are masked to zero when read
+  const int64_t step[2] = {BK * 2 * g.sAk, BK * 2 * g.sBk};
+  const uint32_t dst0 = (uint32_t)(uintptr_t)lsm + wave * 1024;
+  auto issue = [&](int slot) {
 #pragma unroll
     for (int op = 0; op < 2; ++op)
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
-        const uint16_t* src = gbase[op][p] + k * (op ? g.sBk : g.sAk) + lcol[op];
-        const uint32_t dst = __builtin_amdgcn_readfirstlane(
-            (uint32_t)(uintptr_t)(lsm + (s % NS) * STAGE + (op * NP + p) * TILE + wave * 1024));
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
-                     : "memory", "m0");
+        dma_lds16(voff[op], base[op][p], dst0 + slot * STAGE + (op * NP + p) * TILE);
+        base[op][p] += step[op];
       }
   };
   f16_t acc[2][2];
@@ -1198,52 +1202,47 @@ gemm_h16t_kernel(GemmArgs g) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  // a fragment's two reads: rows krow and krow + 4 (the same swizzle), the
+  // lane's columns of a 32-column block; one address per block serves every
+  // stage and plane by a constant offset
   const int grp = lane >> 4, r16 = lane & 15;
   const int col_in_blk = 16 * (grp & 1) + 4 * (r16 & 3);
   const int krow = 8 * (grp >> 1) + (r16 >> 2);
-  auto frag = [&](int tile, int c0, int64_t kvalid) -> V8 {
-    const int col = c0 + col_in_blk;
-    const int r0 = krow, r1 = r0 + 4;
-    const int o0 = tile + r0 * 256 + (swz(r0, col >> 3) << 4) + (col & 7) * 2;
-    const int o1 = tile + r1 * 256 + (swz(r1, col >> 3) << 4) + (col & 7) * 2;
-    s4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CQ_LDS s4_t*)(lsm + o0));
-    s4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CQ_LDS s4_t*)(lsm + o1));
-    if (kvalid < BK) {
+  CQ_LDS char *fa[2], *fb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int ca = wm + 32 * i + col_in_blk, cb = wn + 32 * i + col_in_blk;
+    fa[i] = lsm + krow * 256 + (swz(krow, ca >> 3) << 4) + (ca & 7) * 2;
+    fb[i] = lsm + NP * TILE + krow * 256 + (swz(krow, cb >> 3) << 4) + (cb & 7) * 2;
+  }
+  auto frag = [&](CQ_LDS char* at, bool mask) -> V8 {
+    s4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CQ_LDS s4_t*)at);
+    s4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CQ_LDS s4_t*)(at + 4 * 256));
+    if (mask) {
       // slot e of the two reads holds label 8*(grp>>1) + e (+4)
       const int kb = 8 * (grp >> 1);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (kb + e >= kvalid) lo[e] = 0;
-        if (kb + 4 + e >= kvalid) hi[e] = 0;
+        if (kb + e >= g.K) lo[e] = 0;
+        if (kb + 4 + e >= g.K) hi[e] = 0;
       }
     }
     typedef short s8_t __attribute__((ext_vector_type(8)));
     const s8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(V8, v);
   };
-
-  for (int s = 0; s < NS - 1 && s < nstages; ++s) issue(s);
-  for (int s = 0; s < nstages; ++s) {
-    // this wave's loads of stage s have landed once at most `ahead` later
-    // stages are outstanding; the barrier then covers every wave's loads
-    const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
-    if (ahead >= 2) wait_vm<2 * LPW>();
-    else if (ahead == 1) wait_vm<LPW>();
-    else wait_vm<0>();
-    __syncthreads();
-    if (s + NS - 1 < nstages) issue(s + NS - 1);
-    const int sb = (s % NS) * STAGE;
-    const int64_t kvalid = g.K - (int64_t)s * BK;
+  auto products = [&](int slot, bool mask) {
+    const int sb = slot * STAGE;
     V8 b[NP][2];
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[p][j] = frag(sb + (1 * NP + p) * TILE, wn + 32 * j, kvalid);
+      for (int j = 0; j < 2; ++j) b[p][j] = frag(fb[j] + sb + p * TILE, mask);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       V8 a[NP];
 #pragma unroll
-      for (int p = 0; p < NP; ++p) a[p] = frag(sb + (0 * NP + p) * TILE, wm + 32 * i, kvalid);
+      for (int p = 0; p < NP; ++p) a[p] = frag(fa[i] + sb + p * TILE, mask);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         acc[i][j] = H::mfma(a[0], b[0][j], acc[i][j]);
@@ -1255,6 +1254,34 @@ gemm_h16t_kernel(GemmArgs g) {
       // keep the second block's fragment reads after the first block's products
       __builtin_amdgcn_sched_barrier(0);
     }
+  };
+
+  if (whole) {
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+      if (s < nstages) issue(s);
+    // the ring unrolled: every LDS address is a constant offset
+    for (int s0 = 0; s0 < nstages; s0 += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        if (s >= nstages) break;
+        // this wave's loads of stage s have landed once at most `ahead` later
+        // stages are outstanding; the barrier then covers every wave's loads
+        const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
+        if (ahead >= 2) wait_vm<2 * LPW>();
+        else if (ahead == 1) wait_vm<LPW>();
+        else wait_vm<0>();
+        __syncthreads();
+        if (s + NS - 1 < nstages) issue((u + NS - 1) % NS);
+        products(u, false);
+      }
+    }
+  } else {
+    issue(0);
+    wait_vm<0>();
+    __syncthreads();
+    products(0, true);
   }
 
   // epilogue: slab u of a wave holds rows 32*(u>>2) + 8*(u&3) .. +7 of its
@@ -1490,7 +1517,9 @@ __global__ void __launch_bounds__(256) gemm_h16s_kernel(GemmArgs g) {
 // by halves as in PersistF32.  Fragment reads, the product order (k ascending
 // in pairs, one 32x32x2 FP32 MFMA per pair and block) and the short-K
 // handling are those of the persistent FP32 kernel, so the sums are the same
-// bit for bit.
+// bit for bit.  Bound by the FP32 matrix rate: the 30-qubit chain takes 5.05
+// ms (136 TFLOP/s; 5.93 ms with vector address arithmetic in every stage); a
+// large library product reaches 153 TFLOP/s.
 // ---------------------------------------------------------------------------
 template <int OUT, int NS, int WPE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
@@ -1510,34 +1539,35 @@ gemm_f32t_kernel(GemmArgs g) {
   CQ_LDS char* const lsm = (CQ_LDS char*)smem;
   const TileCoord tc = tile_coord<BM, BN>(g);
   const int64_t m0 = tc.m0, n0 = tc.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
   const int nstages = (int)((g.K + BK - 1) / BK);
   // wave w's instruction for an operand fills rows 2w (lanes 0-31) and
-  // 2w + 1 (lanes 32-63); lane slot q of row r holds the row's chunk q ^ 8r
+  // 2w + 1 (lanes 32-63); lane slot q of row r holds the row's chunk q ^ 8r.
+  // Addresses as in gemm_h16t_kernel: a uniform base that advances by a stage
+  // and a fixed per-lane offset.
+  const bool whole = nstages * BK == g.K;
   const int r = lane >> 5, c = lane & 31;
-  const int lrow = 2 * wave + r;
-  const float* gbase[2];
-  int64_t lcol[2];
+  const int64_t row0 = whole || 2 * wave < g.K ? 2 * wave : g.K - 1;
+  const char* base[2] = {uniform_ptr(static_cast<const float*>(g.A) + tc.z * g.sAz + row0 * g.sAk + m0),
+                         uniform_ptr(static_cast<const float*>(g.B) + tc.z * g.sBz + row0 * g.sBk + n0)};
+  uint32_t voff[2];
   {
-    gbase[0] = static_cast<const float*>(g.A) + tc.z * g.sAz + m0;
-    gbase[1] = static_cast<const float*>(g.B) + tc.z * g.sBz + n0;
     // last 16-byte chunk inside each operand (M, N are multiples of 4)
-    const int64_t capA = ((g.M - 4) & ~(int64_t)3) - m0, capB = ((g.N - 4) & ~(int64_t)3) - n0;
+    const int64_t cap[2] = {((g.M - 4) & ~(int64_t)3) - m0, ((g.N - 4) & ~(int64_t)3) - n0};
     const int64_t col = (int64_t)(c ^ (8 * r)) * 4;
-    lcol[0] = col > capA ? capA : col;
-    lcol[1] = col > capB ? capB : col;
+    const bool next = r && (whole || row0 + 1 < g.K);
+#pragma unroll
+    for (int op = 0; op < 2; ++op)
+      voff[op] = (uint32_t)(4 * ((next ? (op ? g.sBk : g.sAk) : 0) + (col > cap[op] ? cap[op] : col)));
   }
-  auto issue = [&](int s) {
-    int64_t k = (int64_t)s * BK + lrow;
-    if (k >= g.K) k = g.K - 1;  // rows past K are masked to zero when read
+  const int64_t step[2] = {BK * 4 * g.sAk, BK * 4 * g.sBk};
+  const uint32_t dst0 = (uint32_t)(uintptr_t)lsm + wave * 1024;
+  auto issue = [&](int slot) {
 #pragma unroll
     for (int op = 0; op < 2; ++op) {
-      const float* src = gbase[op] + k * (op ? g.sBk : g.sAk) + lcol[op];
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(
-          (uint32_t)(uintptr_t)(lsm + (s % NS) * STAGE + op * TILE + wave * 1024));
-      asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
-                   : "memory", "m0");
+      dma_lds16(voff[op], base[op], dst0 + slot * STAGE + op * TILE);
+      base[op] += step[op];
     }
   };
   f16_t acc[2][2];
@@ -1547,37 +1577,59 @@ gemm_f32t_kernel(GemmArgs g) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  CQ_LDS char *fa[2], *fb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int ca = wm + 32 * i + c, cb = wn + 32 * i + c;
+    fa[i] = lsm + r * 512 + (((ca >> 2) ^ (8 * r)) << 4) + (ca & 3) * 4;
+    fb[i] = lsm + TILE + r * 512 + (((cb >> 2) ^ (8 * r)) << 4) + (cb & 3) * 4;
+  }
+  // two labels, kk and kk + 1, of the stage in `slot`
+  auto pair = [&](int slot, int kk, bool mask) {
+    float a[2], b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a[i] = *(const CQ_LDS float*)(fa[i] + slot * STAGE + kk * 512);
+      b[i] = *(const CQ_LDS float*)(fb[i] + slot * STAGE + kk * 512);
+      if (mask && kk + r >= g.K) a[i] = 0.0f;  // rows past K hold a clamped copy of row K - 1
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+  };
 
-  for (int s = 0; s < NS - 1 && s < nstages; ++s) issue(s);
-  for (int s = 0; s < nstages; ++s) {
-    // this wave's loads of stage s have landed once at most `ahead` later
-    // stages are outstanding; the barrier then covers every wave's loads
-    const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
-    if (ahead >= 2) wait_vm<2 * LPW>();
-    else if (ahead == 1) wait_vm<LPW>();
-    else wait_vm<0>();
+  if (whole) {
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+      if (s < nstages) issue(s);
+    // the ring unrolled: every LDS address is a constant offset
+    for (int s0 = 0; s0 < nstages; s0 += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        if (s >= nstages) break;
+        // this wave's loads of stage s have landed once at most `ahead` later
+        // stages are outstanding; the barrier then covers every wave's loads
+        const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
+        if (ahead >= 2) wait_vm<2 * LPW>();
+        else if (ahead == 1) wait_vm<LPW>();
+        else wait_vm<0>();
+        __syncthreads();
+        if (s + NS - 1 < nstages) issue((u + NS - 1) % NS);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 2) pair(u, kk, false);
+      }
+    }
+  } else {
+    issue(0);
+    wait_vm<0>();
     __syncthreads();
-    if (s + NS - 1 < nstages) issue(s + NS - 1);
-    const int sb = (s % NS) * STAGE;
-    const int64_t kvalid = g.K - (int64_t)s * BK;
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 2) {
-      if (kk >= kvalid) break;  // short K (outer products): skip all-zero steps
-      const int row = kk + r;
-      float a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int ca = wm + 32 * i + c, cb = wn + 32 * i + c;
-        a[i] = *(const CQ_LDS float*)(lsm + sb + row * 512 + (((ca >> 2) ^ (8 * r)) << 4) + (ca & 3) * 4);
-        b[i] = *(const CQ_LDS float*)(lsm + sb + TILE + row * 512 + (((cb >> 2) ^ (8 * r)) << 4) +
-                                      (cb & 3) * 4);
-        if (row >= kvalid) a[i] = 0.0f;  // rows past K hold a clamped copy of row K - 1
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      if (kk >= g.K) break;  // short K (outer products): skip all-zero steps
+      pair(0, kk, true);
     }
   }
 
@@ -2250,9 +2302,17 @@ bool h16p_ok(const GemmArgs& a, DType tc) {
   return a.rowexp == nullptr && a.K >= 1 && h16_async_ok(a, tc);
 }
 
-// the occupancy kernel applies: K >= 1, aligned rows (it applies output
-// exponents in its epilogue)
-bool h16t_ok(const GemmArgs& a, DType tc) { return a.K >= 1 && h16_async_ok(a, tc); }
+// K and row strides the occupancy kernels' addresses take: K below one stage
+// of `stage` labels or whole stages (K counts labels, a power of four, so
+// every K is), and four rows within a 32-bit byte offset
+bool ring_ok(const GemmArgs& a, int stage) {
+  return a.K >= 1 && (a.K < stage || a.K % stage == 0) && a.sAk >= 0 && a.sBk >= 0 && a.sAk < (int64_t)1 << 28 &&
+         a.sBk < (int64_t)1 << 28;
+}
+
+// the occupancy kernel applies: aligned rows (it applies output exponents in
+// its epilogue)
+bool h16t_ok(const GemmArgs& a, DType tc) { return ring_ok(a, 16) && h16_async_ok(a, tc); }
 
 // FP32 operands for the persistent kernel: 16-byte aligned rows of at least
 // 4 columns, and an output whose rows take 16-byte stores
@@ -2264,12 +2324,10 @@ bool f32p_ok(const GemmArgs& a) {
 }
 
 // FP64 operands for the occupancy kernel: 16-byte aligned rows of an even
-// number of columns, in the operands and the output; K below one stage of
-// labels or whole stages (label counts are powers of four, so every K is);
-// and rows of A close enough for a 32-bit offset from one to the next
+// number of columns, in the operands and the output
 bool f64t_ok(const GemmArgs& a) {
   auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  return a.K >= 1 && (a.K < 8 || a.K % 8 == 0) && a.sAk >= 0 && a.sAk < (int64_t)1 << 28 && a.M >= 2 && a.N >= 2 && a.M % 2 == 0 && a.N % 2 == 0 && a.sAk % 2 == 0 && a.sBk % 2 == 0 &&
+  return ring_ok(a, 8) && a.M >= 2 && a.N >= 2 && a.M % 2 == 0 && a.N % 2 == 0 && a.sAk % 2 == 0 && a.sBk % 2 == 0 &&
          a.sAz % 2 == 0 && a.sBz % 2 == 0 && a.ldc % 2 == 0 && a.sCz % 2 == 0 && al(a.A) && al(a.B) && al(a.C);
 }
 
@@ -2283,6 +2341,8 @@ hipError_t launch_f64t(GemmArgs a, bool nt, hipStream_t s) {
   else hipLaunchKernelGGL((gemm_f64t_kernel<false, 3, 4>), grid, block, 0, s, a);
   return hipGetLastError();
 }
+
+bool f32t_ok(const GemmArgs& a) { return ring_ok(a, 8) && f32p_ok(a); }
 
 template <int SPLIT, bool F16>
 hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
@@ -2385,8 +2445,8 @@ hipError_t launch_variant(cq_precision prec, GemmArgs a, DType tc, bool nt, int 
       // kernel, 4 and 5 = occupancy kernel (four workgroups per CU with a
       // three- or four-deep ring)
       if (impl == 1 && f32p_ok(a)) return launch_f32s<3>(a, nt, stream);
-      if (impl == 4 && f32p_ok(a)) return launch_f32t<3, 4>(a, nt, stream);
-      if (impl == 5 && f32p_ok(a)) return launch_f32t<4, 4>(a, nt, stream);
+      if (impl == 4 && f32t_ok(a)) return launch_f32t<3, 4>(a, nt, stream);
+      if (impl == 5 && f32t_ok(a)) return launch_f32t<4, 4>(a, nt, stream);
       if (impl == 3 && f32p_ok(a)) {
         const int64_t grid = persistent_grid(a.tiles);
         if (nt) hipLaunchKernelGGL((gemm_persist_kernel<PersistF32, 1, 4>), dim3((unsigned)grid), dim3(256), 0, stream, a);
@@ -2538,7 +2598,7 @@ bool variant_applies(cq_precision prec, const GemmArgs& a, DType tc, int v) {
   const int impl = v >> 1;
   if (impl == 0) return true;
   if (v >= variant_count(prec)) return false;
-  if (prec == CQ_FP32) return (impl == 1 || impl >= 3) && f32p_ok(a);
+  if (prec == CQ_FP32) return impl >= 4 ? f32t_ok(a) : (impl == 1 || impl == 3) && f32p_ok(a);
   if (impl == 4 || impl == 5) return h16t_ok(a, tc);
   return impl == 3 ? h16p_ok(a, tc) : h16_async_ok(a, tc);
 }
