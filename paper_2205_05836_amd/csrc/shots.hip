@@ -28,38 +28,109 @@ constexpr int kThreads = 256;
 constexpr int kPer = kBlock / kThreads;
 constexpr int kPad = kPer + 1;          // LDS words per thread run (one pad word)
 constexpr int kScanThreads = 1024;      // row scans of block sums and counts
-constexpr int kShotsPerThread = 64;
-constexpr int kShotsPerGroup = kThreads * kShotsPerThread;
+constexpr int kMaxShotsPerThread = 64;  // a shot group: 256 threads of 1..64 shots each
 constexpr int kLdsBins = 4096;          // rows with at most this many blocks search and count in LDS
 constexpr int kFewShots = 64;           // blocks with at most this many shots resolve in registers
+constexpr int kSparseShots = 16;        // shots per block on average up to which only the runs with shots are read again
+constexpr int kRun = 64;                // entries of a run, one a lane
+constexpr int kRuns = kBlock / kRun;
+// rows of one block that a workgroup takes whole: with at most so many shots,
+// or so many rows that the chip is full anyway (else the shots of a row are
+// spread over workgroups)
+constexpr int64_t kRowShots = 16384;
+constexpr int64_t kRowRows = 256;
 
 __device__ inline uint64_t quant52(double p) {
   const double c = p > 0.0 ? (p < 1.0 ? p : 1.0) : 0.0;
   return (uint64_t)(c * 0x1p52);
 }
 
-// Pass 1: the quantised sum of every block of a row (coalesced), and the
-// block's shot counters cleared.
+typedef double d2_t __attribute__((ext_vector_type(2)));
+
+// v of the lane that DPP control CTRL names (a row holds 16 lanes)
+template <int CTRL>
+__device__ inline unsigned long long dpp_u64(unsigned long long v) {
+  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, true);
+  return (unsigned long long)(uint32_t)lo | ((unsigned long long)(uint32_t)hi << 32);
+}
+
+// Pass 1: the quantised sum of every run of 64 entries and of every block of
+// a row (one read of the table, which bounds it), and the block's shot
+// counters cleared.  A thread sums eight neighbours, so a run is eight lanes:
+// three cross-lane additions (pairs, quads, halves of a row) that stay in the
+// vector ALU.  With runs spread over a wave's 64 lanes (one coalesced load
+// each) the ten exchanges through LDS made the pass 1.17 ms at 144 x 2^22
+// (4.8 GB) against 0.79; without run sums it takes 0.75.  Rows off the
+// 16-byte alignment, whose loads would be 64 bytes apart and half as wide, go
+// through LDS (49 us at 3189 x 13059 without run sums, 78 that way).  RUNS
+// only where a resolution form reads them.
+template <bool RUNS>
 __global__ void __launch_bounds__(kThreads) shots_bsum_kernel(const double* __restrict__ P, int64_t cols,
                                                               int64_t nblk, uint64_t* __restrict__ bend,
+                                                              uint64_t* __restrict__ runs,
                                                               uint32_t* __restrict__ bcnt,
                                                               uint32_t* __restrict__ bfill) {
+  static_assert(kPer == 8 && kRun == 64 && kThreads == 256, "eight lanes sum a run");
   const int64_t row = blockIdx.y, blk = blockIdx.x;
   const double* p = P + row * cols + blk * kBlock;
-  const int64_t n = cols - blk * kBlock < kBlock ? cols - blk * kBlock : kBlock;
-  __shared__ unsigned long long part[kThreads];
-  unsigned long long s = 0;
-#pragma unroll 4
-  for (int e = threadIdx.x; e < n; e += kThreads) s += quant52(__builtin_nontemporal_load(p + e));
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = kThreads / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) part[threadIdx.x] += part[threadIdx.x + h];
-    __syncthreads();
+  const int n = (int)(cols - blk * kBlock < kBlock ? cols - blk * kBlock : kBlock);
+  const int64_t k = row * nblk + blk;
+  unsigned long long t = 0;
+  if constexpr (RUNS) {
+    __shared__ double stage[kThreads * kPad];
+    const int e0 = threadIdx.x * kPer;
+    double x[kPer];
+    if (n == kBlock && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+#pragma unroll
+      for (int q = 0; q < kPer / 2; ++q) {
+        const d2_t y = reinterpret_cast<const d2_t*>(p + e0)[q];
+        x[2 * q] = y[0];
+        x[2 * q + 1] = y[1];
+      }
+    } else {
+      // (unconditional loads, so that all eight are in flight)
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int e = threadIdx.x + q * kThreads;
+        x[q] = __builtin_nontemporal_load(p + (e < n ? e : n - 1));
+      }
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int e = threadIdx.x + q * kThreads;
+        stage[(e / kPer) * kPad + e % kPer] = e < n ? x[q] : 0.0;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) x[e] = stage[threadIdx.x * kPad + e];
+    }
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) t += quant52(x[e]);
+    t += dpp_u64<0xb1>(t);   // quad_perm [1, 0, 3, 2]
+    t += dpp_u64<0x4e>(t);   // quad_perm [2, 3, 0, 1]
+    t += dpp_u64<0x141>(t);  // row_half_mirror: the other quad of eight
+    if ((threadIdx.x & 7) == 0) runs[k * kRuns + (threadIdx.x >> 3)] = t;
+  } else {
+    double x[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int e = threadIdx.x + q * kThreads;
+      x[q] = __builtin_nontemporal_load(p + (e < n ? e : n - 1));
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) t += (int)threadIdx.x + q * kThreads < n ? quant52(x[q]) : 0ull;
+    t += dpp_u64<0xb1>(t);
+    t += dpp_u64<0x4e>(t);
+    t += dpp_u64<0x141>(t);
   }
+  t += dpp_u64<0x140>(t);  // row_mirror: the other half of a row
+  t += (unsigned long long)__shfl_xor((long long)t, 16);
+  t += (unsigned long long)__shfl_xor((long long)t, 32);
+  __shared__ unsigned long long part[kThreads / 64];
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const int64_t k = row * nblk + blk;
-    bend[k] = part[0];
+    bend[k] = (part[0] + part[1]) + (part[2] + part[3]);
     bcnt[k] = 0;
     bfill[k] = 0;
   }
@@ -137,16 +208,16 @@ __device__ inline void shot_target(const uint64_t* __restrict__ E, int64_t nblk,
 }
 
 // Pass 3: shots per block.  grid (shot groups, rows); a group takes
-// kShotsPerGroup consecutive shots of one row and, for rows of at most
+// 256 * per consecutive shots of one row and, for rows of at most
 // kLdsBins blocks, searches the block ends and counts its shots in LDS
 // before one global add per block hit.  A row of one block needs no
 // counting at all.
 __global__ void __launch_bounds__(kThreads) shots_count_kernel(const uint64_t* __restrict__ bend, int64_t nblk,
-                                                               int64_t shots, uint64_t seed,
+                                                               int64_t shots, uint64_t seed, int per,
                                                                uint32_t* __restrict__ bcnt) {
   __shared__ uint32_t hist[kLdsBins];
   __shared__ uint64_t Es[kLdsBins];
-  const int64_t row = blockIdx.y, s0 = (int64_t)blockIdx.x * kShotsPerGroup;
+  const int64_t row = blockIdx.y, s0 = (int64_t)blockIdx.x * per * kThreads;
   const uint64_t* E = bend + row * nblk;
   uint32_t* cnt = bcnt + row * nblk;
   const uint64_t T = E[nblk - 1];
@@ -157,7 +228,7 @@ __global__ void __launch_bounds__(kThreads) shots_count_kernel(const uint64_t* _
   }
   if (nblk > kLdsBins) {
 #pragma unroll 4
-    for (int j = 0; j < kShotsPerThread; ++j) {
+    for (int j = 0; j < per; ++j) {
       const int64_t s = s0 + j * kThreads + threadIdx.x;
       if (s < shots) {
         uint64_t t;
@@ -174,7 +245,7 @@ __global__ void __launch_bounds__(kThreads) shots_count_kernel(const uint64_t* _
   }
   __syncthreads();
 #pragma unroll 4
-  for (int j = 0; j < kShotsPerThread; ++j) {
+  for (int j = 0; j < per; ++j) {
     const int64_t s = s0 + j * kThreads + threadIdx.x;
     if (s < shots) {
       uint64_t t;
@@ -203,13 +274,13 @@ __global__ void __launch_bounds__(kScanThreads) shots_bptr_kernel(uint32_t* __re
 // run from LDS, so a group's shots of one bucket land next to each other
 // (plain stores, so that L2 merges each run before it goes to HBM).
 __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t* __restrict__ bend, int64_t nblk,
-                                                                 int64_t shots, uint64_t seed,
+                                                                 int64_t shots, uint64_t seed, int per,
                                                                  const uint32_t* __restrict__ bptr,
                                                                  uint32_t* __restrict__ bfill,
                                                                  uint64_t* __restrict__ slots) {
   __shared__ uint32_t hist[kLdsBins];  // group counts, then the next position in each bucket
   __shared__ uint64_t Es[kLdsBins];
-  const int64_t row = blockIdx.y, s0 = (int64_t)blockIdx.x * kShotsPerGroup;
+  const int64_t row = blockIdx.y, s0 = (int64_t)blockIdx.x * per * kThreads;
   const uint64_t* E = bend + row * nblk;
   const uint32_t* ptr = bptr + row * nblk;
   uint32_t* fill = bfill + row * nblk;
@@ -218,7 +289,7 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
   if (T == 0) return;
   if (nblk == 1) {
 #pragma unroll 4
-    for (int j = 0; j < kShotsPerThread; ++j) {
+    for (int j = 0; j < per; ++j) {
       const int64_t s = s0 + j * kThreads + threadIdx.x;
       if (s < shots) {
         uint64_t t;
@@ -231,7 +302,7 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
   }
   if (nblk > kLdsBins) {
 #pragma unroll 4
-    for (int j = 0; j < kShotsPerThread; ++j) {
+    for (int j = 0; j < per; ++j) {
       const int64_t s = s0 + j * kThreads + threadIdx.x;
       if (s < shots) {
         uint64_t t;
@@ -249,7 +320,7 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
   }
   __syncthreads();
 #pragma unroll 4
-  for (int j = 0; j < kShotsPerThread; ++j) {
+  for (int j = 0; j < per; ++j) {
     const int64_t s = s0 + j * kThreads + threadIdx.x;
     if (s < shots) {
       uint64_t t;
@@ -263,7 +334,7 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
     if (hist[b]) hist[b] = ptr[b] + atomicAdd(&fill[b], hist[b]);
   __syncthreads();
 #pragma unroll 4
-  for (int j = 0; j < kShotsPerThread; ++j) {
+  for (int j = 0; j < per; ++j) {
     const int64_t s = s0 + j * kThreads + threadIdx.x;
     if (s < shots) {
       uint64_t t;
@@ -275,16 +346,102 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
   }
 }
 
-typedef double d2_t __attribute__((ext_vector_type(2)));
+// count / shots, 0 written as 0
+__device__ inline double freq_of(uint32_t c, double ds) { return c ? (double)c / ds : 0.0; }
 
-// Pass 6, blocks with at most kFewShots shots (the usual case: a few shots
-// per block of 2048 outcomes): thread t holds entries t kPer .. t kPer +
-// kPer - 1 in registers, the block scan gives its run's offset, and every
-// thread tests the block's targets against its run (the first entry whose
-// inclusive prefix exceeds the target), counting in registers.  No LDS
-// staging of the entries, so many more blocks stay resident than in the LDS
-// form below; the counts, hence the frequencies, are the same.  A block
-// without shots writes zeros without reading its entries.
+__device__ inline uint64_t lane_u64(uint64_t v, int lane) {  // lane uniform
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32);
+}
+
+// Pass 6, tables with few shots a block (up to kSparseShots on average): a
+// wave per block, blocks with at most kFewShots shots.  It writes the block's
+// zeros first, then finds each shot -- the run sums tell the run, the run's 64
+// entries (one a lane) the entry -- and stores count / shots over the zero.
+// So 512 bytes a shot are read again instead of the block's 16 KB, and the
+// chain of dependent loads of a block hides behind its zeros and the other
+// waves.  Bound by writing the frequencies: 144 x 2^22 with 8192 shots a row
+// takes 1.0 ms for 4.8 GB (1.74 ms when every block was read again).
+__global__ void __launch_bounds__(kThreads) shots_resolve_sparse_kernel(const double* __restrict__ P, int64_t cols,
+                                                                        int64_t nblk, int64_t total, int64_t shots,
+                                                                        const uint64_t* __restrict__ runs,
+                                                                        const uint32_t* __restrict__ bcnt,
+                                                                        const uint32_t* __restrict__ bptr,
+                                                                        const uint64_t* __restrict__ slots,
+                                                                        double* __restrict__ F) {
+  constexpr int kAtOnce = 4;  // shots whose loads are in flight together
+  const int lane = threadIdx.x & 63;
+  const int64_t k = (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (k >= total) return;
+  const int64_t row = k / nblk, c0 = (k - row * nblk) * kBlock;
+  const int n = (int)(cols - c0 < kBlock ? cols - c0 : kBlock);
+  const int m = (int)__builtin_amdgcn_readfirstlane((int)bcnt[k]);
+  if ((uint32_t)m > (uint32_t)kFewShots) return;
+  // the loads that need nothing but m, then the zeros
+  const uint64_t own = m && lane < kRuns ? runs[k * kRuns + lane] : 0ull;
+  const uint64_t target = lane < m ? slots[row * shots + bptr[k] + lane] : 0ull;
+  double* f = F + row * cols + c0;
+  if (n == kBlock && (reinterpret_cast<uintptr_t>(f) & 15) == 0) {
+#pragma unroll
+    for (int q = 0; q < kBlock / 128; ++q)
+      __builtin_nontemporal_store(d2_t{0.0, 0.0}, reinterpret_cast<d2_t*>(f) + lane + 64 * q);
+  } else {
+    for (int e = lane; e < n; e += 64) __builtin_nontemporal_store(0.0, f + e);
+  }
+  if (m == 0) return;
+  unsigned long long incl = own;
+#pragma unroll
+  for (int d = 1; d < kRuns; d <<= 1) {
+    const unsigned long long y = __shfl_up(incl, d);
+    if (lane >= d) incl += y;
+  }
+  const unsigned long long excl = incl - own;
+  const double* p = P + row * cols + c0;
+  int hit = 0;  // lane j: shot j's entry
+  for (int q0 = 0; q0 < m; q0 += kAtOnce) {
+    double x[kAtOnce];
+    uint64_t t[kAtOnce];
+    int run[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      // past the last shot its target is taken again, and not kept
+      t[q] = lane_u64(target, q0 + q < m ? q0 + q : m - 1);
+      // the first run whose inclusive end exceeds the target (there is one
+      // unless the row's sum overflowed 64 bits: then any run, in bounds)
+      const int r = __ffsll((unsigned long long)__ballot(lane < kRuns && incl > t[q])) - 1;
+      run[q] = r < 0 ? 0 : r;
+      t[q] -= lane_u64(excl, run[q]);
+      const int e = run[q] * kRun + lane;
+      x[q] = e < n ? p[e] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      unsigned long long c = quant52(x[q]);
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long y = __shfl_up(c, d);
+        if (lane >= d) c += y;
+      }
+      const int e = __ffsll((unsigned long long)__ballot(c > t[q])) - 1;
+      if (lane == q0 + q) hit = run[q] * kRun + (e < 0 ? 0 : e);
+    }
+  }
+  int c = 0;
+  for (int j = 0; j < m; ++j) c += __builtin_amdgcn_readlane(hit, j) == hit ? 1 : 0;
+  // the zeros are written before any count goes over them
+  __builtin_amdgcn_s_waitcnt((0) | (7 << 4) | (15 << 8));  // vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if (lane < m && hit < n) f[hit] = (double)c / (double)shots;
+}
+
+// Pass 6, tables with more shots a block: blocks with at most kFewShots shots
+// in a workgroup each.  Thread t holds entries t kPer .. t kPer + kPer - 1 in
+// registers, the block scan gives its run's offset, and every thread tests the
+// block's targets against its run (the first entry whose inclusive prefix
+// exceeds the target), counting in registers.  No LDS staging of the entries,
+// so many more blocks stay resident than in the LDS form below.  A block
+// without shots writes zeros without reading its entries.  All forms give the
+// same counts.
 __global__ void __launch_bounds__(kThreads) shots_resolve_few_kernel(const double* __restrict__ P, int64_t cols,
                                                                      int64_t nblk, int64_t shots,
                                                                      const uint32_t* __restrict__ bcnt,
@@ -363,13 +520,13 @@ __global__ void __launch_bounds__(kThreads) shots_resolve_few_kernel(const doubl
   if (vec) {
 #pragma unroll
     for (int q = 0; q < kPer / 2; ++q) {
-      const d2_t y = {c[2 * q] ? (double)c[2 * q] / ds : 0.0, c[2 * q + 1] ? (double)c[2 * q + 1] / ds : 0.0};
+      const d2_t y = {freq_of(c[2 * q], ds), freq_of(c[2 * q + 1], ds)};
       reinterpret_cast<d2_t*>(f + e0)[q] = y;
     }
   } else {
 #pragma unroll
     for (int e = 0; e < kPer; ++e)
-      if (e0 + e < n) __builtin_nontemporal_store(c[e] ? (double)c[e] / ds : 0.0, f + e0 + e);
+      if (e0 + e < n) __builtin_nontemporal_store(freq_of(c[e], ds), f + e0 + e);
   }
 }
 
@@ -385,22 +542,18 @@ struct ResolveLds {
   unsigned long long wtot[kThreads / 64];
 };
 
-__device__ __forceinline__ void resolve_block_lds(ResolveLds& L, const double* __restrict__ P, int64_t cols,
-                                                  int64_t nblk, int64_t shots, int64_t k, uint32_t m,
-                                                  const uint32_t* __restrict__ bptr,
-                                                  const uint64_t* __restrict__ slots, double* __restrict__ F) {
-  const int64_t row = k / nblk, blk = k - row * nblk;
-  const int64_t c0 = blk * kBlock;
-  const int n = (int)(cols - c0 < kBlock ? cols - c0 : kBlock);
-  double* f = F + row * cols + c0;
-  if (m == 0) {
-    for (int e = threadIdx.x; e < n; e += kThreads) __builtin_nontemporal_store(0.0, f + e);
-    return;
-  }
-  const double* p = P + row * cols + c0;
+// The inclusive prefix of n quantised entries into L.C, counts cleared.
+__device__ __forceinline__ void block_prefix_lds(ResolveLds& L, const double* __restrict__ p, int n) {
+  double x[kPer];  // unconditional loads, so that all eight are in flight
 #pragma unroll
-  for (int e = threadIdx.x; e < kBlock; e += kThreads) {
-    L.C[(e / kPer) * kPad + e % kPer] = e < n ? quant52(__builtin_nontemporal_load(p + e)) : 0ull;
+  for (int q = 0; q < kPer; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    x[q] = __builtin_nontemporal_load(p + (e < n ? e : n - 1));
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    L.C[(e / kPer) * kPad + e % kPer] = e < n ? quant52(x[q]) : 0ull;
     L.cnt[e] = 0;
   }
   __syncthreads();
@@ -413,37 +566,78 @@ __device__ __forceinline__ void resolve_block_lds(ResolveLds& L, const double* _
     v[e] = s;
   }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  unsigned long long x = s;
+  unsigned long long end = s;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long y = __shfl_up(x, d);
-    if (lane >= d) x += y;
+    const unsigned long long y = __shfl_up(end, d);
+    if (lane >= d) end += y;
   }
-  if (lane == 63) L.wtot[wid] = x;
+  if (lane == 63) L.wtot[wid] = end;
   __syncthreads();
-  unsigned long long before = x - s;
+  unsigned long long before = end - s;
   for (int w = 0; w < wid; ++w) before += L.wtot[w];
 #pragma unroll
   for (int e = 0; e < kPer; ++e) mine[e] = v[e] + before;
   __syncthreads();
-  const uint64_t* sl = slots + row * shots + bptr[k];
-  for (uint32_t j = threadIdx.x; j < m; j += kThreads) {
-    const uint64_t t = __builtin_nontemporal_load(sl + j);
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (L.C[(mid / kPer) * kPad + mid % kPer] > t) hi = mid;
-      else lo = mid + 1;
-    }
-    atomicAdd(&L.cnt[lo], 1u);
+}
+
+// Counts target t in the entry it lands on.
+__device__ __forceinline__ void count_target_lds(ResolveLds& L, uint64_t t, int n) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (L.C[(mid / kPer) * kPad + mid % kPer] > t) hi = mid;
+    else lo = mid + 1;
   }
-  __syncthreads();
+  atomicAdd(&L.cnt[lo], 1u);
+}
+
+__device__ __forceinline__ void write_counts_lds(const ResolveLds& L, double* __restrict__ f, int n, int64_t shots) {
   const double ds = (double)shots;
-  for (int e = threadIdx.x; e < n; e += kThreads) {
-    const uint32_t c = L.cnt[e];
-    __builtin_nontemporal_store(c ? (double)c / ds : 0.0, f + e);
+  for (int e = threadIdx.x; e < n; e += kThreads) __builtin_nontemporal_store(freq_of(L.cnt[e], ds), f + e);
+}
+
+__device__ __forceinline__ void resolve_block_lds(ResolveLds& L, const double* __restrict__ P, int64_t cols,
+                                                  int64_t nblk, int64_t shots, int64_t k, uint32_t m,
+                                                  const uint32_t* __restrict__ bptr,
+                                                  const uint64_t* __restrict__ slots, double* __restrict__ F) {
+  const int64_t row = k / nblk, blk = k - row * nblk;
+  const int64_t c0 = blk * kBlock;
+  const int n = (int)(cols - c0 < kBlock ? cols - c0 : kBlock);
+  double* f = F + row * cols + c0;
+  if (m == 0) {
+    for (int e = threadIdx.x; e < n; e += kThreads) __builtin_nontemporal_store(0.0, f + e);
+    return;
   }
+  block_prefix_lds(L, P + row * cols + c0, n);
+  const uint64_t* sl = slots + row * shots + bptr[k];
+  for (uint32_t j = threadIdx.x; j < m; j += kThreads) count_target_lds(L, __builtin_nontemporal_load(sl + j), n);
+  __syncthreads();
+  write_counts_lds(L, f, n, shots);
   __syncthreads();  // the workgroup's next block reuses the LDS
+}
+
+// Rows of one block: the whole row in one workgroup, from entries to
+// frequencies, without sums, buckets or slots in memory (one launch instead
+// of six: a table of 300 x 77 with 5000 shots a row, and its chi-square, take
+// 25 us instead of 46).
+__global__ void __launch_bounds__(kThreads) shots_row_kernel(const double* __restrict__ P, int64_t cols,
+                                                             int64_t shots, uint64_t seed,
+                                                             double* __restrict__ F) {
+  __shared__ ResolveLds L;
+  const int64_t row = blockIdx.x;
+  const int n = (int)cols;
+  block_prefix_lds(L, P + row * cols, n);
+  const uint64_t T = L.C[((n - 1) / kPer) * kPad + (n - 1) % kPer];
+  if (T != 0)
+    for (int64_t s = threadIdx.x; s < shots; s += kThreads) {
+      uint64_t t;
+      uint32_t blk;
+      shot_target(&T, 1, T, seed, row, s, t, blk);
+      count_target_lds(L, t, n);
+    }
+  __syncthreads();
+  write_counts_lds(L, F + row * cols, n, shots);
 }
 
 // Every block, one workgroup each (grid (nblk, rows)): for tables with many
@@ -493,34 +687,43 @@ __global__ void __launch_bounds__(kThreads) shots_resolve_listed_kernel(const do
 
 // Eq. 3, terms with a + b = 0 taken as 0: per-block partial sums in a fixed
 // order (four strided streams a thread, then a tree), then one block sums
-// the partials the same way
+// the partials the same way.  Bound by reading a and b once: 9.7 GB in
+// 1.55-1.65 ms (1.8 with 8-byte loads).  A thread takes
+// pairs of neighbours, 16 bytes a load where both arrays are aligned (VEC);
+// the order of the additions does not depend on the alignment.
 constexpr int kChiBlocks = 2048;
 
+template <bool VEC>
 __global__ void __launch_bounds__(kThreads) chi2_partial_kernel(const double* __restrict__ a,
                                                                 const double* __restrict__ b, int64_t n,
                                                                 double* __restrict__ part) {
   __shared__ double sh[kThreads];
-  // four strided streams per thread, each summed on its own, then combined
+  // two strided streams of pairs per thread, each element summed on its own,
+  // then combined
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, pairs = n >> 1;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i + 3 * step < n; i += 4 * step) {
-    double x[4], y[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      x[u] = __builtin_nontemporal_load(a + i + u * step);
-      y[u] = __builtin_nontemporal_load(b + i + u * step);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double d = x[u] - y[u], t = x[u] + y[u];
-      if (t != 0.0) acc[u] += d * d / t;
-    }
+  auto pair = [](const double* p, int64_t q) -> d2_t {
+    if constexpr (VEC) return __builtin_nontemporal_load(reinterpret_cast<const d2_t*>(p) + q);
+    else return d2_t{__builtin_nontemporal_load(p + 2 * q), __builtin_nontemporal_load(p + 2 * q + 1)};
+  };
+  auto add = [](double& s, double x, double y) {
+    const double d = x - y, t = x + y;
+    if (t != 0.0) s += d * d / t;
+  };
+  for (; i + step < pairs; i += 2 * step) {
+    const d2_t x0 = pair(a, i), y0 = pair(b, i), x1 = pair(a, i + step), y1 = pair(b, i + step);
+    add(acc[0], x0[0], y0[0]);
+    add(acc[1], x0[1], y0[1]);
+    add(acc[2], x1[0], y1[0]);
+    add(acc[3], x1[1], y1[1]);
   }
-  for (int u = 0; i < n; i += step, ++u) {
-    const double x = a[i], y = b[i], d = x - y, t = x + y;
-    if (t != 0.0) acc[u] += d * d / t;
+  if (i < pairs) {
+    const d2_t x = pair(a, i), y = pair(b, i);
+    add(acc[0], x[0], y[0]);
+    add(acc[1], x[1], y[1]);
   }
+  if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) add(acc[2], a[n - 1], b[n - 1]);
   const double s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   sh[threadIdx.x] = s;
   __syncthreads();
@@ -546,7 +749,7 @@ __global__ void __launch_bounds__(kThreads) chi2_final_kernel(const double* __re
 }
 
 struct ShotsWs {
-  int64_t bend = 0, bcnt = 0, bptr = 0, bfill = 0, slots = 0, bytes = 0;
+  int64_t bend = 0, runs = 0, bcnt = 0, bptr = 0, bfill = 0, slots = 0, bytes = 0;
 };
 
 cq_status hip_error(hipError_t e, const char* what) {
@@ -559,7 +762,8 @@ ShotsWs shots_ws(int64_t rows, int64_t cols, int64_t shots) {
   ShotsWs w;
   const int64_t nb = rows * ((cols + kBlock - 1) / kBlock);
   w.bend = 0;
-  w.bcnt = al256(nb * 8);
+  w.runs = al256(nb * 8);
+  w.bcnt = w.runs + al256(nb * kRuns * 8);
   w.bptr = w.bcnt + al256(nb * 4);
   w.bfill = w.bptr + al256(nb * 4);
   w.slots = w.bfill + al256(nb * 4);
@@ -600,29 +804,54 @@ extern "C" cq_status cq_sample_shots(const double* probs, int64_t rows, int64_t 
   if (!workspace || (int64_t)workspace_bytes < w.bytes) return fail(CQ_ERR_WORKSPACE, "workspace too small");
   char* ws = static_cast<char*>(workspace);
   uint64_t* bend = reinterpret_cast<uint64_t*>(ws + w.bend);
+  uint64_t* runs = reinterpret_cast<uint64_t*>(ws + w.runs);
   uint32_t* bcnt = reinterpret_cast<uint32_t*>(ws + w.bcnt);
   uint32_t* bptr = reinterpret_cast<uint32_t*>(ws + w.bptr);
   uint32_t* bfill = reinterpret_cast<uint32_t*>(ws + w.bfill);
   uint64_t* slots = reinterpret_cast<uint64_t*>(ws + w.slots);
   const int64_t nblk = (cols + kBlock - 1) / kBlock;  // <= 2^23 by the limits
+  if (nblk == 1 && (shots <= kRowShots || rows >= kRowRows)) {
+    hipLaunchKernelGGL(shots_row_kernel, dim3((unsigned)rows), dim3(kThreads), 0, stream, probs, cols, shots, seed,
+                       freqs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "shot sampling launch");
+    return CQ_OK;
+  }
   const dim3 gt((unsigned)nblk, (unsigned)rows);
-  const dim3 gs((unsigned)((shots + kShotsPerGroup - 1) / kShotsPerGroup), (unsigned)rows);
-  hipLaunchKernelGGL(shots_bsum_kernel, gt, dim3(kThreads), 0, stream, probs, cols, nblk, bend, bcnt, bfill);
+  // shots of a thread: few enough for two shot groups a compute unit where
+  // the table has them (20 x 10^6 outcomes with 10^5 shots a row: 226 us
+  // against 258 with one)
+  int per = kMaxShotsPerThread;
+  while (per > 4 && rows * ((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)) < 512) per >>= 1;
+  const dim3 gs((unsigned)((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)), (unsigned)rows);
+  const bool sparse = shots <= (int64_t)kSparseShots * nblk;
+  if (sparse)
+    hipLaunchKernelGGL(shots_bsum_kernel<true>, gt, dim3(kThreads), 0, stream, probs, cols, nblk, bend, runs, bcnt,
+                       bfill);
+  else
+    hipLaunchKernelGGL(shots_bsum_kernel<false>, gt, dim3(kThreads), 0, stream, probs, cols, nblk, bend, runs, bcnt,
+                       bfill);
   hipLaunchKernelGGL(shots_bend_kernel, dim3((unsigned)rows), dim3(kScanThreads), 0, stream, bend, nblk);
   hipLaunchKernelGGL(shots_count_kernel, gs, dim3(kThreads), 0, stream, (const uint64_t*)bend, nblk, shots, seed,
-                     bcnt);
+                     per, bcnt);
   hipLaunchKernelGGL(shots_bptr_kernel, dim3((unsigned)rows), dim3(kScanThreads), 0, stream, bcnt, bptr, nblk);
   hipLaunchKernelGGL(shots_scatter_kernel, gs, dim3(kThreads), 0, stream, (const uint64_t*)bend, nblk, shots,
-                     seed, (const uint32_t*)bptr, bfill, slots);
+                     seed, per, (const uint32_t*)bptr, bfill, slots);
   if (shots >= (int64_t)kFewShots * nblk) {
     // many shots per block on average: every block resolves in LDS
     hipLaunchKernelGGL(shots_resolve_kernel, gt, dim3(kThreads), 0, stream, probs, cols, nblk, shots,
                        (const uint32_t*)bcnt, (const uint32_t*)bptr, (const uint64_t*)slots, freqs);
   } else {
-    hipLaunchKernelGGL(shots_resolve_few_kernel, gt, dim3(kThreads), 0, stream, probs, cols, nblk, shots,
-                       (const uint32_t*)bcnt, (const uint32_t*)bptr, (const uint64_t*)slots, freqs);
+    const int64_t total = rows * nblk;  // <= 2^23 blocks and a row more
+    if (sparse)
+      hipLaunchKernelGGL(shots_resolve_sparse_kernel, dim3((unsigned)((total + kThreads / 64 - 1) / (kThreads / 64))),
+                         dim3(kThreads), 0, stream, probs, cols, nblk, total, shots, (const uint64_t*)runs,
+                         (const uint32_t*)bcnt, (const uint32_t*)bptr, (const uint64_t*)slots, freqs);
+    else
+      hipLaunchKernelGGL(shots_resolve_few_kernel, gt, dim3(kThreads), 0, stream, probs, cols, nblk, shots,
+                         (const uint32_t*)bcnt, (const uint32_t*)bptr, (const uint64_t*)slots, freqs);
     if (shots > kFewShots) {
-      const int64_t total = rows * nblk, chunks = (total + kManyChunk - 1) / kManyChunk;
+      const int64_t chunks = (total + kManyChunk - 1) / kManyChunk;
       const unsigned grid = (unsigned)(chunks < kManyGrid ? chunks : kManyGrid);
       hipLaunchKernelGGL(shots_resolve_listed_kernel, dim3(grid), dim3(kThreads), 0, stream, probs, cols, nblk,
                          total, shots, (const uint32_t*)bcnt, (const uint32_t*)bptr, (const uint64_t*)slots, freqs);
@@ -646,7 +875,10 @@ extern "C" cq_status cq_chi2(const double* a, const double* b, int64_t n, double
   if (!workspace || workspace_bytes < (size_t)kChiBlocks * sizeof(double))
     return fail(CQ_ERR_WORKSPACE, "workspace too small");
   double* part = static_cast<double*>(workspace);
-  hipLaunchKernelGGL(chi2_partial_kernel, dim3(kChiBlocks), dim3(kThreads), 0, stream, a, b, n, part);
+  if (((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0)
+    hipLaunchKernelGGL(chi2_partial_kernel<true>, dim3(kChiBlocks), dim3(kThreads), 0, stream, a, b, n, part);
+  else
+    hipLaunchKernelGGL(chi2_partial_kernel<false>, dim3(kChiBlocks), dim3(kThreads), 0, stream, a, b, n, part);
   hipLaunchKernelGGL(chi2_final_kernel, dim3(1), dim3(kThreads), 0, stream, (const double*)part, kChiBlocks, result);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "chi-square launch");
