@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libcutqc.so")
 
 CQ_OK = 0
+CQ_ERR_WORKSPACE = -5
 STATUS = {0: "CQ_OK", -1: "CQ_ERR_ARG", -2: "CQ_ERR_SHAPE", -3: "CQ_ERR_CUTMAP",
           -4: "CQ_ERR_MASK", -5: "CQ_ERR_WORKSPACE", -6: "CQ_ERR_UNSUPPORTED", -7: "CQ_ERR_HIP"}
 PRECISION = {"fp64": 0, "fp32": 1, "bf16": 2, "bf16_split": 3, "fp16": 4, "fp16_split": 5}

@@ -9,9 +9,11 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
+from array import array
 
 from . import _lib
-from ._lib import check, lib
+from ._lib import CQ_ERR_WORKSPACE, check, lib
 
 
 def _sub_fields(sub):
@@ -22,24 +24,36 @@ def _sub_fields(sub):
     return int(w), [int(x) for x in ic], [int(x) for x in mc]
 
 
+# cq_subcircuit as bytes (width, padding, two pointers)
+_SUB = struct.Struct("@iiPP")
+assert _SUB.size == C.sizeof(_lib.cq_subcircuit)
+
+
 class _Subs:
-    """Keeps the ctypes arrays of a subcircuit list alive for one call."""
+    """Keeps the C arrays of a subcircuit list alive for one call: every cut
+    list in one int32 buffer, the structs built as bytes over it (ctypes
+    pointer casts per field cost more than a small call takes)."""
 
     def __init__(self, subs):
-        self.keep = []
-        self.arr = (_lib.cq_subcircuit * len(subs))()
-        self.n_out = []
-        for i, s in enumerate(subs):
-            w, ic, mc = _sub_fields(s)
-            a = (C.c_int32 * max(w, 1))(*ic)
-            b = (C.c_int32 * max(w, 1))(*mc)
-            self.keep += [a, b]
-            self.arr[i].width = w
-            self.arr[i].init_cut = C.cast(a, C.POINTER(C.c_int32))
-            self.arr[i].meas_cut = C.cast(b, C.POINTER(C.c_int32))
-            self.n_out.append(sum(1 for m in mc if m == -1))
+        cuts, spans, self.n_out, self.fields = array("i"), [], [], []
+        for sub in subs:
+            w, ic, mc = _sub_fields(sub)
+            self.fields.append((w, ic, mc))
+            n = max(w, 1)
+            if len(ic) > n or len(mc) > n:
+                raise IndexError("invalid index")  # as a ctypes array of `width` entries
+            spans.append((w, len(cuts)))
+            cuts.extend(ic + [0] * (n - len(ic)))
+            cuts.extend(mc + [0] * (n - len(mc)))
+            self.n_out.append(mc.count(-1))
+        base = cuts.buffer_info()[0]
+        raw = bytearray(b"".join(_SUB.pack(w, 0, base + 4 * at, base + 4 * (at + max(w, 1))) for w, at in spans))
+        self.keep = cuts
+        self.arr = (_lib.cq_subcircuit * len(subs)).from_buffer(raw) if raw else (_lib.cq_subcircuit * 0)()
 
     def ptr(self, i=0):
+        if i == 0:
+            return self.arr
         return C.cast(C.byref(self.arr, i * C.sizeof(_lib.cq_subcircuit)),
                       C.POINTER(_lib.cq_subcircuit))
 
@@ -78,11 +92,14 @@ def cq_validate_cutmap(subs):
     return k.value, n.value
 
 
-def cq_attribute_workspace_size(sub):
-    s = _Subs([sub])
+def _attribute_workspace(s):
     b = C.c_size_t()
     check(lib().cq_attribute_workspace_size(s.ptr(), C.byref(b)))
     return b.value
+
+
+def cq_attribute_workspace_size(sub):
+    return _attribute_workspace(_Subs([sub]))
 
 
 def cq_attribute(sub, variants, entries=None, workspace=None, stream=None):
@@ -90,12 +107,11 @@ def cq_attribute(sub, variants, entries=None, workspace=None, stream=None):
     probabilities (4^r, 3^o, 2^w) FP64, both on the device."""
     import torch
     s = _Subs([sub])
-    w, ic, mc = _sub_fields(sub)
-    k = len({c for c in ic + mc if c != -1})
-    n = s.n_out[0]
     if entries is None:
-        entries = torch.empty((4 ** k, 2 ** n), dtype=torch.float64, device=variants.device)
-    nbytes = cq_attribute_workspace_size(sub)
+        _, ic, mc = s.fields[0]
+        k = len({c for c in ic + mc if c != -1})
+        entries = torch.empty((4 ** k, 2 ** s.n_out[0]), dtype=torch.float64, device=variants.device)
+    nbytes = _attribute_workspace(s)
     ws = _workspace(nbytes, variants.device, workspace)
     check(lib().cq_attribute(s.ptr(), _dev_ptr(variants, torch.float64),
                              _dev_ptr(entries, torch.float64), _dev_ptr(ws), C.c_size_t(nbytes),
@@ -109,14 +125,14 @@ def _perm_arr(out_perm):
     return (C.c_int32 * len(out_perm))(*[int(q) for q in out_perm])
 
 
-def cq_fd_workspace_size(subs, prec="fp64", out_perm=None):
-    s = _Subs(subs)
-    perm = _perm_arr(out_perm)
+def _fd_workspace(s, prec, perm):
     b = C.c_size_t()
-    check(lib().cq_fd_workspace_size(len(subs), s.ptr(), _lib.PRECISION[prec],
-                                     C.cast(perm, C.POINTER(C.c_int32)) if perm else None,
-                                     C.byref(b)))
+    check(lib().cq_fd_workspace_size(len(s.fields), s.ptr(), _lib.PRECISION[prec], perm, C.byref(b)))
     return b.value
+
+
+def cq_fd_workspace_size(subs, prec="fp64", out_perm=None):
+    return _fd_workspace(_Subs(subs), prec, _perm_arr(out_perm))
 
 
 def cq_reconstruct_fd(subs, entries, prec="fp64", out_perm=None, out=None, workspace=None,
@@ -133,13 +149,17 @@ def cq_reconstruct_fd(subs, entries, prec="fp64", out_perm=None, out=None, works
     elif out.dtype != dtype or out.numel() != 2 ** n:
         raise ValueError("output tensor has the wrong dtype or size")
     perm = _perm_arr(out_perm)
-    nbytes = cq_fd_workspace_size(subs, prec, out_perm)
-    ws = _workspace(nbytes, dev, workspace)
+    if workspace is None:
+        nbytes = _fd_workspace(s, prec, perm)
+        ws = _workspace(nbytes, dev)
+    else:  # the call itself checks a given workspace (no second plan for its size)
+        ws, nbytes = workspace, workspace.numel() * workspace.element_size()
     ptrs = (C.c_void_p * len(entries))(*[_dev_ptr(e, torch.float64).value for e in entries])
-    check(lib().cq_reconstruct_fd(len(subs), s.ptr(), ptrs, _lib.PRECISION[prec],
-                                  C.cast(perm, C.POINTER(C.c_int32)) if perm else None,
-                                  _dev_ptr(out), _dev_ptr(ws), C.c_size_t(nbytes),
-                                  _stream(stream)))
+    st = lib().cq_reconstruct_fd(len(s.fields), s.ptr(), ptrs, _lib.PRECISION[prec], perm, _dev_ptr(out),
+                                 _dev_ptr(ws), nbytes, _stream(stream))
+    if st == CQ_ERR_WORKSPACE:
+        raise ValueError("workspace too small")
+    check(st)
     return out
 
 
@@ -185,20 +205,17 @@ class _Instances:
             a = self.arr[i]
             a.n_sub = ns
             a.subs = subs.ptr()
-            a.entries = C.cast(ptrs, C.POINTER(C.c_void_p))
-            a.active = C.cast(act, C.POINTER(C.c_uint64))
-            a.merged = C.cast(mer, C.POINTER(C.c_uint64))
-            a.fixed = C.cast(fix, C.POINTER(C.c_uint64))
-            a.fixed_vals = C.cast(fv, C.POINTER(C.c_uint64))
-            a.max_active = C.cast(ma, C.POINTER(C.c_int32))
+            a.entries, a.active, a.merged, a.fixed, a.fixed_vals, a.max_active = ptrs, act, mer, fix, fv, ma
 
 
 def cq_dd_workspace_size(instances, prec="fp64", R=4, bins_stored=False):
-    ins = _Instances(instances)
+    return _dd_workspace(_Instances(instances), len(instances), prec, R, bins_stored)
+
+
+def _dd_workspace(ins, count, prec, R, bins_stored):
     par = _lib.cq_dd_params(_lib.PRECISION[prec], int(R), 0, 0, None, None)
     b = C.c_size_t()
-    check(lib().cq_dd_workspace_size(len(instances), ins.arr, C.byref(par), int(bins_stored),
-                                     C.byref(b)))
+    check(lib().cq_dd_workspace_size(count, ins.arr, C.byref(par), int(bins_stored), C.byref(b)))
     return b.value
 
 
@@ -233,7 +250,7 @@ def cq_reconstruct_dd(instances, prec="fp64", R=4, bins=None, workspace=None, st
     par = _lib.cq_dd_params(_lib.PRECISION[prec], int(R), _lib.DD_LAUNCH[launch], int(recursions),
                             C.cast(res_buf, C.c_void_p) if res_buf is not None else None,
                             C.cast(out_buf, C.c_void_p) if out_buf is not None else None)
-    nbytes = cq_dd_workspace_size(instances, prec, R, bins is not None)
+    nbytes = _dd_workspace(ins, len(instances), prec, R, bins is not None)
     dev = instances[0]["entries"][0].device
     ws = _workspace(nbytes, dev, workspace)
     recs = (_lib.cq_dd_record * (len(instances) * R))()
@@ -348,12 +365,18 @@ def cq_chi2(a, b, out=None, workspace=None, stream=None):
     return out
 
 
+# cq_gate as a numpy record: kind, q0, q1, then the matrix
+_GATE = {"names": ["head", "u"], "formats": [("<i4", 3), ("<f8", 8)],
+         "offsets": [_lib.cq_gate.kind.offset, _lib.cq_gate.u.offset], "itemsize": C.sizeof(_lib.cq_gate)}
+
+
 def _gates(ops):
     """Gate list -> ctypes array.  An op is an object with ``name`` ('u' or
     'cz'), ``qubits`` and ``matrix`` (2 x 2 complex for 'u'), or a tuple
     ('u', q, matrix) / ('cz', q0, q1)."""
+    import numpy as np
     ops = list(ops)
-    arr = (_lib.cq_gate * max(len(ops), 1))()
+    heads, mats, at = [], [], []
     for i, op in enumerate(ops):
         if isinstance(op, tuple):
             name, rest = op[0], op[1:]
@@ -362,15 +385,27 @@ def _gates(ops):
         else:
             name, qubits, matrix = op.name, op.qubits, op.matrix
         if name == "u":
-            arr[i].kind, arr[i].q0 = _lib.GATE_U, int(qubits[0])
-            m = [complex(matrix[r][c]) for r in range(2) for c in range(2)]
-            for j, z in enumerate(m):
-                arr[i].u[2 * j], arr[i].u[2 * j + 1] = z.real, z.imag
+            heads.append((_lib.GATE_U, int(qubits[0]), 0))
+            mats.append(matrix)
+            at.append(i)
         elif name == "cz":
-            arr[i].kind, arr[i].q0, arr[i].q1 = _lib.GATE_CZ, int(qubits[0]), int(qubits[1])
+            heads.append((_lib.GATE_CZ, int(qubits[0]), int(qubits[1])))
         else:
             raise ValueError(f"unknown gate {name!r}")
-    return arr, len(ops)
+    # all matrices in one conversion (element by element they cost more than
+    # the simulation of a small register)
+    buf = np.zeros(max(len(ops), 1), dtype=_GATE)
+    if heads:
+        buf["head"] = heads
+    if mats:
+        try:
+            u = np.array(mats, dtype=np.complex128)
+        except (TypeError, ValueError):
+            u = None
+        if u is None or u.shape != (len(mats), 2, 2):  # anything indexable as matrix[r][c]
+            u = np.array([[[complex(m[r][c]) for c in range(2)] for r in range(2)] for m in mats])
+        buf["u"][at] = u.reshape(len(mats), 4).view(np.float64)
+    return (_lib.cq_gate * len(buf)).from_buffer(buf), len(ops)
 
 
 def cq_simulate_workspace_size(n):
@@ -394,18 +429,22 @@ def cq_simulate_probabilities(n, ops, out=None, workspace=None, device="cuda:0",
     return out
 
 
-def cq_variants_workspace_size(sub):
-    s = _Subs([sub])
+def _variants_workspace(s):
     b = C.c_size_t()
     check(lib().cq_variants_workspace_size(s.ptr(), C.byref(b)))
     return b.value
+
+
+def cq_variants_workspace_size(sub):
+    return _variants_workspace(_Subs([sub]))
 
 
 def cq_variant_probabilities(sub, ops=None, out=None, workspace=None, device="cuda:0", stream=None):
     """Every variant of subcircuit ``sub`` (its ``ops`` unless given) as a
     (4^r, 3^o, 2^width) FP64 device tensor, the layout cq_attribute reads."""
     import torch
-    w, ic, mc = _sub_fields(sub)
+    s = _Subs([sub])
+    w, ic, mc = s.fields[0]
     if ops is None:
         if not hasattr(sub, "ops"):
             raise ValueError("pass ops for a subcircuit given as a tuple")
@@ -417,9 +456,8 @@ def cq_variant_probabilities(sub, ops=None, out=None, workspace=None, device="cu
         out = torch.empty(shape, dtype=torch.float64, device=device)
     elif tuple(out.shape) != shape:
         raise ValueError(f"out must have shape {shape}")
-    s = _Subs([sub])
     arr, cnt = _gates(ops)
-    nbytes = cq_variants_workspace_size(sub)
+    nbytes = _variants_workspace(s)
     ws = _workspace(nbytes, out.device, workspace)
     check(lib().cq_variant_probabilities(s.ptr(), arr, cnt, _dev_ptr(out, torch.float64), _dev_ptr(ws),
                                          C.c_size_t(nbytes), _stream(stream)))

@@ -1,0 +1,49 @@
+"""The binding's argument structs field by field, without a GPU."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+from paper_2205_05836_amd import _lib, api
+
+
+@pytest.mark.parametrize("subs", [
+    [(3, [0, -1, -1], [-1, -1, 1]), (2, [1, -1], [-1, 0])], [(0, [], [])], [(1, [-1], [0]), (0, [], [])],
+    [SimpleNamespace(width=2, init_cut=np.array([-1, 0]), meas_cut=(-1, -1))], []])
+def test_subcircuit_structs(subs):
+    s = api._Subs(subs)
+    assert len(s.arr) == len(subs)
+    for i, sub in enumerate(subs):
+        w, ic, mc = sub if isinstance(sub, tuple) else (sub.width, sub.init_cut, sub.meas_cut)
+        c = s.ptr(i)[0]
+        assert c.width == w and c.init_cut[:w] == list(ic) and c.meas_cut[:w] == list(mc)
+        assert s.n_out[i] == list(mc).count(-1)
+
+
+def test_cut_list_longer_than_the_register_is_refused():
+    with pytest.raises(IndexError):
+        api._Subs([(2, [-1, -1, 0], [-1, -1])])
+
+
+def test_gate_structs():
+    """Matrices as nested lists, tuples, arrays of any number type, and larger
+    ones (their leading 2 x 2 block), alone and mixed."""
+    u = [[[0.5, 1j], [2 - 1j, -3]], ((1, 2), (3, 4)), np.eye(2, dtype=np.float32), np.arange(9).reshape(3, 3),
+         np.array([[1, 1j], [1j, 1]], dtype=np.complex64)]
+    for mats in (u, u[:1], u[4:], u[:3], []):
+        ops = [("cz", 4, 1)]
+        for i, m in enumerate(mats):
+            ops += [("u", np.int64(i), m), SimpleNamespace(name="cz", qubits=(i, i + 1), matrix=None)]
+        arr, n = api._gates(ops)
+        assert n == len(ops)
+        for g, op in zip(arr, ops):
+            if isinstance(op, tuple) and op[0] == "u":
+                want = [complex(op[2][r][c]) for r in range(2) for c in range(2)]
+                assert (g.kind, g.q0) == (_lib.GATE_U, op[1])
+                assert list(g.u) == [x for z in want for x in (z.real, z.imag)]
+            else:
+                q = op[1:] if isinstance(op, tuple) else op.qubits
+                assert (g.kind, g.q0, g.q1) == (_lib.GATE_CZ, *q)
+    assert api._gates([])[1] == 0
+    with pytest.raises(ValueError):
+        api._gates([("cx", 0, 1)])
