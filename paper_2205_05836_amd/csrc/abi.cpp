@@ -150,7 +150,7 @@ cq_status check_perm(const int32_t* out_perm, int n, std::vector<int>& perm) {
 // bal (optional): per-label balance of the 16-bit operands, its row maxima and
 // exponents in the workspace.
 cq_status execute(const Plan& plan, cq_precision prec, const double* const* inputs, void* out,
-                  DType out_t, char* ws, hipStream_t stream, const BalanceLaunch* bal = nullptr) {
+                  DType out_t, char* ws, hipStream_t stream, const BalanceArgs* bal = nullptr) {
   const DType wt = work_dtype(prec);
   const bool f16 = is_f16(prec);
   auto planes = [&](char* base, int64_t elems) -> Operand {
@@ -173,42 +173,28 @@ cq_status execute(const Plan& plan, cq_precision prec, const double* const* inpu
   auto out_bits = [](const TensorRef& t) {
     return t.axes.empty() || t.axes.back().kind != 1 ? 0 : t.axes.back().log2;
   };
-  // per-label balance: row maxima of every converted input, then the
-  // exponents of every row
-  if (bal) {
-    ProfScope ps("balance", 0.0, stream);
-    hipError_t e = hipSuccess;
-    for (size_t i = 0; i < plan.tensors.size() && e == hipSuccess; ++i) {
-      const TensorRef& t = plan.tensors[i];
-      if (t.loc != Loc::Input || plan.input_offset[t.index] < 0) continue;
-      const int nb = out_bits(t);
-      e = launch_rowmax(inputs[t.index], t.elems >> nb, nb,
-                        const_cast<uint64_t*>(bal->rowmax[t.index]), stream);
-    }
-    if (e == hipSuccess) e = launch_balance(*bal, stream);
-    if (e != hipSuccess) return hip_fail(e, "label balance launch");
-  }
-  // operand preparation: FP64 entries -> the precision's storage format
-  for (size_t i = 0; i < plan.tensors.size(); ++i) {
-    const TensorRef& t = plan.tensors[i];
+  // operand preparation: FP64 entries -> the precision's storage format, with
+  // the per-label balance and the column scaling where they apply
+  BalanceLaunch prep;
+  std::memset(static_cast<void*>(&prep), 0, sizeof(prep));
+  if (bal) static_cast<BalanceArgs&>(prep) = *bal;
+  prep.balanced = bal != nullptr;
+  prep.t = wt;
+  prep.f16 = f16;
+  for (const TensorRef& t : plan.tensors) {
     if (t.loc != Loc::Input || plan.input_offset[t.index] < 0) continue;
-    const int32_t* rexp = bal ? bal->rexp[t.index] : nullptr;
-    const int nb = out_bits(t);
-    hipError_t e;
-    {
-      ProfScope ps("prep", 0.0, stream);
-      if (plan.scaled) {
-        const int64_t rows = t.elems >> nb;
-        e = launch_colmax(inputs[t.index], rows, nb, colmax(t.index), stream, rexp);
-        if (e == hipSuccess)
-          e = launch_prep_scaled(inputs[t.index], ws + plan.input_offset[t.index], t.elems, nb,
-                                 colmax(t.index), wt, f16, stream, rexp);
-      } else {
-        e = launch_prep(inputs[t.index], ws + plan.input_offset[t.index], t.elems, wt, f16, stream,
-                        rexp, nb);
-      }
+    OperandIn& in = prep.in[prep.n_in++];
+    const Operand d = planes(ws + plan.input_offset[t.index], t.elems);
+    in.src = inputs[t.index];
+    in.dst = const_cast<void*>(d.p);
+    in.dst_lo = const_cast<void*>(d.lo);
+    in.cols_log2 = out_bits(t);
+    in.rows = t.elems >> in.cols_log2;
+    if (bal) {
+      in.rowmax = const_cast<uint64_t*>(bal->rowmax[t.index]);
+      in.rexp = bal->rexp[t.index];
     }
-    if (e != hipSuccess) return hip_fail(e, "operand prep launch");
+    if (plan.scaled) in.colmax = colmax(t.index);
   }
   int32_t* rowexp = nullptr;
   int32_t* colexp = nullptr;
@@ -219,8 +205,7 @@ cq_status execute(const Plan& plan, cq_precision prec, const double* const* inpu
     int32_t* outs[2] = {rowexp, colexp};
     const int64_t counts[2] = {plan.rowexp_count, plan.colexp_count};
     for (int q = 0; q < 2; ++q) {
-      ExpSumLaunch x;
-      std::memset(&x, 0, sizeof(x));
+      ExpSumLaunch& x = prep.ex[q];
       x.out = outs[q];
       x.count = counts[q];
       x.n = (int)gr[q]->sub.size();
@@ -229,9 +214,19 @@ cq_status execute(const Plan& plan, cq_precision prec, const double* const* inpu
         x.shift[i] = gr[q]->shift[i];
         x.bits[i] = gr[q]->bits[i];
       }
-      hipError_t e = launch_expsum(x, stream);
-      if (e != hipSuccess) return hip_fail(e, "scale exponent launch");
     }
+  }
+  if (bal) {
+    ProfScope ps("balance", 0.0, stream);
+    prep.stage = BalanceLaunch::kExponents;
+    hipError_t e = launch_balance(prep, stream);
+    if (e != hipSuccess) return hip_fail(e, "label balance launch");
+  }
+  if (prep.n_in > 0) {
+    ProfScope ps("prep", 0.0, stream);
+    prep.stage = BalanceLaunch::kConvert;
+    hipError_t e = launch_balance(prep, stream);
+    if (e != hipSuccess) return hip_fail(e, "operand prep launch");
   }
   for (const Step& s : plan.steps) {
     hipError_t e;
@@ -336,8 +331,8 @@ cq_status fd_prepare(int32_t n_sub, const cq_subcircuit* subs, cq_precision prec
 
 // The balance arguments of a plan on workspace ws.
 // The cut structure of a balance launch (pointers left null).
-BalanceLaunch balance_struct(const CutMap& cm) {
-  BalanceLaunch b;
+BalanceArgs balance_struct(const CutMap& cm) {
+  BalanceArgs b;
   std::memset(&b, 0, sizeof(b));
   b.n_sub = cm.n_sub;
   b.K = cm.K;
@@ -355,8 +350,8 @@ BalanceLaunch balance_struct(const CutMap& cm) {
   return b;
 }
 
-BalanceLaunch balance_args(const CutMap& cm, const Plan& plan, char* ws) {
-  BalanceLaunch b = balance_struct(cm);
+BalanceArgs balance_args(const CutMap& cm, const Plan& plan, char* ws) {
+  BalanceArgs b = balance_struct(cm);
   for (int c = 0; c < cm.n_sub; ++c) {
     b.rowmax[c] = reinterpret_cast<const uint64_t*>(ws + plan.lbal_rowmax_offset[c]);
     b.rexp[c] = reinterpret_cast<int32_t*>(ws + plan.lbal_rexp_offset[c]);
@@ -457,7 +452,7 @@ cq_status cq::fd_run(int32_t n_sub, const cq_subcircuit* subs, const double* con
   if (plan.workspace_bytes > 0 && (!workspace || workspace_bytes < (size_t)plan.workspace_bytes))
     return fail(CQ_ERR_WORKSPACE, "workspace too small");
   if (fault_injected("fd")) return fail(CQ_ERR_HIP, "injected fault before launch");
-  BalanceLaunch bal;
+  BalanceArgs bal;
   const bool balanced = balance_applies(prec) && !plan.lbal_rexp_offset.empty();
   if (balanced) bal = balance_args(cm, plan, static_cast<char*>(workspace));
   t_quiet = quiet;

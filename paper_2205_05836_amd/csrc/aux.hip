@@ -1,6 +1,7 @@
 // Layout permutes and entry attribution.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "kernels.hpp"
@@ -91,7 +92,7 @@ __device__ inline void prep_body(const double* __restrict__ src, void* dst, void
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
   const int64_t cmask = ((int64_t)1 << cols_log2) - 1;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
-    // column scaling as prep_scaled_kernel: 2^-e of the column maximum, plus the row exponent
+    // column scaling as operand_convert_kernel: 2^-e of the column maximum, plus the row exponent
     const float x = colmax ? float(ldexp(src[i], -colmax_exp(colmax[i & cmask]) +
                                                      (rexp ? rexp[i >> cols_log2] : 0)))
                            : rexp ? float(ldexp(src[i], rexp[i >> cols_log2])) : float(src[i]);
@@ -105,49 +106,6 @@ __device__ inline void prep_body(const double* __restrict__ src, void* dst, void
   }
 }
 
-// Four elements a thread: two 16-byte loads, 8-byte (16-bit planes) or
-// 16-byte (FP32) stores; the per-element arithmetic is prep_body's.  Needs
-// n % 4 == 0, src 16-byte aligned, dst (and dst_lo) aligned to the stores,
-// and rows of at least 4 elements when rexp is given.
-template <int DK>
-__device__ inline void prep_body4(const double* __restrict__ src, void* dst, void* dst_lo, int64_t n,
-                                  const int32_t* __restrict__ rexp, int cols_log2) {
-  typedef double d2_t __attribute__((ext_vector_type(2)));
-  typedef float f4_t __attribute__((ext_vector_type(4)));
-  typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-  const int64_t n4 = n >> 2;
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += step) {
-    const d2_t v0 = reinterpret_cast<const d2_t*>(src)[2 * i];
-    const d2_t v1 = reinterpret_cast<const d2_t*>(src)[2 * i + 1];
-    const double d[4] = {v0[0], v0[1], v1[0], v1[1]};
-    const int e = rexp ? rexp[(4 * i) >> cols_log2] : 0;
-    float x[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = rexp ? float(ldexp(d[u], e)) : float(d[u]);
-    if constexpr (DK == kF32) {
-      reinterpret_cast<f4_t*>(dst)[i] = f4_t{x[0], x[1], x[2], x[3]};
-    } else {
-      u16x4 h, l;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        h[u] = f_to_h16(x[u], DK == kF16);
-        l[u] = f_to_h16(x[u] - h16_to_f(h[u], DK == kF16), DK == kF16);
-      }
-      reinterpret_cast<u16x4*>(dst)[i] = h;
-      if (dst_lo) reinterpret_cast<u16x4*>(dst_lo)[i] = l;
-    }
-  }
-}
-
-template <int DK, bool V4>
-__global__ void __launch_bounds__(256) prep_kernel(const double* __restrict__ src, void* dst,
-                                                   void* dst_lo, int64_t n,
-                                                   const int32_t* __restrict__ rexp, int cols_log2) {
-  if constexpr (V4) prep_body4<DK>(src, dst, dst_lo, n, rexp, cols_log2);
-  else prep_body<DK>(src, dst, dst_lo, n, rexp, cols_log2);
-}
-
 // blockIdx.y selects the argument block, blockIdx.z the instance
 template <int DK>
 __global__ void __launch_bounds__(256) prep_ind_kernel(const PrepArgs* __restrict__ a, int64_t slot) {
@@ -155,44 +113,199 @@ __global__ void __launch_bounds__(256) prep_ind_kernel(const PrepArgs* __restric
   prep_body<DK>(p.src, p.dst, p.dst_lo, p.n, p.rexp, p.cols_log2, p.colmax);
 }
 
-// Column maxima of |E| (rows x 2^cols_log2, FP64): each thread folds a run of
-// rows of one column, then one atomic max per thread.
-__global__ void __launch_bounds__(256) colmax_kernel(const double* __restrict__ E, int64_t rows,
-                                                     int cols_log2, int rows_per_thread,
-                                                     uint64_t* colmax, const int32_t* __restrict__ rexp) {
-  const int64_t cols = (int64_t)1 << cols_log2;
-  const int64_t chunks = (rows + rows_per_thread - 1) / rows_per_thread;
-  const int64_t total = chunks * cols;
+// Operand preparation of a full-definition call: each kernel serves every
+// operand in one launch, a run of workgroups each (block0), so a call pays one
+// launch a stage instead of one a stage and operand.  At the sizes where that
+// matters (a 25-qubit chain in three, scaled split planes) the stages were 15
+// of the call's 17 launches and 88 of its 129 us; see the figures below.
+struct OperandSet {
+  int n;
+  int balanced;
+  OperandIn in[CQ_MAX_SUBCIRCUITS];
+  ExpSumLaunch ex[2];
+  int ex_block0[2], ex_blocks[2];
+};
+
+// The operand of this workgroup (uniform) and the workgroups it has.
+__device__ inline int operand_of(const OperandSet& s, int nblocks, int& blocks) {
+  int c = 0;
+  for (int i = 1; i < s.n; ++i)
+    if ((int)blockIdx.x >= s.in[i].block0) c = i;
+  blocks = (c + 1 < s.n ? s.in[c + 1].block0 : nblocks) - s.in[c].block0;
+  return c;
+}
+
+// Clears the maxima that the next stages fold into with atomics.
+__global__ void __launch_bounds__(256) operand_clear_kernel(OperandSet s, int rows) {
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += step) {
-    const int64_t col = t & (cols - 1), r0 = (t >> cols_log2) * rows_per_thread;
-    int64_t r1 = r0 + rows_per_thread;
-    if (r1 > rows) r1 = rows;
-    double m = 0.0;
-    for (int64_t r = r0; r < r1; ++r) {
-      const double x = E[(r << cols_log2) + col];
-      m = fmax(m, fabs(rexp ? ldexp(x, rexp[r]) : x));
-    }
-    atomicMax(reinterpret_cast<unsigned long long*>(colmax + col),
-              (unsigned long long)__double_as_longlong(m));
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int c = 0; c < s.n; ++c) {
+    const OperandIn& in = s.in[c];
+    if (rows && in.rowmax)
+      for (int64_t i = i0; i < in.rows; i += step) in.rowmax[i] = 0ull;
+    if (in.colmax)
+      for (int64_t i = i0; i < (int64_t)1 << in.cols_log2; i += step) in.colmax[i] = 0ull;
   }
 }
 
-// max_b |E[l][b]| per row: one wave per row (rows strided over the grid's
-// waves), the wave's lanes striding the columns.
-__global__ void __launch_bounds__(256) rowmax_kernel(const double* __restrict__ E, int64_t rows,
-                                                     int cols_log2, uint64_t* rowmax) {
-  const int64_t cols = (int64_t)1 << cols_log2;
+// max_b |src[l][b]| per row.  A wave takes 64 consecutive entries at a time:
+// rows of at most 64 columns share a wave (a reduction over each row's lanes),
+// longer rows have a wave each, or 2^split waves where the rows alone would
+// leave the chip idle (4 rows of 2^20 columns: 4 waves walked 32 MiB); those
+// fold with one atomic a wave into maxima cleared before.
+__global__ void __launch_bounds__(256) operand_rowmax_kernel(OperandSet s, int clear) {
+  int nb;
+  const OperandIn& in = s.in[operand_of(s, gridDim.x, nb)];
+  const int64_t blk = (int)blockIdx.x - in.block0;
+  if (clear && in.colmax)
+    for (int64_t i = blk * 256 + threadIdx.x; i < (int64_t)1 << in.cols_log2; i += (int64_t)nb * 256)
+      in.colmax[i] = 0ull;
   const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t r = wave; r < rows; r += waves) {
-    const double* row = E + (r << cols_log2);
+  const int64_t waves = (int64_t)nb * 4;
+  const int cl = in.cols_log2;
+  if (cl <= 6) {
+    const int64_t n = in.rows << cl;
+    for (int64_t w = blk * 4 + (threadIdx.x >> 6); w * 64 < n; w += waves) {
+      const int64_t i = w * 64 + lane;
+      double m = i < n ? fabs(in.src[i]) : 0.0;
+      m = fmax(0.0, m);
+      for (int o = (1 << cl) >> 1; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+      if (i < n && (lane & ((1 << cl) - 1)) == 0) in.rowmax[i >> cl] = (uint64_t)__double_as_longlong(m);
+    }
+    return;
+  }
+  const int64_t units = in.rows << in.split;
+  const int64_t len = (int64_t)1 << (cl - in.split);  // a multiple of 64
+  for (int64_t u = blk * 4 + (threadIdx.x >> 6); u < units; u += waves) {
+    const double* p = in.src + u * len + lane;
     double m = 0.0;
-    for (int64_t c = lane; c < cols; c += 64) m = fmax(m, fabs(row[c]));
+    int64_t c = 0;
+    for (; c + 512 <= len; c += 512) {
+      double v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = p[c + 64 * j];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m = fmax(m, fabs(v[j]));
+    }
+    for (; c < len; c += 64) m = fmax(m, fabs(p[c]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if (lane == 0) rowmax[r] = (uint64_t)__double_as_longlong(m);
+    if (lane == 0) {
+      if (in.split == 0) in.rowmax[u] = (uint64_t)__double_as_longlong(m);
+      else atomicMax(reinterpret_cast<unsigned long long*>(in.rowmax + (u >> in.split)),
+                     (unsigned long long)__double_as_longlong(m));
+    }
+  }
+}
+
+// Column maxima of the rows as scaled by the balance: a thread folds `split`
+// rows of one column, eight loads in flight, then one atomic (a plain store
+// where one thread holds the whole column).  64 rows a thread in one chain of
+// loads left 4^5 x 2^7 entries 2048 threads and 12 us.
+constexpr int kColRows = 16;
+__global__ void __launch_bounds__(256) operand_colmax_kernel(OperandSet s) {
+  int nb;
+  const OperandIn& in = s.in[operand_of(s, gridDim.x, nb)];
+  const int cl = in.cols_log2, per = in.split;
+  const int64_t cols = (int64_t)1 << cl;
+  const int64_t total = (in.rows + per - 1) / per * cols;
+  for (int64_t t = ((int64_t)blockIdx.x - in.block0) * 256 + threadIdx.x; t < total; t += (int64_t)nb * 256) {
+    const int64_t col = t & (cols - 1), r0 = (t >> cl) * per;
+    const int64_t r1 = r0 + per < in.rows ? r0 + per : in.rows;
+    double m = 0.0;
+    for (int64_t r = r0; r < r1; r += 8) {
+      double x[8];
+      int e[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {  // the last row again past the end: a maximum does not change
+        const int64_t q = r + j < r1 ? r + j : r1 - 1;
+        x[j] = in.src[(q << cl) + col];
+        e[j] = in.rexp ? in.rexp[q] : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m = fmax(m, fabs(ldexp(x[j], e[j])));
+    }
+    if (per >= in.rows) in.colmax[col] = (uint64_t)__double_as_longlong(m);
+    else atomicMax(reinterpret_cast<unsigned long long*>(in.colmax + col),
+                   (unsigned long long)__double_as_longlong(m));
+  }
+}
+
+template <int DK>
+__device__ inline void store_planes(const OperandIn& in, int64_t i, float x) {
+  if constexpr (DK == kF32) {
+    static_cast<float*>(in.dst)[i] = x;
+  } else {
+    const uint16_t h = f_to_h16(x, DK == kF16);
+    static_cast<uint16_t*>(in.dst)[i] = h;
+    if (in.dst_lo) static_cast<uint16_t*>(in.dst_lo)[i] = f_to_h16(x - h16_to_f(h, DK == kF16), DK == kF16);
+  }
+}
+
+// FP64 -> FP32 or 16-bit planes (hi = rn16(x), lo = rn16(x - hi)), row l scaled
+// by 2^rexp[l] and column b by 2^-e of its maximum (exact); bound by memory.
+// Four elements a thread (two 16-byte loads, one 8- or 16-byte store a plane)
+// where `wide` says that rows hold them and the addresses are aligned.  The
+// last workgroups sum the output exponents, which need the maxima alone.
+template <int DK>
+__global__ void __launch_bounds__(256) operand_convert_kernel(OperandSet s, int nblocks) {
+  typedef double d2_t __attribute__((ext_vector_type(2)));
+  typedef float f4_t __attribute__((ext_vector_type(4)));
+  typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+  if ((int)blockIdx.x >= nblocks) {
+    const int q = (int)blockIdx.x >= s.ex_block0[1] ? 1 : 0;
+    const ExpSumLaunch& x = s.ex[q];
+    const int64_t step = (int64_t)s.ex_blocks[q] * 256;
+    for (int64_t r = ((int64_t)blockIdx.x - s.ex_block0[q]) * 256 + threadIdx.x; r < x.count; r += step) {
+      int e = 0;
+      for (int c = 0; c < x.n; ++c)
+        e += colmax_exp(x.colmax[c][(r >> x.shift[c]) & ((1ll << x.bits[c]) - 1)]);
+      x.out[r] = e;
+    }
+    return;
+  }
+  int nb;
+  const OperandIn& in = s.in[operand_of(s, nblocks, nb)];
+  const int64_t n = in.rows << in.cols_log2;
+  const int cl = in.cols_log2;
+  const int64_t cmask = ((int64_t)1 << cl) - 1;
+  const int64_t t0 = ((int64_t)blockIdx.x - in.block0) * 256 + threadIdx.x, step = (int64_t)nb * 256;
+  if (!in.wide) {
+    for (int64_t i = t0; i < n; i += step) {
+      int e = in.rexp ? in.rexp[i >> cl] : 0;
+      if (in.colmax) e -= colmax_exp(in.colmax[i & cmask]);
+      store_planes<DK>(in, i, float(ldexp(in.src[i], e)));
+    }
+    return;
+  }
+  for (int64_t i = t0; i < n >> 2; i += step) {
+    const d2_t v0 = reinterpret_cast<const d2_t*>(in.src)[2 * i];
+    const d2_t v1 = reinterpret_cast<const d2_t*>(in.src)[2 * i + 1];
+    const double d[4] = {v0[0], v0[1], v1[0], v1[1]};
+    int e[4];
+    const int er = in.rexp ? in.rexp[(4 * i) >> cl] : 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = er;
+    if (in.colmax) {
+      const uint64_t* cm = in.colmax + ((4 * i) & cmask);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) e[u] -= colmax_exp(cm[u]);
+    }
+    float x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = float(ldexp(d[u], e[u]));
+    if constexpr (DK == kF32) {
+      reinterpret_cast<f4_t*>(in.dst)[i] = f4_t{x[0], x[1], x[2], x[3]};
+    } else {
+      u16x4 h, l;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        h[u] = f_to_h16(x[u], DK == kF16);
+        l[u] = f_to_h16(x[u] - h16_to_f(h[u], DK == kF16), DK == kF16);
+      }
+      reinterpret_cast<u16x4*>(in.dst)[i] = h;
+      if (in.dst_lo) reinterpret_cast<u16x4*>(in.dst_lo)[i] = l;
+    }
   }
 }
 
@@ -214,6 +327,160 @@ __device__ inline int wave_max_i32(int v) {
   return v;
 }
 
+constexpr int kBalanceRounds = 4;
+constexpr int kBalThreads = 1024;
+constexpr int kBalLog = 10;            // log2 kBalThreads
+constexpr int kBalFixed = kBalLog / 2;  // digit positions fixed per thread
+constexpr int kBalUnroll = 4;
+
+// The offset per subcircuit that brings its largest scaled row (smax) to the
+// floor of their mean; they sum to zero.
+__device__ inline void balance_offsets(int n_sub, const int* smax, int* goff) {
+  int n = 0, last = -1;
+  long long sum = 0;
+  for (int c = 0; c < n_sub; ++c)
+    if (smax[c] != INT_MIN) {
+      sum += smax[c];
+      ++n;
+      last = c;
+    }
+  const long long mean = n ? (sum >= 0 ? sum / n : -((-sum + n - 1) / n)) : 0;
+  long long tot = 0;
+  for (int c = 0; c < n_sub; ++c) {
+    goff[c] = smax[c] == INT_MIN ? 0 : (int)(mean - smax[c]);
+    tot += goff[c];
+  }
+  if (last >= 0) goff[last] -= (int)tot;
+}
+
+// The balance of few rows (kBalSmallRows over all subcircuits), in one
+// workgroup.  Only the binary exponents of the maxima are used, and a scaled
+// row's exponent is its own plus its digits' shares (exact while it stays a
+// finite normal number: entries within 2^+-200 of one, whatever the shares), so
+// the rows are read once, as exponents held in LDS, and a round is additions:
+// every thread adds its rows' shares, a wave a (subcircuit, position) folds
+// the four digits' rows, a thread a cut makes the step.  Reading the rows from
+// memory and comparing FP64 maxima in every round (below) took 34 us for 1104
+// rows in three subcircuits.  Rows that a round scales past the range of a
+// double count as infinite (no step), or as zero.
+constexpr int kBalSmallRows = 8192;
+constexpr int kExpNone = -16384, kExpInf = 16384;
+
+__device__ __forceinline__ void balance_small(const BalanceArgs& b) {
+  __shared__ int16_t ex[kBalSmallRows], cur[kBalSmallRows];
+  __shared__ int pm[CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS][4];
+  __shared__ int share[CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS][4];  // of a row with digit d there
+  __shared__ int smax[CQ_MAX_SUBCIRCUITS], goff[CQ_MAX_SUBCIRCUITS];
+  __shared__ int changed;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int base = 0;
+  for (int c = 0; c < b.n_sub; ++c) {
+    const int rows = 1 << (2 * b.k[c]);
+    for (int l = tid; l < rows; l += kBalThreads) {
+      const double x = __longlong_as_double((long long)b.rowmax[c][l]);
+      ex[base + l] = (int16_t)(x > 0.0 ? isfinite(x) ? bexp(x) : kExpInf : kExpNone);
+    }
+    base += rows;
+  }
+  if (tid < CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS * 4) (&share[0][0])[tid] = 0;
+  if (tid < CQ_MAX_SUBCIRCUITS) smax[tid] = INT_MIN;
+  // a row's exponent (its digits' shares, positions k-1 .. 0 from the low end)
+  const auto row_exp = [&](int c, int l) {
+    int e = 0;
+    for (int p = b.k[c] - 1; p >= 0; --p, l >>= 2) e += share[c * CQ_MAX_LOCAL_CUTS + p][l & 3];
+    return e;
+  };
+  for (int round = 0; round < kBalanceRounds; ++round) {
+    if (tid == 0) changed = 0;
+    __syncthreads();
+    base = 0;
+    for (int c = 0; c < b.n_sub; ++c) {
+      const int rows = 1 << (2 * b.k[c]);
+      for (int l = tid; l < rows; l += kBalThreads) {
+        const int x = ex[base + l];
+        int y = x;
+        if (x > kExpNone && x < kExpInf) {
+          y = x + row_exp(c, l);
+          y = y > 1023 ? kExpInf : y < -1074 ? kExpNone : y;
+        }
+        cur[base + l] = (int16_t)y;
+      }
+      base += rows;
+    }
+    __syncthreads();
+    int task = 0;
+    base = 0;
+    for (int c = 0; c < b.n_sub; ++c) {
+      const int k = b.k[c];
+      for (int p = 0; p < k; ++p, ++task) {
+        if ((task & (kBalThreads / 64 - 1)) != wave) continue;
+        const int sh = 2 * (k - 1 - p), low = (1 << sh) - 1;
+        int m[4] = {kExpNone, kExpNone, kExpNone, kExpNone};
+        for (int q = lane; q < 1 << (2 * k - 2); q += 64) {
+          const int l = base + (((q & ~low) << 2) | (q & low));
+#pragma unroll
+          for (int d = 0; d < 4; ++d) m[d] = max(m[d], (int)cur[l + (d << sh)]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+          for (int d = 0; d < 4; ++d) m[d] = max(m[d], __shfl_xor(m[d], o, 64));
+        if (lane < 4) pm[c * CQ_MAX_LOCAL_CUTS + p][lane] = lane == 0 ? m[0] : lane == 1 ? m[1] : lane == 2 ? m[2] : m[3];
+      }
+      base += 1 << (2 * k);
+    }
+    __syncthreads();
+    // as below: half the difference of the two sides, less the mean over the
+    // digits, on the upstream side (the downstream side carries its negative)
+    if (tid < b.K) {
+      const int u = b.up[tid] * CQ_MAX_LOCAL_CUTS + b.pos_up[tid];
+      const int w = b.down[tid] * CQ_MAX_LOCAL_CUTS + b.pos_down[tid];
+      int st[4], sum = 0;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const int mu = pm[u][d], md = pm[w][d];
+        st[d] = 0;
+        if (mu > kExpNone && mu < kExpInf && md > kExpNone && md < kExpInf) st[d] = (md - mu) / 2;
+        sum += st[d];
+      }
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        int e = share[u][d] + st[d] - sum / 4;
+        e = e > 200 ? 200 : (e < -200 ? -200 : e);
+        if (e != share[u][d]) {
+          share[u][d] = e;
+          share[w][d] = -e;
+          changed = 1;
+        }
+      }
+    }
+    __syncthreads();
+    const int more = changed;
+    __syncthreads();  // every thread has read the flag before the next round clears it
+    if (!more) break;
+  }
+  // every subcircuit's largest scaled row, and the offsets
+  base = 0;
+  for (int c = 0; c < b.n_sub; ++c) {
+    const int rows = 1 << (2 * b.k[c]);
+    int sm = INT_MIN;
+    for (int l = tid; l < rows; l += kBalThreads) {
+      const int x = ex[base + l];
+      if (x > kExpNone && x < kExpInf) sm = max(sm, x + row_exp(c, l));
+    }
+    if (wave * 64 < rows) {
+      sm = wave_max_i32(sm);
+      if (lane == 0 && sm != INT_MIN) atomicMax(&smax[c], sm);
+    }
+    base += rows;
+  }
+  __syncthreads();
+  if (tid == 0) balance_offsets(b.n_sub, smax, goff);
+  __syncthreads();
+  for (int c = 0; c < b.n_sub; ++c)
+    for (int l = tid; l < 1 << (2 * b.k[c]); l += kBalThreads) b.rexp[c][l] = row_exp(c, l) + goff[c];
+}
+
 // One workgroup: per (subcircuit, digit position, digit) the largest row
 // maximum (LDS), then e_j(d) per cut and digit, then every row's exponent.
 // The largest row of a subcircuit sits at each digit's maximum over the other
@@ -230,13 +497,7 @@ __device__ inline int wave_max_i32(int v) {
 // A handful of LDS atomics per thread remain (a contended atomic per row and
 // position took over a millisecond for 4^8 rows), and four rows are loaded
 // before any is used.
-constexpr int kBalanceRounds = 4;
-constexpr int kBalThreads = 1024;
-constexpr int kBalLog = 10;            // log2 kBalThreads
-constexpr int kBalFixed = kBalLog / 2;  // digit positions fixed per thread
-constexpr int kBalUnroll = 4;
-
-__device__ __forceinline__ void balance_body(const BalanceLaunch& b) {
+__device__ __forceinline__ void balance_body(const BalanceArgs& b) {
   constexpr int kHi = CQ_MAX_LOCAL_CUTS > kBalFixed ? CQ_MAX_LOCAL_CUTS - kBalFixed : 1;
   __shared__ unsigned long long pmax[CQ_MAX_SUBCIRCUITS][CQ_MAX_LOCAL_CUTS][4];
   __shared__ int ej[CQ_MAX_CUTS][4];
@@ -246,6 +507,12 @@ __device__ __forceinline__ void balance_body(const BalanceLaunch& b) {
   __shared__ int changed;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
+  int64_t all = 0;
+  for (int c = 0; c < b.n_sub; ++c) all += (int64_t)1 << (2 * b.k[c]);
+  if (all <= kBalSmallRows) {
+    balance_small(b);
+    return;
+  }
   for (int i = tid; i < CQ_MAX_CUTS * 4; i += blockDim.x) (&ej[0][0])[i] = 0;
   if (tid < CQ_MAX_SUBCIRCUITS) smax[tid] = INT_MIN;
   // exponent share of position p (digit d) in a row of subcircuit c
@@ -383,24 +650,7 @@ __device__ __forceinline__ void balance_body(const BalanceLaunch& b) {
     if (lane == 0 && sm != INT_MIN) atomicMax(&smax[c], sm);
   }
   __syncthreads();
-  if (tid == 0) {
-    int n = 0, last = -1;
-    long long sum = 0;
-    for (int c = 0; c < b.n_sub; ++c)
-      if (smax[c] != INT_MIN) {
-        sum += smax[c];
-        ++n;
-        last = c;
-      }
-    // floor of the mean
-    const long long mean = n ? (sum >= 0 ? sum / n : -((-sum + n - 1) / n)) : 0;
-    long long tot = 0;
-    for (int c = 0; c < b.n_sub; ++c) {
-      goff[c] = smax[c] == INT_MIN ? 0 : (int)(mean - smax[c]);
-      tot += goff[c];
-    }
-    if (last >= 0) goff[last] -= (int)tot;  // the offsets sum to zero
-  }
+  if (tid == 0) balance_offsets(b.n_sub, smax, goff);
   __syncthreads();
   // every row's exponent: its digits' shares plus its subcircuit's offset
   for (int c = 0; c < b.n_sub; ++c) {
@@ -415,7 +665,7 @@ __device__ __forceinline__ void balance_body(const BalanceLaunch& b) {
   }
 }
 
-__global__ void __launch_bounds__(kBalThreads) balance_kernel(BalanceLaunch b) { balance_body(b); }
+__global__ void __launch_bounds__(kBalThreads) balance_kernel(BalanceArgs b) { balance_body(b); }
 
 // The balance of one instance of a dynamic-definition batch (grid z), from
 // its program; nothing when the recursion converts nothing.
@@ -574,40 +824,6 @@ __global__ void __launch_bounds__(256) rowmax_ind_kernel(const DDProgram* P, con
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
     if (lane == 0) rm[r] = (uint64_t)__double_as_longlong(m);
-  }
-}
-
-__global__ void __launch_bounds__(256) fill_u64_kernel(uint64_t* p, int64_t n, uint64_t v) {
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) p[i] = v;
-}
-
-template <int DK>
-__global__ void __launch_bounds__(256) prep_scaled_kernel(const double* __restrict__ src, void* dst,
-                                                          void* dst_lo, int64_t n, int cols_log2,
-                                                          const uint64_t* __restrict__ colmax,
-                                                          const int32_t* __restrict__ rexp) {
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  const int64_t mask = ((int64_t)1 << cols_log2) - 1;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
-    const int e = -colmax_exp(colmax[i & mask]) + (rexp ? rexp[i >> cols_log2] : 0);
-    const float x = float(ldexp(src[i], e));
-    if constexpr (DK == kF32) {
-      static_cast<float*>(dst)[i] = x;
-    } else {
-      const uint16_t h = f_to_h16(x, DK == kF16);
-      static_cast<uint16_t*>(dst)[i] = h;
-      if (dst_lo) static_cast<uint16_t*>(dst_lo)[i] = f_to_h16(x - h16_to_f(h, DK == kF16), DK == kF16);
-    }
-  }
-}
-
-__global__ void __launch_bounds__(256) expsum_kernel(ExpSumLaunch x) {
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < x.count; r += step) {
-    int e = 0;
-    for (int c = 0; c < x.n; ++c) e += colmax_exp(x.colmax[c][(r >> x.shift[c]) & ((1ll << x.bits[c]) - 1)]);
-    x.out[r] = e;
   }
 }
 
@@ -1184,35 +1400,6 @@ hipError_t launch_permute(const PermLaunch& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_prep(const double* src, void* dst, int64_t n, DType t, bool f16,
-                       hipStream_t stream, const int32_t* rexp, int cols_log2) {
-  if (n <= 0) return hipSuccess;
-  void* lo = t == DType::H16X2 ? static_cast<char*>(dst) + n * 2 : nullptr;
-  auto al = [](const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; };
-  const bool v4 = n % 4 == 0 && (!rexp || cols_log2 >= 2) && al(src, 16) &&
-                  al(dst, t == DType::F32 ? 16 : 8) && (!lo || al(lo, 8));
-  const dim3 grid(grid_for(v4 ? n / 4 : n));
-  if (t == DType::F32) {
-    if (v4) hipLaunchKernelGGL((prep_kernel<kF32, true>), grid, dim3(256), 0, stream, src, dst, nullptr, n, rexp, cols_log2);
-    else hipLaunchKernelGGL((prep_kernel<kF32, false>), grid, dim3(256), 0, stream, src, dst, nullptr, n, rexp, cols_log2);
-  } else if (f16) {
-    if (v4) hipLaunchKernelGGL((prep_kernel<kF16, true>), grid, dim3(256), 0, stream, src, dst, lo, n, rexp, cols_log2);
-    else hipLaunchKernelGGL((prep_kernel<kF16, false>), grid, dim3(256), 0, stream, src, dst, lo, n, rexp, cols_log2);
-  } else {
-    if (v4) hipLaunchKernelGGL((prep_kernel<kBF16, true>), grid, dim3(256), 0, stream, src, dst, lo, n, rexp, cols_log2);
-    else hipLaunchKernelGGL((prep_kernel<kBF16, false>), grid, dim3(256), 0, stream, src, dst, lo, n, rexp, cols_log2);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_rowmax(const double* E, int64_t rows, int cols_log2, uint64_t* rowmax,
-                         hipStream_t stream) {
-  if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rowmax_kernel, dim3(grid_for(rows * 64)), dim3(256), 0, stream, E, rows, cols_log2,
-                     rowmax);
-  return hipGetLastError();
-}
-
 hipError_t launch_dd_balance(const DDProgram* prog, const DDLevel* lv, int n_sub, int64_t max_rows,
                              hipStream_t stream, InstSpan span) {
   if (n_sub <= 0 || max_rows <= 0 || span.n <= 0) return hipSuccess;
@@ -1245,46 +1432,88 @@ hipError_t launch_dd_expsum(const DDProgram* prog, const DDState* st, const DDLe
   return hipGetLastError();
 }
 
+// The workgroups of one operand in a launch: one for every 256 work items, at
+// most 2^17 (the kernels loop).
+int operand_blocks(int64_t items) {
+  const int64_t b = (items + 255) / 256;
+  return (int)(b < 1 ? 1 : b > 1 << 17 ? 1 << 17 : b);
+}
+
 hipError_t launch_balance(const BalanceLaunch& b, hipStream_t stream) {
-  hipLaunchKernelGGL(balance_kernel, dim3(1), dim3(kBalThreads), 0, stream, b);
-  return hipGetLastError();
-}
-
-hipError_t launch_colmax(const double* E, int64_t rows, int cols_log2, uint64_t* colmax,
-                         hipStream_t stream, const int32_t* rexp) {
-  const int64_t cols = (int64_t)1 << cols_log2;
-  hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(cols)), dim3(256), 0, stream, colmax, cols,
-                     (uint64_t)0);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int rpt = 64;
-  const int64_t total = (rows + rpt - 1) / rpt * cols;
-  hipLaunchKernelGGL(colmax_kernel, dim3(grid_for(total)), dim3(256), 0, stream, E, rows, cols_log2,
-                     rpt, colmax, rexp);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep_scaled(const double* src, void* dst, int64_t n, int cols_log2,
-                              const uint64_t* colmax, DType t, bool f16, hipStream_t stream,
-                              const int32_t* rexp) {
-  if (n <= 0) return hipSuccess;
-  const dim3 grid(grid_for(n));
-  void* lo = t == DType::H16X2 ? static_cast<char*>(dst) + n * 2 : nullptr;
-  if (t == DType::F32)
-    hipLaunchKernelGGL((prep_scaled_kernel<kF32>), grid, dim3(256), 0, stream, src, dst, nullptr, n,
-                       cols_log2, colmax, rexp);
-  else if (f16)
-    hipLaunchKernelGGL((prep_scaled_kernel<kF16>), grid, dim3(256), 0, stream, src, dst, lo, n,
-                       cols_log2, colmax, rexp);
+  OperandSet s;
+  s.n = b.n_in;
+  s.balanced = b.balanced;
+  for (int c = 0; c < CQ_MAX_SUBCIRCUITS; ++c) s.in[c] = b.in[c];
+  for (int q = 0; q < 2; ++q) s.ex[q] = b.ex[q];
+  int blocks = 0;
+  bool scaled = false;
+  int64_t most = 1;  // maxima of one operand
+  for (int c = 0; c < s.n; ++c) {
+    scaled = scaled || s.in[c].colmax;
+    most = std::max(most, std::max(s.in[c].rows, (int64_t)1 << s.in[c].cols_log2));
+  }
+  const dim3 clear((unsigned)operand_blocks(most));
+  if (b.stage == BalanceLaunch::kExponents) {
+    bool atomics = false;
+    for (int c = 0; c < s.n; ++c) {
+      OperandIn& in = s.in[c];
+      const int64_t n = in.rows << in.cols_log2;
+      in.block0 = blocks;
+      in.split = 0;
+      if (in.cols_log2 > 6) {
+        // rows are split until 8192 waves (32 a CU) have work, or a part is
+        // down to 512 entries (one round of loads in flight)
+        while ((in.rows << in.split) < 8192 && in.cols_log2 - in.split > 9) ++in.split;
+        atomics = atomics || in.split > 0;
+        blocks += operand_blocks((in.rows << in.split) * 64);
+      } else {
+        blocks += operand_blocks(n);
+      }
+    }
+    if (s.n > 0) {
+      if (atomics) hipLaunchKernelGGL(operand_clear_kernel, clear, dim3(256), 0, stream, s, 1);
+      hipLaunchKernelGGL(operand_rowmax_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, s,
+                         scaled && !atomics ? 1 : 0);
+    }
+    hipLaunchKernelGGL(balance_kernel, dim3(1), dim3(kBalThreads), 0, stream, static_cast<const BalanceArgs&>(b));
+    return hipGetLastError();
+  }
+  if (s.n <= 0) return hipSuccess;
+  if (scaled) {
+    bool atomics = false;
+    for (int c = 0; c < s.n; ++c) {
+      OperandIn& in = s.in[c];
+      in.split = kColRows;
+      in.block0 = blocks;
+      atomics = atomics || in.rows > kColRows;
+      blocks += operand_blocks((in.rows + kColRows - 1) / kColRows << in.cols_log2);
+    }
+    // the balance's first stage has cleared them already
+    if (atomics && !s.balanced) hipLaunchKernelGGL(operand_clear_kernel, clear, dim3(256), 0, stream, s, 0);
+    hipLaunchKernelGGL(operand_colmax_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, s);
+  }
+  blocks = 0;
+  const auto al = [](const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; };
+  for (int c = 0; c < s.n; ++c) {
+    OperandIn& in = s.in[c];
+    const int64_t n = in.rows << in.cols_log2;
+    in.wide = n % 4 == 0 && ((!in.rexp && !in.colmax) || in.cols_log2 >= 2) && al(in.src, 16) &&
+              al(in.dst, b.t == DType::F32 ? 16 : 8) && (!in.dst_lo || al(in.dst_lo, 8));
+    in.block0 = blocks;
+    blocks += operand_blocks(in.wide ? n / 4 : n);
+  }
+  int grid = blocks;
+  for (int q = 0; q < 2; ++q) {
+    s.ex_block0[q] = grid;
+    s.ex_blocks[q] = s.ex[q].count > 0 ? operand_blocks(s.ex[q].count) : 0;
+    grid += s.ex_blocks[q];
+  }
+  if (b.t == DType::F32)
+    hipLaunchKernelGGL((operand_convert_kernel<kF32>), dim3((unsigned)grid), dim3(256), 0, stream, s, blocks);
+  else if (b.f16)
+    hipLaunchKernelGGL((operand_convert_kernel<kF16>), dim3((unsigned)grid), dim3(256), 0, stream, s, blocks);
   else
-    hipLaunchKernelGGL((prep_scaled_kernel<kBF16>), grid, dim3(256), 0, stream, src, dst, lo, n,
-                       cols_log2, colmax, rexp);
-  return hipGetLastError();
-}
-
-hipError_t launch_expsum(const ExpSumLaunch& x, hipStream_t stream) {
-  if (x.count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(expsum_kernel, dim3(grid_for(x.count)), dim3(256), 0, stream, x);
+    hipLaunchKernelGGL((operand_convert_kernel<kBF16>), dim3((unsigned)grid), dim3(256), 0, stream, s, blocks);
   return hipGetLastError();
 }
 

@@ -135,12 +135,6 @@ hipError_t launch_gemm_indirect(cq_precision prec, const GemmArgs* dev, int64_t 
                                 DType tc, bool nontemporal, bool topc, hipStream_t stream,
                                 InstSpan span = InstSpan());
 
-// Converts n FP64 values to `t` (FP32, or BF16/FP16 planes when f16 is false/true).
-// rexp (optional): element i is first multiplied by 2^rexp[i >> cols_log2]
-// (the per-label balance of its row, exact).
-hipError_t launch_prep(const double* src, void* dst, int64_t n, DType t, bool f16,
-                       hipStream_t stream, const int32_t* rexp = nullptr, int cols_log2 = 0);
-
 // Per-label balance of the 16-bit operands (powers of two, exact).  Every
 // labelling term of Eq. 1 carries, for each cut j, the factor of the
 // subcircuit that measures j's upstream end (row digit d at j) times that of
@@ -151,7 +145,7 @@ hipError_t launch_prep(const double* src, void* dst, int64_t n, DType t, bool f1
 // of two of each other; the maxima are taken again on the scaled rows and
 // e_j(d) corrected, for up to four rounds (until nothing changes).  rowmax:
 // per subcircuit, max_b |E_c[l][b]| per row l.
-struct BalanceLaunch {
+struct BalanceArgs {
   int n_sub, K;
   const uint64_t* rowmax[CQ_MAX_SUBCIRCUITS];  // FP64 bit patterns, 4^k_c each
   int32_t* rexp[CQ_MAX_SUBCIRCUITS];           // out: row exponents, 4^k_c each
@@ -160,23 +154,12 @@ struct BalanceLaunch {
   int up[CQ_MAX_CUTS], pos_up[CQ_MAX_CUTS];            // measuring subcircuit, digit position
   int down[CQ_MAX_CUTS], pos_down[CQ_MAX_CUTS];        // initialising subcircuit, digit position
 };
-// rowmax of E (rows x 2^cols_log2, FP64)
-hipError_t launch_rowmax(const double* E, int64_t rows, int cols_log2, uint64_t* rowmax,
-                         hipStream_t stream);
-hipError_t launch_balance(const BalanceLaunch& b, hipStream_t stream);
 
 // Column scaling by powers of two (16-bit operands).  colmax[b] receives the
 // bit pattern of max_l |E[l][b]| (FP64, so the unsigned order is the value
-// order); column b is then scaled by 2^-e, e the binary exponent with
-// max = f * 2^e, f in [0.5, 1).  Scaling is exact, and the result's
-// per-subcircuit exponents are added back at the end.
-// rexp (optional) as for launch_prep, applied before the maxima and the
-// conversion.
-hipError_t launch_colmax(const double* E, int64_t rows, int cols_log2, uint64_t* colmax,
-                         hipStream_t stream, const int32_t* rexp = nullptr);
-hipError_t launch_prep_scaled(const double* src, void* dst, int64_t n, int cols_log2,
-                              const uint64_t* colmax, DType t, bool f16, hipStream_t stream,
-                              const int32_t* rexp = nullptr);
+// order), with the balance's row exponents applied; column b is then scaled by
+// 2^-e, e the binary exponent with max = f * 2^e, f in [0.5, 1).  Scaling is
+// exact, and the result's per-subcircuit exponents are added back at the end:
 // out[r] = sum_c e_c(colmax[c][(r >> shift[c]) & (2^bits[c] - 1)]) for r < count.
 struct ExpSumLaunch {
   int32_t* out;
@@ -186,7 +169,37 @@ struct ExpSumLaunch {
   int shift[CQ_MAX_SUBCIRCUITS];
   int bits[CQ_MAX_SUBCIRCUITS];
 };
-hipError_t launch_expsum(const ExpSumLaunch& x, hipStream_t stream);
+
+// One operand of a full-definition call: rows x 2^cols_log2 FP64 entries and
+// what is derived from them.
+struct OperandIn {
+  const double* src;
+  void* dst;            // FP32, or the (hi) 16-bit plane
+  void* dst_lo;         // lo plane of a split operand, else null
+  uint64_t* rowmax;     // balance: max_b |src[l][b]| per row (FP64 bits), else null
+  const int32_t* rexp;  // balance: row l is scaled by 2^rexp[l] (exact), else null
+  uint64_t* colmax;     // column scaling: column maxima (FP64 bits), else null
+  int64_t rows;
+  int32_t cols_log2;
+  int32_t block0;       // first workgroup of the operand in a launch (set by the launcher)
+  int32_t split;        // set by the launcher: see the kernels
+  int32_t wide;         // set by the launcher: four elements a thread are aligned
+};
+
+// Operand preparation of a full-definition call, all operands together.
+// kExponents: the row maxima (balance only), then the row exponents.
+// kConvert: the column maxima (column scaling only), then the operands in `t`
+// (FP32, or BF16/FP16 planes when f16 is false/true) and the output exponents.
+struct BalanceLaunch : BalanceArgs {
+  enum Stage { kExponents, kConvert } stage;
+  bool balanced;  // kExponents runs before kConvert on the same workspace
+  DType t;
+  bool f16;
+  int n_in;
+  OperandIn in[CQ_MAX_SUBCIRCUITS];
+  ExpSumLaunch ex[2];  // count 0: none
+};
+hipError_t launch_balance(const BalanceLaunch& b, hipStream_t stream);
 
 constexpr int kMaxPermAxes = 48;
 struct PermLaunch {
@@ -385,7 +398,7 @@ struct DDProgram {
   RefineArgs total;                          // the recursion total: the row sums' single bin
   int32_t balance;                           // per-label balance of the 16-bit operands
   int32_t pad3;
-  BalanceLaunch bal;                         // its row maxima and exponents (4^k_c each)
+  BalanceArgs bal;                           // its row maxima and exponents (4^k_c each)
   // Column scaling of the FP16 operands (the plan's last step a GEMM writing
   // the bins): column maxima of every reduced entry, and the last GEMM's
   // output exponents -- over its rows (z * M + m) and columns (n), each the
