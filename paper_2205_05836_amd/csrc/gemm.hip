@@ -897,6 +897,17 @@ __device__ inline void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
+// Waits until at most min(ahead, A) stages of LPW loads are outstanding.
+template <int A, int LPW>
+__device__ inline void wait_ahead(int ahead) {
+  if constexpr (A == 0) {
+    wait_vm<0>();
+  } else {
+    if (ahead >= A) wait_vm<A * LPW>();
+    else wait_ahead<A - 1, LPW>(ahead);
+  }
+}
+
 // s_waitcnt vmcnt(n) for a wave-uniform n (above 63: 63, which waits longer).
 // An asm statement with a memory clobber, so no memory access moves across it.
 __device__ inline void wait_vm_n(int n) {
@@ -1815,15 +1826,177 @@ gemm_f64t_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
+// FP64 operands, 32 W x 32 W tiles of four waves (16 W x 16 W each), for GEMMs
+// with too few 64 x 128 tiles to give every CU two (launch_f64t): the more and
+// smaller workgroups reach more CUs, and as few waves share a SIMD a stage's
+// operands are read from LDS while the products of the stage before run, from
+// an NS-deep ring of 16-label stages (256 x 256 outputs of 256 labels: 45 us
+// with the tiled kernel, 20 with 64 x 128 tiles, 6.9; 1024 x 1024: 50, 24, 18).  W = 1: an operand row is
+// 256 bytes and a DMA instruction fills four of them, odd rows with their
+// 16-byte chunks swapped by halves so that the two rows a half wave reads fall
+// into different banks.  W = 2: rows of 512 bytes, two an instruction, and
+// block j of a wave's 32 columns takes columns 2 (l % 16) + j, as in
+// gemm_f64t_kernel.  k runs in ascending steps of four as there, so the sums
+// are the same bit for bit.
+// ---------------------------------------------------------------------------
+template <bool NT, int W, int NS>
+__global__ void __launch_bounds__(256) gemm_f64s_kernel(GemmArgs g) {
+  constexpr int BT = 32 * W, BK = 16, ROW = BT * 8;
+  constexpr int TILE = BK * ROW, STAGE = 2 * TILE;  // bytes of an operand stage, of both
+  constexpr int LPW = 2 * W;  // DMA instructions per wave per stage
+  // the hand-counted vmcnt waits below assume LPW DMA loads per stage; the
+  // build checks the assembly against this marker
+  asm volatile("; cq-vm-lpw %0" ::"n"(LPW));
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
+  CQ_LDS char* const lsm = (CQ_LDS char*)smem;
+  const TileCoord tc = tile_coord<BT, BT>(g);
+  const int64_t m0 = tc.m0, n0 = tc.n0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * 16 * W, wn = (wave & 1) * 16 * W;
+  const int nstages = (int)((g.K + BK - 1) / BK);
+  // instruction h of wave w for an operand fills RPI rows from RPI (w + 4h);
+  // addresses as in gemm_f64t_kernel: a uniform base that advances by a stage
+  // and a fixed per-lane offset, columns past the operand (M, N are even) and
+  // rows past K repeating the last ones
+  constexpr int RPI = 4 / W, LPR = 64 / RPI;  // rows an instruction, lanes a row
+  const bool whole = nstages * BK == g.K;
+  const int dr = lane / LPR;
+  const char* base[2][W];
+  uint32_t voff[2][W];
+#pragma unroll
+  for (int h = 0; h < W; ++h) {
+    const int64_t want = RPI * (wave + 4 * h);
+    const int64_t row0 = whole || want < g.K ? want : g.K - 1;
+    const int64_t d = whole || row0 + dr < g.K ? dr : g.K - 1 - row0;
+    const int chunk = (lane % LPR) ^ (W == 1 ? 8 * (dr & 1) : 0);
+#pragma unroll
+    for (int op = 0; op < 2; ++op) {
+      const int64_t sk = op ? g.sBk : g.sAk;
+      const int64_t cap = op ? g.N - 2 - n0 : g.M - 2 - m0;
+      const double* p = op ? static_cast<const double*>(g.B) + tc.z * g.sBz + n0
+                           : static_cast<const double*>(g.A) + tc.z * g.sAz + m0;
+      base[op][h] = uniform_ptr(p + row0 * sk);
+      voff[op][h] = (uint32_t)(8 * (d * sk + (2 * chunk > cap ? cap : 2 * chunk)));
+    }
+  }
+  const int64_t step[2] = {BK * 8 * g.sAk, BK * 8 * g.sBk};
+  const uint32_t dst0 = (uint32_t)(uintptr_t)lsm + wave * 1024;
+  auto issue = [&](int slot) {
+#pragma unroll
+    for (int op = 0; op < 2; ++op)
+#pragma unroll
+      for (int h = 0; h < W; ++h) {
+        dma_lds16(voff[op][h], base[op][h], dst0 + slot * STAGE + op * TILE + h * 4096);
+        base[op][h] += step[op];
+      }
+  };
+  d4_t acc[W][W];
+#pragma unroll
+  for (int i = 0; i < W; ++i)
+#pragma unroll
+    for (int j = 0; j < W; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+  const int r = lane >> 4, c = lane & 15;
+  // byte of the lane's column(s) in row r of its wave's block at column w0
+  const auto col = [&](int w0) {
+    return W == 2 ? (w0 + 2 * c) * 8 : ((((w0 + c) >> 1) ^ (8 * (r & 1))) << 4) + (c & 1) * 8;
+  };
+  CQ_LDS char* const la = lsm + r * ROW + col(wm);
+  CQ_LDS char* const lb = lsm + TILE + r * ROW + col(wn);
+  double a[2][BK / 4][W], b[2][BK / 4][W];
+  auto read = [&](int slot, int set) {
+#pragma unroll
+    for (int p = 0; p < BK / 4; ++p) {
+      if constexpr (W == 2) {
+        const dv2 x = *(const CQ_LDS dv2*)(la + slot * STAGE + 4 * p * ROW);
+        const dv2 y = *(const CQ_LDS dv2*)(lb + slot * STAGE + 4 * p * ROW);
+        a[set][p][0] = x[0];
+        a[set][p][1] = x[1];
+        b[set][p][0] = y[0];
+        b[set][p][1] = y[1];
+      } else {
+        a[set][p][0] = *(const CQ_LDS double*)(la + slot * STAGE + 4 * p * ROW);
+        b[set][p][0] = *(const CQ_LDS double*)(lb + slot * STAGE + 4 * p * ROW);
+      }
+    }
+  };
+  auto mul = [&](int set, int p) {
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[set][p][i], b[set][p][j], acc[i][j], 0, 0, 0);
+  };
+  if (whole) {
+    static_assert(NS % 2 == 0, "operand sets alternate within the unrolled ring");
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (s < nstages) issue(s);
+    wait_ahead<NS - 1, LPW>(nstages - 1);
+    __syncthreads();
+    read(0, 0);
+    for (int s0 = 0; s0 < nstages; s0 += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        if (s >= nstages) break;
+        if (s + 1 < nstages) {  // as in gemm_f32s_kernel
+          wait_ahead<NS - 2, LPW>(nstages - 2 - s);
+          __syncthreads();
+          if (s + NS < nstages) issue(u);
+          read((u + 1) % NS, (u + 1) & 1);
+        }
+#pragma unroll
+        for (int p = 0; p < BK / 4; ++p) mul(u & 1, p);
+      }
+    }
+  } else {
+    issue(0);
+    wait_vm<0>();
+    __syncthreads();
+    read(0, 0);
+#pragma unroll
+    for (int p = 0; p < BK / 4; ++p) {
+      if (4 * p >= g.K) break;  // short K: skip all-zero steps
+      if (4 * p + r >= g.K)  // rows past K hold a copy of row K - 1
+#pragma unroll
+        for (int i = 0; i < W; ++i) a[0][p][i] = b[0][p][i] = 0.0;
+      mul(0, p);
+    }
+  }
+
+  double* const C = static_cast<double*>(g.C) + tc.z * g.sCz;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      // item v of lane l is row l/16 + 4v of its block, column l%16
+      const int64_t m = m0 + wm + W * (r + 4 * v) + i, n = n0 + wn + W * c;
+      if (m >= g.M || n >= g.N) continue;
+      if constexpr (W == 2)
+        store_out<dv2, NT>(reinterpret_cast<dv2*>(C + m * g.ldc + n),
+                           dv2{g.alpha * acc[i][0][v], g.alpha * acc[i][1][v]});
+      else
+        store_out<double, NT>(C + m * g.ldc + n, g.alpha * acc[0][0][v]);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // FP32 operands, 64 x 64 tiles: for GEMMs with few 128 x 128 tiles (a few
-// hundred outputs per side), four times as many workgroups reach the CUs.
-// Each wave owns one 32 x 32 block; stages hold 16 labels (4 KB per operand,
-// rows of 256 bytes) in an NS-deep ring, one DMA instruction per wave and
-// operand filling four rows, odd rows with their 16-byte chunks swapped by
-// halves so that the two rows an MFMA operand read touches fall into
-// different banks.  Products run in the persistent FP32 kernel's order (k
-// ascending in pairs, one 32x32x2 MFMA per pair), so the sums are the same
-// bit for bit; results are stored from registers.
+// hundred outputs per side), four times as many workgroups reach the CUs, one
+// wave a SIMD in the smallest.  Each wave owns one 32 x 32 block; stages hold
+// 16 labels (4 KB per operand, rows of 256 bytes) in an NS-deep ring, one DMA
+// instruction per wave and operand filling four rows, odd rows with their
+// 16-byte chunks swapped by halves so that the two rows an MFMA operand read
+// touches fall into different banks.  With nothing else on the SIMD a stage's
+// products (512 cycles) have to cover the memory latency by themselves, so the
+// ring is eight deep and a stage's operands are read from LDS while the
+// products of the stage before run (1024 x 1024 outputs of 256 labels: 16.2 us
+// with a three-deep ring and vector address arithmetic in every stage, now
+// 11.7, of which the products are 3.4 to 5 at the clock of a short launch).
+// Products run in the persistent
+// FP32 kernel's order (k ascending in pairs, one 32x32x2 MFMA per pair), so
+// the sums are the same bit for bit; results are stored from registers.
 // ---------------------------------------------------------------------------
 template <int OUT, int NS>
 __global__ void __launch_bounds__(256) gemm_f32s_kernel(GemmArgs g) {
@@ -1834,68 +2007,97 @@ __global__ void __launch_bounds__(256) gemm_f32s_kernel(GemmArgs g) {
   // the hand-counted vmcnt waits below assume LPW DMA loads per stage; the
   // build checks the assembly against this marker
   asm volatile("; cq-vm-lpw %0" ::"n"(LPW));
-  static_assert(NS >= 2 && NS <= 4, "stage count");
+  static_assert(NS >= 2 && NS <= 8, "stage count");
   __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
   CQ_LDS char* const lsm = (CQ_LDS char*)smem;
   const TileCoord tc = tile_coord<BM, BN>(g);
   const int64_t m0 = tc.m0, n0 = tc.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int nstages = (int)((g.K + BK - 1) / BK);
   // wave w's instruction for an operand fills rows 4w .. 4w + 3, sixteen
-  // lanes a row; slot q of row r holds the row's chunk q ^ 8(r & 1)
-  const int lrow = 4 * wave + (lane >> 4);
-  const int slot = lane & 15;
-  const float* gbase[2];
-  int64_t lcol[2];
+  // lanes a row; slot q of row r holds the row's chunk q ^ 8(r & 1).
+  // Addresses as in gemm_h16t_kernel: a uniform base that advances by a stage
+  // and a fixed per-lane offset (rows past K repeat row K - 1).
+  const bool whole = nstages * BK == g.K;
+  const int q4 = lane >> 4, slot16 = lane & 15;
+  const int64_t row0 = whole || 4 * wave < g.K ? 4 * wave : g.K - 1;
+  const char* base[2] = {uniform_ptr(static_cast<const float*>(g.A) + tc.z * g.sAz + row0 * g.sAk + m0),
+                         uniform_ptr(static_cast<const float*>(g.B) + tc.z * g.sBz + row0 * g.sBk + n0)};
+  uint32_t voff[2];
   {
-    gbase[0] = static_cast<const float*>(g.A) + tc.z * g.sAz + m0;
-    gbase[1] = static_cast<const float*>(g.B) + tc.z * g.sBz + n0;
     // last 16-byte chunk inside each operand (M, N are multiples of 4)
-    const int64_t capA = ((g.M - 4) & ~(int64_t)3) - m0, capB = ((g.N - 4) & ~(int64_t)3) - n0;
-    const int64_t col = (int64_t)(slot ^ (8 * (lrow & 1))) * 4;
-    lcol[0] = col > capA ? capA : col;
-    lcol[1] = col > capB ? capB : col;
+    const int64_t cap[2] = {((g.M - 4) & ~(int64_t)3) - m0, ((g.N - 4) & ~(int64_t)3) - n0};
+    const int64_t col = (int64_t)(slot16 ^ (8 * (q4 & 1))) * 4;
+    const int64_t dr = whole || row0 + q4 < g.K ? q4 : g.K - 1 - row0;
+#pragma unroll
+    for (int op = 0; op < 2; ++op)
+      voff[op] = (uint32_t)(4 * (dr * (op ? g.sBk : g.sAk) + (col > cap[op] ? cap[op] : col)));
   }
-  auto issue = [&](int s) {
-    int64_t k = (int64_t)s * BK + lrow;
-    if (k >= g.K) k = g.K - 1;  // rows past K are masked to zero when read
+  const int64_t step[2] = {BK * 4 * g.sAk, BK * 4 * g.sBk};
+  const uint32_t dst0 = (uint32_t)(uintptr_t)lsm + wave * 1024;
+  auto issue = [&](int slot) {
 #pragma unroll
     for (int op = 0; op < 2; ++op) {
-      const float* src = gbase[op] + k * (op ? g.sBk : g.sAk) + lcol[op];
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(
-          (uint32_t)(uintptr_t)(lsm + (s % NS) * STAGE + op * TILE + wave * 1024));
-      asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
-                   : "memory", "m0");
+      dma_lds16(voff[op], base[op], dst0 + slot * STAGE + op * TILE);
+      base[op] += step[op];
     }
   };
   f16_t acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
   const int r = lane >> 5, c = lane & 31;
+  const int ca = wm + c, cb = wn + c;
+  CQ_LDS char* const fa = lsm + r * 256 + (((ca >> 2) ^ (8 * r)) << 4) + (ca & 3) * 4;
+  CQ_LDS char* const fb = lsm + TILE + r * 256 + (((cb >> 2) ^ (8 * r)) << 4) + (cb & 3) * 4;
 
-  for (int s = 0; s < NS - 1 && s < nstages; ++s) issue(s);
-  for (int s = 0; s < nstages; ++s) {
-    // this wave's loads of stage s have landed once at most `ahead` later
-    // stages are outstanding; the barrier then covers every wave's loads
-    const int ahead = (nstages - 1 - s) < (NS - 2) ? (nstages - 1 - s) : (NS - 2);
-    if (ahead >= 2) wait_vm<2 * LPW>();
-    else if (ahead == 1) wait_vm<LPW>();
-    else wait_vm<0>();
-    __syncthreads();
-    if (s + NS - 1 < nstages) issue(s + NS - 1);
-    const int sb = (s % NS) * STAGE;
-    const int64_t kvalid = g.K - (int64_t)s * BK;
+  float a[2][BK / 2], b[2][BK / 2];
+  auto read = [&](int slot, int set) {
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      if (kk >= kvalid) break;  // short K (outer products): skip all-zero steps
-      const int row = kk + r;
-      const int ca = wm + c, cb = wn + c;
-      float a = *(const CQ_LDS float*)(lsm + sb + row * 256 + (((ca >> 2) ^ (8 * r)) << 4) + (ca & 3) * 4);
-      const float b =
-          *(const CQ_LDS float*)(lsm + sb + TILE + row * 256 + (((cb >> 2) ^ (8 * r)) << 4) + (cb & 3) * 4);
-      if (row >= kvalid) a = 0.0f;  // rows past K hold a clamped copy of row K - 1
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+    for (int p = 0; p < BK / 2; ++p) {
+      a[set][p] = *(const CQ_LDS float*)(fa + slot * STAGE + p * 512);
+      b[set][p] = *(const CQ_LDS float*)(fb + slot * STAGE + p * 512);
+    }
+  };
+  if (whole) {
+    static_assert(NS % 2 == 0, "operand sets alternate within the unrolled ring");
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (s < nstages) issue(s);
+    wait_ahead<NS - 1, LPW>(nstages - 1);
+    __syncthreads();
+    read(0, 0);
+    for (int s0 = 0; s0 < nstages; s0 += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        if (s >= nstages) break;
+        if (s + 1 < nstages) {
+          // this wave's loads of stage s + 1 have landed and its reads of
+          // stage s are done; the barrier then covers every wave's, so stage
+          // s + NS may overwrite stage s.  The next operands are read while
+          // this stage's products run.
+          wait_ahead<NS - 2, LPW>(nstages - 2 - s);
+          __syncthreads();
+          if (s + NS < nstages) issue(u);
+          read((u + 1) % NS, (u + 1) & 1);
+        }
+#pragma unroll
+        for (int p = 0; p < BK / 2; ++p)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u & 1][p], b[u & 1][p], acc, 0, 0, 0);
+      }
+    }
+  } else {
+    issue(0);
+    wait_vm<0>();
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < BK / 2; ++p) {
+      if (2 * p >= g.K) break;  // short K (outer products): skip all-zero steps
+      float x = *(const CQ_LDS float*)(fa + p * 512);
+      const float y = *(const CQ_LDS float*)(fb + p * 512);
+      if (2 * p + r >= g.K) x = 0.0f;  // rows past K hold a copy of row K - 1
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
     }
   }
 
@@ -2331,10 +2533,34 @@ bool f64t_ok(const GemmArgs& a) {
          a.sAz % 2 == 0 && a.sBz % 2 == 0 && a.ldc % 2 == 0 && a.sCz % 2 == 0 && al(a.A) && al(a.B) && al(a.C);
 }
 
+constexpr int64_t kF64Few = 512, kF64Fewer = 128;
+template <int W, int NS>
+hipError_t launch_f64s(GemmArgs a, int64_t z, bool nt, hipStream_t s) {
+  a.tilesM = (a.M + 32 * W - 1) / (32 * W);
+  a.tilesN = (a.N + 32 * W - 1) / (32 * W);
+  a.tiles = a.tilesM * a.tilesN * z;
+  if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.tiles), block(256);
+  if (nt) hipLaunchKernelGGL((gemm_f64s_kernel<true, W, NS>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_f64s_kernel<false, W, NS>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+// The FP64 tile: 64 x 128 where that gives every CU two workgroups or more,
+// 64 x 64 down to one workgroup for every second CU, else 32 x 32.
+// A call with 256 labels: 2048 x 1024 outputs take 20.4 us with 64 x 64 tiles
+// against 21.5 with 64 x 128 and 27.2 with 32 x 32; 2048 x 2048 38.3 with 64 x
+// 64 against 35.3 with 64 x 128; 1024 x 512 and fewer 15.1 (the host) against
+// 20 with 64 x 128.
 hipError_t launch_f64t(GemmArgs a, bool nt, hipStream_t s) {
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
   a.tilesM = (a.M + 63) / 64;
   a.tiles = a.tilesM * a.tilesN * z;
+  // (three rows of a stage within a 32-bit byte offset)
+  if (a.tiles < kF64Few && ring_ok(a, 16) && a.sAk < (int64_t)1 << 27 && a.sBk < (int64_t)1 << 27) {
+    if (a.tilesM * ((a.N + 63) / 64) * z >= kF64Fewer) return launch_f64s<2, 4>(a, z, nt, s);
+    return launch_f64s<1, 8>(a, z, nt, s);
+  }
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.tiles), block(256);
   if (nt) hipLaunchKernelGGL((gemm_f64t_kernel<true, 3, 4>), grid, block, 0, s, a);
@@ -2343,6 +2569,7 @@ hipError_t launch_f64t(GemmArgs a, bool nt, hipStream_t s) {
 }
 
 bool f32t_ok(const GemmArgs& a) { return ring_ok(a, 8) && f32p_ok(a); }
+bool f32s_ok(const GemmArgs& a) { return ring_ok(a, 16) && f32p_ok(a); }
 
 template <int SPLIT, bool F16>
 hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
@@ -2358,7 +2585,10 @@ hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int NS>
+// Ring of eight stages (two workgroups a CU) while there are no more tiles
+// than that, else of two: with short K and many tiles the output stores want
+// the workgroups (2^26 outputs of 16 labels: 71 us with eight
+// stages, 46 with two).
 hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
   a.tilesM = (a.M + 63) / 64;
@@ -2366,8 +2596,13 @@ hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   a.tiles = a.tilesM * a.tilesN * z;
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.tiles), block(256);
-  if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, NS>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gemm_f32s_kernel<0, NS>), grid, block, 0, s, a);
+  if (a.tiles <= 512) {
+    if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, 8>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((gemm_f32s_kernel<0, 8>), grid, block, 0, s, a);
+  } else {
+    if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((gemm_f32s_kernel<0, 2>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -2444,7 +2679,7 @@ hipError_t launch_variant(cq_precision prec, GemmArgs a, DType tc, bool nt, int 
       // 0 = tiled kernel, 1 = 64 x 64 tiles (2 repeats 0), 3 = persistent
       // kernel, 4 and 5 = occupancy kernel (four workgroups per CU with a
       // three- or four-deep ring)
-      if (impl == 1 && f32p_ok(a)) return launch_f32s<3>(a, nt, stream);
+      if (impl == 1 && f32s_ok(a)) return launch_f32s(a, nt, stream);
       if (impl == 4 && f32t_ok(a)) return launch_f32t<3, 4>(a, nt, stream);
       if (impl == 5 && f32t_ok(a)) return launch_f32t<4, 4>(a, nt, stream);
       if (impl == 3 && f32p_ok(a)) {
@@ -2598,9 +2833,19 @@ bool variant_applies(cq_precision prec, const GemmArgs& a, DType tc, int v) {
   const int impl = v >> 1;
   if (impl == 0) return true;
   if (v >= variant_count(prec)) return false;
-  if (prec == CQ_FP32) return impl >= 4 ? f32t_ok(a) : (impl == 1 || impl == 3) && f32p_ok(a);
+  if (prec == CQ_FP32) return impl >= 4 ? f32t_ok(a) : impl == 1 ? f32s_ok(a) : impl == 3 && f32p_ok(a);
   if (impl == 4 || impl == 5) return h16t_ok(a, tc);
   return impl == 3 ? h16p_ok(a, tc) : h16_async_ok(a, tc);
+}
+
+// The variant of a GEMM with fewer than 64 tiles of 128 x 128, which is not
+// timed: 64 x 64 tiles where they apply, since 128 x 128 ones leave three in
+// four CUs idle (256 x 256 outputs of 256 labels: FP32 38 us, 9 with 64 x 64;
+// BF16 split 13.4, 3.5).
+int few_tiles_variant(cq_precision prec, const GemmArgs& a, DType tc) {
+  if (prec == CQ_FP64) return 0;  // launch_f64t chooses its tile by the same count
+  if (prec == CQ_FP32) return f32s_ok(a) ? 2 : 0;
+  return h16p_ok(a, tc) ? 4 : 0;
 }
 
 }  // namespace
@@ -2673,7 +2918,8 @@ hipError_t launch_gemm(cq_precision prec, const GemmLaunch& g, hipStream_t strea
     const int v = mode - 2;
     return launch_variant(prec, a, g.tc, nt, variant_applies(prec, a, g.tc, v) ? v : 0, stream);
   }
-  if (mode == 0 || a.tiles < 64) return launch_variant(prec, a, g.tc, nt, 0, stream);
+  if (mode == 0) return launch_variant(prec, a, g.tc, nt, 0, stream);
+  if (a.tiles < 64) return launch_variant(prec, a, g.tc, nt, few_tiles_variant(prec, a, g.tc), stream);
   const TuneKey key{(int)prec, (int)g.tc, nt ? 1 : 0, g.sAz ? 1 : 0, g.sBz ? 1 : 0,
                     h16_async_ok(a, g.tc) ? 1 : 0, g.M, g.N, g.K, g.Z};
   {
@@ -2756,7 +3002,7 @@ std::string variant_schedule(int prec, int v) {
   int ring = 0, wpc = 0, tile = 128;
   if (prec == CQ_FP32 && impl == 1) {
     kernel = "small-tile";
-    ring = 3;
+    ring = 8;
     tile = 64;
   } else if (prec == CQ_FP32 && impl >= 3) {
     kernel = impl == 3 ? "persistent" : "occupancy";
