@@ -70,3 +70,22 @@ def test_prepared_operands_match_oracle(bonds, ns, prec, balance, offset):
     worst = (np.abs(out - ref) / scale).max()
     print(f"{prec} {bonds} {ns}: {worst:.2e} of {tol:.2e}", flush=True)
     assert worst <= tol
+
+
+@pytest.mark.parametrize("outs", [[1, 3], [6, 3]])
+def test_bf16_operands_are_rounded_through_fp32(outs):
+    """FP64 values a little off a BF16 tie that FP32 rounds onto it: the
+    operand is the BF16 of the FP32 value, which goes to the even neighbour.
+    One cut whose only nonzero label pairs each value with a one, so every
+    output is half an operand exactly."""
+    import paper_2205_05836_amd as m
+    cm = syn.chain_cutmap([1], outs)
+    base = 1.0 + 2.0 ** -7 * np.arange(2 ** outs[0])  # BF16 values of [1, 2)
+    off = np.where(np.arange(2 ** outs[0]) % 2 == 0, 2.0 ** -40, -2.0 ** -40)  # towards the odd neighbour
+    E = [np.zeros((4, 2 ** n)) for n in outs]
+    E[0][0] = base + 2.0 ** -8 + off
+    E[1][0] = 1.0
+    want = torch.from_numpy(E[0][0]).float().bfloat16().double().numpy()
+    assert not np.array_equal(want, base + 2.0 ** -7 * (off > 0))  # one rounding would differ
+    out = m.cq_reconstruct_fd(cm, [torch.from_numpy(e).cuda() for e in E], prec="bf16").cpu().numpy()
+    assert np.array_equal(out.reshape(2 ** outs[0], -1), np.repeat(0.5 * want[:, None], 2 ** outs[1], 1))
