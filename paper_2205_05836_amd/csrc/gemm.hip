@@ -21,6 +21,7 @@
 #include <cstdio>
 #include <cstring>
 #include <cstdlib>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <string>
@@ -259,14 +260,17 @@ __device__ inline T tau_as(double tau) {
 // are unrolled, so keys of one lane compare by their offsets); valid(e):
 // inside M x N, asked on partial tiles only.
 //
-// Keys at or above tau take part.  The C-th best of the lanes' own best keys
-// bounds the tile's C-th best key from below (at least C keys reach it), so
-// only keys reaching it are appended to LDS, where each key's rank among
-// them is its place in the answer.  Should more than kTopcCap keys reach the
-// bound (the best keys crowd into a few lanes), each wave instead takes its C
-// best of them by C rounds of a wave arg-max and wave 0 merges the waves'
-// lists the same way.  The per-key steps are selects, not branches, which
-// keeps the unrolled code short.
+// Keys at or above tau take part.  The C-th best of the best keys of groups of
+// lanes (bound_owner) bounds the tile's C-th best key from below (at least C
+// keys reach it), so only keys reaching it are appended to LDS, where each
+// key's rank among them is its place in the answer.  Should more than kTopcCap
+// keys reach the bound (the best keys crowd into a few lanes), each wave
+// instead takes its C best of them by C rounds of a wave arg-max and wave 0
+// merges the waves' lists the same way.  Bound by instruction issue: the
+// passes over a lane's keys are a maximum, the offset of the best, and one
+// comparison and an untaken branch a key (a few keys pass).  1024 FP32 tiles of
+// 16 labels without a threshold yet: 124 us with every lane ranked and masks
+// and selects for every key, 101 with the ranking by groups, 53 now.
 template <typename T, int V, int NTHR, typename Val, typename Off, typename Valid>
 __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t m0, int64_t n0, bool full,
                                           Val val, Off koff, int base, Valid valid) {
@@ -275,7 +279,7 @@ __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t 
   constexpr int kNone = 0x7fffffff;
   static_assert(V <= 64, "one live bit per value");
   __shared__ K lane_best[NTHR];
-  __shared__ K cand[kTopcCap + NTHR];  // beyond kTopcCap: one parking slot per thread
+  __shared__ K cand[kTopcCap];
   __shared__ K wk[NW][kDDMaxC];
   __shared__ K outk[kDDMaxC];
   __shared__ int wn[NW];
@@ -285,60 +289,47 @@ __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t 
   if (C <= 0) return;
   const T tau = tau_as<T>(ord_val(*g.topc_thr));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    // most tiles end here: nothing (not even outside M x N) reaches tau
-    T mx = val(0);
+  // values outside M x N as NaN: no comparison holds for them
+  T x[V];
 #pragma unroll
-    for (int e = 1; e < V; ++e) mx = val(e) > mx ? val(e) : mx;
-    if (__syncthreads_count(mx >= tau) == 0) return;
+  for (int e = 0; e < V; ++e) x[e] = val(e);
+  if (!full) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) x[e] = valid(e) ? x[e] : std::numeric_limits<T>::quiet_NaN();
   }
-  // the keys at or above tau and the lane's best of them
-  uint64_t live = 0;
-  T bv = T(0);
+  T bv = x[0];
+#pragma unroll
+  for (int e = 1; e < V; ++e) bv = fmax(bv, x[e]);
+  const bool has = bv >= tau;
+  const int lanes = __syncthreads_count(has);
+  if (lanes == 0) return;  // most tiles end here: nothing reaches tau
   int bk = kNone;
 #pragma unroll
-  for (int e = 0; e < V; ++e) {
-    const T v = val(e);
-    const int k = koff(e);
-    // bitwise, not short-circuit: selects instead of branches
-    const bool ok = (full | valid(e)) & (v >= tau);
-    live |= (uint64_t)ok << e;
-    const bool b = ok & ((bk == kNone) | (v > bv) | ((v == bv) & (k < bk)));
-    bv = b ? v : bv;
-    bk = b ? k : bk;
-  }
-  live = opaque_mask(live);
-  if (__syncthreads_count(live != 0) == 0) return;
+  for (int e = 0; e < V; ++e) bk = min(bk, x[e] == bv ? koff(e) : kNone);
   if (tid == 0) {
     cnt = 0;
     owner = -1;
   }
-  const bool has = bk != kNone;
   const K mine = has ? K{bv, (uint32_t)(base + bk)} : tc_worst<T>();
-  lane_best[tid] = mine;
-  __syncthreads();
-  if (has && rank_of(lane_best, NTHR, mine) == C - 1) owner = tid;  // distinct keys, distinct ranks
-  __syncthreads();
-  const int own = owner;
-  if (own >= 0) {
-    const K t0 = lane_best[own];
-    const int d = (int)t0.i - base;
+  int own = -1;
+  if (lanes >= C) {  // else fewer than C lanes have a key, and nothing bounds the C-th best
+    own = bound_owner<T, NTHR>(lane_best, owner, mine, has, C, [](const K& k, int q) {
+      return K{__shfl_xor(k.v, q), (uint32_t)__shfl_xor((int)k.i, q)};
+    });
+  } else {
+    __syncthreads();
+  }
+  // the keys that pass: above the bound, or equal to it up to its place
+  const T tv = own >= 0 ? lane_best[own].v : tau;
+  const int td = own >= 0 ? (int)lane_best[own].i - base : kNone;
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const T v = val(e);
-      const bool drop = (t0.v > v) | ((t0.v == v) & (d < koff(e)));
-      live &= ~((uint64_t)drop << e);
+  for (int e = 0; e < V; ++e)
+    if (x[e] >= tv) {
+      if (x[e] > tv || koff(e) <= td) {
+        const int off = atomicAdd(&cnt, 1);
+        if (off < kTopcCap) cand[off] = K{x[e], (uint32_t)(base + koff(e))};
+      }
     }
-    live = opaque_mask(live);
-  }
-  int off = __popcll(live);
-  off = off ? atomicAdd(&cnt, off) : 0;
-#pragma unroll
-  for (int e = 0; e < V; ++e) {
-    const bool l = (live >> e) & 1;
-    cand[(l & (off < kTopcCap)) ? off : kTopcCap + tid] = K{val(e), (uint32_t)(base + koff(e))};
-    off += l ? 1 : 0;
-  }
   __syncthreads();
   int n = cnt;
   if (n > kTopcCap && g.topc_publish_only) {
@@ -355,6 +346,10 @@ __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t 
     }
     n = n < C ? n : C;
   } else {
+    uint64_t live = 0;
+#pragma unroll
+    for (int e = 0; e < V; ++e) live |= (uint64_t)((x[e] > tv) | ((x[e] == tv) & (koff(e) <= td))) << e;
+    live = opaque_mask(live);
     int got = 0;
     for (int round = 0; round < C; ++round) {
       if (__ballot(live != 0) == 0) break;
@@ -362,7 +357,7 @@ __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t 
       int rk = kNone, re = -1;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
-        const T v = val(e);
+        const T v = x[e];
         const int k = koff(e);
         const bool b = (bool)((live >> e) & 1) & ((rk == kNone) | (v > rv) | ((v == rv) & (k < rk)));
         rv = b ? v : rv;
@@ -613,7 +608,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& g, int64_t vb) {
 }
 
 template <bool NT, bool TC = false>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs gv, const GemmArgs* __restrict__ gp,
+__global__ void __launch_bounds__(256, TC ? 2 : 1) gemm_f32_kernel(GemmArgs gv, const GemmArgs* __restrict__ gp,
                                                        int64_t gp_stride) {
   CQ_TILE_LOOP((gemm_f32_tile<NT, TC>(g, vb)))
 }

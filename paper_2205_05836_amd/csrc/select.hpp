@@ -4,9 +4,9 @@
 // index.  Every lane holds up to V keys (bit e of a 64-bit `live` mask marks
 // key e as taking part).
 //
-// Bound, filter, rank: the C-th best of the lanes' own best keys is a key
-// that at least C keys reach, so it bounds the C-th best key overall from
-// below.  Keys that reach it are appended to LDS, and each appended key's
+// Bound, filter, rank: the C-th best of the best keys of small groups of lanes
+// is a key that at least C keys reach, so it bounds the C-th best key overall
+// from below.  Keys that reach it are appended to LDS, and each appended key's
 // rank among them is its place in the answer.  A handful of keys usually
 // pass; when more than CAP do (the best keys crowd into a few lanes), the
 // caller runs its exhaustive selection over the narrowed `live` instead.
@@ -61,6 +61,51 @@ __device__ __forceinline__ int rank_of(const K* S, int n, const K& k) {
   return r;
 }
 
+// The place in `best` (NTHR keys of LDS, NTHR threads) of a bound for the C-th
+// best key, or -1 when fewer than C lanes have one.  mine: the lane's best key
+// (has: it has one, else the worst key); owner: LDS, -1 on entry; other(k, x):
+// key k of lane ^ x.  Ranks are counted among the best keys of kBoundGroups
+// groups of lanes, and among all lanes' only when fewer than C groups have a
+// key: every key is compared with all others through LDS, and
+// ranking 512 lanes took 20 us of a selecting tile's 32.  The
+// coarser bound lets few more keys pass: with C of G groups holding a key at
+// or above it, -G ln(1 - C / G) of evenly spread keys are, 18 for C = 16 and 89
+// for C = 64 of 128 groups.
+constexpr int kBoundGroups = 128;
+
+template <typename T, int NTHR, typename K, typename Other>
+__device__ __forceinline__ int bound_owner(K* best, int& owner, const K& mine, bool has, int C, Other other) {
+  constexpr int G = NTHR / kBoundGroups;
+  static_assert(G >= 1 && (G & (G - 1)) == 0 && G <= 64, "lanes per group");
+  const int tid = threadIdx.x;
+  K k = mine;
+#pragma unroll
+  for (int x = 1; x < G; x <<= 1) {
+    const K o = other(k, x);
+    const bool b = (o.v > k.v) | ((o.v == k.v) & (o.i < k.i));
+    k.v = b ? o.v : k.v;
+    k.i = b ? o.i : k.i;
+  }
+  if ((tid & (G - 1)) == 0) best[tid / G] = k;
+  __syncthreads();
+  // two waves rank the groups (the worst key has the index that no key has)
+  bool ghas = false;
+  if (tid < kBoundGroups) {
+    k = best[tid];
+    ghas = (k.i + 1) != 0;
+  }
+  if (__syncthreads_count(ghas) >= C) {
+    // distinct keys, distinct ranks
+    if (ghas && rank_of(best, kBoundGroups, k) == C - 1) owner = tid;
+  } else {
+    best[tid] = mine;
+    __syncthreads();
+    if (has && rank_of(best, NTHR, mine) == C - 1) owner = tid;
+  }
+  __syncthreads();
+  return owner;
+}
+
 template <typename T, typename I, int NTHR, int CAP>
 struct SelShared {
   SelKey<T, I> lane_best[NTHR];
@@ -95,11 +140,12 @@ __device__ __forceinline__ int sel_bound_top(SelShared<T, I, NTHR, CAP>& sh, uin
     sh.count = 0;
     sh.owner = -1;
   }
-  sh.lane_best[tid] = best;
-  __syncthreads();
-  if (has && rank_of(sh.lane_best, NTHR, best) == C - 1) sh.owner = tid;  // distinct keys, distinct ranks
-  __syncthreads();
-  const int own = sh.owner;
+  const int lanes = __syncthreads_count(has);
+  int own = -1;
+  if (lanes >= C)
+    own = bound_owner<T, NTHR>(sh.lane_best, sh.owner, best, has, C, [](const K& k, int x) {
+      return K{__shfl_xor(k.v, x), (I)__shfl_xor((long long)k.i, x)};
+    });
   if (own >= 0) {
     const K t0 = sh.lane_best[own];
 #pragma unroll
