@@ -261,7 +261,8 @@ typedef struct cq_dd_record {  /* one recursion, written by the library */
                                    the candidate bins in its epilogue (0 when bins are stored) */
   int64_t tiles_run;            /* tile evaluations of that step: the warm-up tiles plus every
                                    tile whose bound reached the threshold (tile pruning skips
-                                   the others) */
+                                   the others); all of them when no recursion of the batch's
+                                   shape has more than 64, which are not pruned */
 } cq_dd_record;
 
 /* Workspace: a control block per instance (device program, recursion

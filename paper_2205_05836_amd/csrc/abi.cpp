@@ -736,6 +736,14 @@ cq_status dd_plan_instance(const cq_dd_instance& in, const cq_dd_params& p, bool
   return CQ_OK;
 }
 
+// Whether the selecting GEMM's tiles are pruned: the warm-up evaluates up to
+// kDDMaxC tiles (those with the largest bounds) to set the threshold, so with
+// no more tiles than that it would evaluate all of them before the main pass
+// does (three 5-bit subcircuits, 8 tiles: bounds, warm-up, threshold and
+// compaction took 60 of a recursion's 147 us).  The same for every
+// member of a lockstep group, whose selection sizes are shared.
+bool dd_prunes(const DDInstancePlan& D) { return D.sel.tiles > kDDMaxC; }
+
 DType tensor_dtype(const Plan& plan, int t, cq_precision prec) {
   const TensorRef& T = plan.tensors[t];
   if (T.loc == Loc::Out) return out_dtype(prec);
@@ -978,6 +986,7 @@ void dd_program(const DDInstancePlan& D, const cq_dd_instance& in, const cq_dd_p
     }
   }
   P.topc_step = D.topc_step;
+  P.prune = dd_prunes(D) ? 1 : 0;
   P.cand_v = reinterpret_cast<double*>(ws + D.cand_off);
   P.cand_i = reinterpret_cast<uint64_t*>(ws + D.cand_off + D.cand_cap * 8);
   if (D.topc_step >= 0) {
@@ -1078,8 +1087,6 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
   if (e != hipSuccess) return hip_fail(e, "merge launch");
   e = launch_merge_indirect(&lv->rowsum[0], ns, rs_threads, stream, span);
   if (e != hipSuccess) return hip_fail(e, "row-sum launch");
-  e = launch_refine_indirect(&prog->total, 1, stream, span);
-  if (e != hipSuccess) return hip_fail(e, "total launch");
   if (D.lbal) {
     int64_t max_rows = 0;
     for (const DDInstancePlan* M : G)
@@ -1112,22 +1119,24 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
     if (s.is_gemm && (int)si == D.topc_step) {
       // fused top-C with tile pruning (see launch_tile_bounds)
       const int64_t tiles = step_max[si];
-      e = launch_tile_bounds(&lv->gemm[si], tensor_dtype(D.plan, s.g.a, prec), is_f16(prec),
+      const bool prune = dd_prunes(D);
+      e = hipSuccess;
+      if (prune) e = launch_tile_bounds(&lv->gemm[si], tensor_dtype(D.plan, s.g.a, prec), is_f16(prec),
                              reinterpret_cast<float*>((ws + D.bound_a_off)),
                              reinterpret_cast<float*>((ws + D.bound_b_off)),
                              reinterpret_cast<float*>(ws + D.bound_u_off), D.seg_a, D.seg_b,
                              tiles, stream, span);
-      if (e == hipSuccess)
+      if (prune && e == hipSuccess)
         e = launch_tile_warm(reinterpret_cast<const float*>(ws + D.bound_u_off), &st->n_tiles,
                              &st->warm_count, reinterpret_cast<uint64_t*>(ws + D.warm_out_off + kDDMaxC * 8),
                              (int)std::min<int64_t>(tiles, kDDMaxC), stream, span);
-      if (e == hipSuccess)
+      if (prune && e == hipSuccess)
         e = launch_gemm_indirect(prec, &lv->topc_warm, std::min<int64_t>(tiles, kDDMaxC),
                                  tensor_dtype(D.plan, s.g.c, prec), false, true, stream, span);
-      if (e == hipSuccess)
+      if (prune && e == hipSuccess)
         e = launch_warm_tau(reinterpret_cast<const double*>(ws + D.cand_off), &st->topc_count, &st->C,
                             &st->topc_thr, stream, span);
-      if (e == hipSuccess)
+      if (prune && e == hipSuccess)
         e = launch_tile_compact(reinterpret_cast<const float*>(ws + D.bound_u_off), &st->n_tiles,
                                 &st->topc_thr, reinterpret_cast<uint64_t*>(ws + D.list_off),
                                 &st->list_count, tiles, stream, span);
@@ -1147,10 +1156,13 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
     }
   }
   if (D.topc_step >= 0) {
+    // unpruned: one workgroup selects straight from the candidates
+    const bool stage = D.sel.cand_cap > kTopcDirect;
     e = launch_topk_candidates(reinterpret_cast<const double*>(ws + D.cand_off),
                                reinterpret_cast<const uint64_t*>(ws + D.cand_off + D.cand_cap * 8),
                                reinterpret_cast<const int64_t*>(&st->topc_count), &st->C,
-                               std::min(4 * p.R, kDDMaxC), reinterpret_cast<double*>(ws + D.stage_off),
+                               std::min(4 * p.R, kDDMaxC),
+                               stage ? reinterpret_cast<double*>(ws + D.stage_off) : nullptr,
                                reinterpret_cast<uint64_t*>(ws + D.stage_off + (int64_t)kTopcStage * kDDMaxC * 8),
                                st->top_val, st->top_idx, stream, span);
   } else {
@@ -1161,11 +1173,9 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
                              D.cand_cap, st->top_val, st->top_idx, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "top-C launch");
-  e = launch_refine_indirect(&lv->refine, std::min(4 * p.R, kDDMaxC), stream, span);
+  e = launch_refine_indirect(&lv->refine[0], std::min(4 * p.R, kDDMaxC), stream, span);
   if (e != hipSuccess) return hip_fail(e, "refine launch");
-  e = launch_dd_update(prog, st, recs, r, stream, span);
-  if (e != hipSuccess) return hip_fail(e, "update launch");
-  return CQ_OK;
+  return CQ_OK;  // the list update opens the next recursion's setup
 }
 
 // Streams and events of the parallel lanes; released with the graph that
@@ -1202,6 +1212,11 @@ cq_status dd_enqueue_group(const std::vector<int>& G, int k, const cq_dd_params&
     }
     cq_status st = dd_enqueue_level(members, p, span, region, ctrl, r, bins, stream);
     if (st != CQ_OK) return st;
+  }
+  if (recursions > 0) {
+    e = launch_dd_update(reinterpret_cast<const DDProgram*>(ctrl + L.prog), reinterpret_cast<DDState*>(ctrl + L.state),
+                         reinterpret_cast<cq_dd_record*>(ctrl + L.recs), recursions - 1, stream, span);
+    if (e != hipSuccess) return hip_fail(e, "update launch");
   }
   return CQ_OK;
 }

@@ -334,39 +334,64 @@ int64_t topk_blocks(int64_t count) {
 // Refine: one workgroup per bin, threads over the 4^K global labels.
 // ---------------------------------------------------------------------------
 
-__device__ inline void refine_body(const RefineArgs& a, double* red) {
+// Bound by latency: the arguments are copied to LDS at once (read where they
+// are used, each was a dependent scalar load in the inner loops), four labels
+// are in flight a thread, and the last six steps of the reduction tree stay in
+// a wave (the additions and their order are those of the LDS tree).
+__global__ void __launch_bounds__(256) refine_ind_kernel(const RefineArgs* __restrict__ args, int64_t slot) {
+  __shared__ RefineArgs a;
+  __shared__ double red[128];
+  static_assert(sizeof(RefineArgs) % 8 == 0, "copied in 8-byte words");
+  const RefineArgs* p = inst_ptr(args, slot) + blockIdx.y;
+  {
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(p);
+    uint64_t* dst = reinterpret_cast<uint64_t*>(&a);
+    for (int i = threadIdx.x; i < (int)(sizeof(RefineArgs) / 8); i += 256) dst[i] = src[i];
+  }
+  __syncthreads();
   if ((int)blockIdx.x >= a.nbins) return;
   const uint64_t bin = a.bins[blockIdx.x];
-  int64_t col[CQ_MAX_SUBCIRCUITS];
-  int shift = 0;
-  for (int c = 0; c < a.n_sub; ++c) shift += a.na[c];
-  for (int c = 0; c < a.n_sub; ++c) {
-    shift -= a.na[c];
-    col[c] = (int64_t)((bin >> shift) & ((((uint64_t)1) << a.na[c]) - 1));
-  }
-  const int64_t labels = (int64_t)1 << (2 * a.K);
+  const int ns = a.n_sub, K = a.K;
+  const int64_t labels = (int64_t)1 << (2 * K);
   double sum = 0.0;
-  for (int64_t l = threadIdx.x; l < labels; l += blockDim.x) {
-    double prod = 1.0;
-    for (int c = 0; c < a.n_sub; ++c) {
-      int64_t row = 0;
-      for (int j = 0; j < a.kc[c]; ++j) row = 4 * row + ((l >> (2 * (a.K - 1 - a.cut[c][j]))) & 3);
-      prod *= a.Ep[c][row * a.ld[c] + col[c]];
+  for (int64_t l0 = threadIdx.x; l0 < labels; l0 += 1024) {
+    double prod[4] = {1.0, 1.0, 1.0, 1.0};
+    int shift = 0;
+    for (int c = ns - 1; c >= 0; --c) shift += a.na[c];
+    for (int c = 0; c < ns; ++c) {
+      shift -= a.na[c];
+      const int64_t col = (int64_t)((bin >> shift) & ((((uint64_t)1) << a.na[c]) - 1));
+      int64_t row[4] = {0, 0, 0, 0};
+      for (int j = 0; j < a.kc[c]; ++j) {
+        const int sh = 2 * (K - 1 - a.cut[c][j]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) row[u] = 4 * row[u] + (((l0 + 256 * u) >> sh) & 3);
+      }
+      const double* E = a.Ep[c] + col;
+      const int64_t ld = a.ld[c];
+      double v[4];
+      // labels past the last repeat the first (their products are not added)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = E[(l0 + 256 * u < labels ? row[u] : row[0]) * ld];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) prod[u] *= v[u];
     }
-    sum += prod;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (l0 + 256 * u < labels) sum += prod[u];
   }
-  red[threadIdx.x] = sum;
+  const int t = threadIdx.x;
+  if (t >= 128) red[t - 128] = sum;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.out[blockIdx.x] = a.scale * red[0];
-}
-
-__global__ void __launch_bounds__(256) refine_ind_kernel(const RefineArgs* __restrict__ a, int64_t slot) {
-  __shared__ double red[256];
-  refine_body(*inst_ptr(a, slot), red);
+  if (t < 128) sum += red[t];
+  __syncthreads();
+  if (t >= 64 && t < 128) red[t - 64] = sum;
+  __syncthreads();
+  if (t >= 64) return;
+  sum += red[t];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+  if (t == 0) a.out[blockIdx.x] = a.scale * sum;
 }
 
 }  // namespace
@@ -383,7 +408,7 @@ hipError_t launch_merge_indirect(const MergeArgs* dev, int count, int64_t max_th
 
 hipError_t launch_refine_indirect(const RefineArgs* dev, int max_bins, hipStream_t stream, InstSpan span) {
   if (max_bins <= 0 || span.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(refine_ind_kernel, dim3((unsigned)max_bins, 1, (unsigned)span.n), dim3(256), 0, stream,
+  hipLaunchKernelGGL(refine_ind_kernel, dim3((unsigned)max_bins, 2, (unsigned)span.n), dim3(256), 0, stream,
                      dev, span.stride);
   return hipGetLastError();
 }
@@ -408,7 +433,9 @@ __device__ inline Key wave_best_key(Key k) {
 template <int KPT>
 __global__ void __launch_bounds__(256) select_small_kernel(const double* __restrict__ vals,
                                                            const uint64_t* __restrict__ idxs,
-                                                           int64_t count, const int32_t* __restrict__ C_dev,
+                                                           int64_t count,
+                                                           const int64_t* __restrict__ count_dev,
+                                                           const int32_t* __restrict__ C_dev,
                                                            double* __restrict__ out_v,
                                                            uint64_t* __restrict__ out_i, int64_t slot) {
   using SK = SelKey<double, uint64_t>;
@@ -423,6 +450,10 @@ __global__ void __launch_bounds__(256) select_small_kernel(const double* __restr
   out_i = inst_ptr(out_i, slot);
   const int C = *C_dev;
   if (C <= 0) return;
+  if (count_dev) {  // at most `count`
+    const int64_t n = *inst_ptr(count_dev, slot);
+    count = n < count ? n : count;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   static_assert(KPT >= 1 && KPT <= 64, "keys per thread");
   Key h[KPT];
@@ -501,18 +532,19 @@ __global__ void __launch_bounds__(256) select_small_kernel(const double* __restr
 
 // one workgroup selects the C best of `count` <= kSelCap keys; the keys per
 // thread follow the count (fewer registers, all loads in flight)
-void launch_select_small(const double* vals, const uint64_t* idxs, int64_t count, const int32_t* C_dev,
-                         double* out_v, uint64_t* out_i, hipStream_t stream, InstSpan span = InstSpan()) {
+void launch_select_small(const double* vals, const uint64_t* idxs, int64_t count, const int64_t* count_dev,
+                         const int32_t* C_dev, double* out_v, uint64_t* out_i, hipStream_t stream,
+                         InstSpan span = InstSpan()) {
   const dim3 grid(1, 1, (unsigned)span.n);
   if (count <= 256 * 4)
-    hipLaunchKernelGGL(select_small_kernel<4>, grid, dim3(256), 0, stream, vals, idxs, count, C_dev, out_v,
-                       out_i, span.stride);
+    hipLaunchKernelGGL(select_small_kernel<4>, grid, dim3(256), 0, stream, vals, idxs, count, count_dev, C_dev,
+                       out_v, out_i, span.stride);
   else if (count <= 256 * 16)
-    hipLaunchKernelGGL(select_small_kernel<16>, grid, dim3(256), 0, stream, vals, idxs, count, C_dev, out_v,
-                       out_i, span.stride);
+    hipLaunchKernelGGL(select_small_kernel<16>, grid, dim3(256), 0, stream, vals, idxs, count, count_dev, C_dev,
+                       out_v, out_i, span.stride);
   else
-    hipLaunchKernelGGL(select_small_kernel<64>, grid, dim3(256), 0, stream, vals, idxs, count, C_dev, out_v,
-                       out_i, span.stride);
+    hipLaunchKernelGGL(select_small_kernel<64>, grid, dim3(256), 0, stream, vals, idxs, count, count_dev, C_dev,
+                       out_v, out_i, span.stride);
 }
 
 int64_t topk_indirect_capacity(int64_t max_count, int C_max) {
@@ -536,7 +568,8 @@ hipError_t launch_topk_indirect(const void* bins, DType t, const int64_t* count_
   if (e != hipSuccess) return e;
   const int64_t nc = blocks * C_max;
   if (nc <= kSelCap)
-    launch_select_small((const double*)cand_val, (const uint64_t*)cand_idx, nc, C_dev, out_val, out_idx, stream);
+    launch_select_small((const double*)cand_val, (const uint64_t*)cand_idx, nc, nullptr, C_dev, out_val, out_idx,
+                        stream);
   else
     hipLaunchKernelGGL((topk_kernel<double, true>), dim3(1), dim3(256), 0, stream,
                        (const double*)cand_val, (const uint64_t*)cand_idx, nc, nc, 0, out_val,
@@ -550,14 +583,18 @@ hipError_t launch_topk_candidates(const double* cand_val, const uint64_t* cand_i
                                   uint64_t* out_idx, hipStream_t stream, InstSpan span) {
   if (C_max < 1 || C_max > kDDMaxC) return hipErrorInvalidValue;
   if (span.n <= 0) return hipSuccess;
+  if (!stage_val) {  // at most kTopcDirect candidates
+    launch_select_small(cand_val, cand_idx, kTopcDirect, count_dev, C_dev, out_val, out_idx, stream, span);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((topk_kernel<double, true>), dim3(kTopcStage, 1, (unsigned)span.n), dim3(256), 0, stream,
                      cand_val, cand_idx, (int64_t)0, (int64_t)0, 0, stage_val, stage_idx, count_dev, C_dev,
                      C_max, span.stride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nc = (int64_t)kTopcStage * C_max;  // <= kSelCap
-  launch_select_small((const double*)stage_val, (const uint64_t*)stage_idx, nc, C_dev, out_val, out_idx, stream,
-                      span);
+  launch_select_small((const double*)stage_val, (const uint64_t*)stage_idx, nc, nullptr, C_dev, out_val, out_idx,
+                      stream, span);
   return hipGetLastError();
 }
 
@@ -620,12 +657,7 @@ __device__ inline int sym_log(const SymLog& s, const int32_t* na) {
 }
 
 // output position i <-> flat bit n-1-i
-__device__ inline uint64_t pos_to_flat(uint64_t m, int n) {
-  uint64_t f = 0;
-  for (int i = 0; i < n; ++i)
-    if ((m >> i) & 1) f |= (uint64_t)1 << (n - 1 - i);
-  return f;
-}
+__device__ inline uint64_t pos_to_flat(uint64_t m, int n) { return n > 0 ? __brevll(m) >> (64 - n) : 0; }
 
 __device__ inline uint64_t low_bits(int k) { return k >= 64 ? ~(uint64_t)0 : (((uint64_t)1 << k) - 1); }
 
@@ -686,20 +718,189 @@ __global__ void dd_init_kernel(const DDProgram* __restrict__ P, DDState* st, cq_
   st->total = 0.0;
 }
 
-// One workgroup of 64 threads: every thread derives the active counts (a
-// few words), thread c < n_sub writes subcircuit c's descriptors, thread
-// 32 + s step s's, and thread 0 the recursion-wide fields -- the descriptor
-// writes are independent, so they no longer run one after another.
-__global__ void dd_setup_kernel(const DDProgram* __restrict__ P, DDState* st, DDLevel* lv,
-                                cq_dd_record* recs, int r, void* bins, int64_t slot) {
-  P = inst_ptr(P, slot);
-  st = inst_ptr(st, slot);
-  lv = inst_ptr(lv, slot);
-  recs = inst_ptr(recs, slot);
-  bins = inst_ptr(bins, slot);
+// The two control steps of a recursion -- list update and descriptors -- work
+// on copies of the program and the state in LDS: read where they are used,
+// their fields were a chain of some twenty dependent loads (16 us for the
+// descriptors and 7 for the update of one instance, 24 and 14 for 16; now 10
+// and 17 for both in one launch).
+constexpr int kCtlThreads = 256;
+static_assert(sizeof(DDProgram) % 8 == 0 && sizeof(DDState) % 8 == 0, "copied in 8-byte words");
+
+template <typename T>
+__device__ inline void ctl_copy(T* dst, const T* src) {
+  constexpr int W = (int)(sizeof(T) / 8), N = (W + kCtlThreads - 1) / kCtlThreads;
+  const uint64_t* s = reinterpret_cast<const uint64_t*>(src);
+  uint64_t* d = reinterpret_cast<uint64_t*>(dst);
+  uint64_t v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int w = i * kCtlThreads + (int)threadIdx.x;
+    v[i] = s[w < W ? w : W - 1];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int w = i * kCtlThreads + (int)threadIdx.x;
+    if (w < W) d[w] = v[i];
+  }
+}
+
+// Order of L: larger FP64 value first, then the earlier recursion, then the
+// smaller bin.  Values compare through an order-preserving integer key (with
+// -0 taken as +0), which agrees with the numeric order on every non-NaN value
+// and still orders NaNs, so ranks of distinct entries are always distinct.
+__device__ inline uint64_t list_ord(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v + 0.0);
+  return (b >> 63) ? ~b : (b | (1ull << 63));
+}
+
+__device__ inline bool list_before(uint64_t o1, int r1, uint64_t b1, uint64_t o2, int r2, uint64_t b2) {
+  if (o1 != o2) return o1 > o2;
+  if (r1 != r2) return r1 < r2;
+  return b1 < b2;
+}
+
+// The list update of recursion r: the C candidates (FP64 refined
+// values of the selected bins) are ranked among themselves, the best
+// min(C, R) of them and the entries of L are ranked against each other (both
+// sides are sorted, so an entry's place in the merged list is its own rank
+// plus the number of the other side's entries before it), and the best R of
+// the union form the new L.  Then the best entry is popped and its bin
+// zoomed into: the first max_active[c] merged outputs of each subcircuit
+// become active.  Every place of the new list receives exactly one entry.
+__device__ inline void update_body(const DDProgram& P, DDState& st, cq_dd_record* recs, int r) {
+  constexpr int W = (int)(sizeof(DDEntry) / 8);
+  static_assert(sizeof(DDEntry) % 8 == 0, "entries copied in 8-byte words");
+  static_assert(kDDMaxC <= 64 && CQ_MAX_DD_R <= 64, "one lane per candidate and per entry");
+  __shared__ DDEntry new_l[CQ_MAX_DD_R];
+  __shared__ uint64_t c_ord[kDDMaxC], c_bin[kDDMaxC];
+  __shared__ double c_val[kDDMaxC];
+  __shared__ int c_rank[kDDMaxC];
+  const int tid = threadIdx.x;
+  if (st.stop || P.r0 + r >= P.r_end) return;
+  const int ra = P.r0 + r;  // the recursion's index (the list orders ties by it)
+  const int ns = P.n_sub, R = P.R, C = st.C, nl = st.n_list;
+  const int take = C < R ? C : R;
+  cq_dd_record& rec = recs[r];
+  const DDEntry* const old_l = st.list;
+  if (tid < C) {
+    c_val[tid] = st.ref_val[tid];
+    c_ord[tid] = list_ord(c_val[tid]);
+    c_bin[tid] = st.top_idx[tid];
+  }
+  __syncthreads();
+  // candidates among themselves (equal keys keep their selection order)
+  if (tid < C) {
+    const uint64_t o = c_ord[tid], b = c_bin[tid];
+    int rk = 0;
+    for (int j = 0; j < C; ++j)
+      rk += (c_ord[j] != o ? c_ord[j] > o : (c_bin[j] != b ? c_bin[j] < b : j < tid)) ? 1 : 0;
+    c_rank[tid] = rk;
+  }
+  __syncthreads();
+  // an entry of L keeps its rank plus the taken candidates before it
+  if (tid < nl) {
+    const DDEntry& e = old_l[tid];
+    const uint64_t o = list_ord(e.v);
+    int pos = tid;
+    for (int j = 0; j < C; ++j)
+      pos += (c_rank[j] < take && list_before(c_ord[j], ra, c_bin[j], o, e.rec, e.bin)) ? 1 : 0;
+    if (pos < R) {
+      const uint64_t* src = reinterpret_cast<const uint64_t*>(&e);
+      uint64_t* dst = reinterpret_cast<uint64_t*>(&new_l[pos]);
+      for (int w = 0; w < W; ++w) dst[w] = src[w];
+    }
+  }
+  // a taken candidate keeps its rank plus the entries of L before it
+  if (tid < C && c_rank[tid] < take) {
+    const uint64_t o = c_ord[tid], bin = c_bin[tid];
+    int pos = c_rank[tid];
+    for (int q = 0; q < nl; ++q)
+      pos += list_before(list_ord(old_l[q].v), old_l[q].rec, old_l[q].bin, o, ra, bin) ? 1 : 0;
+    if (pos < R) {
+      DDEntry& e = new_l[pos];
+      e.v = c_val[tid];
+      e.rec = ra;
+      e.pad = 0;
+      e.bin = bin;
+      // the bin's digits, subcircuit 0 most significant, fix the active
+      // outputs: the lowest active position takes the digit's top bit
+      int shift = st.n_active;
+      for (int c = 0; c < CQ_MAX_SUBCIRCUITS; ++c) {
+        e.fixed[c] = e.fixed_vals[c] = e.merged[c] = 0;
+        if (c >= ns) continue;
+        const int a = st.na[c];
+        shift -= a;
+        const uint64_t bits = (bin >> shift) & low_bits(a);
+        uint64_t act = st.active[c], fv = st.fixed_vals[c];
+        for (int t = a - 1; act; --t) {
+          const uint64_t low = act & (~act + 1);
+          if ((bits >> t) & 1) fv |= low;
+          act ^= low;
+        }
+        e.fixed[c] = st.fixed[c] | st.active[c];
+        e.fixed_vals[c] = fv;
+        e.merged[c] = st.merged[c];
+      }
+    }
+  }
+  __syncthreads();
+  const int nl2 = nl + take < R ? nl + take : R;
+  if (tid == 0) {
+    rec.total = st.total;
+    rec.n_list = nl2;
+    if (P.topc_step >= 0) {
+      rec.tiles = st.n_tiles;
+      rec.tiles_run = st.warm_count + st.list_count;
+    }
+    st.done = ra + 1;
+  }
+  if (tid < nl2) {
+    rec.list_val[tid] = new_l[tid].v;
+    rec.list_rec[tid] = new_l[tid].rec;
+    rec.list_bin[tid] = new_l[tid].bin;
+  }
+  if (nl2 == 0) {
+    if (tid == 0) {
+      st.n_list = 0;
+      st.stop = 1;
+    }
+    __syncthreads();
+    return;
+  }
+  // pop the best entry and zoom into its bin
+  if (tid == 0) rec.popped = 1;
+  if (tid < ns) {
+    const int c = tid;
+    const uint64_t mer = new_l[0].merged[c];
+    uint64_t act = 0, rest = mer;
+    for (int taken = 0; rest && taken < P.max_active[c]; ++taken) {
+      const uint64_t low = rest & (~rest + 1);
+      act |= low;
+      rest ^= low;
+    }
+    st.active[c] = act;
+    st.merged[c] = mer & ~act;
+    st.fixed[c] = new_l[0].fixed[c];
+    st.fixed_vals[c] = new_l[0].fixed_vals[c];
+  }
+  {
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(&new_l[1]);
+    uint64_t* dst = reinterpret_cast<uint64_t*>(st.list);
+    for (int w = tid; w < (nl2 - 1) * W; w += kCtlThreads) dst[w] = src[w];
+  }
+  if (tid == 0) st.n_list = nl2 - 1;
+  __syncthreads();
+}
+
+// Descriptors of recursion r: every thread derives the active counts, thread c
+// < n_sub writes subcircuit c's descriptors, thread 64 + s step s's, and thread
+// 0 the recursion-wide fields; the writes are independent.  P and st: LDS
+// copies; gst: the state that the descriptors point into.
+__device__ inline void setup_body(const DDProgram* P, DDState* st, DDState* gst, DDLevel* lv, cq_dd_record* recs,
+                                  int r, void* bins) {
   const int tid = threadIdx.x;
   const int ns = P->n_sub, nsteps = P->n_steps;
-  const int step = tid - 32;  // the step this thread describes, if in range
+  const int step = tid - 64;  // the step this thread describes, if in range
   // stopped, or past this instance's last recursion of the call: nothing runs
   if (st->stop || P->r0 + r >= P->r_end) {
     if (tid < ns) {
@@ -712,7 +913,8 @@ __global__ void dd_setup_kernel(const DDProgram* __restrict__ P, DDState* st, DD
       lv->perm[step].total = 0;
     }
     if (tid == 0) {
-      lv->refine.nbins = 0;
+      lv->refine[0].nbins = 0;
+      lv->refine[1].nbins = 0;
       st->C = 0;
       st->count = 0;
     }
@@ -789,11 +991,12 @@ __global__ void dd_setup_kernel(const DDProgram* __restrict__ P, DDState* st, DD
       g.rowtmax = scaled ? P->rowtmax : nullptr;
       const bool tc_here = s == P->topc_step;
       g.topc_publish_only = 0;
-      g.tile_list = tc_here ? P->tile_list : nullptr;
-      g.tile_count = tc_here ? &st->list_count : nullptr;
-      g.topc_thr = tc_here ? &st->topc_thr : nullptr;
-      g.topc_count = tc_here ? &st->topc_count : nullptr;
-      g.topc_C = tc_here ? &st->C : nullptr;
+      const bool prune = tc_here && P->prune;
+      g.tile_list = prune ? P->tile_list : nullptr;
+      g.tile_count = prune ? &gst->list_count : nullptr;
+      g.topc_thr = tc_here ? &gst->topc_thr : nullptr;
+      g.topc_count = tc_here ? &gst->topc_count : nullptr;
+      g.topc_C = tc_here ? &gst->C : nullptr;
       g.topc_v = tc_here ? P->cand_v : nullptr;
       g.topc_i = tc_here ? P->cand_i : nullptr;
       g.tilesM = (M + 127) / 128;
@@ -809,14 +1012,16 @@ __global__ void dd_setup_kernel(const DDProgram* __restrict__ P, DDState* st, DD
         // (the candidate list then restarts); only tiles whose bound reaches
         // it are multiplied
         st->n_tiles = g.tiles;
-        st->warm_C = (int)(g.tiles < 64 ? g.tiles : 64);
+        st->warm_C = !prune ? 0 : (int)(g.tiles < 64 ? g.tiles : 64);
         st->warm_count = st->warm_C;
-        st->list_count = 0;
-        GemmArgs w = g;
-        w.tile_list = P->warm_i;
-        w.tile_count = &st->warm_count;
-        w.topc_publish_only = 2;
-        lv->topc_warm = w;
+        st->list_count = prune ? 0 : g.tiles;
+        if (prune) {
+          GemmArgs w = g;
+          w.tile_list = P->warm_i;
+          w.tile_count = &gst->warm_count;
+          w.topc_publish_only = 2;
+          lv->topc_warm = w;
+        }
       }
     } else {
       const DDPermSym& Q = P->perm[s];
@@ -850,189 +1055,84 @@ __global__ void dd_setup_kernel(const DDProgram* __restrict__ P, DDState* st, DD
       st->topc_thr = 0x000fffffffffffffull;  // order-preserving key of -infinity
       st->topc_count = 0;
     }
-    RefineArgs& f = lv->refine;
-    f.n_sub = ns;
-    f.K = P->K;
-    for (int c = 0; c < CQ_MAX_SUBCIRCUITS; ++c) {
+  }
+  // another wave: the refinement of the selected bins, and the total
+  if (tid >= 128 && tid < 128 + CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS) {
+    const int i = tid - 128, c = i / CQ_MAX_LOCAL_CUTS;
+    RefineArgs& f = lv->refine[0];
+    (&f.cut[0][0])[i] = (&P->cut[0][0])[i];
+    if (i % CQ_MAX_LOCAL_CUTS == 0) {
       f.Ep[c] = c < ns ? P->Ep[c] : nullptr;
       f.ld[c] = (int64_t)1 << na[c];
       f.na[c] = na[c];
       f.kc[c] = c < ns ? P->kc[c] : 0;
-      for (int j = 0; j < CQ_MAX_LOCAL_CUTS; ++j) f.cut[c][j] = P->cut[c][j];
     }
-    f.bins = st->top_idx;
-    f.nbins = C;
-    f.scale = ldexp(1.0, -P->K);
-    f.out = st->ref_val;
+    if (i == 0) {
+      f.n_sub = ns;
+      f.K = P->K;
+      f.bins = gst->top_idx;
+      f.nbins = C;
+      f.scale = ldexp(1.0, -P->K);
+      f.out = gst->ref_val;
+    }
+  }
+  if (tid >= 192) {
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(&P->total);
+    uint64_t* dst = reinterpret_cast<uint64_t*>(&lv->refine[1]);
+    for (int w = tid - 192; w < (int)(sizeof(RefineArgs) / 8); w += kCtlThreads - 192) dst[w] = src[w];
   }
 }
 
-// Order of L: larger FP64 value first, then the earlier recursion, then the
-// smaller bin.  Values compare through an order-preserving integer key (with
-// -0 taken as +0), which agrees with the numeric order on every non-NaN value
-// and still orders NaNs, so ranks of distinct entries are always distinct.
-__device__ inline uint64_t list_ord(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v + 0.0);
-  return (b >> 63) ? ~b : (b | (1ull << 63));
-}
-
-__device__ inline bool list_before(uint64_t o1, int r1, uint64_t b1, uint64_t o2, int r2, uint64_t b2) {
-  if (o1 != o2) return o1 > o2;
-  if (r1 != r2) return r1 < r2;
-  return b1 < b2;
-}
-
-// The list update of recursion r, one wave: the C candidates (FP64 refined
-// values of the selected bins) are ranked among themselves, the best
-// min(C, R) of them and the entries of L are ranked against each other (both
-// sides are sorted, so an entry's place in the merged list is its own rank
-// plus the number of the other side's entries before it), and the best R of
-// the union form the new L.  Then the best entry is popped and its bin
-// zoomed into: the first max_active[c] merged outputs of each subcircuit
-// become active.  Every place of the new list receives exactly one entry.
-__global__ void __launch_bounds__(64) dd_update_kernel(const DDProgram* __restrict__ P, DDState* st,
-                                                       cq_dd_record* recs, int r, int64_t slot) {
-  constexpr int W = (int)(sizeof(DDEntry) / 8);
-  static_assert(sizeof(DDEntry) % 8 == 0, "entries copied in 8-byte words");
-  static_assert(kDDMaxC <= 64 && CQ_MAX_DD_R <= 64, "one lane per candidate and per entry");
-  __shared__ DDEntry old_l[CQ_MAX_DD_R];
-  __shared__ DDEntry new_l[CQ_MAX_DD_R];
-  __shared__ uint64_t c_ord[kDDMaxC], c_bin[kDDMaxC];
-  __shared__ double c_val[kDDMaxC];
-  __shared__ int c_rank[kDDMaxC];
-  P = inst_ptr(P, slot);
-  st = inst_ptr(st, slot);
+// (update of r - 1 and) descriptors of r, one workgroup an instance
+__global__ void __launch_bounds__(kCtlThreads) dd_setup_kernel(const DDProgram* __restrict__ Pg, DDState* gst,
+                                                               DDLevel* lv, cq_dd_record* recs, int r, void* bins,
+                                                               int64_t slot) {
+  __shared__ DDProgram P;
+  __shared__ DDState st;
+  gst = inst_ptr(gst, slot);
   recs = inst_ptr(recs, slot);
-  const int tid = threadIdx.x;
-  if (st->stop || P->r0 + r >= P->r_end) return;
-  const int ra = P->r0 + r;  // the recursion's index (the list orders ties by it)
-  const int ns = P->n_sub, R = P->R, C = st->C, nl = st->n_list;
-  const int take = C < R ? C : R;
-  cq_dd_record& rec = recs[r];
-  {
-    const uint64_t* src = reinterpret_cast<const uint64_t*>(st->list);
-    uint64_t* dst = reinterpret_cast<uint64_t*>(old_l);
-    for (int w = tid; w < nl * W; w += 64) dst[w] = src[w];
-  }
-  if (tid < C) {
-    c_val[tid] = st->ref_val[tid];
-    c_ord[tid] = list_ord(c_val[tid]);
-    c_bin[tid] = st->top_idx[tid];
-  }
+  ctl_copy(&P, inst_ptr(Pg, slot));
+  ctl_copy(&st, gst);
   __syncthreads();
-  // candidates among themselves (equal keys keep their selection order)
-  if (tid < C) {
-    const uint64_t o = c_ord[tid], b = c_bin[tid];
-    int rk = 0;
-    for (int j = 0; j < C; ++j)
-      rk += (c_ord[j] != o ? c_ord[j] > o : (c_bin[j] != b ? c_bin[j] < b : j < tid)) ? 1 : 0;
-    c_rank[tid] = rk;
-  }
+  if (r > 0) update_body(P, st, recs, r - 1);
+  setup_body(&P, &st, gst, inst_ptr(lv, slot), recs, r, inst_ptr(bins, slot));
   __syncthreads();
-  // an entry of L keeps its rank plus the taken candidates before it
-  if (tid < nl) {
-    const DDEntry& e = old_l[tid];
-    const uint64_t o = list_ord(e.v);
-    int pos = tid;
-    for (int j = 0; j < C; ++j)
-      pos += (c_rank[j] < take && list_before(c_ord[j], ra, c_bin[j], o, e.rec, e.bin)) ? 1 : 0;
-    if (pos < R) {
-      const uint64_t* src = reinterpret_cast<const uint64_t*>(&e);
-      uint64_t* dst = reinterpret_cast<uint64_t*>(&new_l[pos]);
-      for (int w = 0; w < W; ++w) dst[w] = src[w];
-    }
-  }
-  // a taken candidate keeps its rank plus the entries of L before it
-  if (tid < C && c_rank[tid] < take) {
-    const uint64_t o = c_ord[tid], bin = c_bin[tid];
-    int pos = c_rank[tid];
-    for (int q = 0; q < nl; ++q)
-      pos += list_before(list_ord(old_l[q].v), old_l[q].rec, old_l[q].bin, o, ra, bin) ? 1 : 0;
-    if (pos < R) {
-      DDEntry& e = new_l[pos];
-      e.v = c_val[tid];
-      e.rec = ra;
-      e.pad = 0;
-      e.bin = bin;
-      // the bin's digits, subcircuit 0 most significant, fix the active
-      // outputs: the lowest active position takes the digit's top bit
-      int shift = st->n_active;
-      for (int c = 0; c < CQ_MAX_SUBCIRCUITS; ++c) {
-        e.fixed[c] = e.fixed_vals[c] = e.merged[c] = 0;
-        if (c >= ns) continue;
-        const int a = st->na[c];
-        shift -= a;
-        const uint64_t bits = (bin >> shift) & low_bits(a);
-        uint64_t act = st->active[c], fv = st->fixed_vals[c];
-        for (int t = a - 1; act; --t) {
-          const uint64_t low = act & (~act + 1);
-          if ((bits >> t) & 1) fv |= low;
-          act ^= low;
-        }
-        e.fixed[c] = st->fixed[c] | st->active[c];
-        e.fixed_vals[c] = fv;
-        e.merged[c] = st->merged[c];
-      }
-    }
-  }
+  ctl_copy(gst, &st);
+}
+
+__global__ void __launch_bounds__(kCtlThreads) dd_update_kernel(const DDProgram* __restrict__ Pg, DDState* gst,
+                                                                cq_dd_record* recs, int r, int64_t slot) {
+  __shared__ DDProgram P;
+  __shared__ DDState st;
+  gst = inst_ptr(gst, slot);
+  ctl_copy(&P, inst_ptr(Pg, slot));
+  ctl_copy(&st, gst);
   __syncthreads();
-  const int nl2 = nl + take < R ? nl + take : R;
-  if (tid == 0) {
-    rec.total = st->total;
-    rec.n_list = nl2;
-    if (P->topc_step >= 0) {
-      rec.tiles = st->n_tiles;
-      rec.tiles_run = st->warm_count + st->list_count;
-    }
-    st->done = ra + 1;
-  }
-  if (tid < nl2) {
-    rec.list_val[tid] = new_l[tid].v;
-    rec.list_rec[tid] = new_l[tid].rec;
-    rec.list_bin[tid] = new_l[tid].bin;
-  }
-  if (nl2 == 0) {
-    if (tid == 0) {
-      st->n_list = 0;
-      st->stop = 1;
-    }
-    return;
-  }
-  // pop the best entry and zoom into its bin
-  if (tid == 0) rec.popped = 1;
-  if (tid < ns) {
-    const int c = tid;
-    const uint64_t mer = new_l[0].merged[c];
-    uint64_t act = 0, rest = mer;
-    for (int taken = 0; rest && taken < P->max_active[c]; ++taken) {
-      const uint64_t low = rest & (~rest + 1);
-      act |= low;
-      rest ^= low;
-    }
-    st->active[c] = act;
-    st->merged[c] = mer & ~act;
-    st->fixed[c] = new_l[0].fixed[c];
-    st->fixed_vals[c] = new_l[0].fixed_vals[c];
-  }
-  {
-    const uint64_t* src = reinterpret_cast<const uint64_t*>(&new_l[1]);
-    uint64_t* dst = reinterpret_cast<uint64_t*>(st->list);
-    for (int w = tid; w < (nl2 - 1) * W; w += 64) dst[w] = src[w];
-  }
-  if (tid == 0) st->n_list = nl2 - 1;
+  update_body(P, st, inst_ptr(recs, slot), r);
+  __syncthreads();
+  ctl_copy(gst, &st);
 }
 
 }  // namespace
 
-// Block b copies `words` 32-bit words from src + b * src_stride to
+// Block b copies `words` words of type T from src + b * src_stride to
 // dst + b * dst_stride (strides in bytes): programs from the upload area into
-// the control blocks, and records out of them into one readback block.
+// the control blocks, and records out of them into one readback block.  Four
+// loads are in flight a thread.
+template <typename T>
 __global__ void __launch_bounds__(256) dd_copy_kernel(const char* __restrict__ src, int64_t src_stride,
                                                       char* __restrict__ dst, int64_t dst_stride,
                                                       int64_t words) {
-  const uint32_t* s = reinterpret_cast<const uint32_t*>(src + (int64_t)blockIdx.x * src_stride);
-  uint32_t* d = reinterpret_cast<uint32_t*>(dst + (int64_t)blockIdx.x * dst_stride);
-  for (int64_t w = threadIdx.x; w < words; w += blockDim.x) d[w] = s[w];
+  const T* s = reinterpret_cast<const T*>(src + (int64_t)blockIdx.x * src_stride);
+  T* d = reinterpret_cast<T*>(dst + (int64_t)blockIdx.x * dst_stride);
+  for (int64_t w0 = threadIdx.x; w0 < words; w0 += 1024) {
+    T v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = s[w0 + 256 * u < words ? w0 + 256 * u : w0];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (w0 + 256 * u < words) d[w0 + 256 * u] = v[u];
+  }
 }
 
 hipError_t launch_warm_tau(const double* cand_v, unsigned long long* count, const int32_t* C_dev,
@@ -1049,9 +1149,14 @@ hipError_t launch_dd_copy(const void* src, int64_t src_stride, void* dst, int64_
   if ((bytes & 3) || (src_stride & 3) || (dst_stride & 3) || (reinterpret_cast<uintptr_t>(src) & 3) ||
       (reinterpret_cast<uintptr_t>(dst) & 3))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(dd_copy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
-                     static_cast<const char*>(src), src_stride, static_cast<char*>(dst), dst_stride,
-                     bytes / 4);
+  const bool wide = ((bytes | src_stride | dst_stride | (int64_t)reinterpret_cast<uintptr_t>(src) |
+                      (int64_t)reinterpret_cast<uintptr_t>(dst)) & 7) == 0;
+  if (wide)
+    hipLaunchKernelGGL(dd_copy_kernel<uint64_t>, dim3((unsigned)blocks), dim3(256), 0, stream,
+                       static_cast<const char*>(src), src_stride, static_cast<char*>(dst), dst_stride, bytes / 8);
+  else
+    hipLaunchKernelGGL(dd_copy_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, stream,
+                       static_cast<const char*>(src), src_stride, static_cast<char*>(dst), dst_stride, bytes / 4);
   return hipGetLastError();
 }
 
@@ -1066,7 +1171,7 @@ hipError_t launch_dd_init(const DDProgram* prog, DDState* st, cq_dd_record* recs
 hipError_t launch_dd_setup(const DDProgram* prog, DDState* st, DDLevel* lv, cq_dd_record* recs,
                            int r, void* bins, hipStream_t stream, InstSpan span) {
   if (span.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(dd_setup_kernel, dim3(1, 1, (unsigned)span.n), dim3(64), 0, stream, prog, st, lv, recs, r,
+  hipLaunchKernelGGL(dd_setup_kernel, dim3(1, 1, (unsigned)span.n), dim3(kCtlThreads), 0, stream, prog, st, lv, recs, r,
                      bins, span.stride);
   return hipGetLastError();
 }
@@ -1074,7 +1179,7 @@ hipError_t launch_dd_setup(const DDProgram* prog, DDState* st, DDLevel* lv, cq_d
 hipError_t launch_dd_update(const DDProgram* prog, DDState* st, cq_dd_record* recs, int r,
                             hipStream_t stream, InstSpan span) {
   if (span.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(dd_update_kernel, dim3(1, 1, (unsigned)span.n), dim3(64), 0, stream, prog, st, recs, r,
+  hipLaunchKernelGGL(dd_update_kernel, dim3(1, 1, (unsigned)span.n), dim3(kCtlThreads), 0, stream, prog, st, recs, r,
                      span.stride);
   return hipGetLastError();
 }

@@ -299,6 +299,7 @@ hipError_t launch_prep_indirect(const PrepArgs* dev, int count, DType t, bool f1
                                 int64_t max_n, hipStream_t stream, InstSpan span = InstSpan());
 hipError_t launch_merge_indirect(const MergeArgs* dev, int count, int64_t max_threads,
                                  hipStream_t stream, InstSpan span = InstSpan());
+// dev: two argument blocks, the first of at most max_bins bins, the second of one
 hipError_t launch_refine_indirect(const RefineArgs* dev, int max_bins, hipStream_t stream,
                                   InstSpan span = InstSpan());
 // Top-C of *count bins (value desc, index asc) with C = *C_dev <= C_max
@@ -312,6 +313,9 @@ int64_t topk_indirect_capacity(int64_t max_count, int C_max);
 // Top-C (C = *C_dev) of *count_dev explicit candidate keys, in two passes
 // through kTopcStage * C_max staged keys.
 constexpr int kTopcStage = 256;
+// Without staging buffers (null): at most kTopcDirect candidates, selected in
+// one launch.
+constexpr int kTopcDirect = 4096;
 hipError_t launch_topk_candidates(const double* cand_val, const uint64_t* cand_idx,
                                   const int64_t* count_dev, const int32_t* C_dev, int C_max,
                                   double* stage_val, uint64_t* stage_idx, double* out_val,
@@ -319,9 +323,11 @@ hipError_t launch_topk_candidates(const double* cand_val, const uint64_t* cand_i
 
 // ---------------------------------------------------------------------------
 // Device-driven dynamic definition (Algorithm 1).  One recursion is a fixed
-// sequence of launches: setup (descriptors from the current masks), merge,
-// row sums, FP64 total, operand preparation, the bin contraction, top-C,
-// FP64 refinement and the list update / zoom.  Sizes are products of powers
+// sequence of launches: setup (the list update and zoom of the recursion
+// before, then descriptors from the current masks), merge, row sums, operand
+// preparation, the bin contraction, top-C, and FP64 refinement with the
+// recursion total.  The last recursion's list update is a launch of its own.
+// Sizes are products of powers
 // of two, 2^(c0 + sum of the active counts of the subcircuits in `mask`), so
 // the contraction plan made for the largest active counts is re-evaluated on
 // the device for the current ones.
@@ -384,7 +390,7 @@ struct DDProgram {
   double* Rs[CQ_MAX_SUBCIRCUITS];            // their row sums
   int32_t prep_dst[CQ_MAX_SUBCIRCUITS];      // tensor receiving the converted copy, or -1
   int32_t topc_step;                         // GEMM step that selects top-C instead of storing, or -1
-  int32_t pad2;
+  int32_t prune;                             // its tiles are pruned (dd_prunes)
   double* cand_v;                            // its candidate buffers
   uint64_t* cand_i;
   // tile pruning of that GEMM (see launch_tile_bounds)
@@ -460,7 +466,7 @@ struct DDLevel {  // descriptors of the current recursion
   GemmArgs gemm[kDDMaxSteps];
   GemmArgs topc_warm;            // the top-C GEMM over the warm-up tiles
   PermArgs perm[kDDMaxSteps];
-  RefineArgs refine;
+  RefineArgs refine[2];          // the selected bins, and the recursion total
 };
 
 // Threshold from the warm-up tiles' candidates (the C-th best of them, C =
@@ -474,7 +480,8 @@ hipError_t launch_dd_copy(const void* src, int64_t src_stride, void* dst, int64_
 // State <- the program's recursion-0 masks, list empty, records zeroed.
 hipError_t launch_dd_init(const DDProgram* prog, DDState* st, cq_dd_record* recs, int R,
                           hipStream_t stream, InstSpan span = InstSpan());
-// Descriptors of recursion r from the state; `bins` receives its bins.
+// The list update of recursion r - 1 (r > 0), then the descriptors of
+// recursion r from the state; `bins` receives its bins.
 hipError_t launch_dd_setup(const DDProgram* prog, DDState* st, DDLevel* lv, cq_dd_record* recs,
                            int r, void* bins, hipStream_t stream, InstSpan span = InstSpan());
 // Per-label balance of the recursion's reduced entries, for programs with
