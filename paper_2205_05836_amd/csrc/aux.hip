@@ -237,9 +237,9 @@ __global__ void __launch_bounds__(256) operand_clear_kernel(OperandSet s, int ro
 
 // max_b |src[l][b]| per row.  A wave takes 64 consecutive entries at a time:
 // rows of at most 64 columns share a wave (a reduction over each row's lanes),
-// longer rows have a wave each, or 2^split waves where the rows alone would
+// longer rows have a wave each, or 2^split workgroups where the rows alone would
 // leave the chip idle (4 rows of 2^20 columns: 4 waves walked 32 MiB); those
-// fold with one atomic a wave into maxima cleared before.
+// fold with one atomic a workgroup into maxima cleared before.
 __global__ void __launch_bounds__(256) operand_rowmax_kernel(OperandSet s, int clear) {
   int nb;
   const OperandIn& in = s.in[operand_of(s, gridDim.x, nb)];
@@ -263,25 +263,35 @@ __global__ void __launch_bounds__(256) operand_rowmax_kernel(OperandSet s, int c
   }
   const int64_t units = in.rows << in.split;
   const int64_t len = (int64_t)1 << (cl - in.split);  // a multiple of 64
-  for (int64_t u = blk * 4 + (threadIdx.x >> 6); u < units; u += waves) {
-    const double* p = in.src + u * len + lane;
+  // a wave a unit, or a workgroup where rows are split: one atomic a workgroup
+  // (with one a wave and 2^11 parts a row the atomics on 4 rows took 90 us)
+  const int wave = threadIdx.x >> 6, per = in.split ? 4 : 1;
+  __shared__ double part[4];
+  for (int64_t u = in.split ? blk : blk * 4 + wave; u < units; u += in.split ? nb : waves) {
+    const int64_t sub = len / per;
+    const double* p = in.src + u * len + (in.split ? wave * sub : 0) + lane;
     double m = 0.0;
     int64_t c = 0;
-    for (; c + 512 <= len; c += 512) {
+    for (; c + 512 <= sub; c += 512) {
       double v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = p[c + 64 * j];
 #pragma unroll
       for (int j = 0; j < 8; ++j) m = fmax(m, fabs(v[j]));
     }
-    for (; c < len; c += 64) m = fmax(m, fabs(p[c]));
+    for (; c < sub; c += 64) m = fmax(m, fabs(p[c]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if (lane == 0) {
-      if (in.split == 0) in.rowmax[u] = (uint64_t)__double_as_longlong(m);
-      else atomicMax(reinterpret_cast<unsigned long long*>(in.rowmax + (u >> in.split)),
-                     (unsigned long long)__double_as_longlong(m));
+    if (in.split == 0) {
+      if (lane == 0) in.rowmax[u] = (uint64_t)__double_as_longlong(m);
+      continue;
     }
+    if (lane == 0) part[wave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      atomicMax(reinterpret_cast<unsigned long long*>(in.rowmax + (u >> in.split)),
+                (unsigned long long)__double_as_longlong(fmax(fmax(part[0], part[1]), fmax(part[2], part[3]))));
+    __syncthreads();
   }
 }
 
@@ -1643,11 +1653,12 @@ hipError_t launch_balance(const BalanceLaunch& b, hipStream_t stream) {
       in.block0 = blocks;
       in.split = 0;
       if (in.cols_log2 > 6) {
-        // rows are split until 8192 waves (32 a CU) have work, or a part is
-        // down to 512 entries (one round of loads in flight)
-        while ((in.rows << in.split) < 8192 && in.cols_log2 - in.split > 9) ++in.split;
+        // rows are split until 2048 workgroups (8 a CU) have work, or a part
+        // is down to 2048 entries (one round of loads in flight)
+        while ((in.rows << in.split) < 2048 && in.cols_log2 - in.split > 11) ++in.split;
         atomics = atomics || in.split > 0;
-        blocks += operand_blocks((in.rows << in.split) * 64);
+        const int64_t units = in.rows << in.split;
+        blocks += operand_blocks(in.split ? units * 256 : units * 64);
       } else {
         blocks += operand_blocks(n);
       }
