@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <complex>
 #include <string>
 #include <vector>
 
@@ -36,19 +37,23 @@ constexpr int kMaxU = 36;     // one-qubit unitaries among them
 constexpr int kSvThreads = 256;
 constexpr int kLdsTile = 1 << (kMinTileBits - 1);
 
+// Forms of a one-qubit unitary (normalize).
+enum Form { kGeneral = 0, kNormal = 1 };
+
 // A gate of a pass in one word (whole words, so that uniform reads of the
-// arguments are aligned scalar loads): bits 0-7 CQ_GATE_U or CQ_GATE_CZ, 8-15
-// and 16-23 tile-local bit positions (the second for CZ only), 24-31 the
-// matrix (CQ_GATE_U).
+// arguments are aligned scalar loads): bits 0-5 CQ_GATE_U or CQ_GATE_CZ, 6-7
+// the form (CQ_GATE_U), 8-15 and 16-23 tile-local bit positions (the second
+// for CZ only), 24-31 the matrix (CQ_GATE_U).
 typedef uint32_t TileOp;
-__host__ __device__ inline int op_kind(TileOp g) { return (int)(g & 0xffu); }
+__host__ __device__ inline int op_kind(TileOp g) { return (int)(g & 0x3fu); }
+__host__ __device__ inline int op_form(TileOp g) { return (int)((g >> 6) & 3u); }
 __host__ __device__ inline int op_a(TileOp g) { return (int)((g >> 8) & 0xffu); }
 __host__ __device__ inline int op_b(TileOp g) { return (int)((g >> 16) & 0xffu); }
 __host__ __device__ inline int op_u(TileOp g) { return (int)(g >> 24); }
 
 // One launch: the tile's index bits by local position, the bits that number
 // the tiles, and the gates.  mode 0 writes amplitudes back, mode 1 writes
-// |amplitude|^2 to `probs` in the same index order.  State blockIdx.y of a
+// weight * |amplitude|^2 to `probs` in the same index order.  State blockIdx.y of a
 // batch starts as the basis string whose bit init_bit[t] is bit r - 1 - t of
 // blockIdx.y (all other bits 0) and lies bstride elements after state 0.
 struct TileGroup {
@@ -68,7 +73,9 @@ struct TileGroup {
   uint32_t bits[kMaxTileBits];
   uint32_t outer[CQ_MAX_SV_QUBITS];
   TileOp ops[kMaxOps];
-  double u[kMaxU][8];  // (re, im) of u00, u01, u10, u11
+  // (re, im) of u00, u01, u10, u11, or of the two ratios of the normalised form
+  double u[kMaxU][8];
+  double weight;
 };
 
 static_assert(sizeof(TileGroup) + 2 * sizeof(void*) <= 4096, "kernel arguments exceed 4 KiB");
@@ -129,8 +136,11 @@ __global__ void __launch_bounds__(kSvThreads) sv_tile_kernel(double2* psi, doubl
 // threads, thread t holds local indices t + T e, so the local bits are six
 // lane bits, then the wave bits, then the register bits.  A one-qubit gate on
 // a register bit pairs two of the thread's own elements; on a lane bit the
-// partner comes from another lane by a cross-lane read; on a wave bit it goes
-// through LDS.  The host places the pass's busiest qubits on register bits.
+// partner comes by a lane move of the vector ALU or by exchanging halves of two
+// registers (cross-lane reads went through LDS, the busiest unit: with them and
+// general unitaries the last pass of the 30-qubit circuit, 36 unitaries on 2^30
+// amplitudes, took 17.5 ms, 14.7 now; it is bound by vector issue, of which the
+// products are a third); on a wave bit it goes through LDS.  The host places the pass's busiest qubits on register bits.
 // Tiles of 11 bits run as 256 threads of 8 amplitudes, of 12 bits as 256 of 16
 // (13 bits as 512 of 16 leave one workgroup a compute unit: the 30-qubit
 // circuit took 30.3 ms against 24.6).
@@ -146,23 +156,78 @@ __device__ inline double2 u_row(double r0, double i0, double r1, double i1, doub
   return make_double2(r0 * x.x - i0 * x.y + r1 * y.x - i1 * y.y, r0 * x.y + i0 * x.x + r1 * y.y + i1 * y.x);
 }
 
-template <int R, int NE>
-__device__ inline void u_reg(double2 (&v)[NE], const double* u) {
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    if (e & (1 << R)) continue;
-    const double2 x0 = v[e], x1 = v[e | (1 << R)];
-    v[e] = u_row(u[0], u[1], u[2], u[3], x0, x1);
-    v[e | (1 << R)] = u_row(u[4], u[5], u[6], u[7], x0, x1);
+// x + (r + i i) y
+__device__ inline double2 add_scaled(double2 x, double r, double i, double2 y) {
+  return make_double2(x.x + r * y.x - i * y.y, x.y + r * y.y + i * y.x);
+}
+
+// A one-qubit unitary on a pair in registers.  The normalised form costs four
+// FMA an amplitude, the general one eight (see normalize).
+template <int F>
+__device__ inline void u_pair(double2& x0, double2& x1, const double* u) {
+  const double2 a = x0, b = x1;
+  if constexpr (F == kNormal) {
+    x0 = add_scaled(a, u[0], u[1], b);
+    x1 = add_scaled(b, u[2], u[3], a);
+  } else {
+    x0 = u_row(u[0], u[1], u[2], u[3], a, b);
+    x1 = u_row(u[4], u[5], u[6], u[7], a, b);
   }
 }
 
+template <int F, int R, int NE>
+__device__ inline void u_reg(double2 (&v)[NE], const double* u) {
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+    if (!(e & (1 << R))) u_pair<F>(v[e], v[e | (1 << R)], u);
+}
+
+// Lane bit 5 or 4 of elements a and b changes places with the choice between
+// them: a lane then holds both values of the bit of one element (its own for
+// the low half, the partner's for the high one).  Applying it again undoes it.
+template <int M>
+__device__ inline void lane_swap(double2& a, double2& b) {
+  uint64_t p[2] = {__builtin_bit_cast(uint64_t, a.x), __builtin_bit_cast(uint64_t, a.y)};
+  uint64_t q[2] = {__builtin_bit_cast(uint64_t, b.x), __builtin_bit_cast(uint64_t, b.y)};
+  uint32_t pw[4] = {(uint32_t)p[0], (uint32_t)(p[0] >> 32), (uint32_t)p[1], (uint32_t)(p[1] >> 32)};
+  uint32_t qw[4] = {(uint32_t)q[0], (uint32_t)(q[0] >> 32), (uint32_t)q[1], (uint32_t)(q[1] >> 32)};
+  // in place (the builtin copies its operands first); a swap wants two wait
+  // states after a vector write of its operands
+#define CQ_SWAP4(op)                                                                                              \
+  asm volatile("s_nop 1\n\t" op " %0, %4\n\t" op " %1, %5\n\t" op " %2, %6\n\t" op " %3, %7"                    \
+               : "+v"(pw[0]), "+v"(pw[1]), "+v"(pw[2]), "+v"(pw[3]), "+v"(qw[0]), "+v"(qw[1]), "+v"(qw[2]), "+v"(qw[3]))
+  if constexpr (M == 32) CQ_SWAP4("v_permlane32_swap_b32");
+  else CQ_SWAP4("v_permlane16_swap_b32");
+#undef CQ_SWAP4
+  for (int i = 0; i < 2; ++i) {
+    p[i] = (uint64_t)pw[2 * i] | (uint64_t)pw[2 * i + 1] << 32;
+    q[i] = (uint64_t)qw[2 * i] | (uint64_t)qw[2 * i + 1] << 32;
+  }
+  a = make_double2(__builtin_bit_cast(double, p[0]), __builtin_bit_cast(double, p[1]));
+  b = make_double2(__builtin_bit_cast(double, q[0]), __builtin_bit_cast(double, q[1]));
+}
+
+// x of lane ^ M, M < 16: by a lane move of the vector ALU, for M = 4 (which
+// needs two of those) by a swizzle.
+template <int M>
+__device__ inline uint32_t lane_xor(uint32_t x) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "within a row");
+  if constexpr (M == 4) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x101f);
+  else return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, M == 1 ? 0xb1 : M == 2 ? 0x4e : 0x128, 0xf, 0xf, true);
+}
+
+template <int M>
+__device__ inline double lane_xor(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  return __builtin_bit_cast(double, (uint64_t)lane_xor<M>((uint32_t)b) | (uint64_t)lane_xor<M>((uint32_t)(b >> 32)) << 32);
+}
+
 // An element whose partner (the other value of its pair) sits elsewhere:
-// bit 0 takes u00 * mine + u01 * partner, bit 1 u11 * mine + u10 * partner.
-// The two coefficients are picked once per gate, so each element costs one
-// complex row, not two and a select.
+// bit 0 takes u00 * mine + u01 * partner, bit 1 u11 * mine + u10 * partner,
+// or in the normalised form mine + ratio * partner.  The coefficients are
+// picked once per gate, so each element costs one row, not two and a select.
 struct ExchangeCoef {
-  double ar, ai, br, bi;  // coefficient of mine, of the partner
+  double ar, ai, br, bi;  // coefficient of mine, of the partner; or the ratio in a
 };
 
 // A coefficient every lane reads alike, taken through the first lane so that
@@ -176,28 +241,83 @@ __device__ inline double uniform_coef(const double* p) {
   return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
+template <int F>
 __device__ inline ExchangeCoef exchange_coef(const double* u, int bit) {
-  const ExchangeCoef c0{uniform_coef(u + 0), uniform_coef(u + 1), uniform_coef(u + 2), uniform_coef(u + 3)};
-  const ExchangeCoef c1{uniform_coef(u + 6), uniform_coef(u + 7), uniform_coef(u + 4), uniform_coef(u + 5)};
-  return bit ? c1 : c0;
+  if constexpr (F != kGeneral) {
+    const double r0 = uniform_coef(u + 0), i0 = uniform_coef(u + 1), r1 = uniform_coef(u + 2), i1 = uniform_coef(u + 3);
+    return ExchangeCoef{bit ? r1 : r0, bit ? i1 : i0, 0.0, 0.0};
+  } else {
+    const ExchangeCoef c0{uniform_coef(u + 0), uniform_coef(u + 1), uniform_coef(u + 2), uniform_coef(u + 3)};
+    const ExchangeCoef c1{uniform_coef(u + 6), uniform_coef(u + 7), uniform_coef(u + 4), uniform_coef(u + 5)};
+    return bit ? c1 : c0;
+  }
 }
 
+template <int F>
 __device__ inline double2 u_exchange(const ExchangeCoef& c, double2 mine, double2 y) {
-  return u_row(c.ar, c.ai, c.br, c.bi, mine, y);
+  if constexpr (F == kNormal) return add_scaled(mine, c.ar, c.ai, y);
+  else return u_row(c.ar, c.ai, c.br, c.bi, mine, y);
 }
 
-template <int M, int NE>
+// A gate on lane bit log2 M.
+template <int F, int M, int NE>
 __device__ inline void u_lane(double2 (&v)[NE], const double* u, int lane) {
-  const ExchangeCoef c = exchange_coef(u, (lane & M) ? 1 : 0);
+  if constexpr (M >= 16) {
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const double2 y = make_double2(__shfl_xor(v[e].x, M), __shfl_xor(v[e].y, M));
-    v[e] = u_exchange(c, v[e], y);
+    for (int e = 0; e < NE; e += 2) {
+      lane_swap<M>(v[e], v[e + 1]);
+      u_pair<F>(v[e], v[e + 1], u);
+      lane_swap<M>(v[e], v[e + 1]);
+    }
+  } else {
+    const ExchangeCoef c = exchange_coef<F>(u, (lane & M) ? 1 : 0);
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+      v[e] = u_exchange<F>(c, v[e], make_double2(lane_xor<M>(v[e].x), lane_xor<M>(v[e].y)));
   }
 }
 
 __device__ inline double flip_sign(double x, uint32_t bit31) {
   return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) ^ ((uint64_t)bit31 << 32));
+}
+
+// A one-qubit unitary on local bit ga; S is the workgroup's exchange buffer of
+// 8 elements a thread.
+template <int TB, int F>
+__device__ __forceinline__ void reg_unitary(double2 (&v)[TileShape<TB>::NE], const double* u, int ga, int tid,
+                                            int lane, double2* S) {
+  constexpr int T = TileShape<TB>::T, LogT = TileShape<TB>::LogT, NE = TileShape<TB>::NE;
+  if (ga >= LogT) {
+    switch (ga - LogT) {
+      case 0: u_reg<F, 0, NE>(v, u); break;
+      case 1: u_reg<F, 1, NE>(v, u); break;
+      case 2: u_reg<F, 2, NE>(v, u); break;
+      default:
+        if constexpr (NE > 8) u_reg<F, 3, NE>(v, u);
+        break;
+    }
+  } else if (ga < 6) {
+    switch (ga) {
+      case 0: u_lane<F, 1, NE>(v, u, lane); break;
+      case 1: u_lane<F, 2, NE>(v, u, lane); break;
+      case 2: u_lane<F, 4, NE>(v, u, lane); break;
+      case 3: u_lane<F, 8, NE>(v, u, lane); break;
+      case 4: u_lane<F, 16, NE>(v, u, lane); break;
+      default: u_lane<F, 32, NE>(v, u, lane); break;
+    }
+  } else {
+    const ExchangeCoef c = exchange_coef<F>(u, (tid >> ga) & 1);
+    const int m = 1 << ga;
+#pragma unroll
+    for (int h = 0; h < NE; h += 8) {
+      __syncthreads();  // the previous exchange has read S
+#pragma unroll
+      for (int e = 0; e < 8; ++e) S[tid + e * T] = v[h + e];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[h + e] = u_exchange<F>(c, v[h + e], S[(tid + e * T) ^ m]);
+    }
+  }
 }
 
 // The pass's gates on a thread's elements; S is the workgroup's exchange
@@ -232,44 +352,13 @@ __device__ __forceinline__ void reg_apply(double2 (&v)[TileShape<TB>::NE], const
       }
       continue;
     }
-    const double* u = G.u[op_u(g)];
-    const int ga = op_a(g);
-    if (ga >= LogT) {
-      switch (ga - LogT) {
-        case 0: u_reg<0, NE>(v, u); break;
-        case 1: u_reg<1, NE>(v, u); break;
-        case 2: u_reg<2, NE>(v, u); break;
-        default:
-          if constexpr (NE > 8) u_reg<3, NE>(v, u);
-          break;
-      }
-    } else if (ga < 6) {
-      switch (ga) {
-        case 0: u_lane<1, NE>(v, u, lane); break;
-        case 1: u_lane<2, NE>(v, u, lane); break;
-        case 2: u_lane<4, NE>(v, u, lane); break;
-        case 3: u_lane<8, NE>(v, u, lane); break;
-        case 4: u_lane<16, NE>(v, u, lane); break;
-        default: u_lane<32, NE>(v, u, lane); break;
-      }
-    } else {
-      const ExchangeCoef c = exchange_coef(u, (tid >> ga) & 1);
-      const int m = 1 << ga;
-#pragma unroll
-      for (int h = 0; h < NE; h += 8) {
-        __syncthreads();  // the previous exchange has read S
-#pragma unroll
-        for (int e = 0; e < 8; ++e) S[tid + e * T] = v[h + e];
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[h + e] = u_exchange(c, v[h + e], S[(tid + e * T) ^ m]);
-      }
-    }
+    if (op_form(g) == kNormal) reg_unitary<TB, kNormal>(v, G.u[op_u(g)], op_a(g), tid, lane, S);
+    else reg_unitary<TB, kGeneral>(v, G.u[op_u(g)], op_a(g), tid, lane, S);
   }
 }
 
 template <int TB>
-__global__ void __launch_bounds__(TileShape<TB>::T, TB == 12 ? 3 : 5) sv_reg_kernel(double2* psi, double* probs, TileGroup G) {
+__global__ void __launch_bounds__(TileShape<TB>::T, TB == 12 ? 2 : 4) sv_reg_kernel(double2* psi, double* probs, TileGroup G) {
   constexpr int T = TileShape<TB>::T, LogT = TileShape<TB>::LogT, NE = TileShape<TB>::NE;
   __shared__ double2 S[T * 8];
   psi += blockIdx.y * G.bstride;
@@ -302,15 +391,16 @@ __global__ void __launch_bounds__(TileShape<TB>::T, TB == 12 ? 3 : 5) sv_reg_ker
     }
   }
   if (!zero) reg_apply<TB>(v, G, tid, lane, S);
+  if (G.mode == 0) {
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const uint64_t a = tpart | epart(e);
-    if (G.mode == 0) {
+    for (int e = 0; e < NE; ++e) {
+      const uint64_t a = tpart | epart(e);
       if (((a ^ start) & off1) == 0) psi[a] = v[e];
-    } else {
-      probs[a] = v[e].x * v[e].x + v[e].y * v[e].y;
     }
+    return;
   }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) probs[tpart | epart(e)] = G.weight * (v[e].x * v[e].x + v[e].y * v[e].y);
 }
 
 // Variants by linearity.  An init string prepares each init slot t in
@@ -558,6 +648,8 @@ struct GateSet {
   int n = 0;
   std::vector<cq_gate> g;
   std::vector<uint64_t> mask;
+  std::vector<int> form;  // Form of each one-qubit unitary
+  double weight = 1.0;    // |factor|^2 that the final amplitudes lack
 };
 
 uint64_t gate_mask(int n, const cq_gate& g) {
@@ -585,6 +677,56 @@ GateSet gate_set(int n, const cq_gate* gates, int n_gates, uint64_t rotated) {
   return s;
 }
 
+// Rewrites the unitaries so that most cost four FMA an amplitude instead of
+// eight: U = diag(d0, d1) [1, a; b, 1].  The diagonal commutes with the CZs
+// behind the gate and is multiplied into the columns of the next unitary on
+// its qubit.  A qubit's last unitary stays general, or, where only
+// probabilities are asked for (`probs`) and |d0| = |d1| to rounding (as for
+// every unitary matrix), leaves |d0|^2 to the final weight.  The sums are those
+// of the general form over a common factor, so they round alike.  What is
+// stored meanwhile is the true amplitude over the factors held back: those are
+// kept within 2^-12 .. 2^12 a qubit (2^408 over 34 qubits) by a general gate,
+// which also takes what has no such form or a diagonal below a 16th of the
+// entries beside it.
+void normalize(GateSet& s, bool probs) {
+  typedef long double real;  // the factors and ratios are rounded to double once
+  typedef std::complex<real> cx;
+  std::vector<cx> d0(s.n, 1.0), d1(s.n, 1.0);
+  std::vector<int> last(s.n, -1);
+  for (size_t i = 0; i < s.g.size(); ++i)
+    if (s.g[i].kind == CQ_GATE_U) last[s.g[i].q0] = (int)i;
+  s.form.assign(s.g.size(), kGeneral);
+  if (s.n < kMinTileBits) return;
+  const auto fits = [](real pivot, real other) {  // false for NaN
+    return pivot >= (real)1 / 4096 && pivot <= (real)4096 && other <= 16 * pivot;
+  };
+  for (size_t i = 0; i < s.g.size(); ++i) {
+    cq_gate& g = s.g[i];
+    if (g.kind != CQ_GATE_U) continue;
+    const int q = g.q0;
+    cx u[4];
+    for (int c = 0; c < 4; ++c) u[c] = cx(g.u[2 * c], g.u[2 * c + 1]) * ((c & 1) ? d1[q] : d0[q]);
+    d0[q] = d1[q] = 1.0;
+    bool normal = fits(std::abs(u[0]), std::abs(u[1])) && fits(std::abs(u[3]), std::abs(u[2]));
+    if (normal && (int)i == last[q]) {
+      const real n0 = std::norm(u[0]), n1 = std::norm(u[3]);
+      normal = probs && std::abs(n0 - n1) <= 4e-16L * n0;
+      if (normal) s.weight *= (double)((n0 + n1) / 2);
+    }
+    if (normal) {
+      s.form[i] = kNormal;
+      d0[q] = u[0];
+      d1[q] = u[3];
+      u[0] = u[1] / d0[q];
+      u[1] = u[2] / d1[q];
+    }
+    for (int c = 0; c < (normal ? 2 : 4); ++c) {
+      g.u[2 * c] = (double)u[c].real();
+      g.u[2 * c + 1] = (double)u[c].imag();
+    }
+  }
+}
+
 // How a plan is laid out: tile bits, the lowest index bits every tile holds
 // (gathers then read runs of 2^low amplitudes), and how many qubits join the
 // allowed set when no gate inside it can run.
@@ -599,7 +741,7 @@ struct PlanShape {
 // first, only when none of their gates can run: while t qubits are touched a
 // pass moves 2^t amplitudes.  Returns the modelled time in microseconds, or
 // anything above `limit` once that is passed.  The model, from traces: 3.5 us
-// a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.55 ms for
+// a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.33 ms for
 // every one-qubit gate on 2^30 amplitudes, no less than the serial time of
 // those gates in one tile (0.8 us each with 11 bits, 1.4 us with 12).
 double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int states, double limit,
@@ -646,7 +788,7 @@ double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int states
     rest.swap(left);
     const double before = out.empty() && track ? 0.0 : std::ldexp(16.0, __builtin_popcountll(p.before));
     const double after = std::ldexp(rest.empty() ? 8.0 : 16.0, rest.empty() ? n : __builtin_popcountll(p.after));
-    const double work = nu * std::max(std::ldexp(5.2e-7 * states, __builtin_popcountll(p.after)),
+    const double work = nu * std::max(std::ldexp(3.1e-7 * states, __builtin_popcountll(p.after)),
                                       sh.tile <= 11 ? 0.8 : 1.4);
     us += 3.5 + states * (before + after) / 4.4e6 + work;
     out.push_back(std::move(p));
@@ -725,6 +867,7 @@ TileGroup tile_group(const GateSet& s, const PlanShape& sh, const Pass& pass, in
       else G.fixed |= 1ull << b;
     }
   G.nouter = no;
+  G.weight = s.weight;
   G.nops = (int)pass.gates.size();
   int nu = 0;
   for (int j = 0; j < G.nops; ++j) {
@@ -733,7 +876,7 @@ TileGroup tile_group(const GateSet& s, const PlanShape& sh, const Pass& pass, in
     if (g.kind == CQ_GATE_CZ) {
       G.ops[j] = a | (uint32_t)local[n - 1 - g.q1] << 16;
     } else {
-      G.ops[j] = a | (uint32_t)nu << 24;
+      G.ops[j] = a | (uint32_t)s.form[pass.gates[j]] << 6 | (uint32_t)nu << 24;
       for (int c = 0; c < 8; ++c) G.u[nu][c] = g.u[c];
       ++nu;
     }
@@ -757,8 +900,9 @@ hipError_t launch_tiles(const TileGroup& G, double2* psi, double* probs, unsigne
 // as a basis string (see TileGroup) that the first pass generates; without,
 // as what psi holds.  With probs (one state) the last pass writes
 // |amplitude|^2 there; else it leaves every amplitude in psi.
-hipError_t run_gates(const GateSet& s, double2* psi, double* probs, const std::vector<int>* init_bits,
+hipError_t run_gates(GateSet s, double2* psi, double* probs, const std::vector<int>* init_bits,
                      hipStream_t stream) {
+  normalize(s, probs != nullptr);
   const uint64_t full = (1ull << s.n) - 1;
   const bool track = init_bits != nullptr;
   const unsigned states = track ? 1u << init_bits->size() : 1u;

@@ -109,3 +109,35 @@ def test_variants_one_state_at_a_time(w, r, o):
     assert _lib.lib().cq_variant_probabilities(subs.ptr(), arr, cnt, _dev_ptr(out), _dev_ptr(ws), 16 << w,
                                                _stream(None)) == 0
     assert float((out - want).abs().max()) < 1e-12
+
+
+def matrix(kind, rng):
+    """One-qubit matrices around the edges of the normalised form."""
+    z = np.exp(1j * rng.uniform(0, 2 * np.pi, 4))
+    if kind == "small pivot":  # |u00| = |u11| about a 16th, below and above, and next to nothing
+        c = float(rng.choice([1 / 16 * 0.99, 1 / 16 * 1.01, 1e-3, 1e-30]))
+        s = np.sqrt(1 - c * c)
+        return np.array([[c, -s], [s, c]]) * z[0] * np.array([[1, z[1]], [1, z[1]]])
+    if kind == "exchange":  # zero diagonal or zero off-diagonal
+        return np.array([[0, z[0]], [z[1], 0]]) if rng.random() < 0.5 else np.diag(z[:2])
+    if kind == "not unitary":  # unequal rows, up to a factor of 64 each
+        return (rng.normal(size=(2, 2)) + 1j * rng.normal(size=(2, 2))) * np.exp2(rng.uniform(-3, 3, (2, 1)))
+    return np.outer(rng.normal(size=2), rng.normal(size=2)) + 0j  # rank one: a measured branch
+
+
+@pytest.mark.parametrize("kind", ["small pivot", "exchange", "not unitary", "rank one"])
+@pytest.mark.parametrize("n,layers", [(11, 3), (12, 40), (14, 9)])
+def test_matrix_forms(kind, n, layers):
+    """Matrices that the normalised form takes, just takes and does not, mixed
+    with Haar ones, deep enough that the factors it holds back reach their
+    bound.  Errors are compared with the largest probability (the matrices of
+    two kinds do not keep the norm); the bar is that of the tests above."""
+    import paper_2205_05836_amd as cq
+    rng = np.random.default_rng(n + layers)
+    ops = []
+    for t in range(layers):
+        ops += [wc.Op("u", (q,), matrix(kind, rng) if rng.random() < 0.5 else wc.haar_u2(rng)) for q in range(n)]
+        ops += [wc.Op("cz", (i, i + 1)) for i in range(t % 2, n - 1, 2)]
+    want = sv.probabilities(n, ops)
+    got = cq.cq_simulate_probabilities(n, ops).cpu().numpy()
+    assert np.abs(got - want).max() <= 1e-12 * want.max()
