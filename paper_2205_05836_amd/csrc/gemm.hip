@@ -1821,6 +1821,155 @@ gemm_f64t_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
+// 16-bit operands with one short side (at most 32 rows or columns, too few or
+// too unaligned for the asynchronous kernels: a subcircuit with one or two
+// outputs).  Bound by memory: a wave takes 128 of the long side's columns,
+// four a lane, straight from memory (8 bytes a label row, no LDS) and the short
+// side as the rows of 32 x 32 blocks, so a lane ends up with neighbouring
+// results.  The register-path kernel pads the short side to 128: 2^21 x 4
+// outputs of 4 labels took 270 us in BF16 and 665 in split planes, now 38 in
+// both.  The products and their order are that kernel's (operands exchanged
+// where the columns are short), so the sums are the same bit for bit.
+// ---------------------------------------------------------------------------
+template <int SPLIT, bool F16, int OUT, bool SHORT_N>
+__global__ void __launch_bounds__(256) gemm_h16n_kernel(GemmArgs g, int64_t tiles_l) {
+  using H = Half<F16>;
+  using V8 = typename H::V8;
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  constexpr int NP = SPLIT == 3 ? 2 : 1;
+  const int64_t z = blockIdx.x / tiles_l, tile = blockIdx.x - z * tiles_l;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane >> 5, c = lane & 31;
+  const int64_t nl = SHORT_N ? g.M : g.N;
+  const int ns = (int)(SHORT_N ? g.N : g.M);
+  const int64_t col = tile * 512 + (tid >> 6) * 128 + 4 * c;
+  const int64_t lsk = SHORT_N ? g.sAk : g.sBk, ssk = SHORT_N ? g.sBk : g.sAk;
+  const uint16_t *L[NP], *S[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const uint16_t* a = static_cast<const uint16_t*>(p ? g.A_lo : g.A) + z * g.sAz;
+    const uint16_t* b = static_cast<const uint16_t*>(p ? g.B_lo : g.B) + z * g.sBz;
+    L[p] = (SHORT_N ? a : b) + (col < nl ? col : nl - 4);
+    S[p] = (SHORT_N ? b : a) + (c < ns ? c : 0);
+  }
+  f16_t acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+  for (int64_t k0 = 0; k0 < g.K; k0 += 16) {
+    // labels k0 + 8r .. + 7 of this lane; past K: the last, as zeros
+    u32x2 rows[NP][8];
+    uint32_t sv[NP][8];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int64_t q = k0 + 8 * r + j, k = q < g.K ? q : g.K - 1;
+        rows[p][j] = *reinterpret_cast<const u32x2*>(L[p] + k * lsk);
+        sv[p][j] = S[p][k * ssk];
+      }
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bool in = k0 + 8 * r + j < g.K;
+        rows[p][j] = in ? rows[p][j] : u32x2{0u, 0u};
+        sv[p][j] = in && c < ns ? sv[p][j] : 0u;
+      }
+    V8 s[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      u32x4 w;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) w[d] = sv[p][2 * d] | sv[p][2 * d + 1] << 16;
+      s[p] = __builtin_bit_cast(V8, w);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      V8 l[NP];
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        u32x4 w;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          w[d] = __builtin_amdgcn_perm(rows[p][2 * d + 1][i >> 1], rows[p][2 * d][i >> 1],
+                                       (i & 1) ? 0x07060302u : 0x05040100u);
+        l[p] = __builtin_bit_cast(V8, w);
+      }
+      acc[i] = H::mfma(s[0], l[0], acc[i]);
+      if constexpr (SPLIT == 3) {
+        // A hi x B lo, then A lo x B hi
+        acc[i] = SHORT_N ? H::mfma(s[NP - 1], l[0], acc[i]) : H::mfma(s[0], l[NP - 1], acc[i]);
+        acc[i] = SHORT_N ? H::mfma(s[0], l[NP - 1], acc[i]) : H::mfma(s[NP - 1], l[0], acc[i]);
+      }
+    }
+  }
+  if (col >= nl) return;
+  // item v of column i: row 8 (v/4) + 4r + v%4 of the short side, column col + i
+  const float alpha = float(g.alpha);
+  const bool al = (reinterpret_cast<uintptr_t>(g.C) & 15) == 0 && g.ldc % 4 == 0 && g.sCz % 4 == 0;
+  const auto value = [&](int i, int v, int64_t row) {
+    float x = alpha * acc[i][v];
+    if constexpr (OUT == 2) asm("" : "+v"(x));  // rounded before the lo plane is taken from it
+    if constexpr (OUT != 2)
+      if (g.rowexp)
+        x = __builtin_ldexpf(x, SHORT_N ? g.rowexp[z * g.M + col + i] + g.colexp[row]
+                                        : g.rowexp[z * g.M + row] + g.colexp[col + i]);
+    return x;
+  };
+  const auto put = [&](int64_t idx, float x) {
+    if constexpr (OUT == 2) {
+      const uint16_t h = to_h16<F16>(x);
+      static_cast<uint16_t*>(g.C)[idx] = h;
+      if constexpr (SPLIT == 3) static_cast<uint16_t*>(g.C_lo)[idx] = to_h16<F16>(x - from_h16<F16>(h));
+    } else {
+      store_out<float, OUT == 1>(static_cast<float*>(g.C) + idx, x);
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row0 = 8 * q + 4 * r;
+    if (row0 >= ns) continue;
+    const int left = ns - row0 < 4 ? ns - row0 : 4;
+    if constexpr (SHORT_N) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float x[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = t < left ? value(i, 4 * q + t, row0 + t) : 0.0f;
+        const int64_t idx = z * g.sCz + (col + i) * g.ldc + row0;
+        if (OUT != 2 && al && left == 4) {
+          store_out<f4, OUT == 1>(reinterpret_cast<f4*>(static_cast<float*>(g.C) + idx), f4{x[0], x[1], x[2], x[3]});
+        } else if (OUT != 2 && left == 2 && (reinterpret_cast<uintptr_t>(static_cast<float*>(g.C) + idx) & 7) == 0) {
+          store_out<f2, OUT == 1>(reinterpret_cast<f2*>(static_cast<float*>(g.C) + idx), f2{x[0], x[1]});
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (t < left) put(idx + t, x[t]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (t >= left) continue;
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = value(i, 4 * q + t, row0 + t);
+        const int64_t idx = z * g.sCz + (row0 + t) * g.ldc + col;
+        if (OUT != 2 && al) {
+          store_out<f4, OUT == 1>(reinterpret_cast<f4*>(static_cast<float*>(g.C) + idx), f4{x[0], x[1], x[2], x[3]});
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) put(idx + i, x[i]);
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // FP64 operands, 32 W x 32 W tiles of four waves (16 W x 16 W each), for GEMMs
 // with too few 64 x 128 tiles to give every CU two (launch_f64t): the more and
 // smaller workgroups reach more CUs, and as few waves share a SIMD a stage's
@@ -2618,6 +2767,27 @@ hipError_t launch_h16t(const GemmArgs& a, DType tc, bool nt, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One side of at most 32, the other of whole 4-column segments, aligned to 8
+// bytes, and long enough for a few waves: the short-side kernel applies
+bool h16n_ok(const GemmArgs& a) {
+  const bool n = a.N <= a.M;  // the short side
+  const int64_t nl = n ? a.M : a.N, sk = n ? a.sAk : a.sBk, sz = n ? a.sAz : a.sBz;
+  const void *p = n ? a.A : a.B, *lo = n ? a.A_lo : a.B_lo;
+  return (n ? a.N : a.M) <= 32 && nl >= 128 && nl % 4 == 0 && a.K >= 1 && sk % 4 == 0 && sz % 4 == 0 &&
+         ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(lo)) & 7) == 0;
+}
+
+template <int SPLIT, bool F16, int OUT>
+hipError_t launch_h16n(const GemmArgs& a, hipStream_t s) {
+  const bool n = a.N <= a.M;
+  const int64_t tiles = ((n ? a.M : a.N) + 511) / 512, z = a.tiles / (a.tilesM * a.tilesN);
+  if (tiles * z > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(tiles * z)), block(256);
+  if (n) hipLaunchKernelGGL((gemm_h16n_kernel<SPLIT, F16, OUT, true>), grid, block, 0, s, a, tiles);
+  else hipLaunchKernelGGL((gemm_h16n_kernel<SPLIT, F16, OUT, false>), grid, block, 0, s, a, tiles);
+  return hipGetLastError();
+}
+
 template <int SPLIT, bool F16>
 hipError_t dispatch_h16(const GemmArgs& a, DType tc, bool nt, hipStream_t s, int impl = 0) {
   constexpr int NS = SPLIT == 3 ? 2 : 3;
@@ -2649,6 +2819,10 @@ hipError_t dispatch_h16(const GemmArgs& a, DType tc, bool nt, hipStream_t s, int
       return launch(gemm_h16a_kernel<SPLIT, F16, 0, NS>, a, s);
     }
     return launch(gemm_h16a_kernel<SPLIT, F16, 2, NS>, a, s);
+  }
+  if (!h16_async_ok(a, tc) && h16n_ok(a)) {
+    if (tc != DType::F32) return launch_h16n<SPLIT, F16, 2>(a, s);
+    return nt ? launch_h16n<SPLIT, F16, 1>(a, s) : launch_h16n<SPLIT, F16, 0>(a, s);
   }
   if (tc == DType::F32) {
     if (nt) return launch(gemm_h16_kernel<SPLIT, F16, 1>, a, s);
