@@ -979,7 +979,7 @@ __global__ void __launch_bounds__(256) gemm_h16a_kernel(GemmArgs gv, const GemmA
           const uint16_t* src = gbase[op][p] + k * gsk[op] + col;
           const uint32_t dst = __builtin_amdgcn_readfirstlane(
               (uint32_t)(uintptr_t)(lsm + (s % NS) * STAGE + (op * NP + p) * TILE + chunk0 * 16));
-          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
+          asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
                        : "memory", "m0");
         }
   };
@@ -1433,7 +1433,7 @@ __global__ void __launch_bounds__(256) gemm_h16s_kernel(GemmArgs g) {
         const uint16_t* src = gbase[op][p] + k * (op ? g.sBk : g.sAk) + lcol[op];
         const uint32_t dst = __builtin_amdgcn_readfirstlane(
             (uint32_t)(uintptr_t)(lsm + (s % NS) * STAGE + (op * NP + p) * TILE + wave * 1024));
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
                      : "memory", "m0");
       }
   };
@@ -2456,7 +2456,7 @@ __global__ void __launch_bounds__(256, 2) gemm_persist_kernel(GemmArgs g) {
           const typename P::E* src = isrc[op][p] + k * (op ? g.sBk : g.sAk);
           const uint32_t dst = __builtin_amdgcn_readfirstlane(
               (uint32_t)(uintptr_t)(lsm + is_slot * STAGE + (op * NP + p) * TILE + chunk0 * 16));
-          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
+          asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst)
                        : "memory", "m0");
         }
     if (++is_s == nstages) {
