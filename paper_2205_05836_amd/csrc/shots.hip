@@ -34,11 +34,14 @@ constexpr int kFewShots = 64;           // blocks with at most this many shots r
 constexpr int kSparseShots = 16;        // shots per block on average up to which only the runs with shots are read again
 constexpr int kRun = 64;                // entries of a run, one a lane
 constexpr int kRuns = kBlock / kRun;
-// rows of one block that a workgroup takes whole: with at most so many shots,
-// or so many rows that the chip is full anyway (else the shots of a row are
-// spread over workgroups)
-constexpr int64_t kRowShots = 16384;
-constexpr int64_t kRowRows = 256;
+// rows of one block that a workgroup takes whole: with at most so many shots
+// (one row: 27 us either way at 6000, 40 against 28 at 15000), or so many rows
+// that the chip is full anyway (600 rows of 20000 shots: 93 us whole, 80
+// spread; 1100 rows of 10000: 77 and 85), else the shots of a row are spread
+// over workgroups
+constexpr int64_t kRowShots = 6144;
+constexpr int64_t kRowRows = 1024;
+constexpr int64_t kPartShots = 4096;  // fewest shots of a workgroup where rows are spread
 
 __device__ inline uint64_t quant52(double p) {
   const double c = p > 0.0 ? (p < 1.0 ? p : 1.0) : 0.0;
@@ -640,6 +643,43 @@ __global__ void __launch_bounds__(kThreads) shots_row_kernel(const double* __res
   write_counts_lds(L, F + row * cols, n, shots);
 }
 
+// Rows of one block with too few rows for a workgroup each to fill the chip:
+// a workgroup takes `per` shots of row blockIdx.y, forms the row's prefix
+// again (at most 16 KB, against thousands of shots searched in it), counts in
+// LDS and adds to the row's counters in memory, cleared before and turned
+// into frequencies after.  By buckets one workgroup resolved the whole row: 4
+// rows of 1233 with 510851 shots a row took 1960 us, now 33.
+__global__ void __launch_bounds__(kThreads) shots_row_clear_kernel(uint32_t* __restrict__ cnt, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) cnt[i] = 0;
+}
+
+__global__ void __launch_bounds__(kThreads) shots_row_part_kernel(const double* __restrict__ P, int64_t cols,
+                                                                  int64_t shots, int64_t per, uint64_t seed,
+                                                                  uint32_t* __restrict__ cnt) {
+  __shared__ ResolveLds L;
+  const int64_t row = blockIdx.y, s0 = (int64_t)blockIdx.x * per, s1 = s0 + per < shots ? s0 + per : shots;
+  const int n = (int)cols;
+  block_prefix_lds(L, P + row * cols, n);
+  const uint64_t T = L.C[((n - 1) / kPer) * kPad + (n - 1) % kPer];
+  if (T != 0)
+    for (int64_t s = s0 + threadIdx.x; s < s1; s += kThreads) {
+      uint64_t t;
+      uint32_t blk;
+      shot_target(&T, 1, T, seed, row, s, t, blk);
+      count_target_lds(L, t, n);
+    }
+  __syncthreads();
+  for (int e = threadIdx.x; e < n; e += kThreads)
+    if (const uint32_t c = L.cnt[e]) atomicAdd(cnt + row * cols + e, c);
+}
+
+__global__ void __launch_bounds__(kThreads) shots_row_freq_kernel(const uint32_t* __restrict__ cnt, int64_t n,
+                                                                  int64_t shots, double* __restrict__ F) {
+  const double ds = (double)shots;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
+    F[i] = freq_of(cnt[i], ds);
+}
+
 // Every block, one workgroup each (grid (nblk, rows)): for tables with many
 // shots per block on average.
 __global__ void __launch_bounds__(kThreads) shots_resolve_kernel(const double* __restrict__ P, int64_t cols,
@@ -813,6 +853,24 @@ extern "C" cq_status cq_sample_shots(const double* probs, int64_t rows, int64_t 
   if (nblk == 1 && (shots <= kRowShots || rows >= kRowRows)) {
     hipLaunchKernelGGL(shots_row_kernel, dim3((unsigned)rows), dim3(kThreads), 0, stream, probs, cols, shots, seed,
                        freqs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "shot sampling launch");
+    return CQ_OK;
+  }
+  if (nblk == 1) {
+    // no more than 2048 workgroups unless there are more rows; the counters
+    // take the place of the slots (8 bytes a shot, shots > kRowShots >= the
+    // columns)
+    static_assert(kRowShots * 8 >= kBlock * 4, "counters fit the slots");
+    int64_t per = kPartShots;
+    while (per < shots && rows * ((shots + per - 1) / per) > 2048) per *= 2;
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(slots);
+    const int64_t n = rows * cols;
+    const dim3 gn((unsigned)((n + kThreads - 1) / kThreads));
+    hipLaunchKernelGGL(shots_row_clear_kernel, gn, dim3(kThreads), 0, stream, cnt, n);
+    hipLaunchKernelGGL(shots_row_part_kernel, dim3((unsigned)((shots + per - 1) / per), (unsigned)rows), dim3(kThreads),
+                       0, stream, probs, cols, shots, per, seed, cnt);
+    hipLaunchKernelGGL(shots_row_freq_kernel, gn, dim3(kThreads), 0, stream, cnt, n, shots, freqs);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "shot sampling launch");
     return CQ_OK;

@@ -59,3 +59,17 @@ def test_chi2_sizes_and_alignments(n):
     vals = [float(cq.cq_chi2(on_device(a, i), on_device(b, j))[0]) for i, j in ((0, 0), (1, 0), (1, 1))]
     assert vals[0] == vals[1] == vals[2]
     assert abs(vals[0] - shots.chi2(a, b)) <= 1e-12 * max(shots.chi2(a, b), 1e-300)
+
+
+@pytest.mark.parametrize("rows,cols,n,kind", [
+    (1, 2048, 6144, "plain"), (1, 2048, 6145, "plain"), (3, 1, 8193, "plain"), (5, 17, 2 ** 18 + 3, "dead"),
+    (2, 1233, 4096 * 9, "crowded"), (1023, 64, 8000, "runs"), (1024, 64, 8000, "plain"), (300, 100, 40000, "dead")])
+def test_rows_of_one_block_bit_exact(rows, cols, n, kind):
+    """Rows of one block: whole in a workgroup, or their shots spread over
+    several, at the lines between the two and with a last part that is short."""
+    import paper_2205_05836_amd as cq
+    print(f"rows={rows} cols={cols} shots={n} {kind}", flush=True)
+    P = rows_of(np.random.default_rng(rows + cols + n), rows, cols, kind)
+    out = on_device(np.full(P.shape, np.nan), 1)
+    got = cq.cq_sample_shots(on_device(P, 0), n, n, out=out).cpu().numpy()
+    assert np.array_equal(got, shots.sample_frequencies(P, n, n))
