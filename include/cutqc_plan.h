@@ -50,18 +50,20 @@ cq_status cq_profile_enable(int32_t on);
 cq_status cq_profile_read(char* names, double* ms, double* flops, int32_t cap, int32_t* count);
 
 /* GEMM autotuner for the full-definition label GEMMs.  The first launch of
- * each GEMM shape (outside stream capture, at least 64 output tiles) times
+ * each GEMM shape (outside stream capture, at least 64 output tiles of 128 x
+ * 128; smaller ones take 64 x 64 tiles where those apply) times
  * every kernel variant twice on the caller's stream and keeps the fastest for
  * that shape; that call synchronises the stream.  Under stream capture a
  * shape tuned before keeps its variant and an untuned shape takes variant 0
  * (nothing is timed).  Variant v: bit 0 flips the tile raster order (M- or
  * N-fastest); v >> 1 picks, for the 16-bit forms, the asynchronous
  * LDS-staged kernel with its default ring depth (0), with the other depth
- * (1), the register-path kernel (2), the persistent kernel (3) or the
+ * (1), 64 x 64 tiles (2), the persistent kernel (3) or the
  * occupancy kernel with four (4) or three (5) resident workgroups per compute
- * unit; for FP32 the tiled kernel (0) or the persistent kernel (3).  FP64 has
- * variants 0 and 1; FP32 0, 1, 6 and 7 (6 and 7 where rows are 16-byte
- * aligned); 16-bit forms 0..11 (2..11 only where the asynchronous kernel's
+ * unit; for FP32 the tiled kernel (0), 64 x 64 tiles (1), the persistent
+ * kernel (3) or the occupancy kernel (4, 5).  FP64 has
+ * variants 0 and 1 (its tile follows the tile count); FP32 0..3 and 6..11 (2
+ * and above where rows are 16-byte aligned); 16-bit forms 0..11 (2..11 only where the asynchronous kernel's
  * alignment holds, 6..11 only without output exponents).  Every variant
  * computes the same sums.
  *
@@ -124,8 +126,8 @@ cq_status cq_autotune_save(const char* path);
 
 /* The cached choices as JSON:
  *   [{"prec": ..., "M", "N", "K", "Z", "variant": v,
- *     "schedule": {"kernel": "tiled" | "async" | "register" | "persistent" |
- *                  "occupancy", "tile": [128, 128], "ring": operand stages in
+ *     "schedule": {"kernel": "tiled" | "async" | "small-tile" | "persistent" |
+ *                  "occupancy", "tile": [M, N], "ring": operand stages in
  *                  LDS (0: none), "workgroups_per_cu": resident workgroups the
  *                  kernel is built for (0: as many as fit), "raster": "default"
  *                  | "flipped"},

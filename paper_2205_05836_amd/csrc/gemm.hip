@@ -3164,12 +3164,26 @@ namespace {
 
 // The schedule behind variant v: kernel, tile, ring depth (operand stages in
 // LDS), resident workgroups per compute unit and raster order.
-std::string variant_schedule(int prec, int v) {
+std::string variant_schedule(const TuneKey& k, int v) {
+  const int prec = k.prec;
   const int impl = v >> 1;
   const bool split = prec == CQ_BF16_SPLIT || prec == CQ_FP16_SPLIT;
   const char* kernel = "tiled";
-  int ring = 0, wpc = 0, tile = 128;
-  if (prec == CQ_FP32 && impl == 1) {
+  int ring = 0, wpc = 0, tile = 128, tile_n = 0;
+  if (prec == CQ_FP64 && k.aligned) {  // as launch_f64t chooses
+    const int64_t few = (k.M + 63) / 64 * k.Z;
+    if (few * ((k.N + 127) / 128) >= kF64Few) {
+      kernel = "occupancy";
+      ring = 3;
+      wpc = 4;
+      tile = 64;
+      tile_n = 128;
+    } else {
+      kernel = "small-tile";
+      tile = few * ((k.N + 63) / 64) >= kF64Fewer ? 64 : 32;
+      ring = tile == 64 ? 4 : 8;
+    }
+  } else if (prec == CQ_FP32 && impl == 1) {
     kernel = "small-tile";
     ring = 8;
     tile = 64;
@@ -3191,7 +3205,7 @@ std::string variant_schedule(int prec, int v) {
   const int n = std::snprintf(buf, sizeof(buf),
                               "{\"kernel\": \"%s\", \"tile\": [%d, %d], \"ring\": %d, "
                               "\"workgroups_per_cu\": %d, \"raster\": \"%s\"}",
-                              kernel, tile, tile, ring, wpc, (v & 1) ? "flipped" : "default");
+                              kernel, tile, tile_n ? tile_n : tile, ring, wpc, (v & 1) ? "flipped" : "default");
   return std::string(buf, (size_t)n);
 }
 
@@ -3212,7 +3226,7 @@ std::string autotune_json() {
                           first ? "" : ", ", pname[k.prec], (long long)k.M, (long long)k.N,
                           (long long)k.K, (long long)k.Z, e.variant);
     s.append(buf, n);
-    s += variant_schedule(k.prec, e.variant);
+    s += variant_schedule(k, e.variant);
     s += ", \"ms\": [";
     bool f2 = true;
     for (int v = 0; v < kMaxVariants; ++v)
