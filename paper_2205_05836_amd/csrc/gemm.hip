@@ -339,11 +339,7 @@ __device__ __forceinline__ void topc_tile(const GemmArgs& g, int64_t z, int64_t 
     return;
   }
   if (n <= kTopcCap) {
-    for (int t = tid; t < n; t += NTHR) {
-      const K k = cand[t];
-      const int r = rank_of(cand, n, k);
-      if (r < C) outk[r] = k;
-    }
+    rank_all<NTHR>(cand, n, C, outk);
     n = n < C ? n : C;
   } else {
     uint64_t live = 0;

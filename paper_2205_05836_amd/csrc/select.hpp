@@ -41,6 +41,34 @@ __device__ inline bool sel_better(const SelKey<T, I>& a, const SelKey<T, I>& b) 
   return a.v > b.v || (a.v == b.v && a.i < b.i);
 }
 
+// Number of keys among S[0..n) (LDS) better than k, shared by L neighbouring
+// lanes that hold the same k (every lane gets the count): each compares with
+// every L-th key, then the partial counts are summed.
+template <int L, typename K>
+__device__ __forceinline__ int rank_shared(const K* S, int n, const K& k) {
+  int r = 0;
+#pragma unroll 4
+  for (int t = (int)(threadIdx.x & (L - 1)); t < n; t += L) {
+    const K a = S[t];
+    r += (int)((a.v > k.v) | ((a.v == k.v) & (a.i < k.i)));
+  }
+#pragma unroll
+  for (int o = 1; o < L; o <<= 1) r += __shfl_xor(r, o, 64);
+  return r;
+}
+
+// The first C of S[0..n) (LDS, distinct keys) to out, best first; every thread
+// of the workgroup calls it.  Sixteen lanes rank a key, so that the usual few
+// dozen keys occupy every wave (one lane a key: 2.9 us of a tile, 1.6 so).
+template <int NTHR, typename K>
+__device__ __forceinline__ void rank_all(const K* S, int n, int C, K* out) {
+  for (int t = (int)threadIdx.x / 16; t < n; t += NTHR / 16) {
+    const K k = S[t];
+    const int r = rank_shared<16>(S, n, k);
+    if ((threadIdx.x & 15) == 0 && r < C) out[r] = k;
+  }
+}
+
 // Number of keys among S[0..n) (LDS) better than k.  Eight keys are loaded
 // before any is compared, and the comparison is branch-free, so the LDS reads
 // overlap instead of each waiting for the one before.
@@ -66,11 +94,12 @@ __device__ __forceinline__ int rank_of(const K* S, int n, const K& k) {
 // (has: it has one, else the worst key); owner: LDS, -1 on entry; other(k, x):
 // key k of lane ^ x.  Ranks are counted among the best keys of kBoundGroups
 // groups of lanes, and among all lanes' only when fewer than C groups have a
-// key: every key is compared with all others through LDS, and
-// ranking 512 lanes took 20 us of a selecting tile's 32.  The
-// coarser bound lets few more keys pass: with C of G groups holding a key at
-// or above it, -G ln(1 - C / G) of evenly spread keys are, 18 for C = 16 and 89
-// for C = 64 of 128 groups.
+// key: every key is compared with all others through LDS, and ranking 512
+// lanes took 20 us of a selecting tile's 32.  The lanes of a group share its
+// ranking: by one lane each it took 5.3 us of a tile's 16.3 (FP64, 512
+// threads), shared 2.4 of 12.3.  The coarser bound lets few more keys pass:
+// with C of G groups holding a key at or above it, -G ln(1 - C / G) of evenly
+// spread keys are, 18 for C = 16 and 89 for C = 64 of 128 groups.
 constexpr int kBoundGroups = 128;
 
 template <typename T, int NTHR, typename K, typename Other>
@@ -86,17 +115,14 @@ __device__ __forceinline__ int bound_owner(K* best, int& owner, const K& mine, b
     k.v = b ? o.v : k.v;
     k.i = b ? o.i : k.i;
   }
-  if ((tid & (G - 1)) == 0) best[tid / G] = k;
-  __syncthreads();
-  // two waves rank the groups (the worst key has the index that no key has)
-  bool ghas = false;
-  if (tid < kBoundGroups) {
-    k = best[tid];
-    ghas = (k.i + 1) != 0;
-  }
-  if (__syncthreads_count(ghas) >= C) {
+  // every lane of a group holds its best key (the worst key has the index that
+  // no key has)
+  const bool ghas = (k.i + 1) != 0, lead = (tid & (G - 1)) == 0;
+  if (lead) best[tid / G] = k;
+  if (__syncthreads_count(ghas & lead) >= C) {
     // distinct keys, distinct ranks
-    if (ghas && rank_of(best, kBoundGroups, k) == C - 1) owner = tid;
+    const int r = rank_shared<G>(best, kBoundGroups, k);
+    if (ghas & lead & (r == C - 1)) owner = tid / G;
   } else {
     best[tid] = mine;
     __syncthreads();
@@ -166,11 +192,7 @@ __device__ __forceinline__ int sel_bound_top(SelShared<T, I, NTHR, CAP>& sh, uin
   __syncthreads();
   const int n = sh.count;
   if (n > CAP) return -1;
-  for (int t = tid; t < n; t += NTHR) {
-    const K k = sh.cand[t];
-    const int r = rank_of(sh.cand, n, k);
-    if (r < C) out[r] = k;
-  }
+  rank_all<NTHR>(sh.cand, n, C, out);
   __syncthreads();
   return n < C ? n : C;
 }
