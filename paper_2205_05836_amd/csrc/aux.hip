@@ -446,6 +446,18 @@ __device__ inline int wave_max_i32(int v) {
   return v;
 }
 
+// The largest v of a wave whose lanes are all active, the same in every lane:
+// lane moves of the vector ALU within rows of 16 lanes, then scalars (a
+// shuffle is an LDS access a step).
+__device__ __forceinline__ int wave_max_full(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xb1, 0xf, 0xf, false));   // lane ^ 1
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4e, 0xf, 0xf, false));   // lane ^ 2
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false));  // mirrored in 8 lanes
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false));  // mirrored in 16
+  return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
 constexpr int kBalanceRounds = 4;
 constexpr int kBalThreads = 1024;
 constexpr int kBalLog = 10;            // log2 kBalThreads
@@ -480,8 +492,11 @@ __device__ inline void balance_offsets(int n_sub, const int* smax, int* goff) {
 // every thread adds its rows' shares, a wave a (subcircuit, position) folds
 // the four digits' rows, a thread a cut makes the step.  Reading the rows from
 // memory and comparing FP64 maxima in every round (below) took 34 us for 1104
-// rows in three subcircuits.  Rows that a round scales past the range of a
-// double count as infinite (no step), or as zero.
+// rows in three subcircuits.  What is left is latency (barriers, LDS lookups):
+// 12.3 us with shuffled maxima, four barriers a round and every subcircuit's
+// first rows on wave 0; 10.2 with lane moves, three barriers, rows spread.
+// Rows that a round scales past the range of a double count as infinite (no
+// step), or as zero.
 constexpr int kBalSmallRows = 8192;
 constexpr int kExpNone = -16384, kExpInf = 16384;
 
@@ -492,12 +507,15 @@ __device__ __forceinline__ void balance_small(const BalanceArgs& b) {
   // zeros past the subcircuit's last (where the digit is 0)
   __shared__ int share[CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS][4];
   __shared__ int smax[CQ_MAX_SUBCIRCUITS], goff[CQ_MAX_SUBCIRCUITS];
-  __shared__ int changed;
+  __shared__ int changed[kBalanceRounds];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the thread's first row of a subcircuit whose rows begin at `base`: small
+  // subcircuits fall to different waves
+  const auto first = [&](int base) { return (tid - base) & (kBalThreads - 1); };
   int base = 0;
   for (int c = 0; c < b.n_sub; ++c) {
     const int rows = 1 << (2 * b.k[c]);
-    for (int l = tid; l < rows; l += kBalThreads) {
+    for (int l = first(base); l < rows; l += kBalThreads) {
       const double x = __longlong_as_double((long long)b.rowmax[c][l]);
       ex[base + l] = (int16_t)(x > 0.0 ? isfinite(x) ? bexp(x) : kExpInf : kExpNone);
     }
@@ -505,6 +523,7 @@ __device__ __forceinline__ void balance_small(const BalanceArgs& b) {
   }
   if (tid < CQ_MAX_SUBCIRCUITS * CQ_MAX_LOCAL_CUTS * 4) (&share[0][0])[tid] = 0;
   if (tid < CQ_MAX_SUBCIRCUITS) smax[tid] = INT_MIN;
+  if (tid < kBalanceRounds) changed[tid] = 0;
   // the cut of this thread, and where its two sides are
   int u = 0, w = 0;
   if (tid < b.K) {
@@ -517,13 +536,12 @@ __device__ __forceinline__ void balance_small(const BalanceArgs& b) {
     for (int q = 0; q < CQ_MAX_LOCAL_CUTS; ++q) e += share[c * CQ_MAX_LOCAL_CUTS + q][(l >> (2 * q)) & 3];
     return e;
   };
+  __syncthreads();
   for (int round = 0; round < kBalanceRounds; ++round) {
-    if (tid == 0) changed = 0;
-    __syncthreads();
     base = 0;
     for (int c = 0; c < b.n_sub; ++c) {
       const int rows = 1 << (2 * b.k[c]);
-      for (int l = tid; l < rows; l += kBalThreads) {
+      for (int l = first(base); l < rows; l += kBalThreads) {
         const int x = ex[base + l];
         int y = x;
         if (x > kExpNone && x < kExpInf) {
@@ -549,9 +567,7 @@ __device__ __forceinline__ void balance_small(const BalanceArgs& b) {
           for (int d = 0; d < 4; ++d) m[d] = max(m[d], (int)cur[l + (d << sh)]);
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-          for (int d = 0; d < 4; ++d) m[d] = max(m[d], __shfl_xor(m[d], o, 64));
+        for (int d = 0; d < 4; ++d) m[d] = wave_max_full(m[d]);
         if (lane < 4) pm[c * CQ_MAX_LOCAL_CUTS + p][lane] = lane == 0 ? m[0] : lane == 1 ? m[1] : lane == 2 ? m[2] : m[3];
       }
       base += 1 << (2 * k);
@@ -575,35 +591,35 @@ __device__ __forceinline__ void balance_small(const BalanceArgs& b) {
         if (e != share[u][d]) {
           share[u][d] = e;
           share[w][d] = -e;
-          changed = 1;
+          changed[round] = 1;
         }
       }
     }
     __syncthreads();
-    const int more = changed;
-    __syncthreads();  // every thread has read the flag before the next round clears it
-    if (!more) break;
+    if (!changed[round]) break;
   }
   // every subcircuit's largest scaled row, and the offsets
   base = 0;
   for (int c = 0; c < b.n_sub; ++c) {
     const int rows = 1 << (2 * b.k[c]);
     int sm = INT_MIN;
-    for (int l = tid; l < rows; l += kBalThreads) {
+    for (int l = first(base); l < rows; l += kBalThreads) {
       const int x = ex[base + l];
       if (x > kExpNone && x < kExpInf) sm = max(sm, x + row_exp(c, l));
     }
-    if (wave * 64 < rows) {
-      sm = wave_max_i32(sm);
-      if (lane == 0 && sm != INT_MIN) atomicMax(&smax[c], sm);
-    }
+    sm = wave_max_full(sm);
+    if (lane == 0 && sm != INT_MIN) atomicMax(&smax[c], sm);
     base += rows;
   }
   __syncthreads();
   if (tid == 0) balance_offsets(b.n_sub, smax, goff);
   __syncthreads();
-  for (int c = 0; c < b.n_sub; ++c)
-    for (int l = tid; l < 1 << (2 * b.k[c]); l += kBalThreads) b.rexp[c][l] = row_exp(c, l) + goff[c];
+  base = 0;
+  for (int c = 0; c < b.n_sub; ++c) {
+    const int rows = 1 << (2 * b.k[c]);
+    for (int l = first(base); l < rows; l += kBalThreads) b.rexp[c][l] = row_exp(c, l) + goff[c];
+    base += rows;
+  }
 }
 
 // One workgroup: per (subcircuit, digit position, digit) the largest row
