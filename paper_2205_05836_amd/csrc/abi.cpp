@@ -518,6 +518,14 @@ struct DDSel {  // sizes of the top-C selection scratch
   int64_t cand_cap = 0, seg_a = 0, seg_b = 0, tiles = 0;
 };
 
+// Whether the selecting GEMM's tiles are pruned: the warm-up evaluates up to
+// kDDMaxC tiles (those with the largest bounds) to set the threshold, so with
+// no more tiles than that it would evaluate all of them before the main pass
+// does (three 5-bit subcircuits, 8 tiles: bounds, warm-up, threshold and
+// compaction took 60 of a recursion's 147 us).  Instances advanced together
+// share their launches, so the largest sizes among them decide for all.
+bool dd_prunes(const DDSel& s) { return s.tiles > kDDMaxC; }
+
 struct DDInstancePlan {
   CutMap cm;
   std::vector<DDSub> s0;
@@ -528,6 +536,7 @@ struct DDInstancePlan {
   int64_t max_count = 0, bins_bytes = 0;
   std::vector<int64_t> step_max;  // grid bound per step: tiles or elements
   DDSel sel;                      // this instance's own selection sizes
+  bool prune = false;             // the selecting GEMM's tiles are pruned (dd_prunes)
   // region layout (dd_layout): offsets, and the selection sizes laid out
   int64_t cand_off = 0, cand_cap = 0, stage_off = 0;
   int64_t seg_a = 0, seg_b = 0, bound_a_off = 0, bound_b_off = 0, bound_u_off = 0, list_off = 0;
@@ -732,17 +741,10 @@ cq_status dd_plan_instance(const cq_dd_instance& in, const cq_dd_params& p, bool
   } else {
     D.sel.cand_cap = topk_indirect_capacity(D.max_count, C_max);
   }
+  D.prune = dd_prunes(D.sel);
   dd_layout(D, D.sel);
   return CQ_OK;
 }
-
-// Whether the selecting GEMM's tiles are pruned: the warm-up evaluates up to
-// kDDMaxC tiles (those with the largest bounds) to set the threshold, so with
-// no more tiles than that it would evaluate all of them before the main pass
-// does (three 5-bit subcircuits, 8 tiles: bounds, warm-up, threshold and
-// compaction took 60 of a recursion's 147 us).  The same for every
-// member of a lockstep group, whose selection sizes are shared.
-bool dd_prunes(const DDInstancePlan& D) { return D.sel.tiles > kDDMaxC; }
 
 DType tensor_dtype(const Plan& plan, int t, cq_precision prec) {
   const TensorRef& T = plan.tensors[t];
@@ -893,6 +895,7 @@ cq_status dd_plan_all(int32_t n_inst, const cq_dd_instance* inst, const cq_dd_pa
         s.tiles = std::max(s.tiles, o.tiles);
       }
       for (int i : G) {
+        plans[i].prune = dd_prunes(s);
         dd_layout(plans[i], s);
         region = std::max(region, plans[i].big);
         B.slot_of[i] = k++;
@@ -986,7 +989,7 @@ void dd_program(const DDInstancePlan& D, const cq_dd_instance& in, const cq_dd_p
     }
   }
   P.topc_step = D.topc_step;
-  P.prune = dd_prunes(D) ? 1 : 0;
+  P.prune = D.prune ? 1 : 0;
   P.cand_v = reinterpret_cast<double*>(ws + D.cand_off);
   P.cand_i = reinterpret_cast<uint64_t*>(ws + D.cand_off + D.cand_cap * 8);
   if (D.topc_step >= 0) {
@@ -1119,7 +1122,7 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
     if (s.is_gemm && (int)si == D.topc_step) {
       // fused top-C with tile pruning (see launch_tile_bounds)
       const int64_t tiles = step_max[si];
-      const bool prune = dd_prunes(D);
+      const bool prune = D.prune;  // the same for every member
       e = hipSuccess;
       if (prune) e = launch_tile_bounds(&lv->gemm[si], tensor_dtype(D.plan, s.g.a, prec), is_f16(prec),
                              reinterpret_cast<float*>((ws + D.bound_a_off)),

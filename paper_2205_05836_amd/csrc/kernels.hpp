@@ -390,7 +390,7 @@ struct DDProgram {
   double* Rs[CQ_MAX_SUBCIRCUITS];            // their row sums
   int32_t prep_dst[CQ_MAX_SUBCIRCUITS];      // tensor receiving the converted copy, or -1
   int32_t topc_step;                         // GEMM step that selects top-C instead of storing, or -1
-  int32_t prune;                             // its tiles are pruned (dd_prunes)
+  int32_t prune;                             // its tiles are pruned (the same for instances advanced together)
   double* cand_v;                            // its candidate buffers
   uint64_t* cand_i;
   // tile pruning of that GEMM (see launch_tile_bounds)

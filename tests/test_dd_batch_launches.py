@@ -1,0 +1,80 @@
+"""A batch of dynamic-definition instances that advance together: what the
+host launches for all of them fits what every member's device program says.
+Members share a step sequence but not their sizes (host only, launches are
+recorded instead of run)."""
+import json
+
+import pytest
+
+import launch_recorder
+from workloads import synthetic as syn
+
+# active outputs of two subcircuits with two cuts between them: 2^13, 2^20
+# (64 output tiles, up to which nothing is pruned) and 2^21 bins (128 tiles)
+SIZES = {"one tile": ([7, 7], [6, 7]), "64 tiles": ([11, 11], [10, 10]), "128 tiles": ([11, 12], [10, 11])}
+
+SCRIPT = """
+import itertools
+def batch(shapes, prec, R):
+    subs = [api._Subs(cm) for cm, _ in shapes]
+    arr = (_lib.cq_dd_instance * len(shapes))()
+    keep, base = [], 1 << 40
+    for a, s, (cm, M) in zip(arr, subs, shapes):
+        n = len(cm)
+        act = [(1 << m) - 1 for m in M]
+        mer = [((1 << o) - 1) & ~x for o, x in zip(s.n_out, act)]
+        u64 = C.c_uint64 * n
+        f = [(C.c_void_p * n)(*[base + (i << 36) for i in range(n)]), u64(*act), u64(*mer), u64(), u64(),
+             (C.c_int32 * n)(*M)]
+        keep += f
+        a.n_sub, a.subs = n, s.ptr()
+        a.entries, a.active, a.merged, a.fixed, a.fixed_vals, a.max_active = f
+        base += 1 << 39
+    par = _lib.cq_dd_params(_lib.PRECISION[prec], R, _lib.DD_LAUNCH["direct"], 1, None, None)
+    need = C.c_size_t()
+    assert L.cq_dd_workspace_size(len(shapes), arr, C.byref(par), 0, C.byref(need)) == 0
+    recs = (_lib.cq_dd_record * (len(shapes) * R))()
+    done = (C.c_int32 * len(shapes))()
+    events()
+    st = L.cq_reconstruct_dd(len(shapes), arr, C.byref(par), recs, None, done, C.c_void_p(1 << 50), need, None)
+    assert st == 0, L.cq_last_error()
+    return events()
+out = [batch(shapes, prec, R) for shapes, prec, R in json.loads(CASES)]
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return launch_recorder.build(tmp_path_factory.mktemp("recorder"))
+
+
+def record(recorder, cases):
+    return launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + SCRIPT)
+
+
+def shape(name):
+    ns, M = SIZES[name]
+    return syn.chain_cutmap([2], ns), M
+
+
+def kernels(events):
+    return [e["kernel"] for e in events if "kernel" in e]
+
+
+def programs(events):
+    return next(e["programs"] for e in events if "programs" in e)
+
+
+ORDERS = [["one tile"], ["64 tiles"], ["128 tiles"], ["one tile", "128 tiles"], ["128 tiles", "one tile"],
+          ["64 tiles", "128 tiles", "one tile"], ["one tile", "64 tiles"]]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16_split"])
+def test_members_are_pruned_together(recorder, prec):
+    """Tiles are pruned for all members or for none, as the largest asks for,
+    and the launches that pruning needs are there exactly then."""
+    for names, ev in zip(ORDERS, record(recorder, [([shape(n) for n in names], prec, 4) for names in ORDERS])):
+        prune = [p["prune"] for p in programs(ev)]
+        assert prune == [int("128 tiles" in names)] * len(names), names
+        for part in ("tile_bound_kernel", "tile_warm_kernel", "warm_tau_kernel", "tile_compact_kernel"):
+            assert any(part in k for k in kernels(ev)) == bool(prune[0]), (names, part)
