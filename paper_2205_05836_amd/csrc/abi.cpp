@@ -1159,8 +1159,8 @@ cq_status dd_enqueue_level(const std::vector<const DDInstancePlan*>& G, const cq
     }
   }
   if (D.topc_step >= 0) {
-    // unpruned: one workgroup selects straight from the candidates
-    const bool stage = D.sel.cand_cap > kTopcDirect;
+    // few candidates (the most any member can hold): one workgroup selects straight from them
+    const bool stage = D.cand_cap > kTopcDirect;
     e = launch_topk_candidates(reinterpret_cast<const double*>(ws + D.cand_off),
                                reinterpret_cast<const uint64_t*>(ws + D.cand_off + D.cand_cap * 8),
                                reinterpret_cast<const int64_t*>(&st->topc_count), &st->C,

@@ -78,3 +78,11 @@ def test_members_are_pruned_together(recorder, prec):
         assert prune == [int("128 tiles" in names)] * len(names), names
         for part in ("tile_bound_kernel", "tile_warm_kernel", "warm_tau_kernel", "tile_compact_kernel"):
             assert any(part in k for k in kernels(ev)) == bool(prune[0]), (names, part)
+
+
+def test_selection_is_staged_for_the_largest_candidate_list(recorder):
+    """One workgroup selects from at most 4096 candidates; a member that can
+    hold more (128 tiles of 64 keys) has them staged, whatever its place."""
+    for names, ev in zip(ORDERS, record(recorder, [([shape(n) for n in names], "fp32", 16) for names in ORDERS])):
+        staged = any("topk_kernel" in k for k in kernels(ev))
+        assert staged == ("128 tiles" in names), names

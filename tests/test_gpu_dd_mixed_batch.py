@@ -55,3 +55,11 @@ def check(kind, R, prec, launch, order):
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16_split", "fp16"])
 def test_records_follow_no_other_member(prec, launch, order):
     check("integer", 4, prec, launch, order)
+
+
+@pytest.mark.parametrize("order", [(0, 2), (2, 0), (1, 2, 0)])
+@pytest.mark.parametrize("kind", ["integer", "equal", "zero"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16_split"])
+def test_most_candidates(prec, kind, order):
+    """With ties everywhere the largest member holds 8192 candidates."""
+    check(kind, 16, prec, "graph", order)
