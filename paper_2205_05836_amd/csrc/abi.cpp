@@ -753,15 +753,18 @@ DType tensor_dtype(const Plan& plan, int t, cq_precision prec) {
   return work_dtype(prec);
 }
 
-// Instances whose launches can be shared: the same subcircuit count and the
-// same step sequence with the same operand formats (their sizes may differ;
-// the launches are sized for the largest).
+// Instances whose launches can be shared: the same subcircuit count, the same
+// preparation of the operands (the balance needs a cut) and the same step
+// sequence with the same operand formats (their sizes may differ; the
+// launches are sized for the largest).
 std::string dd_signature(const DDInstancePlan& D, cq_precision prec) {
   std::string k;
   auto put = [&](int v) { k.append(reinterpret_cast<const char*>(&v), sizeof v); };
   put(D.cm.n_sub);
   put((int)D.plan.steps.size());
   put(D.topc_step);
+  put(D.lbal ? 1 : 0);
+  put(D.cscale ? 1 : 0);
   for (const Step& s : D.plan.steps) {
     put(s.is_gemm ? 1 : 0);
     if (s.is_gemm) {

@@ -86,3 +86,23 @@ def test_selection_is_staged_for_the_largest_candidate_list(recorder):
     for names, ev in zip(ORDERS, record(recorder, [([shape(n) for n in names], "fp32", 16) for names in ORDERS])):
         staged = any("topk_kernel" in k for k in kernels(ev))
         assert staged == ("128 tiles" in names), names
+
+
+def uncut(ns, M):
+    return syn.chain_cutmap([0], ns), M
+
+
+@pytest.mark.parametrize("prec", ["bf16", "bf16_split", "fp16", "fp16_split"])
+def test_members_take_the_same_preparation(recorder, prec):
+    """Label balance needs a cut and column scaling an output axis a
+    subcircuit: members launched together agree on both, and one that is
+    balanced finds its balance launched, whichever comes first."""
+    cut, bare = shape("one tile"), uncut([7, 7], [6, 7])
+    for ev in record(recorder, [([bare, cut], prec, 4), ([cut, bare], prec, 4), ([bare], prec, 4), ([cut], prec, 4)]):
+        progs = programs(ev)
+        for flag, part in (("balance", "balance_ind_kernel"), ("cscale", "colmax_ind_kernel")):
+            launches = sum(part in k for k in kernels(ev))
+            groups = sum("dd_init_kernel" in k for k in kernels(ev))
+            sets = {p[flag] for p in progs}
+            assert launches == (groups if sets == {1} else 0 if sets == {0} else 1), (flag, progs)
+            assert len(sets) <= groups

@@ -63,3 +63,29 @@ def test_records_follow_no_other_member(prec, launch, order):
 def test_most_candidates(prec, kind, order):
     """With ties everywhere the largest member holds 8192 candidates."""
     check(kind, 16, prec, "graph", order)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16", "fp16_split"])
+@pytest.mark.parametrize("cut_first", [False, True])
+def test_with_and_without_cuts(prec, cut_first):
+    """An instance without cuts is not balanced; one with cuts is, whichever
+    comes first.  The workspace starts as bytes of ones, so an exponent that
+    no launch has written would show."""
+    import paper_2205_05836_amd as m
+    print(f"mixed batch {prec} cut_first={cut_first}", flush=True)
+    rng = np.random.default_rng(3)
+    insts = []
+    for bonds in ([0], [2]):
+        cm, ks = syn.chain_cutmap(bonds, [6, 7]), syn.chain_ks(bonds, 2)
+        st = dd.initial_states(cm, [4, 4])
+        insts.append(dict(subs=cm, entries=[torch.from_numpy(syn.integer_entries(rng, k, n, lo=-2, hi=3)).to(DEV)
+                                            for k, n in zip(ks, [6, 7])],
+                          active=[sum(1 << int(i) for i in s.active) for s in st],
+                          merged=[sum(1 << int(i) for i in s.merged) for s in st],
+                          fixed=[0, 0], fixed_vals=[0, 0], max_active=[4, 4]))
+    if cut_first:
+        insts.reverse()
+    alone = [m.cq_reconstruct_dd([x], prec, 3)[0][0] for x in insts]
+    ws = torch.full((m.cq_dd_workspace_size(insts, prec, 3),), 255, dtype=torch.uint8, device=DEV)
+    recs, _ = m.cq_reconstruct_dd(insts, prec, 3, workspace=ws)
+    assert [[fields(r) for r in rec] for rec in recs] == [[fields(r) for r in rec] for rec in alone]
