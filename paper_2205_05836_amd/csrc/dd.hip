@@ -901,7 +901,9 @@ __device__ inline void setup_body(const DDProgram* P, DDState* st, DDState* gst,
   const int tid = threadIdx.x;
   const int ns = P->n_sub, nsteps = P->n_steps;
   const int step = tid - 64;  // the step this thread describes, if in range
-  // stopped, or past this instance's last recursion of the call: nothing runs
+  // stopped, or past this instance's last recursion of the call: nothing runs.
+  // The GEMM descriptors are written whole: a resumed instance may stop here
+  // before any recursion has, and the kernels read more than the tile count.
   if (st->stop || P->r0 + r >= P->r_end) {
     if (tid < ns) {
       lv->merge[tid].outputs = 0;
@@ -909,14 +911,18 @@ __device__ inline void setup_body(const DDProgram* P, DDState* st, DDState* gst,
       lv->prep[tid].n = 0;
     }
     if (step >= 0 && step < nsteps) {
-      lv->gemm[step].tiles = 0;
+      lv->gemm[step] = GemmArgs{};
       lv->perm[step].total = 0;
     }
     if (tid == 0) {
+      lv->topc_warm = GemmArgs{};
       lv->refine[0].nbins = 0;
       lv->refine[1].nbins = 0;
       st->C = 0;
       st->count = 0;
+      st->n_tiles = 0;
+      st->warm_count = 0;
+      st->list_count = 0;
     }
     return;
   }

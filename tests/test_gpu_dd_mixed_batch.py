@@ -89,3 +89,24 @@ def test_with_and_without_cuts(prec, cut_first):
     ws = torch.full((m.cq_dd_workspace_size(insts, prec, 3),), 255, dtype=torch.uint8, device=DEV)
     recs, _ = m.cq_reconstruct_dd(insts, prec, 3, workspace=ws)
     assert [[fields(r) for r in rec] for rec in recs] == [[fields(r) for r in rec] for rec in alone]
+
+
+@pytest.mark.parametrize("order", [(0, 2), (2, 0)])
+@pytest.mark.parametrize("launch", ["graph", "direct"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16_split"])
+def test_resumed_at_different_recursions(prec, launch, order):
+    """Members resume at recursions of their own; those at their end are
+    launched along with the others, on a workspace of bytes of ones, and run
+    nothing."""
+    import paper_2205_05836_amd as m
+    print(f"resume {prec} {launch} {order}", flush=True)
+    R, insts = 5, [instance("integer", *SIZES[q]) for q in order]
+    full = [m.cq_reconstruct_dd([x], prec, R, launch=launch) for x in insts]
+    for cut in ((5, 1), (1, 5), (4, 1), (1, 4)):
+        cks = [m.cq_reconstruct_dd([x], prec, R, launch=launch, recursions=c, checkpoint=True)[2]
+               for x, c in zip(insts, cut)]
+        ws = torch.full((m.cq_dd_workspace_size(insts, prec, R),), 255, dtype=torch.uint8, device=DEV)
+        recs, done = m.cq_reconstruct_dd(insts, prec, R, launch=launch, resume=b"".join(cks), workspace=ws)
+        for got, n, (want, total), c in zip(recs, done, full, cut):
+            assert n == max(total[0] - c, 0)
+            assert [fields(r) for r in got] == [fields(r) for r in want[0][c:]]
