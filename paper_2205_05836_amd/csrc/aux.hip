@@ -1522,10 +1522,11 @@ constexpr int kPermBigBits = 22;
 
 // The tile map of a permutation of `bits` index bits in tiles of 2^tb: false
 // when it is not one (a source stride that is no power of two, or that two
-// bits share) or is smaller than a tile, which the generic kernel takes.  The
-// tile takes source and destination bits in turn from the lowest.
+// bits share), is smaller than a tile, or has more tiles than a launch has
+// workgroups of 256 (fewer than 2^32 threads), which the generic kernel takes.
+// The tile takes source and destination bits in turn from the lowest.
 bool perm_tile_map(const PermLaunch& p, int bits, int tb, PermTileMap& m) {
-  if (bits < tb || bits > kMaxPermAxes || bits - tb > 30) return false;
+  if (bits < tb || bits > kMaxPermAxes || bits - tb > 23) return false;
   int src_of[64], dst_of[64];  // source bit of a destination bit, and back (-1: none)
   std::fill(dst_of, dst_of + 64, -1);
   int b = 0;
