@@ -500,7 +500,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_combine_kernel(const double2* _
     }
   }
   __syncthreads();
-  const int64_t t = (int64_t)blockIdx.x * kSvThreads + threadIdx.x;
+  const int64_t t = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * kSvThreads + threadIdx.x;
   if (t >= (int64_t)1 << (A.w - A.o)) return;
   int64_t x0 = t;  // around the measured bits, which ascend from the last slot to the first
   for (int u = A.o - 1; u >= 0; --u)
@@ -931,11 +931,13 @@ hipError_t run_gates(GateSet s, double2* psi, double* probs, const std::vector<i
 
 template <int R, int O>
 void launch_combine(const CombineArgs& A, const double2* psi, double* probs, hipStream_t stream) {
-  const int64_t nx = (int64_t)1 << (A.w - A.o);
+  const int64_t nx = (((int64_t)1 << (A.w - A.o)) + kSvThreads - 1) / kSvThreads;
   unsigned ny = 1u << (2 * (A.r - R));
   for (int u = 0; u < A.o - O; ++u) ny *= 6;
-  hipLaunchKernelGGL((sv_combine_kernel<R, O>), dim3((unsigned)((nx + kSvThreads - 1) / kSvThreads), ny),
-                     dim3(kSvThreads), 0, stream, psi, probs, A);
+  // x and z number the columns: a dimension holds fewer than 2^32 threads
+  const unsigned nz = nx > 1 << 23 ? (unsigned)(nx >> 23) : 1u;
+  hipLaunchKernelGGL((sv_combine_kernel<R, O>), dim3((unsigned)(nx / nz), ny, nz), dim3(kSvThreads), 0, stream, psi,
+                     probs, A);
 }
 
 hipError_t combine(const SubInfo& si, const double2* psi, double* probs, hipStream_t stream) {

@@ -35,3 +35,35 @@ def test_permuted_full_definition(recorder, outs):
         assert any("permute" in e["kernel"] for e in ev)
         assert [e for e in ev if not e["ok"]] == [], prec
         assert status == 0, prec
+
+
+VARIANTS = """
+def variants(sub, states):
+    s = api._Subs([sub])
+    gates, n = api._gates([("u", q, [[0.6, 0.8], [0.8, -0.6]]) for q in range(sub[0])])
+    events()
+    st = L.cq_variant_probabilities(s.ptr(), gates, n, C.c_void_p(1 << 50), C.c_void_p(1 << 51), states << (sub[0] + 4),
+                                    None)
+    return [st, events()]
+def simulate(n):
+    gates, cnt = api._gates([("u", q, [[0.6, 0.8], [0.8, -0.6]]) for q in range(n)])
+    events()
+    st = L.cq_simulate_probabilities(n, gates, cnt, C.c_void_p(1 << 50), C.c_void_p(1 << 51), 1 << (n + 4), None)
+    return [st, events()]
+out = [variants(*c) for c in json.loads(CASES)] + [simulate(n) for n in range(32, 35)]
+"""
+
+
+def test_widest_registers(recorder):
+    """32 slots with and without cut ends, one state of workspace and enough;
+    34 qubits."""
+    cases = []
+    for w in (31, 32):
+        for r, o in ((0, 0), (1, 0), (0, 1), (2, 2), (0, 8), (8, 0), (5, 3)):
+            init = [c for c in range(r)] + [-1] * (w - r)
+            meas = [-1] * (w - o) + [r + c for c in range(o)]
+            cases += [((w, init, meas), 1), ((w, init, meas), 1 << r)]
+    for c, (status, ev) in zip(cases + [(n, 1) for n in range(32, 35)],
+                               launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + VARIANTS)):
+        assert ev and [e for e in ev if not e["ok"]] == [], c
+        assert status == 0, c
