@@ -2992,12 +2992,20 @@ int variant_count(cq_precision prec) {
   return prec == CQ_FP64 ? 2 : kMaxVariants;
 }
 
+// whether the output's 64 x 64 tiles, a workgroup of 256 each, fit a launch
+// (fewer than 2^32 threads)
+bool small_tiles_fit(const GemmArgs& a) {
+  const int64_t z = a.tiles / (a.tilesM * a.tilesN);
+  return (a.M + 63) / 64 * ((a.N + 63) / 64) * z < (int64_t)1 << 24;
+}
+
 // whether variant v has a kernel of its own for this launch (else it would
 // repeat variant v & 1)
 bool variant_applies(cq_precision prec, const GemmArgs& a, DType tc, int v) {
   const int impl = v >> 1;
   if (impl == 0) return true;
   if (v >= variant_count(prec)) return false;
+  if (impl == (prec == CQ_FP32 ? 1 : 2) && !small_tiles_fit(a)) return false;
   if (prec == CQ_FP32) return impl >= 4 ? f32t_ok(a) : impl == 1 ? f32s_ok(a) : impl == 3 && f32p_ok(a);
   if (impl == 4 || impl == 5) return h16t_ok(a, tc);
   return impl == 3 ? h16p_ok(a, tc) : h16_async_ok(a, tc);

@@ -37,6 +37,18 @@ def test_permuted_full_definition(recorder, outs):
         assert status == 0, prec
 
 
+@pytest.mark.parametrize("outs", [[18, 18], [12, 12, 12], [7, 29], [3, 30]])
+def test_tuned_full_definition(recorder, outs):
+    """The autotuner tries only variants whose launch is possible."""
+    n = sum(outs)
+    cases = [(syn.chain_cutmap([1] * (len(outs) - 1), outs), list(range(n)), prec)
+             for prec in ("fp32", "bf16", "bf16_split", "fp16_split")]
+    script = f"L.cq_autotune_enable(1)\nCASES = {json.dumps(cases)!r}\n" + FD
+    for (_, _, prec), (status, ev) in zip(cases, launch_recorder.run(recorder, script)):
+        assert [e for e in ev if not e["ok"]] == [], prec
+        assert status == 0, prec
+
+
 VARIANTS = """
 def variants(sub, states):
     s = api._Subs([sub])
