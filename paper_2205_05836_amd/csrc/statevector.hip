@@ -19,26 +19,19 @@
 
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <string>
 #include <vector>
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "svplan.hpp"
 
 namespace cq {
 
 namespace {
 
-constexpr int kMinTileBits = 11;  // narrower registers take the LDS kernel
-constexpr int kMaxTileBits = 12;
-constexpr int kMaxOps = 160;  // gates of a pass
-constexpr int kMaxU = 36;     // one-qubit unitaries among them
 constexpr int kSvThreads = 256;
 constexpr int kLdsTile = 1 << (kMinTileBits - 1);
-
-// Forms of a one-qubit unitary (normalize).
-enum Form { kGeneral = 0, kNormal = 1 };
 
 // A gate of a pass in one word (whole words, so that uniform reads of the
 // arguments are aligned scalar loads): bits 0-5 CQ_GATE_U or CQ_GATE_CZ, 6-7
@@ -634,191 +627,6 @@ cq_status check_gates(int32_t n, const cq_gate* gates, int32_t n_gates) {
         if (!std::isfinite(v)) return fail(CQ_ERR_ARG, "non-finite gate matrix");
   }
   return CQ_OK;
-}
-
-// One pass of a plan: its gates (indices into the gate list, circuit order),
-// the qubits they act on as index bits, and the bits touched before and
-// after it.
-struct Pass {
-  std::vector<int> gates;
-  uint64_t mask = 0, before = 0, after = 0;
-};
-
-struct GateSet {
-  int n = 0;
-  std::vector<cq_gate> g;
-  std::vector<uint64_t> mask;
-  std::vector<int> form;  // Form of each one-qubit unitary
-  double weight = 1.0;    // |factor|^2 that the final amplitudes lack
-};
-
-uint64_t gate_mask(int n, const cq_gate& g) {
-  return (1ull << (n - 1 - g.q0)) | (g.kind == CQ_GATE_CZ ? 1ull << (n - 1 - g.q1) : 0ull);
-}
-
-// The gates that matter to probabilities: a CZ none of whose qubits sees a
-// later one-qubit gate (of the list, or of the rotations on `rotated`, index
-// bits) commutes to the end, where it only changes phases.
-GateSet gate_set(int n, const cq_gate* gates, int n_gates, uint64_t rotated) {
-  GateSet s;
-  s.n = n;
-  uint64_t live = rotated;
-  std::vector<int> keep;
-  for (int i = n_gates - 1; i >= 0; --i) {
-    const uint64_t m = gate_mask(n, gates[i]);
-    if (gates[i].kind == CQ_GATE_U) live |= m;
-    else if ((m & live) == 0) continue;
-    keep.push_back(i);
-  }
-  for (auto it = keep.rbegin(); it != keep.rend(); ++it) {
-    s.g.push_back(gates[*it]);
-    s.mask.push_back(gate_mask(n, gates[*it]));
-  }
-  return s;
-}
-
-// Rewrites the unitaries so that most cost four FMA an amplitude instead of
-// eight: U = diag(d0, d1) [1, a; b, 1].  The diagonal commutes with the CZs
-// behind the gate and is multiplied into the columns of the next unitary on
-// its qubit.  A qubit's last unitary stays general, or, where only
-// probabilities are asked for (`probs`) and |d0| = |d1| to rounding (as for
-// every unitary matrix), leaves |d0|^2 to the final weight.  The sums are those
-// of the general form over a common factor, so they round alike.  What is
-// stored meanwhile is the true amplitude over the factors held back: those are
-// kept within 2^-12 .. 2^12 a qubit (2^408 over 34 qubits) by a general gate,
-// which also takes what has no such form or a diagonal below a 16th of the
-// entries beside it.
-void normalize(GateSet& s, bool probs) {
-  typedef long double real;  // the factors and ratios are rounded to double once
-  typedef std::complex<real> cx;
-  std::vector<cx> d0(s.n, 1.0), d1(s.n, 1.0);
-  std::vector<int> last(s.n, -1);
-  for (size_t i = 0; i < s.g.size(); ++i)
-    if (s.g[i].kind == CQ_GATE_U) last[s.g[i].q0] = (int)i;
-  s.form.assign(s.g.size(), kGeneral);
-  if (s.n < kMinTileBits) return;
-  const auto fits = [](real pivot, real other) {  // false for NaN
-    return pivot >= (real)1 / 4096 && pivot <= (real)4096 && other <= 16 * pivot;
-  };
-  for (size_t i = 0; i < s.g.size(); ++i) {
-    cq_gate& g = s.g[i];
-    if (g.kind != CQ_GATE_U) continue;
-    const int q = g.q0;
-    cx u[4];
-    for (int c = 0; c < 4; ++c) u[c] = cx(g.u[2 * c], g.u[2 * c + 1]) * ((c & 1) ? d1[q] : d0[q]);
-    d0[q] = d1[q] = 1.0;
-    bool normal = fits(std::abs(u[0]), std::abs(u[1])) && fits(std::abs(u[3]), std::abs(u[2]));
-    if (normal && (int)i == last[q]) {
-      const real n0 = std::norm(u[0]), n1 = std::norm(u[3]);
-      normal = probs && std::abs(n0 - n1) <= 4e-16L * n0;
-      if (normal) s.weight *= (double)((n0 + n1) / 2);
-    }
-    if (normal) {
-      s.form[i] = kNormal;
-      d0[q] = u[0];
-      d1[q] = u[3];
-      u[0] = u[1] / d0[q];
-      u[1] = u[2] / d1[q];
-    }
-    for (int c = 0; c < (normal ? 2 : 4); ++c) {
-      g.u[2 * c] = (double)u[c].real();
-      g.u[2 * c + 1] = (double)u[c].imag();
-    }
-  }
-}
-
-// How a plan is laid out: tile bits, the lowest index bits every tile holds
-// (gathers then read runs of 2^low amplitudes), and how many qubits join the
-// allowed set when no gate inside it can run.
-struct PlanShape {
-  int tile = 0, low = 0, grow = 0;
-};
-
-// Passes for one shape.  A pass takes, in circuit order, every gate inside the
-// allowed qubits that fits the tile and shares no qubit with an earlier gate
-// left for a later pass.  With `track` the state starts as a basis string and
-// the allowed qubits start as the lowest `tile` index bits and grow, lowest
-// first, only when none of their gates can run: while t qubits are touched a
-// pass moves 2^t amplitudes.  Returns the modelled time in microseconds, or
-// anything above `limit` once that is passed.  The model, from traces: 3.5 us
-// a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.33 ms for
-// every one-qubit gate on 2^30 amplitudes, no less than the serial time of
-// those gates in one tile (0.8 us each with 11 bits, 1.4 us with 12).
-double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int states, double limit,
-                   std::vector<Pass>& out) {
-  const int n = s.n;
-  const uint64_t full = (1ull << n) - 1;
-  const uint64_t low = (1ull << std::min(n, sh.low)) - 1;
-  uint64_t allowed = track ? (1ull << std::min(n, sh.tile)) - 1 : full, touched = track ? 0 : full;
-  std::vector<int> rest(s.g.size()), left;
-  for (size_t i = 0; i < rest.size(); ++i) rest[i] = (int)i;
-  out.clear();
-  double us = 0.0;
-  while (!rest.empty()) {
-    Pass p;
-    uint64_t blocked = 0, cur = low;
-    int nu = 0;
-    left.clear();
-    for (size_t q = 0; q < rest.size(); ++q) {
-      const int i = rest[q];
-      const uint64_t m = s.mask[i];
-      const int is_u = s.g[i].kind == CQ_GATE_U;
-      if ((m & (blocked | ~allowed)) == 0 && (int)p.gates.size() < kMaxOps && nu + is_u <= kMaxU &&
-          __builtin_popcountll(cur | m) <= sh.tile) {
-        p.gates.push_back(i);
-        p.mask |= m;
-        cur |= m;
-        nu += is_u;
-      } else {
-        blocked |= m;
-        left.push_back(i);
-        if ((allowed & ~blocked) == 0) {  // nothing after it can run
-          left.insert(left.end(), rest.begin() + q + 1, rest.end());
-          break;
-        }
-      }
-    }
-    if (p.gates.empty()) {
-      for (int a = 0; a < sh.grow && allowed != full; ++a) allowed |= allowed + 1;  // the lowest bit not allowed yet
-      continue;
-    }
-    p.before = touched;
-    touched |= p.mask;
-    p.after = touched;
-    rest.swap(left);
-    const double before = out.empty() && track ? 0.0 : std::ldexp(16.0, __builtin_popcountll(p.before));
-    const double after = std::ldexp(rest.empty() ? 8.0 : 16.0, rest.empty() ? n : __builtin_popcountll(p.after));
-    const double work = nu * std::max(std::ldexp(3.1e-7 * states, __builtin_popcountll(p.after)),
-                                      sh.tile <= 11 ? 0.8 : 1.4);
-    us += 3.5 + states * (before + after) / 4.4e6 + work;
-    out.push_back(std::move(p));
-    if (us > limit) break;
-  }
-  return us;
-}
-
-// The cheapest plan by the model over a few shapes.  Wider tiles mean fewer
-// passes; growing the allowed set by several qubits at a time merges passes
-// that one at a time would leave nearly empty; runs of 8 amplitudes (128
-// bytes, one line) leave a tile one bit more than runs of 16.  Below 18
-// qubits launches decide, so only the extreme shapes are tried there.
-PlanShape best_plan(const GateSet& s, bool track, int states, std::vector<Pass>& out) {
-  PlanShape best;
-  double least = 1e300;
-  std::vector<Pass> cand;
-  for (int tile = std::min(s.n, kMaxTileBits); tile >= std::min(s.n, kMinTileBits); --tile)
-    for (int low = 4; low >= 3; --low)
-      for (int grow : {s.n, 6, 4, 3, 2, 1}) {
-        if (grow != s.n && (!track || s.n < 18)) continue;
-        const PlanShape sh{tile, low, grow};
-        const double us = plan_passes(s, sh, track, states, least, cand);
-        if (us < least) {
-          least = us;
-          best = sh;
-          out.swap(cand);
-        }
-      }
-  return best;
 }
 
 TileGroup tile_group(const GateSet& s, const PlanShape& sh, const Pass& pass, int mode) {
