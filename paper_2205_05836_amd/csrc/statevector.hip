@@ -413,6 +413,7 @@ struct CombineArgs {
   int32_t w, r, o;
   int32_t vec;  // the last measured slot is index bit 0 and probs is 16-byte aligned
   int64_t bstride;
+  double weight;  // of every |amplitude|^2
   uint32_t meas_bit[CQ_MAX_LOCAL_CUTS];  // index bit of measured slot u
 };
 
@@ -444,7 +445,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_combine_kernel(const double2* _
   const int ro = A.r - R, oo = A.o - O;
   int64_t dst = 0, jo = 0, bo = 0;
   int nt = 0;
-  double outer_scale = 1.0;
+  double outer_scale = A.weight;
   {
     unsigned y = blockIdx.y;
     const int q = threadIdx.x;
@@ -675,7 +676,7 @@ TileGroup tile_group(const GateSet& s, const PlanShape& sh, const Pass& pass, in
       else G.fixed |= 1ull << b;
     }
   G.nouter = no;
-  G.weight = s.weight;
+  G.weight = (double)s.weight;
   G.nops = (int)pass.gates.size();
   int nu = 0;
   for (int j = 0; j < G.nops; ++j) {
@@ -704,13 +705,13 @@ hipError_t launch_tiles(const TileGroup& G, double2* psi, double* probs, unsigne
   return hipGetLastError();
 }
 
-// Applies the gates to `states` states of a batch.  With init_bits each starts
+// Applies the (normalised) gates to `states` states of a batch.  With init_bits each starts
 // as a basis string (see TileGroup) that the first pass generates; without,
 // as what psi holds.  With probs (one state) the last pass writes
-// |amplitude|^2 there; else it leaves every amplitude in psi.
-hipError_t run_gates(GateSet s, double2* psi, double* probs, const std::vector<int>* init_bits,
+// weight * |amplitude|^2 there; else it leaves every amplitude in psi, and the
+// weight to whoever squares them.
+hipError_t run_gates(const GateSet& s, double2* psi, double* probs, const std::vector<int>* init_bits,
                      hipStream_t stream) {
-  normalize(s, probs != nullptr);
   const uint64_t full = (1ull << s.n) - 1;
   const bool track = init_bits != nullptr;
   const unsigned states = track ? 1u << init_bits->size() : 1u;
@@ -748,8 +749,9 @@ void launch_combine(const CombineArgs& A, const double2* psi, double* probs, hip
                      probs, A);
 }
 
-hipError_t combine(const SubInfo& si, const double2* psi, double* probs, hipStream_t stream) {
+hipError_t combine(const SubInfo& si, const double2* psi, double* probs, double weight, hipStream_t stream) {
   CombineArgs A{};
+  A.weight = weight;
   A.w = si.width;
   A.r = si.r();
   A.o = si.o();
@@ -799,8 +801,9 @@ extern "C" cq_status cq_simulate_probabilities(int32_t n, const cq_gate* gates, 
   if (st != CQ_OK) return st;
   if (!workspace || workspace_bytes < ((size_t)16 << n)) return fail(CQ_ERR_WORKSPACE, "workspace too small");
   const std::vector<int> no_bits;
-  const hipError_t e = run_gates(gate_set(n, gates, n_gates, 0), static_cast<double2*>(workspace), probs, &no_bits,
-                                 stream);
+  GateSet circuit = gate_set(n, gates, n_gates, 0);
+  normalize(circuit, true);
+  const hipError_t e = run_gates(circuit, static_cast<double2*>(workspace), probs, &no_bits, stream);
   if (e != hipSuccess) return sv_hip_error(e, "state-vector launch");
   return CQ_OK;
 }
@@ -832,14 +835,15 @@ extern "C" cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq
   const int r = si.r(), o = si.o();
   uint64_t rotated = 0;
   for (int q : si.meas_slots) rotated |= 1ull << (w - 1 - q);
-  const GateSet circuit = gate_set(w, gates, n_gates, rotated);
+  GateSet circuit = gate_set(w, gates, n_gates, rotated);
+  normalize(circuit, false);
   if (workspace_bytes >> r >= ((size_t)16 << w)) {
     // the 2^r computational init strings as one batch, then every variant
     // from them in one pass
     std::vector<int> init_bits;
     for (int q : si.init_slots) init_bits.push_back(w - 1 - q);
     hipError_t e = run_gates(circuit, psi, nullptr, &init_bits, stream);
-    if (e == hipSuccess) e = combine(si, psi, variants, stream);
+    if (e == hipSuccess) e = combine(si, psi, variants, (double)circuit.weight, stream);
     if (e != hipSuccess) return sv_hip_error(e, "variant launch");
     return CQ_OK;
   }
@@ -881,8 +885,10 @@ extern "C" cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq
       }
       // at most CQ_MAX_LOCAL_CUTS rotations, so one pass that reads psi and
       // writes probabilities only: psi stays the post-circuit state
-      e = run_gates(gate_set(w, rot.data(), (int)rot.size(), 0), psi, variants + (j * n_basis + b) * size, nullptr,
-                    stream);
+      GateSet basis = gate_set(w, rot.data(), (int)rot.size(), 0);
+      normalize(basis, true);
+      basis.weight *= circuit.weight;
+      e = run_gates(basis, psi, variants + (j * n_basis + b) * size, nullptr, stream);
     }
     if (e != hipSuccess) return sv_hip_error(e, "variant launch");
   }

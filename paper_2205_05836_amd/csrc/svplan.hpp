@@ -4,7 +4,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <cstdint>
 #include <vector>
 
@@ -33,7 +32,7 @@ struct GateSet {
   std::vector<cq_gate> g;
   std::vector<uint64_t> mask;
   std::vector<int> form;  // Form of each one-qubit unitary
-  double weight = 1.0;    // |factor|^2 that the final amplitudes lack
+  long double weight = 1.0L;  // |factor|^2 that the final amplitudes lack
 };
 
 inline uint64_t gate_mask(int n, const cq_gate& g) {
@@ -66,47 +65,93 @@ inline GateSet gate_set(int n, const cq_gate* gates, int n_gates, uint64_t rotat
 // behind the gate and is multiplied into the columns of the next unitary on
 // its qubit.  A qubit's last unitary stays general, or, where only
 // probabilities are asked for (`probs`) and |d0| = |d1| to rounding (as for
-// every unitary matrix), leaves |d0|^2 to the final weight.  The sums are those
-// of the general form over a common factor, so they round alike.  What is
-// stored meanwhile is the true amplitude over the factors held back: those are
-// kept within 2^-12 .. 2^12 a qubit (2^408 over 34 qubits) by a general gate,
-// which also takes what has no such form or a diagonal below a 16th of the
-// entries beside it.
+// every unitary matrix), leaves |d0|^2 to the final weight.  What is stored
+// meanwhile is the true amplitude over the factors held back: those are kept
+// within 2^-12 .. 2^12 a qubit (2^408 over 34 qubits) by a general gate, which
+// also takes what has no such form or a diagonal below a 16th of the entries
+// beside it.
+//
+// Error: the ratios are rounded, where a general gate has its entries as
+// given, but an amplitude is rounded twice instead of four times.  What a
+// row's rounding takes from its norm and phase is made good: the diagonal is
+// the one that fits the row best with the rounded ratio, the entries of a
+// general gate behind it pass on their norm, and the weight collects the
+// factors in long double.  (Brickwork of Haar unitaries on 16 qubits, 8 layers
+// deep, relative l2 error of the probabilities against long double: 6.4e-16,
+// with general gates 6.5e-16; the sum of all probabilities 1.3e-16 off, 1.2e-16
+// with general gates.  With the diagonal taken as it stands and the weight in
+// double 12 layers had 10e-16 against 8.6e-16, and the sum was 5e-16 off.)  The
+// rounded ratios cost a qubit's first and last gates more than the fewer
+// roundings gain: 4 layers have 4.9e-16 against 4.6e-16, 6 5.5e-16 against
+// 5.4e-16, 10 7.2e-16 against 7.4e-16, so qubits with fewer than kNormalGates
+// unitaries keep them general.
+constexpr int kNormalGates = 8;
+
 inline void normalize(GateSet& s, bool probs) {
-  typedef long double real;  // the factors and ratios are rounded to double once
-  typedef std::complex<real> cx;
-  std::vector<cx> d0(s.n, 1.0), d1(s.n, 1.0);
-  std::vector<int> last(s.n, -1);
+  typedef long double real;
+  struct cx {
+    real re, im;
+  };
+  const auto mul = [](cx x, cx y) { return cx{x.re * y.re - x.im * y.im, x.re * y.im + x.im * y.re}; };
+  const auto mulc = [](cx x, cx y) { return cx{x.re * y.re + x.im * y.im, x.im * y.re - x.re * y.im}; };  // x conj(y)
+  const auto norm = [](cx x) { return x.re * x.re + x.im * x.im; };
+  std::vector<cx> d0(s.n, cx{1, 0}), d1(s.n, cx{1, 0});
+  std::vector<int> last(s.n, -1), count(s.n, 0);
   for (size_t i = 0; i < s.g.size(); ++i)
-    if (s.g[i].kind == CQ_GATE_U) last[s.g[i].q0] = (int)i;
+    if (s.g[i].kind == CQ_GATE_U) {
+      last[s.g[i].q0] = (int)i;
+      ++count[s.g[i].q0];
+    }
   s.form.assign(s.g.size(), kGeneral);
   if (s.n < kMinTileBits) return;
-  const auto fits = [](real pivot, real other) {  // false for NaN
-    return pivot >= (real)1 / 4096 && pivot <= (real)4096 && other <= 16 * pivot;
+  const auto fits = [](real pivot, real other) {  // squared magnitudes; false for NaN
+    return pivot >= (real)1 / (1 << 24) && pivot <= (real)(1 << 24) && other <= 256 * pivot;
+  };
+  // x / y as the kernel has it, and the factor p that makes p (1, ratio) fit
+  // the row (y, x) best
+  const auto ratio = [&](cx x, cx y, cx& p) {
+    const cx q = mulc(x, y);
+    const real n = norm(y);
+    const cx a{(double)(q.re / n), (double)(q.im / n)};
+    const cx t = mulc(x, a);
+    const real m = 1 + norm(a);
+    p = cx{(y.re + t.re) / m, (y.im + t.im) / m};
+    return a;
   };
   for (size_t i = 0; i < s.g.size(); ++i) {
     cq_gate& g = s.g[i];
-    if (g.kind != CQ_GATE_U) continue;
     const int q = g.q0;
+    if (g.kind != CQ_GATE_U || count[q] < kNormalGates) continue;
     cx u[4];
-    for (int c = 0; c < 4; ++c) u[c] = cx(g.u[2 * c], g.u[2 * c + 1]) * ((c & 1) ? d1[q] : d0[q]);
-    d0[q] = d1[q] = 1.0;
-    bool normal = fits(std::abs(u[0]), std::abs(u[1])) && fits(std::abs(u[3]), std::abs(u[2]));
-    if (normal && (int)i == last[q]) {
-      const real n0 = std::norm(u[0]), n1 = std::norm(u[3]);
-      normal = probs && std::abs(n0 - n1) <= 4e-16L * n0;
-      if (normal) s.weight *= (double)((n0 + n1) / 2);
-    }
+    for (int c = 0; c < 4; ++c) u[c] = mul(cx{g.u[2 * c], g.u[2 * c + 1]}, (c & 1) ? d1[q] : d0[q]);
+    d0[q] = d1[q] = cx{1, 0};
+    const bool end = (int)i == last[q];
+    bool normal = (probs || !end) && fits(norm(u[0]), norm(u[1])) && fits(norm(u[3]), norm(u[2]));
     if (normal) {
-      s.form[i] = kNormal;
-      d0[q] = u[0];
-      d1[q] = u[3];
-      u[0] = u[1] / d0[q];
-      u[1] = u[2] / d1[q];
+      cx p0, p1;
+      const cx a = ratio(u[1], u[0], p0), b = ratio(u[2], u[3], p1);
+      const real n0 = norm(p0), n1 = norm(p1);
+      if (end) normal = std::abs(n0 - n1) <= 2e-16L * n0;
+      if (normal) {
+        s.form[i] = kNormal;
+        if (end) s.weight *= (n0 + n1) / 2;
+        d0[q] = p0;
+        d1[q] = p1;
+        u[0] = a;
+        u[1] = b;
+      }
     }
+    real given = 0, rounded = 0;
     for (int c = 0; c < (normal ? 2 : 4); ++c) {
-      g.u[2 * c] = (double)u[c].real();
-      g.u[2 * c + 1] = (double)u[c].imag();
+      g.u[2 * c] = (double)u[c].re;
+      g.u[2 * c + 1] = (double)u[c].im;
+      given += norm(u[c]);
+      rounded += norm(cx{g.u[2 * c], g.u[2 * c + 1]});
+    }
+    if (!normal && rounded > given / 2 && rounded < given * 2) {  // not for a zero matrix, or one out of range
+      const real lost = given / rounded;
+      if (end) s.weight *= lost;
+      else d0[q] = d1[q] = cx{std::sqrt(lost), 0};
     }
   }
 }
