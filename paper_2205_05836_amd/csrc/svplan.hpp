@@ -107,17 +107,6 @@ inline void normalize(GateSet& s, bool probs) {
   const auto fits = [](real pivot, real other) {  // squared magnitudes; false for NaN
     return pivot >= (real)1 / (1 << 24) && pivot <= (real)(1 << 24) && other <= 256 * pivot;
   };
-  // x / y as the kernel has it, and the factor p that makes p (1, ratio) fit
-  // the row (y, x) best
-  const auto ratio = [&](cx x, cx y, cx& p) {
-    const cx q = mulc(x, y);
-    const real n = norm(y);
-    const cx a{(double)(q.re / n), (double)(q.im / n)};
-    const cx t = mulc(x, a);
-    const real m = 1 + norm(a);
-    p = cx{(y.re + t.re) / m, (y.im + t.im) / m};
-    return a;
-  };
   for (size_t i = 0; i < s.g.size(); ++i) {
     cq_gate& g = s.g[i];
     const int q = g.q0;
@@ -128,8 +117,16 @@ inline void normalize(GateSet& s, bool probs) {
     const bool end = (int)i == last[q];
     bool normal = (probs || !end) && fits(norm(u[0]), norm(u[1])) && fits(norm(u[3]), norm(u[2]));
     if (normal) {
-      cx p0, p1;
-      const cx a = ratio(u[1], u[0], p0), b = ratio(u[2], u[3], p1);
+      // the ratios as the kernel has them, then the diagonal that fits the rows
+      // (divisions are slow: one for both of each)
+      const real m0 = norm(u[0]), m1 = norm(u[3]), inv = 1 / (m0 * m1);
+      const cx x = mulc(u[1], u[0]), y = mulc(u[2], u[3]);
+      const cx a{(double)(x.re * (m1 * inv)), (double)(x.im * (m1 * inv))};
+      const cx b{(double)(y.re * (m0 * inv)), (double)(y.im * (m0 * inv))};
+      const real na = 1 + norm(a), nb = 1 + norm(b), fit = 1 / (na * nb);
+      const cx ta = mulc(u[1], a), tb = mulc(u[2], b);
+      const cx p0{(u[0].re + ta.re) * (nb * fit), (u[0].im + ta.im) * (nb * fit)};
+      const cx p1{(u[3].re + tb.re) * (na * fit), (u[3].im + tb.im) * (na * fit)};
       const real n0 = norm(p0), n1 = norm(p1);
       if (end) normal = std::abs(n0 - n1) <= 2e-16L * n0;
       if (normal) {
@@ -141,14 +138,21 @@ inline void normalize(GateSet& s, bool probs) {
         u[1] = b;
       }
     }
+    if (normal) {
+      g.u[0] = (double)u[0].re;
+      g.u[1] = (double)u[0].im;
+      g.u[2] = (double)u[1].re;
+      g.u[3] = (double)u[1].im;
+      continue;
+    }
     real given = 0, rounded = 0;
-    for (int c = 0; c < (normal ? 2 : 4); ++c) {
+    for (int c = 0; c < 4; ++c) {
       g.u[2 * c] = (double)u[c].re;
       g.u[2 * c + 1] = (double)u[c].im;
       given += norm(u[c]);
       rounded += norm(cx{g.u[2 * c], g.u[2 * c + 1]});
     }
-    if (!normal && rounded > given / 2 && rounded < given * 2) {  // not for a zero matrix, or one out of range
+    if (given != rounded && rounded > given / 2 && rounded < given * 2) {  // not if out of range
       const real lost = given / rounded;
       if (end) s.weight *= lost;
       else d0[q] = d1[q] = cx{std::sqrt(lost), 0};
@@ -226,27 +230,47 @@ inline double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int
   return us;
 }
 
-// The cheapest plan by the model over a few shapes.  Wider tiles mean fewer
-// passes; growing the allowed set by several qubits at a time merges passes
-// that one at a time would leave nearly empty; runs of 8 amplitudes (128
-// bytes, one line) leave a tile one bit more than runs of 16.  Below 18
-// qubits launches decide, so only the extreme shapes are tried there.
+// Shapes in the order in which trying them pays (tile bits, growth; 0: every
+// qubit at once), for registers of 18 to 24 qubits and for wider ones, by the
+// model over line, random-pair and grid circuits of 18 to 32 qubits and 2 to 16
+// layers.  The first alone is within 8% and 6% of the best of all on average,
+// the first three within 3% and 1%.  Runs of 8 amplitudes (128 bytes, one line)
+// leave a tile one bit more than runs of 16; a tile's spare bits go to the
+// lowest anyway.
+constexpr int kShapes = 12;
+constexpr int8_t kNarrow[kShapes][2] = {{11, 4}, {11, 0}, {12, 2}, {11, 3}, {11, 6}, {11, 2},
+                                        {12, 4}, {12, 1}, {12, 3}, {12, 6}, {12, 0}, {11, 1}};
+constexpr int8_t kWide[kShapes][2] = {{12, 2}, {12, 1}, {12, 4}, {11, 4}, {12, 3}, {12, 0},
+                                      {11, 3}, {11, 1}, {11, 2}, {11, 0}, {12, 6}, {11, 6}};
+
+// The cheapest plan by the model.  Wider tiles mean fewer passes; growing the
+// allowed set by several qubits at a time merges passes that one at a time
+// would leave nearly empty.  Laying out a shape costs the host some 0.03 us a
+// gate, so shapes are tried only while that stays below a 16th of the best
+// plan's modelled time: two shapes for 18 qubits and 8 layers (135 us), all of
+// them from 25 qubits.  (24 shapes whatever the size took 124 us there, as
+// long as the passes.)  Below 18 qubits launches decide: every qubit at once,
+// either tile.
 inline PlanShape best_plan(const GateSet& s, bool track, int states, std::vector<Pass>& out) {
   PlanShape best;
   double least = 1e300;
   std::vector<Pass> cand;
-  for (int tile = std::min(s.n, kMaxTileBits); tile >= std::min(s.n, kMinTileBits); --tile)
-    for (int low = 4; low >= 3; --low)
-      for (int grow : {s.n, 6, 4, 3, 2, 1}) {
-        if (grow != s.n && (!track || s.n < 18)) continue;
-        const PlanShape sh{tile, low, grow};
-        const double us = plan_passes(s, sh, track, states, least, cand);
-        if (us < least) {
-          least = us;
-          best = sh;
-          out.swap(cand);
-        }
-      }
+  const bool grows = track && s.n >= 18;
+  int tried = 0;
+  for (int q = 0; q < kShapes; ++q) {
+    const int8_t* const t = s.n <= 24 ? kNarrow[q] : kWide[q];
+    if (!grows && t[1] != 0) continue;
+    if (t[0] > std::max(s.n, kMinTileBits)) continue;
+    if (tried && tried * 0.03 * (double)s.g.size() > least / 16) break;
+    const PlanShape sh{std::min(s.n, (int)t[0]), 3, t[1] ? t[1] : s.n};
+    const double us = plan_passes(s, sh, track, states, least, cand);
+    ++tried;
+    if (us < least) {
+      least = us;
+      best = sh;
+      out.swap(cand);
+    }
+  }
   return best;
 }
 
