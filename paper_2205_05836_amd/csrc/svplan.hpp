@@ -232,25 +232,23 @@ inline double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int
 
 // Shapes in the order in which trying them pays (tile bits, growth; 0: every
 // qubit at once), for registers of 18 to 24 qubits and for wider ones, by the
-// model over line, random-pair and grid circuits of 18 to 32 qubits and 2 to 16
-// layers.  The first alone is within 8% and 6% of the best of all on average,
-// the first three within 3% and 1%.  Runs of 8 amplitudes (128 bytes, one line)
-// leave a tile one bit more than runs of 16; a tile's spare bits go to the
-// lowest anyway.
+// model over line and random-pair circuits of 18 to 28 qubits and 3 to 12
+// layers.  Runs of 8 amplitudes (128 bytes, one line) leave a tile one bit more
+// than runs of 16; a tile's spare bits go to the lowest anyway.
 constexpr int kShapes = 12;
-constexpr int8_t kNarrow[kShapes][2] = {{11, 4}, {11, 0}, {12, 2}, {11, 3}, {11, 6}, {11, 2},
-                                        {12, 4}, {12, 1}, {12, 3}, {12, 6}, {12, 0}, {11, 1}};
+constexpr int8_t kNarrow[kShapes][2] = {{11, 4}, {11, 6}, {11, 2}, {11, 3}, {11, 0}, {11, 1},
+                                        {12, 2}, {12, 4}, {12, 1}, {12, 3}, {12, 6}, {12, 0}};
 constexpr int8_t kWide[kShapes][2] = {{12, 2}, {12, 1}, {12, 4}, {11, 4}, {12, 3}, {12, 0},
                                       {11, 3}, {11, 1}, {11, 2}, {11, 0}, {12, 6}, {11, 6}};
 
 // The cheapest plan by the model.  Wider tiles mean fewer passes; growing the
 // allowed set by several qubits at a time merges passes that one at a time
-// would leave nearly empty.  Laying out a shape costs the host some 0.03 us a
+// would leave nearly empty.  Laying out a shape costs the host some 0.02 us a
 // gate, so shapes are tried only while that stays below a 16th of the best
-// plan's modelled time: two shapes for 18 qubits and 8 layers (135 us), all of
-// them from 25 qubits.  (24 shapes whatever the size took 124 us there, as
-// long as the passes.)  Below 18 qubits launches decide: every qubit at once,
-// either tile.
+// plan's modelled time: three for 18 qubits and 8 layers (135 us), which the
+// model puts within 1.5% of the best of all up to 21 qubits and within 3% to 24,
+// and all of them from there.  (24 shapes whatever the size took 124 us at 18
+// qubits.)  Below 18 qubits launches decide: every qubit at once, either tile.
 inline PlanShape best_plan(const GateSet& s, bool track, int states, std::vector<Pass>& out) {
   PlanShape best;
   double least = 1e300;
@@ -261,7 +259,7 @@ inline PlanShape best_plan(const GateSet& s, bool track, int states, std::vector
     const int8_t* const t = s.n <= 24 ? kNarrow[q] : kWide[q];
     if (!grows && t[1] != 0) continue;
     if (t[0] > std::max(s.n, kMinTileBits)) continue;
-    if (tried && tried * 0.03 * (double)s.g.size() > least / 16) break;
+    if (tried && tried * 0.02 * (double)s.g.size() > least / 16) break;
     const PlanShape sh{std::min(s.n, (int)t[0]), 3, t[1] ? t[1] : s.n};
     const double us = plan_passes(s, sh, track, states, least, cand);
     ++tried;
