@@ -433,9 +433,10 @@ cq_status cq_simulate_probabilities(int32_t n, const cq_gate* gates, int32_t n_g
 
 /* 16 * 2^width bytes per state, 2^r states: one for each computational init
  * string of the r initialised ends (every variant is a combination of their
- * results).  Never more than the variants themselves take when r or o is
- * at least 1.  cq_variant_probabilities works with any workspace of at least
- * one state, more slowly below this size. */
+ * results); half as many, and so on down to one, where they and the variants
+ * would take more than 240 GiB together.  cq_variant_probabilities works with
+ * any workspace of at least one state: with 2^s states it runs 4^(r - s)
+ * batches, one for each digit string of the first r - s ends. */
 cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t* bytes);
 
 /* Every variant of subcircuit `sub` running `gates` (qubits = its register
@@ -447,7 +448,8 @@ cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t* bytes);
  * variants: device, FP64, layout (4^r, 3^o, 2^width) as cq_attribute reads
  * it, written whole.  workspace: device, at least one state (16 * 2^width
  * bytes); cq_variants_workspace_size bytes let it simulate the computational
- * init strings as one batch and write every variant from them in one pass.
+ * init strings as one batch (see there) and write every variant from them in
+ * one pass.
  * Asynchronous on `stream`; errors as for cq_simulate_probabilities plus
  * the cut-map checks of the subcircuit. */
 cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq_gate* gates, int32_t n_gates,

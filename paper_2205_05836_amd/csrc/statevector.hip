@@ -577,39 +577,6 @@ __global__ void __launch_bounds__(kSvThreads) sv_combine_kernel(const double2* _
   }
 }
 
-// Product state: amplitude(x) = prod over qubits q of ket_q[bit q of x].
-struct Kets {
-  int32_t n;
-  double k[CQ_MAX_WIDTH][4];  // (re, im) of <0|ket>, <1|ket> per qubit
-  uint64_t zero;              // index bits of the qubits whose ket is exactly |0>
-};
-
-// Qubits in |0> contribute a factor of exactly 1 where their bit is 0 and
-// make the amplitude 0 where it is 1, so only the others are multiplied.
-__global__ void __launch_bounds__(kSvThreads) sv_product_kernel(double2* __restrict__ psi, int64_t size, Kets K) {
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < size; x += step) {
-    if ((uint64_t)x & K.zero) {
-      psi[x] = make_double2(0.0, 0.0);
-      continue;
-    }
-    double re = 1.0, im = 0.0;
-    for (int q = 0; q < K.n; ++q) {
-      if ((K.zero >> (K.n - 1 - q)) & 1ull) continue;
-      const int bit = (int)((x >> (K.n - 1 - q)) & 1);
-      const double kr = K.k[q][2 * bit], ki = K.k[q][2 * bit + 1];
-      const double nr = re * kr - im * ki;
-      im = re * ki + im * kr;
-      re = nr;
-    }
-    psi[x] = make_double2(re, im);
-  }
-}
-
-unsigned fill_grid(int64_t size) {
-  return (unsigned)std::min<int64_t>((size + kSvThreads - 1) / kSvThreads, 1 << 16);
-}
-
 cq_status sv_hip_error(hipError_t e, const char* what) {
   return fail(CQ_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -705,34 +672,20 @@ hipError_t launch_tiles(const TileGroup& G, double2* psi, double* probs, unsigne
   return hipGetLastError();
 }
 
-// Applies the (normalised) gates to `states` states of a batch.  With init_bits each starts
-// as a basis string (see TileGroup) that the first pass generates; without,
-// as what psi holds.  With probs (one state) the last pass writes
-// weight * |amplitude|^2 there; else it leaves every amplitude in psi, and the
-// weight to whoever squares them.
-hipError_t run_gates(const GateSet& s, double2* psi, double* probs, const std::vector<int>* init_bits,
-                     hipStream_t stream) {
-  const uint64_t full = (1ull << s.n) - 1;
-  const bool track = init_bits != nullptr;
-  const unsigned states = track ? 1u << init_bits->size() : 1u;
-  std::vector<Pass> passes;
-  const PlanShape sh = best_plan(s, track, (int)states, passes);
-  if (passes.empty()) {
-    if (!track && !probs) return hipSuccess;
-    passes.push_back(Pass());
-    passes[0].before = passes[0].after = track ? 0 : full;
-  }
-  passes.back().after = full;  // every amplitude or probability is written
+// Applies the (normalised) gates in the planned passes to a batch of states, one
+// for each string of init_bits, that start as basis strings (see TileGroup).
+// With probs (one state) the last pass writes weight * |amplitude|^2 there; else
+// it leaves every amplitude in psi, and the weight to whoever squares them.
+hipError_t run_gates(const GateSet& s, const PlanShape& sh, const std::vector<Pass>& passes, double2* psi,
+                     double* probs, const std::vector<int>& init_bits, hipStream_t stream) {
   for (size_t i = 0; i < passes.size(); ++i) {
     const bool last = i + 1 == passes.size();
     TileGroup G = tile_group(s, sh, passes[i], last && probs ? 1 : 0);
     G.bstride = (int64_t)1 << s.n;
-    if (track) {
-      G.first = i == 0;
-      G.r = (int32_t)init_bits->size();
-      for (int t = 0; t < G.r; ++t) G.init_bit[t] = (uint32_t)(*init_bits)[t];
-    }
-    const hipError_t e = launch_tiles(G, psi, probs, states, stream);
+    G.first = i == 0;
+    G.r = (int32_t)init_bits.size();
+    for (int t = 0; t < G.r; ++t) G.init_bit[t] = (uint32_t)init_bits[t];
+    const hipError_t e = launch_tiles(G, psi, probs, 1u << G.r, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -749,11 +702,12 @@ void launch_combine(const CombineArgs& A, const double2* psi, double* probs, hip
                      probs, A);
 }
 
-hipError_t combine(const SubInfo& si, const double2* psi, double* probs, double weight, hipStream_t stream) {
+// r: the init slots whose 2^r computational strings psi holds, the last of `si`
+hipError_t combine(const SubInfo& si, int r, const double2* psi, double* probs, double weight, hipStream_t stream) {
   CombineArgs A{};
   A.weight = weight;
   A.w = si.width;
-  A.r = si.r();
+  A.r = r;
   A.o = si.o();
   A.bstride = (int64_t)1 << si.width;
   for (int u = 0; u < A.o; ++u) A.meas_bit[u] = (uint32_t)(si.width - 1 - si.meas_slots[u]);
@@ -772,13 +726,9 @@ hipError_t combine(const SubInfo& si, const double2* psi, double* probs, double 
   return hipGetLastError();
 }
 
-cq_gate u_gate(int q, const double (&m)[8]) {
-  cq_gate g{};
-  g.kind = CQ_GATE_U;
-  g.q0 = q;
-  for (int c = 0; c < 8; ++c) g.u[c] = m[c];
-  return g;
-}
+// What cq_variants_workspace_size asks for together with the variants at most:
+// beyond it (of the card's 288 GB) fewer states are batched.
+constexpr size_t kVariantBytes = (size_t)240 << 30;
 
 }  // namespace
 
@@ -800,10 +750,11 @@ extern "C" cq_status cq_simulate_probabilities(int32_t n, const cq_gate* gates, 
   cq_status st = check_gates(n, gates, n_gates);
   if (st != CQ_OK) return st;
   if (!workspace || workspace_bytes < ((size_t)16 << n)) return fail(CQ_ERR_WORKSPACE, "workspace too small");
-  const std::vector<int> no_bits;
   GateSet circuit = gate_set(n, gates, n_gates, 0);
   normalize(circuit, true);
-  const hipError_t e = run_gates(circuit, static_cast<double2*>(workspace), probs, &no_bits, stream);
+  std::vector<Pass> passes;
+  const PlanShape shape = best_plan(circuit, 1, passes);
+  const hipError_t e = run_gates(circuit, shape, passes, static_cast<double2*>(workspace), probs, {}, stream);
   if (e != hipSuccess) return sv_hip_error(e, "state-vector launch");
   return CQ_OK;
 }
@@ -814,7 +765,11 @@ extern "C" cq_status cq_variants_workspace_size(const cq_subcircuit* sub, size_t
   cq_status st = build_subinfo(sub, si);
   if (st != CQ_OK) return st;
   if (si.width < 1) return fail(CQ_ERR_SHAPE, "subcircuit has no slots");
-  *bytes = ((size_t)16 << si.width) << si.r();
+  size_t variants = ((size_t)8 << si.width) << (2 * si.r());
+  for (int u = 0; u < si.o(); ++u) variants *= 3;
+  int r = si.r();
+  while (r > 0 && variants + (((size_t)16 << si.width) << r) > kVariantBytes) --r;
+  *bytes = ((size_t)16 << si.width) << r;
   return CQ_OK;
 }
 
@@ -831,65 +786,41 @@ extern "C" cq_status cq_variant_probabilities(const cq_subcircuit* sub, const cq
   if (st != CQ_OK) return st;
   if (!workspace || workspace_bytes < ((size_t)16 << w)) return fail(CQ_ERR_WORKSPACE, "workspace too small");
   double2* psi = static_cast<double2*>(workspace);
-  const int64_t size = (int64_t)1 << w;
   const int r = si.r(), o = si.o();
   uint64_t rotated = 0;
   for (int q : si.meas_slots) rotated |= 1ull << (w - 1 - q);
-  GateSet circuit = gate_set(w, gates, n_gates, rotated);
-  normalize(circuit, false);
-  if (workspace_bytes >> r >= ((size_t)16 << w)) {
-    // the 2^r computational init strings as one batch, then every variant
-    // from them in one pass
-    std::vector<int> init_bits;
-    for (int q : si.init_slots) init_bits.push_back(w - 1 - q);
-    hipError_t e = run_gates(circuit, psi, nullptr, &init_bits, stream);
-    if (e == hipSuccess) e = combine(si, psi, variants, (double)circuit.weight, stream);
-    if (e != hipSuccess) return sv_hip_error(e, "variant launch");
-    return CQ_OK;
-  }
-  // one state at a time (a workspace of fewer than 2^r states): each init
-  // string's product state, the circuit, then one pass per measurement basis
-  int64_t n_init = 1, n_basis = 1;
-  for (int i = 0; i < r; ++i) n_init *= 4;
-  for (int i = 0; i < o; ++i) n_basis *= 3;
-  // prepared states of a cut's downstream end: |0>, |1>, |+>, |+i>
+  // As many of the last init slots as the workspace holds strings for go as one
+  // batch of computational strings, from which one pass writes every variant of
+  // theirs; the slots before them are prepared by a unitary each, one string of
+  // digits after another (none with a workspace of 2^r states).
+  int inner = r;
+  while (((size_t)16 << w) << inner > workspace_bytes) --inner;
+  const int outer = r - inner;
+  std::vector<int> init_bits;
+  for (int t = outer; t < r; ++t) init_bits.push_back(w - 1 - si.init_slots[t]);
   const double h = 1.0 / std::sqrt(2.0);
-  const double init_ket[4][4] = {{1, 0, 0, 0}, {0, 0, 1, 0}, {h, 0, h, 0}, {h, 0, 0, h}};
-  // rotations before a computational-basis measurement: Z (none), X (H),
-  // Y (S^dagger then H, i.e. H S^dagger = [[1, -i], [1, i]] / sqrt 2)
-  const double rot_x[8] = {h, 0, h, 0, h, 0, -h, 0};
-  const double rot_y[8] = {h, 0, 0, -h, h, 0, 0, h};
-  for (int64_t j = 0; j < n_init; ++j) {
-    Kets K{};
-    K.n = w;
-    for (int q = 0; q < w; ++q) {
-      K.k[q][0] = 1.0;
-      K.k[q][1] = K.k[q][2] = K.k[q][3] = 0.0;
+  const double prepare[4][8] = {{1, 0, 0, 0, 0, 0, 1, 0},    // |0>
+                                {0, 0, 1, 0, 1, 0, 0, 0},    // |1>
+                                {h, 0, h, 0, h, 0, -h, 0},   // |+>
+                                {h, 0, h, 0, 0, h, 0, -h}};  // |+i>
+  std::vector<cq_gate> all((size_t)outer + n_gates);
+  std::copy(gates, gates + n_gates, all.begin() + outer);
+  int64_t stride = (int64_t)1 << (w + 2 * inner);  // variants of a string
+  for (int u = 0; u < o; ++u) stride *= 3;
+  std::vector<Pass> passes;
+  PlanShape shape;
+  for (int64_t j = 0; j < (int64_t)1 << (2 * outer); ++j) {
+    for (int t = 0; t < outer; ++t) {
+      all[t].kind = CQ_GATE_U;
+      all[t].q0 = si.init_slots[t];
+      for (int c = 0; c < 8; ++c) all[t].u[c] = prepare[(j >> (2 * (outer - 1 - t))) & 3][c];
     }
-    for (int t = 0; t < r; ++t) {
-      const int digit = (int)((j >> (2 * (r - 1 - t))) & 3);
-      for (int c = 0; c < 4; ++c) K.k[si.init_slots[t]][c] = init_ket[digit][c];
-    }
-    K.zero = 0;
-    for (int q = 0; q < w; ++q)
-      if (K.k[q][0] == 1.0 && K.k[q][1] == 0.0 && K.k[q][2] == 0.0 && K.k[q][3] == 0.0) K.zero |= 1ull << (w - 1 - q);
-    hipLaunchKernelGGL(sv_product_kernel, dim3(fill_grid(size)), dim3(kSvThreads), 0, stream, psi, size, K);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = run_gates(circuit, psi, nullptr, nullptr, stream);
-    for (int64_t b = 0; b < n_basis && e == hipSuccess; ++b) {
-      std::vector<cq_gate> rot;  // basis b: digit 1 X, 2 Y per measured slot
-      int64_t rest = b;
-      for (int u = o - 1; u >= 0; --u, rest /= 3) {
-        if (rest % 3 == 1) rot.push_back(u_gate(si.meas_slots[u], rot_x));
-        if (rest % 3 == 2) rot.push_back(u_gate(si.meas_slots[u], rot_y));
-      }
-      // at most CQ_MAX_LOCAL_CUTS rotations, so one pass that reads psi and
-      // writes probabilities only: psi stays the post-circuit state
-      GateSet basis = gate_set(w, rot.data(), (int)rot.size(), 0);
-      normalize(basis, true);
-      basis.weight *= circuit.weight;
-      e = run_gates(basis, psi, variants + (j * n_basis + b) * size, nullptr, stream);
-    }
+    GateSet circuit = gate_set(w, all.data(), (int)all.size(), rotated);
+    normalize(circuit, false);
+    if (j == 0) shape = best_plan(circuit, 1 << inner, passes);
+    hipError_t e = run_gates(circuit, shape, passes, psi, nullptr, init_bits, stream);
+    if (e == hipSuccess)
+      e = combine(si, inner, psi, variants + j * stride, (double)circuit.weight, stream);
     if (e != hipSuccess) return sv_hip_error(e, "variant launch");
   }
   return CQ_OK;

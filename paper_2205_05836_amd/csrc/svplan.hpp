@@ -169,20 +169,20 @@ struct PlanShape {
 
 // Passes for one shape.  A pass takes, in circuit order, every gate inside the
 // allowed qubits that fits the tile and shares no qubit with an earlier gate
-// left for a later pass.  With `track` the state starts as a basis string and
-// the allowed qubits start as the lowest `tile` index bits and grow, lowest
-// first, only when none of their gates can run: while t qubits are touched a
-// pass moves 2^t amplitudes.  Returns the modelled time in microseconds, or
+// left for a later pass.  The state starts as a basis string, and the allowed
+// qubits start as the lowest `tile` index bits and grow, lowest first, only when
+// none of their gates can run: while t qubits are touched a pass moves 2^t
+// amplitudes.  The last pass writes every amplitude, also without gates.  Returns the modelled time in microseconds, or
 // anything above `limit` once that is passed.  The model, from traces: 3.5 us
 // a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.33 ms for
 // every one-qubit gate on 2^30 amplitudes, no less than the serial time of
 // those gates in one tile (0.8 us each with 11 bits, 1.4 us with 12).
-inline double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int states, double limit,
+inline double plan_passes(const GateSet& s, const PlanShape& sh, int states, double limit,
                    std::vector<Pass>& out) {
   const int n = s.n;
   const uint64_t full = (1ull << n) - 1;
   const uint64_t low = (1ull << std::min(n, sh.low)) - 1;
-  uint64_t allowed = track ? (1ull << std::min(n, sh.tile)) - 1 : full, touched = track ? 0 : full;
+  uint64_t allowed = (1ull << std::min(n, sh.tile)) - 1, touched = 0;
   std::vector<int> rest(s.g.size()), left;
   for (size_t i = 0; i < rest.size(); ++i) rest[i] = (int)i;
   out.clear();
@@ -219,7 +219,7 @@ inline double plan_passes(const GateSet& s, const PlanShape& sh, bool track, int
     touched |= p.mask;
     p.after = touched;
     rest.swap(left);
-    const double before = out.empty() && track ? 0.0 : std::ldexp(16.0, __builtin_popcountll(p.before));
+    const double before = out.empty() ? 0.0 : std::ldexp(16.0, __builtin_popcountll(p.before));
     const double after = std::ldexp(rest.empty() ? 8.0 : 16.0, rest.empty() ? n : __builtin_popcountll(p.after));
     const double work = nu * std::max(std::ldexp(3.1e-7 * states, __builtin_popcountll(p.after)),
                                       sh.tile <= 11 ? 0.8 : 1.4);
@@ -249,19 +249,18 @@ constexpr int8_t kWide[kShapes][2] = {{12, 2}, {12, 1}, {12, 4}, {11, 4}, {12, 3
 // model puts within 1.5% of the best of all up to 21 qubits and within 3% to 24,
 // and all of them from there.  (24 shapes whatever the size took 124 us at 18
 // qubits.)  Below 18 qubits launches decide: every qubit at once, either tile.
-inline PlanShape best_plan(const GateSet& s, bool track, int states, std::vector<Pass>& out) {
+inline PlanShape best_plan(const GateSet& s, int states, std::vector<Pass>& out) {
   PlanShape best;
   double least = 1e300;
   std::vector<Pass> cand;
-  const bool grows = track && s.n >= 18;
   int tried = 0;
   for (int q = 0; q < kShapes; ++q) {
     const int8_t* const t = s.n <= 24 ? kNarrow[q] : kWide[q];
-    if (!grows && t[1] != 0) continue;
+    if (s.n < 18 && t[1] != 0) continue;
     if (t[0] > std::max(s.n, kMinTileBits)) continue;
     if (tried && tried * 0.02 * (double)s.g.size() > least / 16) break;
     const PlanShape sh{std::min(s.n, (int)t[0]), 3, t[1] ? t[1] : s.n};
-    const double us = plan_passes(s, sh, track, states, least, cand);
+    const double us = plan_passes(s, sh, states, least, cand);
     ++tried;
     if (us < least) {
       least = us;
@@ -269,6 +268,8 @@ inline PlanShape best_plan(const GateSet& s, bool track, int states, std::vector
       out.swap(cand);
     }
   }
+  if (out.empty()) out.push_back(Pass());
+  out.back().after = (1ull << s.n) - 1;
   return best;
 }
 

@@ -79,3 +79,43 @@ def test_widest_registers(recorder):
                                launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + VARIANTS)):
         assert ev and [e for e in ev if not e["ok"]] == [], c
         assert status == 0, c
+
+
+STATES = """
+def launches(sub, states):
+    s = api._Subs([sub])
+    gates, n = api._gates([("u", q, [[0.6, 0.8], [0.8, -0.6]]) for q in range(sub[0])] +
+                          [("cz", q, q + 1) for q in range(sub[0] - 1)])
+    events()
+    assert L.cq_variant_probabilities(s.ptr(), gates, n, C.c_void_p(1 << 50), C.c_void_p(1 << 51),
+                                      states << (sub[0] + 4), None) == 0
+    return len(events())
+def query(sub):
+    s, b = api._Subs([sub]), C.c_size_t()
+    assert L.cq_variants_workspace_size(s.ptr(), C.byref(b)) == 0
+    return b.value
+out = [[launches(sub, n) for n in states] + [query(sub)] for sub, states in json.loads(CASES)]
+"""
+
+
+def slots(w, r, o):
+    return w, list(range(r)) + [-1] * (w - r), [-1] * (w - o) + list(range(r, r + o))
+
+
+@pytest.mark.parametrize("w,r,o", [(6, 2, 1), (12, 1, 2), (12, 3, 2), (13, 2, 4), (14, 4, 0)])
+def test_variants_use_what_the_workspace_holds(recorder, w, r, o):
+    """2^s states of workspace take 4^(r - s) batches, each with the launches
+    of a full one: its passes and one that writes every basis."""
+    states = list(range(1, 2 ** r + 1))
+    cases = [(slots(w, r, o), states)]
+    *got, _ = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + STATES)[0]
+    for n, launches in zip(states, got):
+        assert launches <= 4 ** (r - (n.bit_length() - 1)) * (got[-1] + 1), n  # a prepared slot may cost a pass
+
+
+def test_variants_workspace_leaves_room_for_the_variants(recorder):
+    """The query asks for every computational init string, but not past 240 GiB
+    with the variants: what fitted the card with one state still does."""
+    cases = [(slots(w, r, o), []) for w, r, o in ((12, 3, 2), (22, 2, 2), (27, 4, 0), (29, 3, 0), (31, 1, 1), (32, 0, 0))]
+    got = [q[0] for q in launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + STATES)]
+    assert got == [16 << 15, 16 << 24, 16 << 27, 16 << 29, 16 << 31, 16 << 32]
