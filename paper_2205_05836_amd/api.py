@@ -392,16 +392,18 @@ def _gates(ops):
             heads.append((_lib.GATE_CZ, int(qubits[0]), int(qubits[1])))
         else:
             raise ValueError(f"unknown gate {name!r}")
-    # all matrices in one conversion (element by element they cost more than
-    # the simulation of a small register)
+    # arrays and nested lists in one conversion (element by element they cost
+    # more than the simulation of a small register)
     buf = np.zeros(max(len(ops), 1), dtype=_GATE)
     if heads:
         buf["head"] = heads
     if mats:
-        try:
-            u = np.array(mats, dtype=np.complex128)
-        except (TypeError, ValueError):
-            u = None
+        u = None
+        if all(type(m) in (np.ndarray, list, tuple) for m in mats):
+            try:
+                u = np.array(mats, dtype=np.complex128)
+            except (TypeError, ValueError, RuntimeError):
+                pass
         if u is None or u.shape != (len(mats), 2, 2):  # anything indexable as matrix[r][c]
             u = np.array([[[complex(m[r][c]) for c in range(2)] for r in range(2)] for m in mats])
         buf["u"][at] = u.reshape(len(mats), 4).view(np.float64)

@@ -47,3 +47,46 @@ def test_gate_structs():
     assert api._gates([])[1] == 0
     with pytest.raises(ValueError):
         api._gates([("cx", 0, 1)])
+
+
+class Rows:
+    """Indexable as matrix[r][c], and nothing an array can be made of."""
+
+    def __init__(self, m):
+        self.m = m
+
+    def __getitem__(self, r):
+        return self.m[r]
+
+
+class Columns:
+    """matrix[r][c] is the element in row r and column c, the array form its
+    transpose (as of a table whose columns are indexed first)."""
+
+    def __init__(self, m):
+        self.m = np.array(m)
+
+    def __getitem__(self, r):
+        return list(self.m[r])
+
+    def __array__(self, dtype=None, copy=None):
+        return self.m.T.astype(dtype)
+
+
+def tensors():
+    import torch
+    m = torch.tensor([[0.5, 1j], [2 - 1j, -3]], dtype=torch.complex128)
+    return [m, m.conj(), m.mH, m.clone().requires_grad_(), m.real, torch.eye(3)]
+
+
+def test_gate_matrices_are_read_by_element():
+    """Anything indexable as matrix[r][c] gives the elements that indexing
+    gives, whatever an array made of it would hold or refuse."""
+    m = [[0.5, 1j], [2 - 1j, -3]]
+    for u in [Rows(m), Columns(m), {0: {0: 1, 1: 2}, 1: {0: 3, 1: 4}}, [["1", "2j"], ["3", "4"]],
+              [list(row) for row in tensors()[3]]] + tensors():
+        for ops in ([("u", 0, u)], [("u", 0, np.eye(2)), ("u", 1, u)], [("u", 0, u), ("u", 1, m)]):
+            arr, n = api._gates(ops)
+            for g, op in zip(arr, ops):
+                want = [complex(op[2][r][c]) for r in range(2) for c in range(2)]
+                assert list(g.u) == [x for z in want for x in (z.real, z.imag)]
