@@ -29,6 +29,18 @@ _SUB = struct.Struct("@iiPP")
 assert _SUB.size == C.sizeof(_lib.cq_subcircuit)
 
 
+def _wrap32(x):
+    """x as a ctypes int32 field stores it; the library judges the value."""
+    return (x + 2 ** 31) % 2 ** 32 - 2 ** 31
+
+
+def _int32s(xs):
+    try:
+        return array("i", xs)
+    except OverflowError:
+        return array("i", [_wrap32(x) for x in xs])
+
+
 class _Subs:
     """Keeps the C arrays of a subcircuit list alive for one call: every cut
     list in one int32 buffer, the structs built as bytes over it (ctypes
@@ -43,8 +55,8 @@ class _Subs:
             if len(ic) > n or len(mc) > n:
                 raise IndexError("invalid index")  # as a ctypes array of `width` entries
             spans.append((w, len(cuts)))
-            cuts.extend(ic + [0] * (n - len(ic)))
-            cuts.extend(mc + [0] * (n - len(mc)))
+            cuts.extend(_int32s(ic + [0] * (n - len(ic))))
+            cuts.extend(_int32s(mc + [0] * (n - len(mc))))
             self.n_out.append(mc.count(-1))
         base = cuts.buffer_info()[0]
         raw = bytearray(b"".join(_SUB.pack(w, 0, base + 4 * at, base + 4 * (at + max(w, 1))) for w, at in spans))
@@ -396,7 +408,10 @@ def _gates(ops):
     # more than the simulation of a small register)
     buf = np.zeros(max(len(ops), 1), dtype=_GATE)
     if heads:
-        buf["head"] = heads
+        try:
+            buf["head"] = heads
+        except OverflowError:
+            buf["head"] = [[_wrap32(x) for x in h] for h in heads]
     if mats:
         u = None
         if all(type(m) in (np.ndarray, list, tuple) for m in mats):

@@ -90,3 +90,14 @@ def test_gate_matrices_are_read_by_element():
             for g, op in zip(arr, ops):
                 want = [complex(op[2][r][c]) for r in range(2) for c in range(2)]
                 assert list(g.u) == [x for z in want for x in (z.real, z.imag)]
+
+
+@pytest.mark.parametrize("q,stored", [(2 ** 31 - 1, 2 ** 31 - 1), (2 ** 31, -2 ** 31), (2 ** 32, 0), (-2 ** 40 - 1, -1)])
+def test_numbers_beyond_32_bits_are_left_to_the_library(q, stored):
+    """Stored modulo 2^32, as a C field of a ctypes struct is, and judged by
+    the entry point."""
+    s = api._Subs([(2, [q, -1], [-1, q])])
+    c = s.ptr(0)[0]
+    assert (c.init_cut[0], c.init_cut[1], c.meas_cut[0], c.meas_cut[1]) == (stored, -1, -1, stored)
+    arr, _ = api._gates([("u", q, np.eye(2)), ("cz", 0, q)])
+    assert (arr[0].q0, arr[1].q1) == (stored, stored)
