@@ -458,7 +458,10 @@ def cq_variants_workspace_size(sub):
 
 def cq_variant_probabilities(sub, ops=None, out=None, workspace=None, device="cuda:0", stream=None):
     """Every variant of subcircuit ``sub`` (its ``ops`` unless given) as a
-    (4^r, 3^o, 2^width) FP64 device tensor, the layout cq_attribute reads."""
+    (4^r, 3^o, 2^width) FP64 device tensor, the layout cq_attribute reads.
+    ``workspace`` may be any of at least one state (16 * 2^width bytes); without
+    one, what cq_variants_workspace_size asks for, or one state where memory
+    does not hold that."""
     import torch
     s = _Subs([sub])
     w, ic, mc = s.fields[0]
@@ -474,10 +477,17 @@ def cq_variant_probabilities(sub, ops=None, out=None, workspace=None, device="cu
     elif tuple(out.shape) != shape:
         raise ValueError(f"out must have shape {shape}")
     arr, cnt = _gates(ops)
-    nbytes = _variants_workspace(s)
-    ws = _workspace(nbytes, out.device, workspace)
-    check(lib().cq_variant_probabilities(s.ptr(), arr, cnt, _dev_ptr(out, torch.float64), _dev_ptr(ws),
-                                         C.c_size_t(nbytes), _stream(stream)))
+    ws = workspace
+    if ws is None:
+        try:
+            ws = _workspace(_variants_workspace(s), out.device)
+        except torch.OutOfMemoryError:
+            ws = _workspace(16 << w, out.device)
+    st = lib().cq_variant_probabilities(s.ptr(), arr, cnt, _dev_ptr(out, torch.float64), _dev_ptr(ws),
+                                        ws.numel() * ws.element_size(), _stream(stream))
+    if st == CQ_ERR_WORKSPACE:
+        raise ValueError("workspace too small")
+    check(st)
     return out
 
 

@@ -48,3 +48,29 @@ def test_every_workspace(w, r, o):
         assert _lib.lib().cq_variant_probabilities(subs.ptr(), arr, cnt, _dev_ptr(out), _dev_ptr(ws),
                                                    C.c_size_t(16 * states << w), _stream(None)) == 0
         assert np.max(np.abs(out.cpu().numpy() - want)) < 1e-12
+
+
+def test_python_workspaces(monkeypatch):
+    """Any workspace of one state or more is taken, and one state is what is
+    left when memory does not hold the rest."""
+    import paper_2205_05836_amd as cq
+    from paper_2205_05836_amd import api
+    spec = spec_of(12, 2, 1, np.random.default_rng(4))
+    want = sv.variant_probabilities(spec)
+    for n in (16 << 12, (16 << 12) + 8, 3 * (16 << 12)):
+        got = cq.cq_variant_probabilities(spec, workspace=torch.empty(n, dtype=torch.uint8, device=DEV))
+        assert np.max(np.abs(got.cpu().numpy() - want)) < 1e-12
+    with pytest.raises(ValueError):
+        cq.cq_variant_probabilities(spec, workspace=torch.empty((16 << 12) - 1, dtype=torch.uint8, device=DEV))
+    real, asked = api._workspace, []
+
+    def short(nbytes, device, workspace=None):
+        asked.append(nbytes)
+        if nbytes > 16 << 12:
+            raise torch.OutOfMemoryError("no room")
+        return real(nbytes, device, workspace)
+
+    monkeypatch.setattr(api, "_workspace", short)
+    got = cq.cq_variant_probabilities(spec)
+    assert asked == [16 << 14, 16 << 12]
+    assert np.max(np.abs(got.cpu().numpy() - want)) < 1e-12
