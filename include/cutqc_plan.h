@@ -127,7 +127,8 @@ cq_status cq_autotune_save(const char* path);
 /* The cached choices as JSON:
  *   [{"prec": ..., "M", "N", "K", "Z", "variant": v,
  *     "schedule": {"kernel": "tiled" | "async" | "small-tile" | "persistent" |
- *                  "occupancy", "tile": [M, N], "ring": operand stages in
+ *                  "occupancy" | "register" | "short-side" (16-bit rows the
+ *                  others do not take), "tile": [M, N], "ring": operand stages in
  *                  LDS (0: none), "workgroups_per_cu": resident workgroups the
  *                  kernel is built for (0: as many as fit), "raster": "default"
  *                  | "flipped"},

@@ -1967,7 +1967,7 @@ __global__ void __launch_bounds__(256) gemm_h16n_kernel(GemmArgs g, int64_t tile
 
 // ---------------------------------------------------------------------------
 // FP64 operands, 32 W x 32 W tiles of four waves (16 W x 16 W each), for GEMMs
-// with too few 64 x 128 tiles to give every CU two (launch_f64t): the more and
+// with too few 64 x 128 tiles to give every CU two (f64_form): the more and
 // smaller workgroups reach more CUs, and as few waves share a SIMD a stage's
 // operands are read from LDS while the products of the stage before run, from
 // an NS-deep ring of 16-label stages (256 x 256 outputs of 256 labels: 45 us
@@ -2692,15 +2692,26 @@ hipError_t launch_f64s(GemmArgs a, int64_t z, bool nt, hipStream_t s) {
 // against 21.5 with 64 x 128 and 27.2 with 32 x 32; 2048 x 2048 38.3 with 64 x
 // 64 against 35.3 with 64 x 128; 1024 x 512 and fewer 15.1 (the host) against
 // 20 with 64 x 128.
-hipError_t launch_f64t(GemmArgs a, bool nt, hipStream_t s) {
+enum F64Form { kF64Tiled, kF64Occupancy, kF64Small64, kF64Small32 };
+F64Form f64_form(const GemmArgs& a) {
+  if (!f64t_ok(a)) return kF64Tiled;
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
+  const int64_t rows = (a.M + 63) / 64 * z;
+  // (three rows of a stage within a 32-bit byte offset)
+  if (rows * a.tilesN < kF64Few && ring_ok(a, 16) && a.sAk < (int64_t)1 << 27 && a.sBk < (int64_t)1 << 27)
+    return rows * ((a.N + 63) / 64) >= kF64Fewer ? kF64Small64 : kF64Small32;
+  return kF64Occupancy;
+}
+
+hipError_t launch_f64(GemmArgs a, bool nt, hipStream_t s) {
+  const F64Form form = f64_form(a);
+  if (form == kF64Tiled)
+    return nt ? launch(gemm_f64_kernel<true>, a, s, 512) : launch(gemm_f64_kernel<false>, a, s, 512);
+  const int64_t z = a.tiles / (a.tilesM * a.tilesN);
+  if (form == kF64Small64) return launch_f64s<2, 4>(a, z, nt, s);
+  if (form == kF64Small32) return launch_f64s<1, 8>(a, z, nt, s);
   a.tilesM = (a.M + 63) / 64;
   a.tiles = a.tilesM * a.tilesN * z;
-  // (three rows of a stage within a 32-bit byte offset)
-  if (a.tiles < kF64Few && ring_ok(a, 16) && a.sAk < (int64_t)1 << 27 && a.sBk < (int64_t)1 << 27) {
-    if (a.tilesM * ((a.N + 63) / 64) * z >= kF64Fewer) return launch_f64s<2, 4>(a, z, nt, s);
-    return launch_f64s<1, 8>(a, z, nt, s);
-  }
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.tiles), block(256);
   if (nt) hipLaunchKernelGGL((gemm_f64t_kernel<true, 3, 4>), grid, block, 0, s, a);
@@ -2729,6 +2740,7 @@ hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
 // than that, else of two: with short K and many tiles the output stores want
 // the workgroups (2^26 outputs of 16 labels: 71 us with eight
 // stages, 46 with two).
+constexpr int64_t kF32Deep = 512;
 hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
   a.tilesM = (a.M + 63) / 64;
@@ -2736,7 +2748,7 @@ hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   a.tiles = a.tilesM * a.tilesN * z;
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.tiles), block(256);
-  if (a.tiles <= 512) {
+  if (a.tiles <= kF32Deep) {
     if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, 8>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((gemm_f32s_kernel<0, 8>), grid, block, 0, s, a);
   } else {
@@ -2838,8 +2850,7 @@ hipError_t launch_variant(cq_precision prec, GemmArgs a, DType tc, bool nt, int 
   const int impl = v >> 1;
   switch (prec) {
     case CQ_FP64:
-      if (f64t_ok(a)) return launch_f64t(a, nt, stream);
-      return nt ? launch(gemm_f64_kernel<true>, a, stream, 512) : launch(gemm_f64_kernel<false>, a, stream, 512);
+      return launch_f64(a, nt, stream);
     case CQ_FP32:
       // 0 = tiled kernel, 1 = 64 x 64 tiles (2 repeats 0), 3 = persistent
       // kernel, 4 and 5 = occupancy kernel (four workgroups per CU with a
@@ -2886,6 +2897,7 @@ struct TuneEntry {
   int variant;
   float ms[kMaxVariants];
   int tried;
+  int form = -1;  // launch_form of the last launch, -1 before the first (a choice read from a file)
 };
 
 std::mutex g_tune_mu;
@@ -3011,12 +3023,21 @@ bool variant_applies(cq_precision prec, const GemmArgs& a, DType tc, int v) {
   return impl == 3 ? h16p_ok(a, tc) : h16_async_ok(a, tc);
 }
 
+// What the report needs to know of a launch beside its variant: the FP64 form,
+// or for 16-bit operands whether the register path (1) or the short-side kernel
+// (2) takes the place of every variant.
+int launch_form(cq_precision prec, const GemmArgs& a, DType tc) {
+  if (prec == CQ_FP64) return f64_form(a);
+  if (prec == CQ_FP32 || h16_async_ok(a, tc)) return 0;
+  return h16n_ok(a) ? 2 : 1;
+}
+
 // The variant of a GEMM with fewer than 64 tiles of 128 x 128, which is not
 // timed: 64 x 64 tiles where they apply, since 128 x 128 ones leave three in
 // four CUs idle (256 x 256 outputs of 256 labels: FP32 38 us, 9 with 64 x 64;
 // BF16 split 13.4, 3.5).
 int few_tiles_variant(cq_precision prec, const GemmArgs& a, DType tc) {
-  if (prec == CQ_FP64) return 0;  // launch_f64t chooses its tile by the same count
+  if (prec == CQ_FP64) return 0;  // f64_form chooses its tile by the same count
   if (prec == CQ_FP32) return f32s_ok(a) ? 2 : 0;
   return h16p_ok(a, tc) ? 4 : 0;
 }
@@ -3098,13 +3119,16 @@ hipError_t launch_gemm(cq_precision prec, const GemmLaunch& g, hipStream_t strea
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(key);
-    if (it != g_tune.end()) return launch_variant(prec, a, g.tc, nt, it->second.variant, stream);
+    if (it != g_tune.end()) {
+      it->second.form = launch_form(prec, a, g.tc);
+      return launch_variant(prec, a, g.tc, nt, it->second.variant, stream);
+    }
   }
   if (g.no_tune) return launch_variant(prec, a, g.tc, nt, 0, stream);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
     return launch_variant(prec, a, g.tc, nt, 0, stream);
-  TuneEntry te{0, {}, 0};
+  TuneEntry te{0, {}, 0, launch_form(prec, a, g.tc)};
   hipEvent_t ev[3];
   for (int i = 0; i < 3; ++i)
     if (hipEventCreate(&ev[i]) != hipSuccess) return launch_variant(prec, a, g.tc, nt, 0, stream);
@@ -3168,34 +3192,54 @@ namespace {
 
 // The schedule behind variant v: kernel, tile, ring depth (operand stages in
 // LDS), resident workgroups per compute unit and raster order.
-std::string variant_schedule(const TuneKey& k, int v) {
-  const int prec = k.prec;
+std::string variant_schedule(const TuneKey& k, const TuneEntry& e) {
+  const int prec = k.prec, v = e.variant;
   const int impl = v >> 1;
   const bool split = prec == CQ_BF16_SPLIT || prec == CQ_FP16_SPLIT;
+  int form = e.form;
+  if (form < 0) {  // not launched yet: what the shape takes with packed rows, aligned or not as recorded
+    GemmArgs a{};
+    a.M = k.M;
+    a.N = k.N;
+    a.K = k.K;
+    a.sAk = k.M;
+    a.sBk = a.ldc = k.N;
+    a.tilesM = (k.M + 127) / 128;
+    a.tilesN = (k.N + 127) / 128;
+    a.tiles = a.tilesM * a.tilesN * k.Z;
+    const bool odd = !k.aligned && k.M % 8 == 0 && k.N % 8 == 0;  // off the alignment, not for its size
+    if (prec == CQ_FP64) form = odd ? kF64Tiled : f64_form(a);
+    else form = prec == CQ_FP32 || k.aligned ? 0 : odd ? 1 : launch_form((cq_precision)prec, a, (DType)k.tc);
+  }
   const char* kernel = "tiled";
   int ring = 0, wpc = 0, tile = 128, tile_n = 0;
-  if (prec == CQ_FP64 && k.aligned) {  // as launch_f64t chooses
-    const int64_t few = (k.M + 63) / 64 * k.Z;
-    if (few * ((k.N + 127) / 128) >= kF64Few) {
+  if (prec == CQ_FP64) {
+    if (form == kF64Occupancy) {
       kernel = "occupancy";
       ring = 3;
       wpc = 4;
       tile = 64;
       tile_n = 128;
-    } else {
+    } else if (form != kF64Tiled) {
       kernel = "small-tile";
-      tile = few * ((k.N + 63) / 64) >= kF64Fewer ? 64 : 32;
+      tile = form == kF64Small64 ? 64 : 32;
       ring = tile == 64 ? 4 : 8;
     }
   } else if (prec == CQ_FP32 && impl == 1) {
     kernel = "small-tile";
-    ring = 8;
+    ring = (k.M + 63) / 64 * ((k.N + 63) / 64) * k.Z <= kF32Deep ? 8 : 2;
     tile = 64;
   } else if (prec == CQ_FP32 && impl >= 3) {
     kernel = impl == 3 ? "persistent" : "occupancy";
     ring = impl == 4 ? 3 : 4;
     wpc = impl == 3 ? 2 : 4;
-  } else if (prec != CQ_FP64 && prec != CQ_FP32) {
+  } else if (prec != CQ_FP32 && form == 2) {
+    kernel = "short-side";
+    tile = k.N <= k.M ? 512 : 32;  // the long side in 512s, the short one whole
+    tile_n = k.N <= k.M ? 32 : 512;
+  } else if (prec != CQ_FP32 && form == 1) {
+    kernel = "register";
+  } else if (prec != CQ_FP32) {
     switch (impl) {
       case 0: kernel = "async"; ring = split ? 2 : 3; break;
       case 1: kernel = "async"; ring = split ? 3 : 2; break;
@@ -3230,7 +3274,7 @@ std::string autotune_json() {
                           first ? "" : ", ", pname[k.prec], (long long)k.M, (long long)k.N,
                           (long long)k.K, (long long)k.Z, e.variant);
     s.append(buf, n);
-    s += variant_schedule(k, e.variant);
+    s += variant_schedule(k, e);
     s += ", \"ms\": [";
     bool f2 = true;
     for (int v = 0; v < kMaxVariants; ++v)
