@@ -213,8 +213,7 @@ __device__ inline void shot_target(const uint64_t* __restrict__ E, int64_t nblk,
 // Pass 3: shots per block.  grid (shot groups, rows); a group takes
 // 256 * per consecutive shots of one row and, for rows of at most
 // kLdsBins blocks, searches the block ends and counts its shots in LDS
-// before one global add per block hit.  A row of one block needs no
-// counting at all.
+// before one global add per block hit.
 __global__ void __launch_bounds__(kThreads) shots_count_kernel(const uint64_t* __restrict__ bend, int64_t nblk,
                                                                int64_t shots, uint64_t seed, int per,
                                                                uint32_t* __restrict__ bcnt) {
@@ -225,10 +224,6 @@ __global__ void __launch_bounds__(kThreads) shots_count_kernel(const uint64_t* _
   uint32_t* cnt = bcnt + row * nblk;
   const uint64_t T = E[nblk - 1];
   if (T == 0) return;
-  if (nblk == 1) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[0] = (uint32_t)shots;
-    return;
-  }
   if (nblk > kLdsBins) {
 #pragma unroll 4
     for (int j = 0; j < per; ++j) {
@@ -290,19 +285,6 @@ __global__ void __launch_bounds__(kThreads) shots_scatter_kernel(const uint64_t*
   uint64_t* S = slots + row * shots;
   const uint64_t T = E[nblk - 1];
   if (T == 0) return;
-  if (nblk == 1) {
-#pragma unroll 4
-    for (int j = 0; j < per; ++j) {
-      const int64_t s = s0 + j * kThreads + threadIdx.x;
-      if (s < shots) {
-        uint64_t t;
-        uint32_t blk;
-        shot_target(E, 1, T, seed, row, s, t, blk);
-        S[s] = t;
-      }
-    }
-    return;
-  }
   if (nblk > kLdsBins) {
 #pragma unroll 4
     for (int j = 0; j < per; ++j) {
