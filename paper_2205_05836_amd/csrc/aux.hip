@@ -1460,11 +1460,15 @@ int kind_of(DType t, bool f16) {
   return f16 ? kF16 : kBF16;
 }
 
-// tb: bits of a tile, 0 for the generic kernel
+// tb: bits of a tile (10 for doubles), 0 for the generic kernel
 template <int SK, int DK>
 void permute_dispatch(dim3 grid, const PermArgs& a, int tb, const PermTileMap& m, hipStream_t s) {
-  if (tb == 12) hipLaunchKernelGGL((permute_tile_kernel<SK, DK, 12>), grid, dim3(256), 0, s, a, m);
-  else if (tb == 10) hipLaunchKernelGGL((permute_tile_kernel<SK, DK, 10>), grid, dim3(256), 0, s, a, m);
+  if constexpr (DK != kF64)
+    if (tb == 12) {
+      hipLaunchKernelGGL((permute_tile_kernel<SK, DK, 12>), grid, dim3(256), 0, s, a, m);
+      return;
+    }
+  if (tb == 10) hipLaunchKernelGGL((permute_tile_kernel<SK, DK, 10>), grid, dim3(256), 0, s, a, m);
   else hipLaunchKernelGGL((permute_kernel<SK, DK>), grid, dim3(256), 0, s, a);
 }
 
