@@ -32,6 +32,11 @@ constexpr int kMaxShotsPerThread = 64;  // a shot group: 256 threads of 1..64 sh
 constexpr int kLdsBins = 4096;          // rows with at most this many blocks search and count in LDS
 constexpr int kFewShots = 64;           // blocks with at most this many shots resolve in registers
 constexpr int kSparseShots = 16;        // shots per block on average up to which only the runs with shots are read again
+// fewest blocks of a table for that: a wave a block and the run sums cost small
+// tables more than the second read (416 blocks of 7 shots: 28 us with a
+// workgroup a block, 31.7 with a wave; 2048 blocks 41.1 and 41.0; 4096 blocks
+// 67.8 and 63.3)
+constexpr int64_t kSparseBlocks = 2048;
 constexpr int kRun = 64;                // entries of a run, one a lane
 constexpr int kRuns = kBlock / kRun;
 // rows of one block that a workgroup takes whole: with at most so many shots
@@ -864,7 +869,7 @@ extern "C" cq_status cq_sample_shots(const double* probs, int64_t rows, int64_t 
   int per = kMaxShotsPerThread;
   while (per > 4 && rows * ((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)) < 512) per >>= 1;
   const dim3 gs((unsigned)((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)), (unsigned)rows);
-  const bool sparse = shots <= (int64_t)kSparseShots * nblk;
+  const bool sparse = shots <= (int64_t)kSparseShots * nblk && rows * nblk >= kSparseBlocks;
   if (sparse)
     hipLaunchKernelGGL(shots_bsum_kernel<true>, gt, dim3(kThreads), 0, stream, probs, cols, nblk, bend, runs, bcnt,
                        bfill);

@@ -119,3 +119,21 @@ def test_variants_workspace_leaves_room_for_the_variants(recorder):
     cases = [(slots(w, r, o), []) for w, r, o in ((12, 3, 2), (22, 2, 2), (27, 4, 0), (29, 3, 0), (31, 1, 1), (32, 0, 0))]
     got = [q[0] for q in launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + STATES)]
     assert got == [16 << 15, 16 << 24, 16 << 27, 16 << 29, 16 << 31, 16 << 32]
+
+
+SHOTS = """
+def kernels(rows, cols, shots):
+    b = C.c_size_t()
+    assert L.cq_sample_shots_workspace_size(rows, cols, shots, C.byref(b)) == 0
+    events()
+    assert L.cq_sample_shots(C.c_void_p(1 << 50), rows, cols, shots, 1, C.c_void_p(1 << 51), C.c_void_p(1 << 52), b, None) == 0
+    return [e["kernel"] for e in events()]
+out = [kernels(*c) for c in json.loads(CASES)]
+"""
+
+
+def test_small_tables_resolve_by_workgroups(recorder):
+    """A wave a block only where the blocks fill the chip."""
+    cases = [(52, 16320, 119), (255, 16320, 119), (256, 16320, 119), (144, 1 << 22, 8192), (144, 1 << 22, 1 << 16)]
+    got = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + SHOTS)
+    assert [any("resolve_sparse" in k for k in ks) for ks in got] == [False, False, True, True, False]
