@@ -2736,26 +2736,34 @@ hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Ring of eight stages (two workgroups a CU) while there are no more tiles
-// than that, else of two: with short K and many tiles the output stores want
-// the workgroups (2^26 outputs of 16 labels: 71 us with eight
-// stages, 46 with two).
-constexpr int64_t kF32Deep = 512;
+// The ring of the FP32 64 x 64 tiles: eight stages (two workgroups a CU) while
+// there are no more tiles than that, else two: with short K and many tiles the
+// output stores want the workgroups (2^26 outputs of 16 labels: 71 us with
+// eight stages, 46 with two).  Below one stage of labels nothing but the stores
+// is left, and too many workgroups a CU scatter them: four stages' worth of LDS
+// leave five (4 labels, 2^20 x 2^9 outputs: 327 us, 370 with two stages; 2^18 x
+// 2^10 165 and 191; 2^15 x 2^13 170 and 180; 64 labels 2^13 x 2^13 105 and 98).
+int f32s_ring(int64_t tiles, int64_t K) { return tiles <= 512 ? 8 : K < 16 ? 4 : 2; }
+
+template <int NS>
+hipError_t launch_f32s_ring(const GemmArgs& a, bool nt, hipStream_t s) {
+  const dim3 grid((unsigned)a.tiles), block(256);
+  if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, NS>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_f32s_kernel<0, NS>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
   a.tilesM = (a.M + 63) / 64;
   a.tilesN = (a.N + 63) / 64;
   a.tiles = a.tilesM * a.tilesN * z;
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)a.tiles), block(256);
-  if (a.tiles <= kF32Deep) {
-    if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, 8>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((gemm_f32s_kernel<0, 8>), grid, block, 0, s, a);
-  } else {
-    if (nt) hipLaunchKernelGGL((gemm_f32s_kernel<1, 2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((gemm_f32s_kernel<0, 2>), grid, block, 0, s, a);
+  switch (f32s_ring(a.tiles, a.K)) {
+    case 8: return launch_f32s_ring<8>(a, nt, s);
+    case 4: return launch_f32s_ring<4>(a, nt, s);
+    default: return launch_f32s_ring<2>(a, nt, s);
   }
-  return hipGetLastError();
 }
 
 template <int NS, int WPE>
@@ -3227,7 +3235,7 @@ std::string variant_schedule(const TuneKey& k, const TuneEntry& e) {
     }
   } else if (prec == CQ_FP32 && impl == 1) {
     kernel = "small-tile";
-    ring = (k.M + 63) / 64 * ((k.N + 63) / 64) * k.Z <= kF32Deep ? 8 : 2;
+    ring = f32s_ring((k.M + 63) / 64 * ((k.N + 63) / 64) * k.Z, k.K);
     tile = 64;
   } else if (prec == CQ_FP32 && impl >= 3) {
     kernel = impl == 3 ? "persistent" : "occupancy";

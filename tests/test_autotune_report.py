@@ -48,9 +48,19 @@ def test_report_names_what_runs(recorder, prec, shift):
             assert names == {e["schedule"]["kernel"]}, (outs, launched, e)
 
 
+def test_small_fp32_tiles_of_short_products(recorder):
+    """The ring of forced 64 x 64 tiles: four stages' LDS below 16 labels where
+    there are many tiles."""
+    cases = [(syn.chain_cutmap([b], outs), "fp32", 0) for b, outs in ((1, [10, 10]), (1, [12, 12]), (2, [12, 12]))]
+    script = SCRIPT.replace("L.cq_autotune_enable(1)", "L.cq_autotune_enable(4)")
+    got = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + script)
+    assert [int(k[0].split(", ")[1].split(">")[0]) for k, _ in got] == [8, 4, 2]
+
+
 def test_report_of_loaded_choices(recorder, tmp_path):
-    """FP32 64 x 64 tiles run an eight-deep ring up to 512 of them and a
-    two-deep one beyond; FP64 rows of 2 or 4 columns take the aligned kernels."""
+    """FP32 64 x 64 tiles run an eight-deep ring up to 512 of them and a two-
+    or four-deep one beyond; FP64 rows of 2 or 4 columns take the aligned
+    kernels."""
     ms = " ".join(["0.5"] * 12)
     rows = [(1, 1, 1024, 2048, 2), (1, 1, 2048, 2048, 2), (0, 0, 4, 1 << 15, 0), (0, 0, 4, 1 << 17, 0),
             (0, 0, 1024, 1024, 0), (0, 1, 1024, 1024, 0)]
