@@ -2743,7 +2743,12 @@ hipError_t launch_h16s(GemmArgs a, DType tc, bool nt, hipStream_t s) {
 // is left, and too many workgroups a CU scatter them: four stages' worth of LDS
 // leave five (4 labels, 2^20 x 2^9 outputs: 327 us, 370 with two stages; 2^18 x
 // 2^10 165 and 191; 2^15 x 2^13 170 and 180; 64 labels 2^13 x 2^13 105 and 98).
-int f32s_ring(int64_t tiles, int64_t K) { return tiles <= 512 ? 8 : K < 16 ? 4 : 2; }
+// A side below the tile's 64 leaves each workgroup less to store, and more of
+// them are wanted again (4 labels, 2^23 x 2^4: 426 us with four, 347 with two;
+// 2^22 x 2^5 178 and 144; 2^3 x 2^22 162 and 138; 2^21 x 2^6 100 and 105).
+int f32s_ring(int64_t tiles, int64_t K, int64_t M, int64_t N) {
+  return tiles <= 512 ? 8 : K < 16 && M >= 64 && N >= 64 ? 4 : 2;
+}
 
 template <int NS>
 hipError_t launch_f32s_ring(const GemmArgs& a, bool nt, hipStream_t s) {
@@ -2759,7 +2764,7 @@ hipError_t launch_f32s(GemmArgs a, bool nt, hipStream_t s) {
   a.tilesN = (a.N + 63) / 64;
   a.tiles = a.tilesM * a.tilesN * z;
   if (a.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  switch (f32s_ring(a.tiles, a.K)) {
+  switch (f32s_ring(a.tiles, a.K, a.M, a.N)) {
     case 8: return launch_f32s_ring<8>(a, nt, s);
     case 4: return launch_f32s_ring<4>(a, nt, s);
     default: return launch_f32s_ring<2>(a, nt, s);
@@ -3235,7 +3240,7 @@ std::string variant_schedule(const TuneKey& k, const TuneEntry& e) {
     }
   } else if (prec == CQ_FP32 && impl == 1) {
     kernel = "small-tile";
-    ring = f32s_ring((k.M + 63) / 64 * ((k.N + 63) / 64) * k.Z, k.K);
+    ring = f32s_ring((k.M + 63) / 64 * ((k.N + 63) / 64) * k.Z, k.K, k.M, k.N);
     tile = 64;
   } else if (prec == CQ_FP32 && impl >= 3) {
     kernel = impl == 3 ? "persistent" : "occupancy";

@@ -50,11 +50,12 @@ def test_report_names_what_runs(recorder, prec, shift):
 
 def test_small_fp32_tiles_of_short_products(recorder):
     """The ring of forced 64 x 64 tiles: four stages' LDS below 16 labels where
-    there are many tiles."""
-    cases = [(syn.chain_cutmap([b], outs), "fp32", 0) for b, outs in ((1, [10, 10]), (1, [12, 12]), (2, [12, 12]))]
+    there are many tiles, whole ones."""
+    cases = [(syn.chain_cutmap([b], outs), "fp32", 0)
+             for b, outs in ((1, [10, 10]), (1, [12, 12]), (2, [12, 12]), (1, [18, 6]), (1, [18, 5]), (1, [5, 18]))]
     script = SCRIPT.replace("L.cq_autotune_enable(1)", "L.cq_autotune_enable(4)")
     got = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + script)
-    assert [int(k[0].split(", ")[1].split(">")[0]) for k, _ in got] == [8, 4, 2]
+    assert [int(k[0].split(", ")[1].split(">")[0]) for k, _ in got] == [8, 4, 2, 4, 2, 2]
 
 
 def test_report_of_loaded_choices(recorder, tmp_path):
