@@ -2692,10 +2692,20 @@ hipError_t launch_f64s(GemmArgs a, int64_t z, bool nt, hipStream_t s) {
 // against 21.5 with 64 x 128 and 27.2 with 32 x 32; 2048 x 2048 38.3 with 64 x
 // 64 against 35.3 with 64 x 128; 1024 x 512 and fewer 15.1 (the host) against
 // 20 with 64 x 128.
+// Below one stage of labels nothing but the output stores is left, and of
+// outputs beyond the cache (1 GiB) with rows of 256 to 1024 columns the 64 x
+// 128 tiles write too many rows at once: 128 x 128 tiles take over (4 labels,
+// 64 x 128 and 128 x 128: 2^21 x 2^8 688 and 645 us, 2^20 x 2^9 717 and 660,
+// 2^19 x 2^10 654 and 617, 2^18 x 2^9 184 and 173, 2^17 x 2^10 168 and 162).
+// Not so for other rows (2^21 x 2^7 348 and 370, 2^17 x 2^11 332 and 343, 2^14
+// x 2^14 383 and 407, 2^8 x 2^20 392 and 401) and fewer outputs (2^18 x 2^8 92
+// and 93, 2^16 x 2^8 26.3 and 27.4), nor from 16 labels (2^20 x 2^8: 337 us;
+// 128 x 128 tiles took 401).
 enum F64Form { kF64Tiled, kF64Occupancy, kF64Small64, kF64Small32 };
 F64Form f64_form(const GemmArgs& a) {
   if (!f64t_ok(a)) return kF64Tiled;
   const int64_t z = a.tiles / (a.tilesM * a.tilesN);  // batches (the tile counts are for 128 x 128)
+  if (a.K < 8 && a.N >= 256 && a.N <= 1024 && a.M * a.N * z >= (int64_t)1 << 27) return kF64Tiled;
   const int64_t rows = (a.M + 63) / 64 * z;
   // (three rows of a stage within a 32-bit byte offset)
   if (rows * a.tilesN < kF64Few && ring_ok(a, 16) && a.sAk < (int64_t)1 << 27 && a.sBk < (int64_t)1 << 27)
