@@ -172,11 +172,21 @@ struct PlanShape {
 // left for a later pass.  The state starts as a basis string, and the allowed
 // qubits start as the lowest `tile` index bits and grow, lowest first, only when
 // none of their gates can run: while t qubits are touched a pass moves 2^t
-// amplitudes.  The last pass writes every amplitude, also without gates.  Returns the modelled time in microseconds, or
-// anything above `limit` once that is passed.  The model, from traces: 3.5 us
-// a launch, the bytes at the rate of a large copy (4.4 TB/s), and 0.33 ms for
-// every one-qubit gate on 2^30 amplitudes, no less than the serial time of
-// those gates in one tile (0.8 us each with 11 bits, 1.4 us with 12).
+// amplitudes.  The last pass writes every amplitude, also without gates.
+// Returns the modelled time in microseconds, or anything above `limit` once
+// that is passed.  The model, from traces: 3.5 us a launch, the bytes at the
+// rate of a large copy (4.4 TB/s), and 0.33 ms for every one-qubit gate on 2^30
+// amplitudes, no less than the serial time of those gates in one tile (0.8 us
+// each with 11 bits, 1.4 us with 12).
+//
+// The order leaves the amplitudes as exact as circuit order does, but spreads
+// their errors differently: what a gate rounds while few qubits are touched is
+// passed on in proportion to the amplitudes that grow from it, so the large
+// probabilities carry more of it.  (20 qubits, 8 layers, general gates, against
+// long double: relative l2 error of the amplitudes 9.2e-16 in circuit order and
+// 9.1e-16 in this one, sum of |dp| 8.5e-16 and 9.3e-16, 8.6e-16 with the
+// rewritten unitaries; l2 error of the probabilities, which weighs the large
+// ones, 6.3e-16 and 8.3e-16, 7.8e-16 with the rewritten ones.)
 inline double plan_passes(const GateSet& s, const PlanShape& sh, int states, double limit,
                    std::vector<Pass>& out) {
   const int n = s.n;
