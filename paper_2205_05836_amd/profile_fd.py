@@ -105,11 +105,11 @@ def summarize(argv):
                     "Commands (repository root), one counter per run:", ""]
     for c in ("FETCH_SIZE", "WRITE_SIZE"):
         md.append(f"    rocprofv3 --kernel-include-regex \"gemm|prep|opy\" --pmc {c} --output-format csv "
-                  f"-d gpurun_out/prof/pmc_<prec>_{c} -o run -- python3 -m "
+                  f"-d prof/pmc_<prec>_{c} -o run -- python3 -m "
                   f"paper_2205_05836_amd.profile_fd <prec> {reps}")
     md += ["", "Summary (this file and the JSON beside it):", "",
            f"    python3 -m paper_2205_05836_amd.profile_fd summarize {out_json} {out_md} "
-           f"gpurun_out/prof {reps} {' '.join(precs)}", "",
+           f"prof {reps} {' '.join(precs)}", "",
            "The driver ends with a 1 GiB device-to-device copy (`__amd_rocclr_copyBuffer`, "
            "1 GiB read + 1 GiB written): its counters give the calibration factors "
            "(counter KiB x 1024 / true bytes).  Per GEMM step: the mean over the last "
