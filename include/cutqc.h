@@ -366,15 +366,19 @@ cq_status cq_reconstruct_dd_bfs(const cq_dd_instance* root, const cq_dd_bfs_para
 
 /* Limits: 1 <= rows <= 65535, rows * cols <= 2^34, shots < 2^32,
  * rows * shots <= 2^34.  The workspace holds per-block sums and shot
- * counters of each row (2048 entries a block), the sums of each block's 32
- * runs of 64 entries, and one 8-byte slot per shot. */
+ * counters of each row (2048 entries a block: 8 + 4 + 4 + 4 bytes, each array
+ * rounded up to 256) and one 8-byte slot per shot (rounded up likewise), which
+ * every call needs.  Where few shots fall on many blocks the size returned adds
+ * the sums of each block's 32 runs of 64 entries (256 bytes a block), unless
+ * the workspace and both tables would take more than 240 GiB together;
+ * cq_sample_shots does without them in a workspace that has no room for them,
+ * more slowly. */
 cq_status cq_sample_shots_workspace_size(int64_t rows, int64_t cols, int64_t shots, size_t* bytes);
 
 /* probs: device, rows x cols row-major FP64, read only.  freqs: device,
  * rows x cols FP64, written (may not alias probs).  workspace: device, at
- * least cq_sample_shots_workspace_size bytes (prefix sums and counts),
- * owned by the caller, contents on entry ignored.  Asynchronous on `stream`;
- * arguments are checked before any launch (CQ_ERR_ARG, CQ_ERR_SHAPE,
+ * least the bytes that every call needs (see there), owned by the caller,
+ * contents on entry ignored.  Asynchronous on `stream`; arguments are checked before any launch (CQ_ERR_ARG, CQ_ERR_SHAPE,
  * CQ_ERR_WORKSPACE leave freqs untouched). */
 cq_status cq_sample_shots(const double* probs, int64_t rows, int64_t cols, int64_t shots, uint64_t seed,
                           double* freqs, void* workspace, size_t workspace_bytes, hipStream_t stream);

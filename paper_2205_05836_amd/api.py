@@ -348,10 +348,13 @@ def cq_sample_shots(probs, shots, seed, out=None, workspace=None, stream=None):
     elif out.shape != probs.shape:
         raise ValueError("out must have the shape of probs")
     nbytes = cq_sample_shots_workspace_size(rows, cols, shots)
-    ws = _workspace(nbytes, probs.device, workspace)
-    check(lib().cq_sample_shots(_dev_ptr(probs), rows, cols, int(shots), C.c_uint64(int(seed)),
-                                _dev_ptr(out, torch.float64), _dev_ptr(ws), C.c_size_t(nbytes),
-                                _stream(stream)))
+    ws = workspace if workspace is not None else _workspace(nbytes, probs.device)
+    st = lib().cq_sample_shots(_dev_ptr(probs), rows, cols, int(shots), C.c_uint64(int(seed)),
+                               _dev_ptr(out, torch.float64), _dev_ptr(ws),
+                               C.c_size_t(ws.numel() * ws.element_size()), _stream(stream))
+    if st == CQ_ERR_WORKSPACE:
+        raise ValueError("workspace too small")
+    check(st)
     return out
 
 

@@ -775,9 +775,15 @@ __global__ void __launch_bounds__(kThreads) chi2_final_kernel(const double* __re
   if (threadIdx.x == 0) out[0] = sh[0];
 }
 
+// bytes: what every call needs; `runs` (the run sums) and `with_runs` bytes in
+// all where blocks may resolve a wave each, which smaller workspaces leave out
 struct ShotsWs {
-  int64_t bend = 0, runs = 0, bcnt = 0, bptr = 0, bfill = 0, slots = 0, bytes = 0;
+  int64_t bend = 0, bcnt = 0, bptr = 0, bfill = 0, slots = 0, bytes = 0, runs = 0, with_runs = 0;
 };
+
+// What cq_sample_shots_workspace_size asks for together with the two tables at
+// most: beyond it (of the card's 288 GB) the run sums are left out.
+constexpr int64_t kShotsBytes = (int64_t)240 << 30;
 
 cq_status hip_error(hipError_t e, const char* what) {
   return fail(CQ_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
@@ -787,14 +793,17 @@ int64_t al256(int64_t x) { return (x + 255) / 256 * 256; }
 
 ShotsWs shots_ws(int64_t rows, int64_t cols, int64_t shots) {
   ShotsWs w;
-  const int64_t nb = rows * ((cols + kBlock - 1) / kBlock);
+  const int64_t nblk = (cols + kBlock - 1) / kBlock, nb = rows * nblk;
   w.bend = 0;
-  w.runs = al256(nb * 8);
-  w.bcnt = w.runs + al256(nb * kRuns * 8);
+  w.bcnt = al256(nb * 8);
   w.bptr = w.bcnt + al256(nb * 4);
   w.bfill = w.bptr + al256(nb * 4);
   w.slots = w.bfill + al256(nb * 4);
   w.bytes = w.slots + al256(rows * shots * 8);
+  if (nblk > 1 && shots <= (int64_t)kSparseShots * nblk && nb >= kSparseBlocks) {
+    w.runs = w.bytes;
+    w.with_runs = w.runs + al256(nb * kRuns * 8);
+  }
   return w;
 }
 
@@ -817,7 +826,8 @@ extern "C" cq_status cq_sample_shots_workspace_size(int64_t rows, int64_t cols, 
   if (!bytes) return fail(CQ_ERR_ARG, "null argument");
   cq_status st = shots_check(rows, cols, shots);
   if (st != CQ_OK) return st;
-  *bytes = (size_t)shots_ws(rows, cols, shots).bytes;
+  const ShotsWs w = shots_ws(rows, cols, shots);
+  *bytes = (size_t)(w.with_runs && 16 * rows * cols + w.with_runs <= kShotsBytes ? w.with_runs : w.bytes);
   return CQ_OK;
 }
 
@@ -869,7 +879,7 @@ extern "C" cq_status cq_sample_shots(const double* probs, int64_t rows, int64_t 
   int per = kMaxShotsPerThread;
   while (per > 4 && rows * ((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)) < 512) per >>= 1;
   const dim3 gs((unsigned)((shots + (int64_t)per * kThreads - 1) / ((int64_t)per * kThreads)), (unsigned)rows);
-  const bool sparse = shots <= (int64_t)kSparseShots * nblk && rows * nblk >= kSparseBlocks;
+  const bool sparse = w.with_runs && (int64_t)workspace_bytes >= w.with_runs;
   if (sparse)
     hipLaunchKernelGGL(shots_bsum_kernel<true>, gt, dim3(kThreads), 0, stream, probs, cols, nblk, bend, runs, bcnt,
                        bfill);

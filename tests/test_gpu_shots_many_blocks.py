@@ -38,3 +38,22 @@ def test_forms_bit_exact(rows, cols, n, kind, offset):
     src.copy_(torch.from_numpy(P))
     got = cq.cq_sample_shots(src, n, 2 ** 33 + n, out=out).cpu().numpy()
     assert np.array_equal(got, shots.sample_frequencies(P, n, 2 ** 33 + n))
+
+
+@pytest.mark.parametrize("rows,cols,n", [(1024, 2049, 32), (410, 5 * 2048, 80)])
+def test_no_room_for_run_sums(rows, cols, n):
+    """Workspaces from what every call needs up to a byte below what is asked for."""
+    import paper_2205_05836_amd as cq
+    print(f"rows={rows} cols={cols} shots={n}", flush=True)
+    P = table(rows, cols, "plain")
+    src, want = torch.from_numpy(P).to(DEV), shots.sample_frequencies(P, n, 5)
+    up = lambda b: (b + 255) // 256 * 256
+    blocks = rows * -(-cols // 2048)
+    need = up(8 * blocks) + 3 * up(4 * blocks) + up(8 * rows * n)
+    asked = cq.cq_sample_shots_workspace_size(rows, cols, n)
+    assert asked == need + 256 * blocks
+    for size in (need, asked - 1, asked):
+        got = cq.cq_sample_shots(src, n, 5, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+        assert np.array_equal(got.cpu().numpy(), want)
+    with pytest.raises(ValueError):
+        cq.cq_sample_shots(src, n, 5, workspace=torch.empty(need - 1, dtype=torch.uint8, device=DEV))

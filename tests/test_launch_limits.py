@@ -137,3 +137,33 @@ def test_small_tables_resolve_by_workgroups(recorder):
     cases = [(52, 16320, 119), (255, 16320, 119), (256, 16320, 119), (144, 1 << 22, 8192), (144, 1 << 22, 1 << 16)]
     got = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + SHOTS)
     assert [any("resolve_sparse" in k for k in ks) for ks in got] == [False, False, True, True, False]
+
+
+SMALL_SHOTS = """
+def kernels(rows, cols, shots):
+    up = lambda n: (n + 255) // 256 * 256
+    blocks = rows * -(-cols // 2048)
+    need = up(8 * blocks) + 3 * up(4 * blocks) + up(8 * rows * shots)
+    b = C.c_size_t()
+    assert L.cq_sample_shots_workspace_size(rows, cols, shots, C.byref(b)) == 0
+    call = lambda n: L.cq_sample_shots(C.c_void_p(1 << 50), rows, cols, shots, 1, C.c_void_p(1 << 51),
+                                       C.c_void_p(1 << 52), n, None)
+    codes, sparse = [], []
+    for n in (need - 1, need, b.value - 1, b.value):
+        events()
+        codes.append(call(n))
+        sparse.append(any("resolve_sparse" in e["kernel"] for e in events()))
+    return [b.value - need, codes, sparse]
+out = [kernels(*c) for c in json.loads(CASES)]
+"""
+
+
+def test_shots_without_room_for_run_sums(recorder):
+    """The run sums (256 bytes a block) are asked for where blocks resolve a wave
+    each, up to 240 GiB with the tables; a workspace without room for them is
+    taken as ever."""
+    cases = [(144, 1 << 22, 8192), (2, 8, 100), (52, 16320, 119), (144, 1 << 22, 1 << 16), (64, 1 << 28, 8192)]
+    got = launch_recorder.run(recorder, f"CASES = {json.dumps(cases)!r}\n" + SMALL_SHOTS)
+    refused, plain = [-5, 0, -5, 0], [0, 0, 0, 0]
+    assert got[0] == [144 * 2048 * 256, [-5] + plain[1:], [False, False, False, True]]
+    assert got[1:] == [[0, refused, [False] * 4]] * 4
